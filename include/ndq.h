@@ -168,6 +168,32 @@ int ndq_nested_encode_with_step(const void* g, int dt, size_t n, const float* st
                                 float alpha, const ndq_dither* d, void* codes_out, float* steps_out,
                                 void* stream);
 
+/* Several workers' vectors of one length and type, encoded by one call.  The bytes are
+ * those of W calls of the functions above in the given order; what is saved is launches:
+ * vectors that share a quantizer are one launch (up to 16 of them), the max-norm passes of
+ * a group are one launch, and no launch ends with an idle chip W times.
+ *   kind, levels, M, alpha, dither: the worker's quantizer, as in ndq_dq_encode /
+ *     ndq_nested_encode (M and alpha: nested workers only)
+ *   step_in: NULL, or -- bucket == 0 only -- one step in device memory, as in the
+ *     _with_step calls; it may be the steps_out of an earlier worker of this call
+ * delta and bucket as in ndq_dq_encode (workers with a step_in do not use delta).
+ * jobs: HOST array of W entries (1 <= W <= 1024).  Apart from step_in no worker may read
+ * what another one writes. */
+typedef enum { NDQ_WORKER_DQ = 0, NDQ_WORKER_NESTED = 1 } ndq_worker_kind;
+typedef struct {
+    const void* g;          /* n elements of type dt                                       */
+    void* codes_out;        /* ndq_packed_bytes(n, ndq_code_bits(levels or M)) bytes       */
+    float* steps_out;       /* ndq_num_buckets(n, bucket) floats                           */
+    const float* step_in;
+    uint32_t kind;          /* ndq_worker_kind: group P1 (DQSG) or group P2 (nested)       */
+    uint32_t levels;
+    uint32_t M;
+    float alpha;
+    ndq_dither dither;
+} ndq_encode_job;
+int ndq_encode_workers(const ndq_encode_job* jobs, uint32_t W, int dt, size_t n, float delta,
+                       uint32_t bucket, void* stream);
+
 /* Server side of Algorithm 2 for a worker of group P2 (eq. (8)).
  * The side information is y_i = side[i] * side_scale, so `side` may be the
  * running SUM of the gradients decoded so far and side_scale = 1/count (the
@@ -227,7 +253,6 @@ int ndq_aggregate(const float* const* gs, uint32_t W, size_t n, float scale, flo
 
 /* One worker's message as the server holds it (Algorithm 2, "Server"): the packed
  * codes and steps it sent (DEVICE pointers), how they were made, and its dither. */
-typedef enum { NDQ_WORKER_DQ = 0, NDQ_WORKER_NESTED = 1 } ndq_worker_kind;
 typedef struct {
     const void* codes;      /* ndq_packed_bytes(n, ndq_code_bits(levels_or_M)) bytes   */
     const float* steps;     /* ndq_num_buckets(n, bucket) floats                        */

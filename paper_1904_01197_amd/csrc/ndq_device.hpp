@@ -490,8 +490,9 @@ __device__ __forceinline__ uint4 load_streaming(const void* p)
 
 // Loads the 8 elements at element offset `o` (a multiple of 8) of a tile with
 // `len` valid elements.  FULL: the whole tile is valid, plain 16-byte loads.
-// Otherwise elements past the end read as zero.
-template <int DT, bool FULL>
+// Otherwise elements past the end read as zero.  KEEP: the vector is read again soon
+// (the max-norm pass before an encoder), so its lines may stay in the caches.
+template <int DT, bool FULL, bool KEEP = false>
 __device__ __forceinline__ typename Elem<DT>::Row load_row(const void* tile, uint32_t o, uint32_t len)
 {
     using T = Elem<DT>;
@@ -502,7 +503,7 @@ __device__ __forceinline__ typename Elem<DT>::Row load_row(const void* tile, uin
         constexpr uint32_t per = kLaneElems / T::V;        // elements per vector
         const uint32_t oj = o + j * per;
         if (FULL || oj + per <= len) {
-            row.v[j] = load_streaming(base + j * per);
+            row.v[j] = KEEP ? *(const uint4*)(base + j * per) : load_streaming(base + j * per);
         } else {
             uint32_t w[4] = {0u, 0u, 0u, 0u};
 #pragma unroll

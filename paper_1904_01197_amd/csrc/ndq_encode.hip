@@ -10,6 +10,8 @@
 // tile maxima between the waves of a workgroup.
 #include <hip/hip_runtime.h>
 
+#include <string.h>
+
 #include <type_traits>
 
 #include "ndq.h"
@@ -21,20 +23,77 @@ namespace ndq {
 // ---------------------------------------------------------------------------
 // Encoder: Algorithm 1 worker block (DQSG) / Algorithm 2 worker block (NDQSG)
 // ---------------------------------------------------------------------------
-struct EncodeArgs {
+// One vector to encode.
+struct EncodeJob {
     const void* g;
     unsigned char* codes;
-    float* steps;          // written (fused / preset) or read (two-pass, or a step handed over in device memory)
-    Tiling tl;
+    float* steps;          // written (fused, preset, handed over) or already there (two-pass)
+    const float* step_in;  // where a step that is not found here is read: `steps`, or the one handed over
     uint64_t index0;       // dither offset of element 0
-    uint64_t total_bytes;  // size of the packed stream incl. zero padding
     DitherStream ds;
+};
+
+// What a wave works with: its vector, and what all vectors of the launch share.
+struct EncodeArgs : EncodeJob {
+    Tiling tl;
+    uint64_t total_bytes;  // size of the packed stream incl. zero padding
     Quant qp;
     float preset_step;     // > 0: bucket == 0 with a caller-set step
     uint32_t rows_log2;    // MULTI: a bucket is 2^rows_log2 rows of a tile
     uint32_t num_buckets;  // MULTI: buckets in the call (steps to write)
     uint32_t waves_log2;   // FUSED, not MULTI: a bucket is 2^waves_log2 tiles of one workgroup
 };
+
+// A launch encodes up to kEncJobs vectors of one length, type and quantizer (blockIdx.y, or
+// the tiles of all of them in turn in the streaming kernel): the vectors of a group of
+// workers, or the one of a single call.
+constexpr uint32_t kEncJobs = 16;
+struct EncodeBatch {
+    EncodeArgs common;     // its EncodeJob part is unused
+    EncodeJob job[kEncJobs];
+    uint32_t jobs;
+};
+// read through the constant address space: scalar loads, no copy of the arguments
+typedef const __attribute__((address_space(4))) EncodeBatch* EncodeBatchPtr;
+
+__device__ __forceinline__ void select_job(EncodeArgs& a, EncodeBatchPtr b, uint32_t j)
+{
+    a.g = b->job[j].g;
+    a.codes = b->job[j].codes;
+    a.steps = b->job[j].steps;
+    a.step_in = b->job[j].step_in;
+    a.index0 = b->job[j].index0;
+    a.ds.key0 = b->job[j].ds.key0;
+    a.ds.key1 = b->job[j].ds.key1;
+    a.ds.step = b->job[j].ds.step;
+    a.ds.worker = b->job[j].ds.worker;
+}
+
+__device__ __forceinline__ EncodeArgs common_args(EncodeBatchPtr b)
+{
+    EncodeArgs a;
+    a.tl.n = b->common.tl.n;
+    a.tl.bucket_len = b->common.tl.bucket_len;
+    a.tl.tiles_per_bucket = b->common.tl.tiles_per_bucket;
+    a.tl.total_tiles = b->common.tl.total_tiles;
+    a.total_bytes = b->common.total_bytes;
+    a.qp.q_min_f = b->common.qp.q_min_f;
+    a.qp.q_max_f = b->common.qp.q_max_f;
+    a.qp.q_min = b->common.qp.q_min;
+    a.qp.levels = b->common.qp.levels;
+    a.qp.M = b->common.qp.M;
+    a.qp.M_f = b->common.qp.M_f;
+    a.qp.inv_M_f = b->common.qp.inv_M_f;
+    a.qp.bits = b->common.qp.bits;
+    a.qp.pack_bias = b->common.qp.pack_bias;
+    a.qp.alpha = b->common.qp.alpha;
+    a.qp.beta = b->common.qp.beta;
+    a.preset_step = b->common.preset_step;
+    a.rows_log2 = b->common.rows_log2;
+    a.num_buckets = b->common.num_buckets;
+    a.waves_log2 = b->common.waves_log2;
+    return a;
+}
 
 template <int DT> struct EncRows { static constexpr int R = kEncLoads / Elem<DT>::V; };
 template <int DT> struct EncTile { static constexpr uint32_t N = kWave * kLaneElems * EncRows<DT>::R; };
@@ -45,14 +104,14 @@ template <int DT> struct TileRegs { typename Elem<DT>::Row row[EncRows<DT>::R]; 
 
 // Issues all 16-byte loads of a tile back to back.  FULL: every element of the
 // tile is valid, no guards; otherwise elements past the end read as zero.
-template <int DT, bool FULL>
+template <int DT, bool FULL, bool KEEP = false>
 __device__ __forceinline__ void load_tile(const void* g, const TileRef& t, int lane, TileRegs<DT>& regs)
 {
     using T = Elem<DT>;
     const typename T::scalar* tile = (const typename T::scalar*)g + t.start;
 #pragma unroll
     for (int r = 0; r < EncRows<DT>::R; ++r)
-        regs.row[r] = load_row<DT, FULL>(tile, (uint32_t)(r * kWave + lane) * kLaneElems, t.len);
+        regs.row[r] = load_row<DT, FULL, KEEP>(tile, (uint32_t)(r * kWave + lane) * kLaneElems, t.len);
 }
 
 // folds the lane's share of a tile into its running max |g|
@@ -125,12 +184,11 @@ __device__ __forceinline__ void encode_tile(const EncodeArgs& a, const TileRef& 
             step = step_from_kappa(kappa, a.qp.levels);
             if (REFILL) a.steps[t.bucket] = step;     // every lane, the same value: no branch around the store
             else if (lane == 0 && writes_step) a.steps[t.bucket] = step;
-        } else if (a.preset_step > 0.0f) {
-            step = a.preset_step;
-            // (the streaming kernel writes the preset step itself, outside its tile loop)
-            if (!REFILL && tile_id == 0 && lane == 0) a.steps[0] = step;
         } else {
-            step = a.steps[t.bucket];
+            step = a.preset_step > 0.0f ? a.preset_step : a.step_in[t.bucket];
+            // one step for the whole vector, preset or handed over: the worker's transmitted step
+            // (the streaming kernel writes it itself, outside its tile loop)
+            if (!REFILL && tile_id == 0 && lane == 0) a.steps[0] = step;
         }
         const float inv_all = a.qp.alpha * inv_step(step);   // alpha = 1 unless a nested worker shrinks
 #pragma unroll
@@ -246,8 +304,11 @@ template <int DT> struct EncWaves { static constexpr int W = DT == 1 ? NDQ_ENC_W
 // row's codes are then straight-line code); 0: any width, read from the arguments.
 template <int DT, int MODE, bool FUSED, bool MULTI, bool BLOCK, int BITSW = 0>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(EncWaves<DT>::W)))
-void encode_kernel(EncodeArgs a)
+void encode_kernel(EncodeBatch by_value)
 {
+    const EncodeBatchPtr batch = (EncodeBatchPtr)__builtin_amdgcn_kernarg_segment_ptr();
+    EncodeArgs a = common_args(batch);
+    select_job(a, batch, blockIdx.y);
     constexpr uint32_t TILE = EncTile<DT>::N;
     __shared__ __align__(16) unsigned char stage_all[kWavesPerBlock][TILE + 8];
     const int lane = threadIdx.x & (kWave - 1);
@@ -336,7 +397,7 @@ __device__ __forceinline__ void stage_to_stream_full(const EncodeArgs& a, const 
 constexpr int kStreamWaves = NDQ_STREAM_WAVES;   // per SIMD
 
 template <int DT>
-__device__ __forceinline__ TileRef stream_tile_ref(const EncodeArgs& a, uint32_t tile_id, bool fused)
+__device__ __forceinline__ TileRef stream_tile_ref(uint32_t tile_id, bool fused)
 {
     TileRef t;
     t.start = (uint64_t)tile_id * EncTile<DT>::N;
@@ -347,40 +408,52 @@ __device__ __forceinline__ TileRef stream_tile_ref(const EncodeArgs& a, uint32_t
 
 template <int DT, int MODE, bool FUSED, int BITSW>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kStreamWaves, kStreamWaves)))
-void encode_stream_kernel(EncodeArgs a, uint32_t full_tiles)
+void encode_stream_kernel(EncodeBatch by_value, uint32_t full_tiles)
 {
     constexpr uint32_t TILE = EncTile<DT>::N;
     __shared__ __align__(16) unsigned char stage_all[kWavesPerBlock][TILE + 8];
+    const EncodeBatchPtr batch = (EncodeBatchPtr)__builtin_amdgcn_kernarg_segment_ptr();
+    EncodeArgs a = common_args(batch);
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     unsigned char* stage = stage_all[wave];
     const uint32_t stride = gridDim.x * kWavesPerBlock;
     const uint32_t first = blockIdx.x * kWavesPerBlock + wave;
-    if (!FUSED && a.preset_step > 0.0f && first == 0u && lane == 0) a.steps[0] = a.preset_step;
-    if (first < full_tiles) {
+    const uint32_t jobs = batch->jobs;
+    const uint32_t all_tiles = jobs * full_tiles;      // job after job: tile `t` of job j is j * full_tiles + t
+    if (!FUSED && first < jobs) {                      // the transmitted step of one vector
+        select_job(a, batch, first);
+        const float step = a.preset_step > 0.0f ? a.preset_step : a.step_in[0];
+        if (lane == 0) a.steps[0] = step;
+    }
+    if (first < all_tiles) {
         // Every pass over a tile issues exactly one load per row, also the last one (then of the
         // vector's first 16 bytes per row, all lanes alike: one cache line, no traffic to speak
         // of), and the code width is a compile-time constant, so that the number of memory
         // operations in flight at every wait is known at compile time: they complete in order,
         // and a wait must cover a row's load but not the loads and stores issued after it.
         TileRegs<DT> regs;
-        uint32_t cur = first;
+        uint32_t cur = first, job = first / full_tiles, tile = first - job * full_tiles;
         // The arbiter serves the oldest wave of a SIMD first, so left alone the waves of a
         // SIMD finish one after the other and the last one runs alone, at a third of the
         // SIMD's rate.  Lower a wave's priority as it gets ahead: they finish together.
-        const uint32_t my_tiles = (full_tiles - first + stride - 1) / stride;
+        const uint32_t my_tiles = (all_tiles - first + stride - 1) / stride;
         uint32_t done = 0;
         __builtin_amdgcn_s_setprio(3);
-        load_tile<DT, true>(a.g, stream_tile_ref<DT>(a, cur, FUSED), lane, regs);
+        select_job(a, batch, job);
+        load_tile<DT, true>(a.g, stream_tile_ref<DT>(tile, FUSED), lane, regs);
         for (;;) {
             const uint32_t nxt = cur + stride;
-            const bool more = nxt < full_tiles;
-            const TileRef t = stream_tile_ref<DT>(a, cur, FUSED);
+            const bool more = nxt < all_tiles;
+            uint32_t next_job = job, next_tile = tile + stride;
+            while (next_tile >= full_tiles && more) { next_tile -= full_tiles; ++next_job; }
+            const void* next_g = batch->job[more ? next_job : job].g;
+            const TileRef t = stream_tile_ref<DT>(tile, FUSED);
             const float kappa = FUSED ? tile_max<DT>(regs) : 0.0f;
             wave_lds_sync();     // the previous tile's copy-out has read the stage
             encode_tile<DT, MODE, FUSED, true, false, BITSW, true>(
-                a, t, cur, regs, kappa, true, stage, lane,
-                (const typename Elem<DT>::scalar*)a.g + (uint64_t)(more ? nxt : 0u) * TILE, more ? lane : 0);
+                a, t, tile, regs, kappa, true, stage, lane,
+                (const typename Elem<DT>::scalar*)next_g + (uint64_t)(more ? next_tile : 0u) * TILE, more ? lane : 0);
             wave_lds_sync();
             stage_to_stream_full<DT, BITSW>(a, t, stage, lane);
             if (!more) break;
@@ -389,20 +462,25 @@ void encode_stream_kernel(EncodeArgs a, uint32_t full_tiles)
             if (quarter == 1u) __builtin_amdgcn_s_setprio(2);
             else if (quarter == 2u) __builtin_amdgcn_s_setprio(1);
             else if (quarter >= 3u) __builtin_amdgcn_s_setprio(0);
-            cur = nxt;
+            cur = nxt; job = next_job; tile = next_tile;
+            select_job(a, batch, job);
         }
     }
-    // the ragged last tile, if there is one, by the wave whose turn it would be
-    if (full_tiles < a.tl.total_tiles && full_tiles % stride == first) {
-        const TileRef t = locate_tile(a.tl, full_tiles, TILE);
-        if (t.len != 0) {
-            TileRegs<DT> regs;
-            load_tile<DT, false>(a.g, t, lane, regs);
-            const float kappa = FUSED ? tile_max<DT>(regs) : 0.0f;
-            wave_lds_sync();
-            encode_tile<DT, MODE, FUSED, false, false, BITSW>(a, t, full_tiles, regs, kappa, true, stage, lane);
-            wave_lds_sync();
-            stage_to_stream(a, t, BITSW ? (uint32_t)BITSW : a.qp.bits, stage, lane);
+    // the ragged last tile of every vector, if there is one, by the wave whose turn it would be
+    if (full_tiles < a.tl.total_tiles) {
+        for (uint32_t j = 0; j < jobs; ++j) {
+            if ((all_tiles + j) % stride != first) continue;
+            select_job(a, batch, j);
+            const TileRef t = locate_tile(a.tl, full_tiles, TILE);
+            if (t.len != 0) {
+                TileRegs<DT> regs;
+                load_tile<DT, false>(a.g, t, lane, regs);
+                const float kappa = FUSED ? tile_max<DT>(regs) : 0.0f;
+                wave_lds_sync();
+                encode_tile<DT, MODE, FUSED, false, false, BITSW>(a, t, full_tiles, regs, kappa, true, stage, lane);
+                wave_lds_sync();
+                stage_to_stream(a, t, BITSW ? (uint32_t)BITSW : a.qp.bits, stage, lane);
+            }
         }
     }
 }
@@ -410,10 +488,22 @@ void encode_stream_kernel(EncodeArgs a, uint32_t full_tiles)
 // ---------------------------------------------------------------------------
 // Max-norm per bucket (two-pass path and ndq_absmax)
 // ---------------------------------------------------------------------------
-__global__ void fill_zero_kernel(uint32_t* p, uint64_t n)
+struct AbsmaxBatch {
+    const void* g[kEncJobs];        // blockIdx.y: vectors of one length and type
+    uint32_t* kappa_bits[kEncJobs]; // K words each
+    uint32_t levels[kEncJobs];
+    float* parts[kEncJobs];         // absmax_span_kernel: K * blocks_per_bucket floats each; null: atomics
+    Tiling tl;
+    uint64_t K;                     // buckets per vector
+    uint32_t blocks_per_bucket;     // absmax_span_kernel
+};
+typedef const __attribute__((address_space(4))) AbsmaxBatch* AbsmaxBatchPtr;
+
+__global__ void fill_zero_kernel(AbsmaxBatch by_value)
 {
+    const AbsmaxBatchPtr b = (AbsmaxBatchPtr)__builtin_amdgcn_kernarg_segment_ptr();
     const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0u;
+    if (i < b->K) b->kappa_bits[blockIdx.y][i] = 0u;
 }
 
 // levels != 0: the bucket's step is wanted, not its max-norm.  The step rule is monotone in
@@ -427,34 +517,41 @@ __device__ __forceinline__ uint32_t absmax_word(float m, uint32_t levels)
 }
 
 template <int DT>
-__global__ __launch_bounds__(kBlock) void absmax_kernel(const void* g, Tiling tl, uint32_t* kappa_bits,
-                                                       uint32_t levels)
+__global__ __launch_bounds__(kBlock) void absmax_kernel(AbsmaxBatch by_value)
 {
-    using T = Elem<DT>;
     constexpr uint32_t TILE = EncTile<DT>::N;
+    const AbsmaxBatchPtr b = (AbsmaxBatchPtr)__builtin_amdgcn_kernarg_segment_ptr();
+    const Tiling tl = {b->tl.n, b->tl.bucket_len, b->tl.tiles_per_bucket, b->tl.total_tiles};
+    const void* g = b->g[blockIdx.y];
     const int lane = threadIdx.x & (kWave - 1);
     const uint32_t tile_id =
         blockIdx.x * kWavesPerBlock + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const TileRef t = locate_tile(tl, tile_id, TILE);
     if (t.len == 0) return;
     TileRegs<DT> regs;
-    if (t.len == TILE) load_tile<DT, true>(g, t, lane, regs);
-    else load_tile<DT, false>(g, t, lane, regs);
+    if (t.len == TILE) load_tile<DT, true, true>(g, t, lane, regs);
+    else load_tile<DT, false, true>(g, t, lane, regs);
     const float m = tile_max<DT>(regs);
-    if (lane == 0) atomicMax(kappa_bits + t.bucket, absmax_word(m, levels));
+    if (lane == 0) atomicMax(b->kappa_bits[blockIdx.y] + t.bucket, absmax_word(m, b->levels[blockIdx.y]));
 }
 
-// The same for buckets of many tiles (a whole vector at the extreme), where one
-// atomic per tile would serialize every tile on one address: a workgroup's
-// waves stride over the bucket's tiles with the running max in registers, and
-// the workgroup issues a single atomic at the end.
+// The same for buckets of many tiles (a whole vector at the extreme): a workgroup's
+// waves stride over the bucket's tiles with the running max in registers, and each
+// workgroup leaves one float.  Atomics on one address are served one after the other,
+// about 18 ns each (a vector of 11 M binary32 elements: 11.5 us with 256 workgroups, 12,
+// 18 and 27 us with 512, 1,024 and 1,365, which is the number that streams fastest), so an
+// encoder's pass stores its parts and absmax_finish_kernel reduces them; the parts
+// lie in the vector's code stream, which the encoder overwrites afterwards.
+// ndq_absmax has no such memory: few workgroups, one atomic each.
 template <int DT>
-__global__ __launch_bounds__(kBlock) void absmax_span_kernel(const void* g, Tiling tl, uint32_t* kappa_bits,
-                                                            uint32_t blocks_per_bucket, uint32_t levels)
+__global__ __launch_bounds__(kBlock) void absmax_span_kernel(AbsmaxBatch by_value)
 {
     using T = Elem<DT>;
     constexpr uint32_t TILE = EncTile<DT>::N;
-    constexpr int ROWS = EncRows<DT>::R;
+    const AbsmaxBatchPtr b = (AbsmaxBatchPtr)__builtin_amdgcn_kernarg_segment_ptr();
+    const Tiling tl = {b->tl.n, b->tl.bucket_len, b->tl.tiles_per_bucket, b->tl.total_tiles};
+    const void* g = b->g[blockIdx.y];
+    const uint32_t blocks_per_bucket = b->blocks_per_bucket;
     __shared__ float part[kWavesPerBlock];
     const int lane = threadIdx.x & (kWave - 1);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -466,8 +563,8 @@ __global__ __launch_bounds__(kBlock) void absmax_span_kernel(const void* g, Tili
         const TileRef t = locate_tile(tl, bucket * tl.tiles_per_bucket + j, TILE);
         if (t.len == 0) break;   // past the end of the vector: so are this wave's later tiles
         TileRegs<DT> regs;
-        if (t.len == TILE) load_tile<DT, true>(g, t, lane, regs);
-        else load_tile<DT, false>(g, t, lane, regs);
+        if (t.len == TILE) load_tile<DT, true, true>(g, t, lane, regs);
+        else load_tile<DT, false, true>(g, t, lane, regs);
         acc = lane_max<DT>(acc, regs);
     }
     const float m = wave_max(T::max_final(acc));
@@ -477,46 +574,70 @@ __global__ __launch_bounds__(kBlock) void absmax_span_kernel(const void* g, Tili
         float all = part[0];
 #pragma unroll
         for (int w = 1; w < kWavesPerBlock; ++w) all = __builtin_fmaxf(all, part[w]);
-        atomicMax(kappa_bits + bucket, absmax_word(all, levels));
+        float* parts = b->parts[blockIdx.y];
+        if (parts) parts[blockIdx.x] = all;
+        else atomicMax(b->kappa_bits[blockIdx.y] + bucket, absmax_word(all, b->levels[blockIdx.y]));
     }
 }
 
-// A step that already lies in device memory becomes this worker's transmitted step.
-__global__ void copy_step_kernel(const float* step_in, float* steps)
+// The step of one bucket from the parts absmax_span_kernel left.
+__global__ __launch_bounds__(kBlock) void absmax_finish_kernel(AbsmaxBatch by_value)
 {
-    if (threadIdx.x == 0 && blockIdx.x == 0) steps[0] = step_in[0];
+    const AbsmaxBatchPtr b = (AbsmaxBatchPtr)__builtin_amdgcn_kernarg_segment_ptr();
+    const uint32_t count = b->blocks_per_bucket;
+    const float* parts = b->parts[blockIdx.y] + (size_t)blockIdx.x * count;
+    __shared__ float part[kWavesPerBlock];
+    float m = 0.0f;
+    for (uint32_t i = threadIdx.x; i < count; i += kBlock) m = __builtin_fmaxf(m, parts[i]);
+    m = wave_max(m);
+    if ((threadIdx.x & (kWave - 1)) == 0u) part[threadIdx.x / kWave] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        float all = part[0];
+#pragma unroll
+        for (int w = 1; w < kWavesPerBlock; ++w) all = __builtin_fmaxf(all, part[w]);
+        b->kappa_bits[blockIdx.y][blockIdx.x] = absmax_word(all, b->levels[blockIdx.y]);
+    }
 }
 
 // ---------------------------------------------------------------------------
 // Host side: dispatch
 // ---------------------------------------------------------------------------
+// b: vectors, words, levels, tiling and (for an encoder) memory for the parts are set.
 template <int DT>
-static int run_absmax(const void* g, const Tiling& tl, uint64_t K, float* kappa, uint32_t levels, hipStream_t s)
+static int run_absmax(AbsmaxBatch& b, uint32_t jobs, hipStream_t s)
 {
-    if (launch(fill_zero_kernel, dim3((uint32_t)((K + 255) / 256)), dim3(256), s, (uint32_t*)kappa, K) != NDQ_OK)
+    // many tiles per bucket: workgroups that stride over one.  With memory for the parts (4 bytes
+    // per workgroup, and a workgroup has at least one tile: 256 bytes of 1-bit codes) a full chip
+    // of waves; with atomics one workgroup per compute unit.
+    constexpr uint32_t kSpanMinTiles = 16, kSpanMaxBuckets = 2048;
+    const uint32_t target = b.parts[0] ? 2048u : 256u;
+    const bool span = b.tl.tiles_per_bucket >= kSpanMinTiles && b.K * jobs <= kSpanMaxBuckets;
+    const bool fill = !(span && b.parts[0]);
+    if (fill && launch(fill_zero_kernel, dim3((uint32_t)((b.K + 255) / 256), jobs), dim3(256), s, b) != NDQ_OK)
         return NDQ_ELAUNCH;
-    // many tiles per bucket: a few hundred tiles per workgroup, about 4096 workgroups in all
-    constexpr uint32_t kSpanMinTiles = 64, kSpanTarget = 4096;
-    if (tl.tiles_per_bucket >= kSpanMinTiles && K <= kSpanTarget) {
-        uint32_t per_bucket = kSpanTarget / (uint32_t)K;
-        const uint32_t most = tl.tiles_per_bucket / (2 * kWavesPerBlock);   // at least two tiles per wave
+    if (span) {
+        uint32_t per_bucket = target / (uint32_t)(b.K * jobs);
+        const uint32_t most = blocks_for(b.tl.tiles_per_bucket);
         if (per_bucket > most) per_bucket = most;
-        if (per_bucket < 1) per_bucket = 1;
-        return launch(absmax_span_kernel<DT>, dim3((uint32_t)K * per_bucket), dim3(kBlock), s, g, tl,
-                      (uint32_t*)kappa, per_bucket, levels);
+        if (per_bucket < 1u) per_bucket = 1u;
+        b.blocks_per_bucket = per_bucket;
+        if (launch(absmax_span_kernel<DT>, dim3((uint32_t)b.K * per_bucket, jobs), dim3(kBlock), s, b) != NDQ_OK)
+            return NDQ_ELAUNCH;
+        if (!b.parts[0]) return NDQ_OK;
+        return launch(absmax_finish_kernel, dim3((uint32_t)b.K, jobs), dim3(kBlock), s, b);
     }
-    return launch(absmax_kernel<DT>, dim3(blocks_for(tl.total_tiles)), dim3(kBlock), s, g, tl, (uint32_t*)kappa,
-                  levels);
+    return launch(absmax_kernel<DT>, dim3(blocks_for(b.tl.total_tiles), jobs), dim3(kBlock), s, b);
 }
 
 // Waves of the streaming kernel: kStreamWaves on each of the 1,024 SIMDs.
 constexpr uint32_t kStreamSlots = 1024u * kStreamWaves;
 
 template <int DT, int MODE, bool FUSED, int BITSW>
-static int launch_stream(const EncodeArgs& a, uint32_t full_tiles, hipStream_t s)
+static int launch_stream(const EncodeBatch& b, uint32_t full_tiles, hipStream_t s)
 {
-    const uint32_t blocks = persistent_blocks(full_tiles, kStreamSlots);
-    return launch((encode_stream_kernel<DT, MODE, FUSED, BITSW>), dim3(blocks), dim3(kBlock), s, a, full_tiles);
+    const uint32_t blocks = persistent_blocks(full_tiles * b.jobs, kStreamSlots);
+    return launch((encode_stream_kernel<DT, MODE, FUSED, BITSW>), dim3(blocks), dim3(kBlock), s, b, full_tiles);
 }
 
 // The streaming kernel serves vectors cut into whole tiles (a ragged last one aside):
@@ -524,8 +645,9 @@ static int launch_stream(const EncodeArgs& a, uint32_t full_tiles, hipStream_t s
 // the max-norm pass), in the quantizer modes and code widths of the common
 // configurations.  Returns 1 when it does not apply.
 template <int DT, int MODE>
-static int try_stream(const EncodeArgs& a, bool fused, bool multi, uint32_t bucket, hipStream_t s)
+static int try_stream(const EncodeBatch& b, bool fused, bool multi, uint32_t bucket, hipStream_t s)
 {
+    const EncodeArgs& a = b.common;
     constexpr uint32_t TILE = EncTile<DT>::N;
     // binary32 input: one tile per wave is faster at every length (2^27 elements: 112 against 120 us,
     // 25.6 M: 22.8 against 23.2; its tile carries half the arithmetic of a bfloat16 tile per byte, so
@@ -539,68 +661,86 @@ static int try_stream(const EncodeArgs& a, bool fused, bool multi, uint32_t buck
     if (fused != (bucket == TILE)) return 1;
     const uint32_t full_tiles = (uint32_t)(a.tl.n / TILE);
     // shorter vectors: with only a few tiles per wave a fixed share leaves SIMDs idle at the end
-    if (full_tiles == 0u || full_tiles < stream_tuning().enc_min_tiles_per_wave * kStreamSlots) return 1;
+    const uint64_t all_tiles = (uint64_t)full_tiles * b.jobs;
+    if (full_tiles == 0u || all_tiles < stream_tuning().enc_min_tiles_per_wave * kStreamSlots ||
+        all_tiles >= ((uint64_t)1 << 31))
+        return 1;
     const uint32_t bits = a.qp.bits;
     if (bits != 1u && bits != 2u && bits != 4u) return 1;
     if (fused) {
         if constexpr (MODE == kNestedPow2) {
             return 1;      // a preset step comes with bucket == 0
         } else {
-            if (bits == 1u) return launch_stream<DT, MODE, true, 1>(a, full_tiles, s);
-            if (bits == 2u) return launch_stream<DT, MODE, true, 2>(a, full_tiles, s);
-            return launch_stream<DT, MODE, true, 4>(a, full_tiles, s);
+            if (bits == 1u) return launch_stream<DT, MODE, true, 1>(b, full_tiles, s);
+            if (bits == 2u) return launch_stream<DT, MODE, true, 2>(b, full_tiles, s);
+            return launch_stream<DT, MODE, true, 4>(b, full_tiles, s);
         }
     }
-    if (bits == 1u) return launch_stream<DT, MODE, false, 1>(a, full_tiles, s);
-    if (bits == 2u) return launch_stream<DT, MODE, false, 2>(a, full_tiles, s);
-    return launch_stream<DT, MODE, false, 4>(a, full_tiles, s);
+    if (bits == 1u) return launch_stream<DT, MODE, false, 1>(b, full_tiles, s);
+    if (bits == 2u) return launch_stream<DT, MODE, false, 2>(b, full_tiles, s);
+    return launch_stream<DT, MODE, false, 4>(b, full_tiles, s);
     }
 }
 
 template <int DT, int MODE>
-static int run_encode(const EncodeArgs& a, bool fused, bool multi, uint32_t bucket, hipStream_t s)
+static int run_encode(const EncodeBatch& b, bool fused, bool multi, uint32_t bucket, hipStream_t s)
 {
+    const EncodeArgs& a = b.common;
 #ifndef NDQ_NO_STREAM_ENCODER
-    const int rc = try_stream<DT, MODE>(a, fused, multi, bucket, s);
+    const int rc = try_stream<DT, MODE>(b, fused, multi, bucket, s);
     if (rc != 1) return rc;
 #endif
-    const dim3 grid(blocks_for(a.tl.total_tiles)), block(kBlock);
-    if (a.waves_log2 != 0u) return launch((encode_kernel<DT, MODE, true, false, true>), grid, block, s, a);
-    if (multi) return launch((encode_kernel<DT, MODE, true, true, false>), grid, block, s, a);
+    const dim3 grid(blocks_for(a.tl.total_tiles), b.jobs), block(kBlock);
+    if (a.waves_log2 != 0u) return launch((encode_kernel<DT, MODE, true, false, true>), grid, block, s, b);
+    if (multi) return launch((encode_kernel<DT, MODE, true, true, false>), grid, block, s, b);
     if constexpr (MODE == kDqNarrow || MODE == kNestedPow2Bounded || MODE == kNestedPow2) {
         const uint32_t bits = a.qp.bits;
         if (fused) {
-            if (bits == 1u) return launch((encode_kernel<DT, MODE, true, false, false, 1>), grid, block, s, a);
-            if (bits == 2u) return launch((encode_kernel<DT, MODE, true, false, false, 2>), grid, block, s, a);
-            if (bits == 4u) return launch((encode_kernel<DT, MODE, true, false, false, 4>), grid, block, s, a);
+            if (bits == 1u) return launch((encode_kernel<DT, MODE, true, false, false, 1>), grid, block, s, b);
+            if (bits == 2u) return launch((encode_kernel<DT, MODE, true, false, false, 2>), grid, block, s, b);
+            if (bits == 4u) return launch((encode_kernel<DT, MODE, true, false, false, 4>), grid, block, s, b);
         } else {
-            if (bits == 1u) return launch((encode_kernel<DT, MODE, false, false, false, 1>), grid, block, s, a);
-            if (bits == 2u) return launch((encode_kernel<DT, MODE, false, false, false, 2>), grid, block, s, a);
-            if (bits == 4u) return launch((encode_kernel<DT, MODE, false, false, false, 4>), grid, block, s, a);
+            if (bits == 1u) return launch((encode_kernel<DT, MODE, false, false, false, 1>), grid, block, s, b);
+            if (bits == 2u) return launch((encode_kernel<DT, MODE, false, false, false, 2>), grid, block, s, b);
+            if (bits == 4u) return launch((encode_kernel<DT, MODE, false, false, false, 4>), grid, block, s, b);
         }
     }
-    if (fused) return launch((encode_kernel<DT, MODE, true, false, false>), grid, block, s, a);
-    return launch((encode_kernel<DT, MODE, false, false, false>), grid, block, s, a);
+    if (fused) return launch((encode_kernel<DT, MODE, true, false, false>), grid, block, s, b);
+    return launch((encode_kernel<DT, MODE, false, false, false>), grid, block, s, b);
 }
 
-// step_in != nullptr: one step for the whole vector, read from device memory when the
-// kernels run (bucket and delta are then 0, and `levels` is not used to derive a step).
-static int encode_common(const void* g, int dt, size_t n, float delta, const float* step_in,
-                         uint32_t levels, uint32_t M, bool nested, float alpha, uint32_t bucket,
-                         const ndq_dither* d, void* codes_out, float* steps_out, void* stream)
-{
+// One vector's call, checked and planned.  Vectors whose plans agree in everything but the
+// EncodeJob part share a launch.
+struct EncodePlan {
     EncodeArgs a;
-    int rc = make_quant(levels, M, nested, alpha, &a.qp);
+    int mode;
+    bool fused, multi;
+    bool two_pass;       // the steps come from a max-norm pass of their own
+};
+
+static bool same_launch(const EncodePlan& p, const EncodePlan& q)
+{
+    return p.mode == q.mode && p.two_pass == q.two_pass && p.a.preset_step == q.a.preset_step &&
+           memcmp(&p.a.qp, &q.a.qp, sizeof(Quant)) == 0;   // (length, type and bucket are the call's)
+}
+
+// job.step_in != nullptr: one step for the whole vector, read from device memory when the
+// kernels run (bucket and delta are then not used, nor `levels` to derive a step).
+static int plan_encode(const ndq_encode_job& job, int dt, size_t n, float delta, uint32_t bucket, EncodePlan* plan)
+{
+    EncodeArgs& a = plan->a;
+    const bool nested = job.kind == NDQ_WORKER_NESTED;
+    const uint32_t levels = job.levels;
+    int rc = make_quant(levels, job.M, nested, job.alpha, &a.qp);
     if (rc != NDQ_OK) return rc;
     if (dt != NDQ_F32 && dt != NDQ_BF16) return NDQ_EINVAL;
-    if (!d) return NDQ_EINVAL;
     if (n == 0) return NDQ_OK;
-    if (!g || !codes_out || !steps_out) return NDQ_EINVAL;
+    if (!job.g || !job.codes_out || !job.steps_out) return NDQ_EINVAL;
     if (!(delta == delta)) return NDQ_EINVAL;
     if (n >= kMaxN) return NDQ_EUNSUPPORTED;
-    if (!aligned16(g) || !aligned16(codes_out) || !aligned4(steps_out)) return NDQ_EALIGN;
-    if (step_in && !aligned4(step_in)) return NDQ_EALIGN;
-    if (bucket % 64u != 0u || (d->offset & 7u) != 0u) return NDQ_EALIGN;
+    if (!aligned16(job.g) || !aligned16(job.codes_out) || !aligned4(job.steps_out)) return NDQ_EALIGN;
+    if (job.step_in && !aligned4(job.step_in)) return NDQ_EALIGN;
+    if (bucket % 64u != 0u || (job.dither.offset & 7u) != 0u) return NDQ_EALIGN;
 
     const uint32_t tile = dt == NDQ_F32 ? EncTile<0>::N : EncTile<1>::N;
     // buckets of 1, 2 or 4 whole rows (2, 4 or 8 to a tile) share tiles: the tiling is
@@ -615,50 +755,103 @@ static int encode_common(const void* g, int dt, size_t n, float delta, const flo
     const bool block_fused = kWavesPerBlock == 4 && (bucket == 2u * tile || bucket == 4u * tile);
     a.waves_log2 = block_fused ? (bucket == 2u * tile ? 1u : 2u) : 0u;
     a.num_buckets = (uint32_t)((n + (bucket ? bucket : n) - 1) / (bucket ? bucket : n));
-    a.g = g;
-    a.codes = (unsigned char*)codes_out;
-    a.steps = steps_out;
-    a.index0 = d->offset;
+    a.g = job.g;
+    a.codes = (unsigned char*)job.codes_out;
+    a.steps = job.steps_out;
+    a.step_in = job.step_in ? job.step_in : job.steps_out;
+    a.index0 = job.dither.offset;
     a.total_bytes = packed_bytes(n, a.qp.bits);
-    a.ds = make_stream(d);
-    a.preset_step = (bucket == 0u && delta > 0.0f) ? delta : 0.0f;
-    hipStream_t s = (hipStream_t)stream;
+    a.ds = make_stream(&job.dither);
+    a.preset_step = (bucket == 0u && delta > 0.0f && !job.step_in) ? delta : 0.0f;
 
-    const bool fused = (bucket != 0u && bucket <= tile) || block_fused;   // (multi implies fused)
-    if (step_in) {
-        // the kernels read steps_out[0], as after the max-norm passes below
-        if (step_in != steps_out &&
-            launch(copy_step_kernel, dim3(1), dim3(kWave), s, step_in, steps_out) != NDQ_OK)
-            return NDQ_ELAUNCH;
-    } else if (!fused && a.preset_step == 0.0f) {
-        // two passes: the step of every bucket from its max-norm, then the encoder reads them
-        const uint64_t K = bucket ? (n + bucket - 1) / bucket : 1;
-        rc = dt == NDQ_F32 ? run_absmax<0>(g, a.tl, K, steps_out, levels, s)
-                           : run_absmax<1>(g, a.tl, K, steps_out, levels, s);
-        if (rc != NDQ_OK) return rc;
-    }
+    plan->multi = multi;
+    plan->fused = (bucket != 0u && bucket <= tile) || block_fused;   // (multi implies fused)
+    plan->two_pass = !job.step_in && !plan->fused && a.preset_step == 0.0f;
 #ifndef NDQ_NARROW_MAX_BITS
 #define NDQ_NARROW_MAX_BITS 6u
 #endif
     // a step derived from the data bounds |g/Delta|; a caller's step (preset, or in device memory) does not
-    const bool own_step = a.preset_step == 0.0f && !step_in;
-    const int mode = !nested ? (a.qp.bits <= NDQ_NARROW_MAX_BITS ? kDqNarrow : kDq)
-                             : (!is_pow2(M) ? ((!own_step || a.qp.bits > 6u) ? kNestedAnyM : kNestedAnyMBounded)
+    const bool own_step = a.preset_step == 0.0f && !job.step_in;
+    plan->mode = !nested ? (a.qp.bits <= NDQ_NARROW_MAX_BITS ? kDqNarrow : kDq)
+                         : (!is_pow2(job.M) ? ((!own_step || a.qp.bits > 6u) ? kNestedAnyM : kNestedAnyMBounded)
                                             : (!own_step ? kNestedPow2 : kNestedPow2Bounded));
-    if (dt == NDQ_F32) {
-        if (mode == kDqNarrow) return run_encode<0, kDqNarrow>(a, fused, multi, bucket, s);
-        if (mode == kDq) return run_encode<0, kDq>(a, fused, multi, bucket, s);
-        if (mode == kNestedPow2) return run_encode<0, kNestedPow2>(a, fused, multi, bucket, s);
-        if (mode == kNestedPow2Bounded) return run_encode<0, kNestedPow2Bounded>(a, fused, multi, bucket, s);
-        if (mode == kNestedAnyMBounded) return run_encode<0, kNestedAnyMBounded>(a, fused, multi, bucket, s);
-        return run_encode<0, kNestedAnyM>(a, fused, multi, bucket, s);
+    return NDQ_OK;
+}
+
+template <int DT>
+static int run_encode_mode(const EncodeBatch& b, const EncodePlan& p, uint32_t bucket, hipStream_t s)
+{
+    if (p.mode == kDqNarrow) return run_encode<DT, kDqNarrow>(b, p.fused, p.multi, bucket, s);
+    if (p.mode == kDq) return run_encode<DT, kDq>(b, p.fused, p.multi, bucket, s);
+    if (p.mode == kNestedPow2) return run_encode<DT, kNestedPow2>(b, p.fused, p.multi, bucket, s);
+    if (p.mode == kNestedPow2Bounded) return run_encode<DT, kNestedPow2Bounded>(b, p.fused, p.multi, bucket, s);
+    if (p.mode == kNestedAnyMBounded) return run_encode<DT, kNestedAnyMBounded>(b, p.fused, p.multi, bucket, s);
+    return run_encode<DT, kNestedAnyM>(b, p.fused, p.multi, bucket, s);
+}
+
+// Up to kEncJobs planned vectors: first the max-norm passes of those that need one, all in
+// one launch, then the encoders, one launch for all vectors of a kind.  Launches of many
+// vectors instead of one per vector: a launch ramps up and drains once, and the next
+// vector's loads overlap with this one's arithmetic.
+static int run_plans(const EncodePlan* plans, uint32_t jobs, int dt, uint32_t bucket, hipStream_t s)
+{
+    AbsmaxBatch m;
+    uint32_t need = 0;
+    for (uint32_t j = 0; j < jobs; ++j) {
+        if (!plans[j].two_pass) continue;
+        m.g[need] = plans[j].a.g;
+        m.kappa_bits[need] = (uint32_t*)plans[j].a.steps;
+        m.levels[need] = plans[j].a.qp.levels;
+        m.parts[need] = (float*)plans[j].a.codes;
+        ++need;
     }
-    if (mode == kDqNarrow) return run_encode<1, kDqNarrow>(a, fused, multi, bucket, s);
-    if (mode == kDq) return run_encode<1, kDq>(a, fused, multi, bucket, s);
-    if (mode == kNestedPow2) return run_encode<1, kNestedPow2>(a, fused, multi, bucket, s);
-    if (mode == kNestedPow2Bounded) return run_encode<1, kNestedPow2Bounded>(a, fused, multi, bucket, s);
-    if (mode == kNestedAnyMBounded) return run_encode<1, kNestedAnyMBounded>(a, fused, multi, bucket, s);
-    return run_encode<1, kNestedAnyM>(a, fused, multi, bucket, s);
+    if (need != 0u) {
+        m.tl = plans[0].a.tl;
+        m.K = plans[0].a.num_buckets;
+        const int rc = dt == NDQ_F32 ? run_absmax<0>(m, need, s) : run_absmax<1>(m, need, s);
+        if (rc != NDQ_OK) return rc;
+    }
+    bool done[kEncJobs] = {};
+    for (uint32_t j = 0; j < jobs; ++j) {
+        if (done[j]) continue;
+        EncodeBatch b;
+        b.common = plans[j].a;
+        b.jobs = 0u;
+        for (uint32_t k = j; k < jobs; ++k) {
+            if (done[k] || !same_launch(plans[j], plans[k])) continue;
+            b.job[b.jobs++] = plans[k].a;
+            done[k] = true;
+        }
+        const int rc = dt == NDQ_F32 ? run_encode_mode<0>(b, plans[j], bucket, s)
+                                     : run_encode_mode<1>(b, plans[j], bucket, s);
+        if (rc != NDQ_OK) return rc;
+    }
+    return NDQ_OK;
+}
+
+// one vector
+static int encode_single(const ndq_encode_job& job, int dt, size_t n, float delta, uint32_t bucket, void* stream)
+{
+    EncodePlan p;
+    const int rc = plan_encode(job, dt, n, delta, bucket, &p);
+    if (rc != NDQ_OK || n == 0) return rc;
+    return run_plans(&p, 1u, dt, bucket, (hipStream_t)stream);
+}
+
+static bool encode_job_from(ndq_encode_job* job, const void* g, const float* step_in, uint32_t levels, uint32_t M,
+                            bool nested, float alpha, const ndq_dither* d, void* codes_out, float* steps_out)
+{
+    if (!d) return false;
+    job->g = g;
+    job->codes_out = codes_out;
+    job->steps_out = steps_out;
+    job->step_in = step_in;
+    job->kind = nested ? NDQ_WORKER_NESTED : NDQ_WORKER_DQ;
+    job->levels = levels;
+    job->M = M;
+    job->alpha = alpha;
+    job->dither = *d;
+    return true;
 }
 
 }  // namespace ndq
@@ -674,52 +867,94 @@ int ndq_absmax(const void* g, int dt, size_t n, uint32_t bucket, float* kappa_ou
     if (n >= kMaxN) return NDQ_EUNSUPPORTED;
     if (!aligned4(kappa_out) || bucket % 64u != 0u) return NDQ_EALIGN;
     hipStream_t s = (hipStream_t)stream;
+    AbsmaxBatch b;
+    b.g[0] = g;
+    b.kappa_bits[0] = (uint32_t*)kappa_out;
+    b.levels[0] = 0u;
+    b.parts[0] = nullptr;
+    b.K = bucket ? (n + bucket - 1) / bucket : 1;
     if (n == 0) {   // one (empty) bucket: its max-norm is 0
         if (bucket != 0u) return NDQ_OK;
-        return launch(fill_zero_kernel, dim3(1), dim3(256), s, (uint32_t*)kappa_out, (uint64_t)1);
+        return launch(fill_zero_kernel, dim3(1), dim3(256), s, b);
     }
     if (!g) return NDQ_EINVAL;
     if (!aligned16(g)) return NDQ_EALIGN;
-    Tiling tl;
     const uint32_t tile = dt == NDQ_F32 ? EncTile<0>::N : EncTile<1>::N;
-    int rc = make_tiling(n, bucket, tile, &tl);
+    int rc = make_tiling(n, bucket, tile, &b.tl);
     if (rc != NDQ_OK) return rc;
+    return dt == NDQ_F32 ? run_absmax<0>(b, 1u, s) : run_absmax<1>(b, 1u, s);
+}
+
+int ndq_encode_workers(const ndq_encode_job* jobs, uint32_t W, int dt, size_t n, float delta, uint32_t bucket,
+                       void* stream)
+{
+    using namespace ndq;
+    if (!jobs || W < 1u || W > 1024u) return NDQ_EINVAL;
+    EncodePlan plans[kEncJobs];
+    for (uint32_t w = 0; w < W; ++w) {
+        if (jobs[w].kind != NDQ_WORKER_DQ && jobs[w].kind != NDQ_WORKER_NESTED) return NDQ_EINVAL;
+        if (jobs[w].step_in && bucket != 0u) return NDQ_EINVAL;     // one step belongs to one bucket
+        const int rc = plan_encode(jobs[w], dt, n, delta, bucket, &plans[0]);
+        if (rc != NDQ_OK) return rc;
+    }
+    if (n == 0) return NDQ_OK;
     const uint64_t K = bucket ? (n + bucket - 1) / bucket : 1;
-    return dt == NDQ_F32 ? run_absmax<0>(g, tl, K, kappa_out, 0u, s) : run_absmax<1>(g, tl, K, kappa_out, 0u, s);
+    for (uint32_t w0 = 0; w0 < W;) {
+        uint32_t count = 0;
+        for (; w0 + count < W && count < kEncJobs; ++count) {
+            const ndq_encode_job& job = jobs[w0 + count];
+            // a step handed over by an earlier worker of this call: there after the max-norm
+            // passes, or else only after that worker's encoder, which then has to be enqueued first
+            bool waits = false;
+            for (uint32_t k = 0; k < count && job.step_in; ++k)
+                waits = waits || (!plans[k].two_pass && job.step_in >= plans[k].a.steps &&
+                                  job.step_in < plans[k].a.steps + K);
+            if (waits) break;
+            plan_encode(job, dt, n, delta, bucket, &plans[count]);
+        }
+        const int rc = run_plans(plans, count, dt, bucket, (hipStream_t)stream);
+        if (rc != NDQ_OK) return rc;
+        w0 += count;
+    }
+    return NDQ_OK;
 }
 
 int ndq_dq_encode(const void* g, int dt, size_t n, float delta, uint32_t levels,
                   uint32_t bucket, const ndq_dither* d, void* codes_out, float* steps_out,
                   void* stream)
 {
-    return ndq::encode_common(g, dt, n, delta, nullptr, levels, 0u, false, 1.0f, bucket, d, codes_out,
-                              steps_out, stream);
+    ndq_encode_job job;
+    if (!ndq::encode_job_from(&job, g, nullptr, levels, 0u, false, 1.0f, d, codes_out, steps_out)) return NDQ_EINVAL;
+    return ndq::encode_single(job, dt, n, delta, bucket, stream);
 }
 
 int ndq_dq_encode_with_step(const void* g, int dt, size_t n, const float* step_in, uint32_t levels,
                             const ndq_dither* d, void* codes_out, float* steps_out, void* stream)
 {
+    ndq_encode_job job;
     if (!step_in && n != 0) return NDQ_EINVAL;
-    return ndq::encode_common(g, dt, n, 0.0f, step_in, levels, 0u, false, 1.0f, 0u, d, codes_out,
-                              steps_out, stream);
+    if (!ndq::encode_job_from(&job, g, step_in, levels, 0u, false, 1.0f, d, codes_out, steps_out)) return NDQ_EINVAL;
+    return ndq::encode_single(job, dt, n, 0.0f, 0u, stream);
 }
 
 int ndq_nested_encode(const void* g, int dt, size_t n, float delta, uint32_t levels,
                       uint32_t M, float alpha, uint32_t bucket, const ndq_dither* d,
                       void* codes_out, float* steps_out, void* stream)
 {
-    return ndq::encode_common(g, dt, n, delta, nullptr, levels, M, true, alpha, bucket, d, codes_out,
-                              steps_out, stream);
+    ndq_encode_job job;
+    if (!ndq::encode_job_from(&job, g, nullptr, levels, M, true, alpha, d, codes_out, steps_out)) return NDQ_EINVAL;
+    return ndq::encode_single(job, dt, n, delta, bucket, stream);
 }
 
 int ndq_nested_encode_with_step(const void* g, int dt, size_t n, const float* step_in, uint32_t M,
                                 float alpha, const ndq_dither* d, void* codes_out, float* steps_out,
                                 void* stream)
 {
+    ndq_encode_job job;
     if (!step_in && n != 0) return NDQ_EINVAL;
     // the number of fine levels only ever served to derive a step: any valid value will do
-    return ndq::encode_common(g, dt, n, 0.0f, step_in, 2u, M, true, alpha, 0u, d, codes_out,
-                              steps_out, stream);
+    if (!ndq::encode_job_from(&job, g, step_in, 2u, M, true, alpha, d, codes_out, steps_out)) return NDQ_EINVAL;
+    return ndq::encode_single(job, dt, n, 0.0f, 0u, stream);
 }
 
 }  // extern "C"

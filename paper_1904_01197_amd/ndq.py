@@ -18,7 +18,7 @@ NDQ_F32, NDQ_BF16 = 0, 1
 NDQ_OK, NDQ_EINVAL, NDQ_EALIGN, NDQ_EUNSUPPORTED, NDQ_ELAUNCH = 0, -1, -2, -3, -4
 
 EXPORTS = ("ndq_code_bits", "ndq_packed_bytes", "ndq_num_buckets", "ndq_absmax", "ndq_dq_encode",
-           "ndq_dq_encode_with_step", "ndq_nested_encode_with_step",
+           "ndq_dq_encode_with_step", "ndq_nested_encode_with_step", "ndq_encode_workers",
            "ndq_dq_decode", "ndq_dq_decode_half", "ndq_nested_encode", "ndq_nested_decode", "ndq_aggregate",
            "ndq_decode_chain", "ndq_code_entropy", "ndq_dense_group", "ndq_dense_bytes",
            "ndq_dense_pack", "ndq_dense_unpack", "ndq_alpha_for_equal_variance",
@@ -39,6 +39,13 @@ class ndq_worker(C.Structure):
     """Mirror of the C struct: one worker's message as the server holds it."""
     _fields_ = [("codes", C.c_void_p), ("steps", C.c_void_p), ("kind", C.c_uint32),
                 ("levels_or_M", C.c_uint32), ("alpha", C.c_float), ("dither", ndq_dither)]
+
+
+class ndq_encode_job(C.Structure):
+    """Mirror of the C struct: one worker's vector to encode."""
+    _fields_ = [("g", C.c_void_p), ("codes_out", C.c_void_p), ("steps_out", C.c_void_p),
+                ("step_in", C.c_void_p), ("kind", C.c_uint32), ("levels", C.c_uint32),
+                ("M", C.c_uint32), ("alpha", C.c_float), ("dither", ndq_dither)]
 
 
 class NdqError(RuntimeError):
@@ -77,6 +84,8 @@ def lib():
         L.ndq_dq_encode_with_step.restype = ci
         L.ndq_nested_encode_with_step.argtypes = [vp, ci, sz, vp, u32, f32, dp, vp, vp, vp]
         L.ndq_nested_encode_with_step.restype = ci
+        L.ndq_encode_workers.argtypes = [C.POINTER(ndq_encode_job), u32, ci, sz, f32, u32, vp]
+        L.ndq_encode_workers.restype = ci
         L.ndq_nested_decode.argtypes = [vp, sz, u32, f32, u32, vp, dp, vp, f32, vp, ci, vp]
         L.ndq_nested_decode.restype = ci
         L.ndq_aggregate.argtypes, L.ndq_aggregate.restype = [vp, u32, sz, f32, vp, vp], ci
@@ -149,22 +158,36 @@ def ndq_absmax(g, bucket, kappa_out=None):
     return kappa_out
 
 
+def _bits(levels_or_M):
+    # ndq_code_bits and the two size rules below without a call into the library: they are
+    # evaluated several times per call, and a foreign call costs as much as a launch's half
+    return (levels_or_M - 1).bit_length() if 2 <= levels_or_M <= 256 else 0
+
+
+def _packed(n, bits):
+    return ((n * bits + 7) // 8 + 15) // 16 * 16
+
+
+def _buckets(n, bucket):
+    return (n + bucket - 1) // bucket if bucket else 1
+
+
 def _enc_outputs(g, bits, bucket, codes_out, steps_out):
     n = g.numel()
     if codes_out is None:
-        codes_out = torch.empty(ndq_packed_bytes(n, bits), dtype=torch.uint8, device=g.device)
+        codes_out = torch.empty(_packed(n, bits), dtype=torch.uint8, device=g.device)
     if steps_out is None:
-        steps_out = torch.empty(ndq_num_buckets(n, bucket), dtype=torch.float32, device=g.device)
-    if codes_out.numel() * codes_out.element_size() < ndq_packed_bytes(n, bits):
+        steps_out = torch.empty(_buckets(n, bucket), dtype=torch.float32, device=g.device)
+    if codes_out.numel() * codes_out.element_size() < _packed(n, bits):
         raise ValueError("codes_out too small")
-    if steps_out.numel() < ndq_num_buckets(n, bucket):
+    if steps_out.numel() < _buckets(n, bucket):
         raise ValueError("steps_out too small")
     return codes_out, steps_out
 
 
 def ndq_dq_encode(g, delta, levels, bucket, d, codes_out=None, steps_out=None):
     """-> (codes uint8 tensor, steps float32 tensor)"""
-    codes_out, steps_out = _enc_outputs(g, ndq_code_bits(levels), bucket, codes_out, steps_out)
+    codes_out, steps_out = _enc_outputs(g, _bits(levels), bucket, codes_out, steps_out)
     _check(lib().ndq_dq_encode(_dev(g, "g"), _dt(g), g.numel(), delta, levels, bucket, C.byref(d),
                                _dev(codes_out, "codes_out"), _dev(steps_out, "steps_out"),
                                _stream()), "ndq_dq_encode")
@@ -172,7 +195,7 @@ def ndq_dq_encode(g, delta, levels, bucket, d, codes_out=None, steps_out=None):
 
 
 def ndq_nested_encode(g, delta, levels, M, alpha, bucket, d, codes_out=None, steps_out=None):
-    codes_out, steps_out = _enc_outputs(g, ndq_code_bits(M), bucket, codes_out, steps_out)
+    codes_out, steps_out = _enc_outputs(g, _bits(M), bucket, codes_out, steps_out)
     _check(lib().ndq_nested_encode(_dev(g, "g"), _dt(g), g.numel(), delta, levels, M, alpha, bucket,
                                    C.byref(d), _dev(codes_out, "codes_out"),
                                    _dev(steps_out, "steps_out"), _stream()), "ndq_nested_encode")
@@ -188,7 +211,7 @@ def _step_in(step_in):
 
 def ndq_dq_encode_with_step(g, step_in, levels, d, codes_out=None, steps_out=None):
     """-> (codes, steps); the step is read from the device tensor step_in"""
-    codes_out, steps_out = _enc_outputs(g, ndq_code_bits(levels), 0, codes_out, steps_out)
+    codes_out, steps_out = _enc_outputs(g, _bits(levels), 0, codes_out, steps_out)
     _check(lib().ndq_dq_encode_with_step(_dev(g, "g"), _dt(g), g.numel(), _step_in(step_in), levels,
                                          C.byref(d), _dev(codes_out, "codes_out"),
                                          _dev(steps_out, "steps_out"), _stream()),
@@ -197,7 +220,7 @@ def ndq_dq_encode_with_step(g, step_in, levels, d, codes_out=None, steps_out=Non
 
 
 def ndq_nested_encode_with_step(g, step_in, M, alpha, d, codes_out=None, steps_out=None):
-    codes_out, steps_out = _enc_outputs(g, ndq_code_bits(M), 0, codes_out, steps_out)
+    codes_out, steps_out = _enc_outputs(g, _bits(M), 0, codes_out, steps_out)
     _check(lib().ndq_nested_encode_with_step(_dev(g, "g"), _dt(g), g.numel(), _step_in(step_in), M, alpha,
                                              C.byref(d), _dev(codes_out, "codes_out"),
                                              _dev(steps_out, "steps_out"), _stream()),
@@ -205,16 +228,36 @@ def ndq_nested_encode_with_step(g, step_in, M, alpha, d, codes_out=None, steps_o
     return codes_out, steps_out
 
 
+def ndq_encode_workers(jobs, delta, bucket):
+    """jobs: sequence of (g, kind, levels, M, alpha, ndq_dither, codes_out, steps_out, step_in) with
+    vectors of one length and type; M and alpha count for nested workers, step_in is None or a
+    device tensor holding one float32 step (bucket 0)."""
+    g0 = jobs[0][0]
+    n, dt = g0.numel(), _dt(g0)
+    arr = (ndq_encode_job * len(jobs))()
+    for a, (g, kind, levels, M, alpha, d, codes_out, steps_out, step_in) in zip(arr, jobs):
+        if g.numel() != n or g.dtype != g0.dtype:
+            raise ValueError("all gradients must have one length and type")
+        bits = _bits(M if kind == NDQ_WORKER_NESTED else levels)
+        _enc_outputs(g, bits, bucket, codes_out, steps_out)
+        a.g = _dev(g, "g").value
+        a.codes_out = _dev(codes_out, "codes_out").value
+        a.steps_out = _dev(steps_out, "steps_out").value
+        a.step_in = None if step_in is None else _step_in(step_in).value
+        a.kind, a.levels, a.M, a.alpha, a.dither = kind, levels, M, alpha, d
+    _check(lib().ndq_encode_workers(arr, len(jobs), dt, n, delta, bucket, _stream()), "ndq_encode_workers")
+
+
 def _check_message(codes, steps, n, bits, bucket):
     """A worker's message must be as large as the call will read."""
-    if codes.numel() * codes.element_size() < ndq_packed_bytes(n, bits):
+    if codes.numel() * codes.element_size() < _packed(n, bits):
         raise ValueError("codes hold fewer than ndq_packed_bytes(n, bits) bytes")
-    if steps.dtype != torch.float32 or steps.numel() < ndq_num_buckets(n, bucket):
+    if steps.dtype != torch.float32 or steps.numel() < _buckets(n, bucket):
         raise ValueError("steps must hold ndq_num_buckets(n, bucket) float32")
 
 
 def ndq_dq_decode(codes, n, levels, bucket, steps, d, out=None, accumulate=False):
-    _check_message(codes, steps, n, ndq_code_bits(levels), bucket)
+    _check_message(codes, steps, n, _bits(levels), bucket)
     if out is None:
         if accumulate:
             raise ValueError("accumulate needs an existing out")
@@ -228,7 +271,7 @@ def ndq_dq_decode(codes, n, levels, bucket, steps, d, out=None, accumulate=False
 
 
 def ndq_dq_decode_half(codes, n, levels, bucket, steps, out=None, accumulate=False):
-    _check_message(codes, steps, n, ndq_code_bits(levels), bucket)
+    _check_message(codes, steps, n, _bits(levels), bucket)
     if out is None:
         if accumulate:
             raise ValueError("accumulate needs an existing out")
@@ -243,7 +286,7 @@ def ndq_dq_decode_half(codes, n, levels, bucket, steps, out=None, accumulate=Fal
 
 def ndq_nested_decode(codes, n, M, alpha, bucket, steps, d, side, side_scale=1.0, out=None,
                       accumulate=False):
-    _check_message(codes, steps, n, ndq_code_bits(M), bucket)
+    _check_message(codes, steps, n, _bits(M), bucket)
     if out is None:
         if accumulate:
             raise ValueError("accumulate needs an existing out")
@@ -275,7 +318,7 @@ def ndq_decode_chain(workers, n, bucket, scale=1.0, out=None):
     arr = (ndq_worker * len(workers))()
     for i, wk in enumerate(workers):
         codes, steps, kind, arg, d = wk[:5]
-        _check_message(codes, steps, n, ndq_code_bits(arg), bucket)
+        _check_message(codes, steps, n, _bits(arg), bucket)
         arr[i].codes = _dev(codes, "codes").value
         arr[i].steps = _dev(steps, "steps").value
         arr[i].kind = kind
@@ -295,7 +338,7 @@ def ndq_code_entropy(codes, n, bits, hist_out=None, entropy_out=None, want_entro
     """-> (histogram int64 tensor of 2^bits counts, entropy float64 tensor of 1 element;
     None with want_entropy=False: the C call then gets a null entropy_out)"""
     dev = codes.device
-    if n and codes.numel() * codes.element_size() < ndq_packed_bytes(n, bits):
+    if n and codes.numel() * codes.element_size() < _packed(n, bits):
         raise ValueError("codes hold fewer than ndq_packed_bytes(n, bits) bytes")
     if hist_out is None:
         hist_out = torch.empty(1 << bits, dtype=torch.int64, device=dev)
@@ -330,7 +373,7 @@ def ndq_dense_pack(codes, n, levels, dense_out=None):
 
 
 def ndq_dense_unpack(dense, n, levels, codes_out=None):
-    nbytes = ndq_packed_bytes(n, ndq_code_bits(levels))
+    nbytes = _packed(n, _bits(levels))
     if codes_out is None:
         codes_out = torch.empty(nbytes, dtype=torch.uint8, device=dense.device)
     if codes_out.numel() * codes_out.element_size() < nbytes:

@@ -46,21 +46,18 @@ def allocate(wl: Workload, n: int, device="cuda", separate=False) -> Buffers:
 
 
 def encode_all(wl: Workload, grads, bufs: Buffers, ds, preset_step: float = 0.0):
-    """Worker side.  With wl.shared_step and no preset, worker 0 chooses the step and
+    """Worker side, all workers in one library call.  With wl.shared_step and no preset, worker 0 chooses the step and
     the other workers read it from worker 0's steps in device memory (Algorithm 1,
     initialisation: one Delta for all): no host round trip between the calls."""
+    jobs = []
     for w, (kind, arg) in enumerate(wl.plan):
-        shared = wl.shared_step and w > 0 and preset_step == 0.0
-        if kind == "dq" and shared:
-            ndq.ndq_dq_encode_with_step(grads[w], bufs.steps[0], arg, ds[w], bufs.codes[w], bufs.steps[w])
-        elif kind == "dq":
-            ndq.ndq_dq_encode(grads[w], preset_step, arg, wl.bucket, ds[w], bufs.codes[w], bufs.steps[w])
-        elif shared:
-            ndq.ndq_nested_encode_with_step(grads[w], bufs.steps[0], arg, 1.0, ds[w], bufs.codes[w],
-                                            bufs.steps[w])
+        step_in = bufs.steps[0] if wl.shared_step and w > 0 and preset_step == 0.0 else None
+        if kind == "dq":
+            jobs.append((grads[w], ndq.NDQ_WORKER_DQ, arg, 0, 1.0, ds[w], bufs.codes[w], bufs.steps[w], step_in))
         else:
-            ndq.ndq_nested_encode(grads[w], preset_step, wl.fine_levels, arg, 1.0, wl.bucket, ds[w],
-                                  bufs.codes[w], bufs.steps[w])
+            jobs.append((grads[w], ndq.NDQ_WORKER_NESTED, wl.fine_levels, arg, 1.0, ds[w], bufs.codes[w],
+                         bufs.steps[w], step_in))
+    ndq.ndq_encode_workers(jobs, preset_step, wl.bucket)
 
 
 def decode_chain(wl: Workload, n: int, bufs: Buffers, ds):

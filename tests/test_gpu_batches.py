@@ -1,0 +1,113 @@
+"""Calls that take several workers at once, against the oracle: codes and steps bit for bit
+(they are defined by the same IEEE operations on both sides, so there is no tolerance)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from oracle import pipeline as opipe
+from paper_1904_01197_amd import ndq, workloads
+
+pytestmark = pytest.mark.gpu
+
+F = np.float32
+
+
+def _host(W, n, dtype, seed):
+    rng = np.random.default_rng(seed)
+    common = rng.standard_normal(n) * 0.01
+    out = [(common + rng.standard_normal(n) * 0.003).astype(F) for _ in range(W)]
+    return [workloads.f32_to_bf16_bits(x) for x in out] if dtype == "bf16" else out
+
+
+def _dev(g):
+    t = torch.from_numpy(g)
+    return (t.view(torch.bfloat16) if g.dtype == np.uint16 else t).cuda()
+
+
+def _encode(plan, fine, bucket, shared, host, seeds, preset=0.0):
+    n = host[0].size
+    codes = [torch.full((ndq.ndq_packed_bytes(n, ndq.ndq_code_bits(arg)) + 64,), 0xA5, dtype=torch.uint8,
+                        device="cuda") for _, arg in plan]
+    steps = [torch.full((ndq.ndq_num_buckets(n, bucket),), -1.0, device="cuda") for _ in plan]
+    jobs = []
+    for w, (kind, arg) in enumerate(plan):
+        step_in = steps[0] if shared and w > 0 else None
+        d = ndq.ndq_dither(seeds[w], 3, w, 0)
+        jobs.append((_dev(host[w]), ndq.NDQ_WORKER_DQ if kind == "dq" else ndq.NDQ_WORKER_NESTED,
+                     arg if kind == "dq" else fine, arg, 1.0, d, codes[w], steps[w], step_in))
+    ndq.ndq_encode_workers(jobs, preset, bucket)
+    return codes, steps
+
+
+def _compare(plan, fine, bucket, shared, host, preset=0.0):
+    n = host[0].size
+    seeds = [7 + w for w in range(len(plan))]
+    ds = opipe.dithers(len(plan), seeds, step=3)
+    c_ref, s_ref, _ = opipe.encode_all(plan, fine, bucket, shared, host, ds, preset)
+    codes, steps = _encode(plan, fine, bucket, shared, host, seeds, preset)
+    for w in range(len(plan)):
+        got = codes[w].cpu().numpy()
+        assert np.array_equal(steps[w].cpu().numpy(), s_ref[w]), (n, bucket, w)
+        assert got[:c_ref[w].size].tobytes() == c_ref[w].tobytes(), (n, bucket, w)
+        assert (got[c_ref[w].size:] == 0xA5).all(), "written past the stream"
+
+
+# tile edges (2,048 binary32 / 4,096 bfloat16 elements), the length from which the max-norm
+# pass leaves parts instead of using atomics (16 tiles), and more than one workgroup of parts
+SIZES = [1, 2047, 2049, 4097, 16 * 2048 - 1, 16 * 4096 + 1, 70001, 300007]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("bucket,shared", [(0, False), (0, True), (1024, False), (4096, False), (8192, False),
+                                           (6400, False), (32768, False)])
+def test_several_workers_in_one_call_match_oracle(dtype, bucket, shared):
+    plan = (("dq", 5), ("nested", 3), ("dq", 5), ("nested", 4), ("dq", 16), ("nested", 4))
+    for n in SIZES:
+        _compare(plan, 7, bucket, shared, _host(len(plan), n, dtype, n))
+
+
+@pytest.mark.parametrize("preset", [0.0, 0.004])
+def test_more_workers_than_one_launch_holds_and_a_step_from_an_earlier_worker(preset):
+    # preset: the shared step exists only after the first worker's encoder, not after a max-norm pass
+    W = 35
+    plan = (("dq", 16),) + (("nested", 4),) * (W - 1)
+    host = _host(W, 5000, "f32", 1)
+    if preset == 0.0:
+        _compare(plan, 16, 0, True, host)
+        return
+    n, seeds = 5000, list(range(W))
+    codes = [torch.empty(ndq.ndq_packed_bytes(n, 4), dtype=torch.uint8, device="cuda") for _ in plan]
+    steps = [torch.full((1,), -1.0, device="cuda") for _ in plan]
+    jobs = [(_dev(host[w]), ndq.NDQ_WORKER_DQ if w == 0 else ndq.NDQ_WORKER_NESTED, 16, 4, 1.0,
+             ndq.ndq_dither(seeds[w], 3, w, 0), codes[w], steps[w], steps[w - 1] if w % 3 else None)
+            for w in range(W)]
+    ndq.ndq_encode_workers(jobs, preset, 0)
+    for w in range(W):
+        d = oracle.dither(seeds[w], 3, w)
+        ref, s_ref = (oracle.dq_encode(host[w], preset, 16, 0, d) if w == 0
+                      else oracle.nested_encode(host[w], preset, 16, 4, 0, d))
+        assert steps[w].item() == s_ref[0]
+        assert codes[w].cpu().numpy()[:ref.size].tobytes() == ref.tobytes(), w
+
+
+@pytest.mark.parametrize("bucket,shared", [(4096, False), (0, True)])
+def test_streaming_encoder_over_several_vectors(bucket, shared):
+    # together two tiles per wave slot (8,192 tiles of 4,096 elements) and a ragged end each:
+    # waves walk from one vector into the next
+    plan = (("dq", 4), ("nested", 2), ("nested", 2), ("nested", 2), ("nested", 2))
+    _compare(plan, 4, bucket, shared, _host(len(plan), 2050 * 4096 + 77, "bf16", 5))
+
+
+def test_bad_workers_are_reported_and_nothing_is_launched():
+    g = torch.zeros(4096, device="cuda")
+    codes, steps = torch.full((4096,), 7, dtype=torch.uint8, device="cuda"), torch.full((1,), -1.0, device="cuda")
+    d = ndq.ndq_dither(1, 1, 1, 0)
+    good = (g, ndq.NDQ_WORKER_DQ, 4, 0, 1.0, d, codes, steps, None)
+    bad_M = (g, ndq.NDQ_WORKER_NESTED, 4, 1, 1.0, d, codes, steps, None)
+    for jobs, bucket in (([good, bad_M], 0), ([good, good[:8] + (steps,)], 4096)):
+        with pytest.raises(ndq.NdqError) as e:
+            ndq.ndq_encode_workers(jobs, 0.0, bucket)
+        assert e.value.rc == ndq.NDQ_EINVAL
+    torch.cuda.synchronize()
+    assert steps.item() == -1.0 and (codes == 7).all()
