@@ -2,6 +2,8 @@
 // Algorithm 2, aggregation.  See include/ndq.h for the contract.
 #include <hip/hip_runtime.h>
 
+#include <utility>
+
 #include "ndq.h"
 #include "ndq_device.hpp"
 #include "ndq_host.hpp"
@@ -171,6 +173,7 @@ struct ChainWorker {
     uint32_t bits;
     uint32_t mode;        // Mode
     uint32_t first;       // S <- value instead of S + value
+    PhiloxUniform keys;   // chain_stream_kernel
 };
 
 struct ChainArgs {
@@ -536,93 +539,145 @@ __device__ __forceinline__ void stream_fold(const DitherStream& ds, uint64_t blo
     }
 }
 
-// The same fold of one row with its instructions in a fixed order, and one Philox
-// block (the dither of a later row) advanced by its ten rounds in between.  On
-// gfx950 a binary32 add / multiply / fma issued right after a quarter-rate
-// instruction (the 32x32 multiply, the round-to-integer) costs next to nothing,
-// and alternating integer and float instructions issue faster than runs of
-// either (measured with fixed instruction patterns); the compiler's own order
-// has the Philox rounds in one run and the float arithmetic in another.  The
-// values are those of stream_fold: the same operations on the same operands,
-// only their order in the program differs.  Per element the float stages are
-// 0: v = unit dither of the cell (DQSG: minus q_min)   1: code field -> c (DQSG) or m' = m/M (nested)
-// DQSG    2: c - v   3: Delta * (...)   4: S + (...)
-// nested  2: y = S * (1/count)   3: c = fma(y, 1/Delta, v)   4: fma(c, 1/M, -m')
-//         [round to integer]     5: + m'   6: fma(q', M, -v)   7: Delta * (...)   8: S + (...)
+// The same fold with fewer and cheaper instructions, in a fixed order, and one Philox
+// block (the dither of a later row) advanced by its ten rounds in between.
+// Bound by instruction issue (a wave64 fma, add, xor, and: 2.45 cycles of a SIMD; the 32x32
+// multiply 4.6; round-to-integer, conversions, 16-bit multiply 4.2, and a binary32 operation
+// beside one of these is almost free unless it is a sub-dword (SDWA) form).  133
+// vector instructions per row and nested 1-bit worker, 143 before; 4 workers of 2^27
+// elements: 204 -> 188 us, 16 workers of 11.2 M: 76 -> 69 us, and no more register spills:
+// - The dither goes through the mantissa: the bits of 64 + 2^-17 plus twice the cell are
+//   the float 64 + (cell + 1/2) 2^-16 (v_mad_u32_u16, which takes the low half of a word; the
+//   half-word conversions it replaces are SDWA), and an exact subtraction follows.  DQSG:
+//   c - (x - 64.5) = (c + 64.5) - x needs not even that.
+// - A 1-bit code j, shifted to bits 23..30, is masked in place: alone in the exponent field
+//   it is the float 0 or 2^(2^j - 127), and m' = m/2 comes out of the fma that uses it, as a
+//   product with 2^(126 - 2^j).  This fold is divided by M = 2 throughout,
+//     c' = fma(y, 1/(M Delta), v/M)   k = rint(c' - m')   q' = k + m'   S = S + (M Delta) (q' - v/M)
+//   which is exact, and S that of stream_fold bit for bit, while every step of the tile is 0
+//   or in [2^-60, 2^50]: then |S| < 2^60 and |c'| < 2^120.  Tiles with another step are
+//   decoded again in the plain form afterwards (step_out_of_range).
+// - What the Philox rounds do with wave-uniform operands is done on the host (PhiloxUniform):
+//   two of the twenty multiplies, three of the forty other operations.
+// - Order: the slow instructions are spread among the float operations (RowProgram); the
+//   compiler's own order has them in runs.
+__device__ __forceinline__ bool step_out_of_range(float step)
+{
+    return step > 0x1p50f || (step < 0x1p-60f && step != 0.0f);
+}
+
+// Low word of the number of the Philox block of this lane's elements in the first row.
+__device__ __forceinline__ uint32_t block_low(uint64_t index0, uint64_t start, int lane)
+{
+    return (uint32_t)((index0 + start) >> 3) + (uint32_t)lane;
+}
+
+__device__ __forceinline__ PhiloxUniform uniform_keys(ChainArgsPtr a, uint32_t w)
+{
+    return {a->w[w].keys.c2, a->w[w].keys.c0, a->w[w].keys.c2b, a->w[w].keys.c3, a->w[w].keys.key0, a->w[w].keys.key1};
+}
+
+// The order of a row's instructions, made at compile time: element k runs through its
+// stages `lag` steps behind element k - 1, so that at any place operations of about
+// (stages / lag) elements and of different kinds stand next to each other; the Philox
+// block's multiplies and xors are spread evenly among them.
+//   nested  x raised dither  v dither/M  a masked code [b m']  y S/count  c c'  t c' - m'  r rint
+//           q + m'  d - v/M  p times M Delta  s added to S
+//   DQSG    x raised dither  a masked code  b c + 64.5  d minus x  p times Delta  [s added to S]
+//   m, X    the next multiply, the next xor of the Philox block
+struct RowProgram {
+    char op[160];
+    uint8_t element[160];
+    int n;
+};
+constexpr RowProgram row_program(const char* stages, int lag)
+{
+    const char philox[] = "mXmXXmmXXmmXXmmXXmmXXmmXXmmXXmmXXmmXX";
+    constexpr int kPhilox = sizeof(philox) - 1;
+    int count = 0;
+    while (stages[count] != 0) ++count;
+    const int own = 8 * count;
+    RowProgram p = {};
+    int done = 0, advanced = 0;
+    for (int t = 0; t < count + 7 * lag; ++t)
+        for (int k = 0; k < 8; ++k) {
+            const int s = t - lag * k;
+            if (s < 0 || s >= count) continue;
+            p.op[p.n] = stages[s];
+            p.element[p.n++] = (uint8_t)k;
+            ++done;
+            for (; advanced < done * kPhilox / own; ++advanced) p.op[p.n++] = philox[advanced];
+        }
+    return p;
+}
+// Elements two stages apart: 188 us where 1 gives 193 and 3 gives 190 (4 workers, 2^27 elements).
+constexpr int kRowLag = 2;
+
+// nested workers with 1-bit codes take the fold divided by M
+template <int MODE, int WIDTH> struct RowScaled { static constexpr bool value = MODE != kDq && WIDTH == 1; };
+template <int MODE, int WIDTH, bool FIRST> struct RowOrder {
+    static constexpr bool BIT = RowScaled<MODE, WIDTH>::value;
+    static constexpr RowProgram program =
+        row_program(MODE == kDq ? (FIRST ? "xabdp" : "xabdps") : BIT ? "xvayctrqdps" : "xvabyctrqdps", kRowLag);
+};
+
+template <int MODE, int WIDTH, bool FIRST>
+struct RowFold {
+    static constexpr bool BIT = RowOrder<MODE, WIDTH, FIRST>::BIT;
+    static constexpr int NF = WIDTH == 4 ? 4 : 8;
+    static constexpr float M_f = (float)(1u << WIDTH), inv_M_f = 1.0f / M_f;
+    const uint32_t (&words)[4];
+    uint32_t code, code_hi, dither_bits;
+    float step, inv, side_scale;
+    float (&S)[8];
+    PhiloxFlight& fl;
+    float x[8], v[8], m[8], w[8];
+
+    template <int I> __device__ __forceinline__ void run()
+    {
+        constexpr char op = RowOrder<MODE, WIDTH, FIRST>::program.op[I];
+        constexpr int k = RowOrder<MODE, WIDTH, FIRST>::program.element[I];
+        constexpr int j = NF == 8 ? k : (k & 3);
+        constexpr float bit_scale = __builtin_bit_cast(float, (uint32_t)(253u - (1u << (k & 7))) << 23);   // 2^(126 - 2^k)
+        constexpr uint32_t mask = ((1u << WIDTH) - 1u) << (j * WIDTH);
+        constexpr uint32_t base = (150u - j * WIDTH - (MODE == kDq ? 0u : WIDTH)) << 23;
+        if constexpr (op == 'm') fl.next_multiply();
+        if constexpr (op == 'X') fl.next_xor();
+        if constexpr (op == 'x') x[k] = dither_raised((k & 1) ? words[k >> 1] >> 16 : words[k >> 1], dither_bits);
+        if constexpr (op == 'v') v[k] = x[k] - (BIT ? 64.5f * inv_M_f : 64.5f);
+        if constexpr (op == 'a' && BIT) m[k] = __uint_as_float(code & (1u << (23 + k)));
+        if constexpr (op == 'a' && !BIT)
+            m[k] = __uint_as_float(__builtin_amdgcn_bitop3_b32(NF == 8 || k < 4 ? code : code_hi, mask, base, 0xEA));
+        if constexpr (op == 'b') m[k] = m[k] - (__builtin_bit_cast(float, base) - (MODE == kDq ? 64.5f : 0.0f));
+        if constexpr (op == 'y') w[k] = S[k] * side_scale;
+        if constexpr (op == 'c') w[k] = __builtin_fmaf(w[k], inv, v[k]);
+        if constexpr (op == 't') w[k] = BIT ? __builtin_fmaf(m[k], -bit_scale, w[k]) : __builtin_fmaf(w[k], inv_M_f, -m[k]);
+        if constexpr (op == 'r') w[k] = __builtin_rintf(w[k]);
+        if constexpr (op == 'q') w[k] = BIT ? __builtin_fmaf(m[k], bit_scale, w[k]) : w[k] + m[k];
+        if constexpr (op == 'd') w[k] = MODE == kDq ? m[k] - x[k] : BIT ? w[k] - v[k] : __builtin_fmaf(w[k], M_f, -v[k]);
+        if constexpr (op == 'p' && FIRST) S[k] = step * w[k];
+        if constexpr (op == 'p' && !FIRST) w[k] = step * w[k];
+        if constexpr (op == 's') S[k] = S[k] + w[k];
+        NDQ_PIN();
+    }
+    template <int... I> __device__ __forceinline__ void run_all(std::integer_sequence<int, I...>) { (run<I>(), ...); }
+};
+
 template <int MODE, int WIDTH, bool FIRST>
 __device__ __forceinline__ void fold_row_piped(const uint32_t (&words)[4], uint32_t code, float step, float inv,
-                                               float side_scale, float q_min_f, float (&S)[8], PhiloxFlight& fl)
+                                               float side_scale, int32_t q_min, float (&S)[8], PhiloxFlight& fl)
 {
-    constexpr int NF = WIDTH == 4 ? 4 : 8;
-    constexpr float M_f = (float)(1u << WIDTH), inv_M_f = 1.0f / M_f;
-    const FieldScaled<NF> field((uint32_t)WIDTH, MODE == kDq ? 0u : (uint32_t)WIDTH);
-    // DQSG: the index offset q_min goes into the dither (see stream_fold)
-    const float centre = (MODE == kDq ? -q_min_f : 0.0f) + (-0.5f + 0x1p-17f);
-    const uint32_t lo = code, hi = WIDTH == 4 ? code >> 16 : code;
-    float v[8], m[8], w[8];
-    // float stages of an element, in order; nested: the round-to-integer sits between stages 4 and 5
-    constexpr int kStages = MODE == kDq ? (FIRST ? 4 : 5) : 9;
-    auto stage = [&](int st, int k) __attribute__((always_inline)) {
-        const int j = NF == 8 ? k : (k & 3);
-        if (st == 0) { v[k] = __builtin_fmaf(v[k], 0x1p-16f, centre); return; }   // unit_dither (shifted)
-        if (st == 1) { m[k] = field.finish(m[k], j); return; }
-        if (MODE == kDq) {
-            if (st == 2) w[k] = m[k] - v[k];
-            if (st == 3) { w[k] = step * w[k]; if (FIRST) S[k] = w[k]; }
-            if (st == 4) S[k] = S[k] + w[k];
-        } else {
-            if (st == 2) w[k] = S[k] * side_scale;
-            if (st == 3) w[k] = __builtin_fmaf(w[k], inv, v[k]);
-            if (st == 4) w[k] = __builtin_fmaf(w[k], inv_M_f, -m[k]);
-            if (st == 5) w[k] = w[k] + m[k];
-            if (st == 6) w[k] = __builtin_fmaf(w[k], M_f, -v[k]);
-            if (st == 7) w[k] = step * w[k];
-            if (st == 8) S[k] = S[k] + w[k];
-        }
-    };
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        const uint32_t word = words[k >> 1];
-        v[k] = (float)((k & 1) ? word >> 16 : word & 0xFFFFu);
-        m[k] = field.raw(NF == 8 ? lo : (k < 4 ? lo : hi), NF == 8 ? k : (k & 3));
-        NDQ_PIN();
-    }
-    constexpr int kInRounds = (MODE == kDq ? kStages : 5) * 8;
-#pragma unroll
-    for (int round = 0; round < 10; ++round) {
-        const int s0 = 4 * round;
-        fl.mul0();
-        if (s0 + 0 < kInRounds) stage((s0 + 0) >> 3, (s0 + 0) & 7);
-        NDQ_PIN();
-        fl.mul1();
-        if (s0 + 1 < kInRounds) stage((s0 + 1) >> 3, (s0 + 1) & 7);
-        NDQ_PIN();
-        fl.mix0();
-        if (s0 + 2 < kInRounds) stage((s0 + 2) >> 3, (s0 + 2) & 7);
-        NDQ_PIN();
-        fl.mix1();
-        fl.next_round();
-        if (s0 + 3 < kInRounds) stage((s0 + 3) >> 3, (s0 + 3) & 7);
-        NDQ_PIN();
-    }
-    if (MODE != kDq) {
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            w[k] = __builtin_rintf(w[k]);
-            if (k > 0) stage(5, k - 1);
-            NDQ_PIN();
-        }
-        stage(5, 7);
-#pragma unroll
-        for (int st = 6; st < kStages; ++st)
-#pragma unroll
-            for (int k = 0; k < 8; ++k) stage(st, k);
-    }
+    using Fold = RowFold<MODE, WIDTH, FIRST>;
+    // raised dither: v + 64 (DQSG: v - q_min + 64, so that c minus it is (c + q_min) - v; nested: divided by M)
+    const uint32_t dither_bits = MODE == kDq ? kDitherBits - ((uint32_t)q_min << 17)
+                                             : Fold::BIT ? kDitherBits - ((uint32_t)WIDTH << 23) : kDitherBits;
+    Fold f = {words, Fold::BIT ? code << 23 : code, code >> 16, dither_bits, step, inv, side_scale, S, fl, {}, {}, {}, {}};
+    f.run_all(std::make_integer_sequence<int, RowOrder<MODE, WIDTH, FIRST>::program.n>());
 }
 
 template <int MODE, int WIDTH, bool FIRST>
-__device__ __forceinline__ void stream_fold_piped(const DitherStream& ds, uint64_t block0, const DitherStream& ds_next,
-                                                  uint64_t block_next, float q_min_f, float side_scale,
+__device__ __forceinline__ void stream_fold_piped(const PhiloxUniform& keys, uint32_t block0, const PhiloxUniform& keys_next,
+                                                  uint32_t block_next, int32_t q_min, float side_scale,
                                                   const ChainCodes& f, float step, float inv,
                                                   float (&S)[kChainRows][8], PhiloxFlight& fl)
 {
@@ -630,9 +685,9 @@ __device__ __forceinline__ void stream_fold_piped(const DitherStream& ds, uint64
     for (int r = 0; r < kChainRows; ++r) {
         uint32_t words[4];
         fl.words(words);
-        if (r + 1 < kChainRows) fl.start(ds, block0 + (uint32_t)((r + 1) * kWave));
-        else fl.start(ds_next, block_next);
-        fold_row_piped<MODE, WIDTH, FIRST>(words, f.w[r], step, inv, side_scale, q_min_f, S[r], fl);
+        if (r + 1 < kChainRows) fl.start(keys, block0 + (uint32_t)((r + 1) * kWave));
+        else fl.start(keys_next, block_next);
+        fold_row_piped<MODE, WIDTH, FIRST>(words, f.w[r], step, inv, side_scale, q_min, S[r], fl);
     }
 }
 
@@ -672,6 +727,24 @@ __device__ __forceinline__ void stream_ragged_tile(ChainArgsPtr a, uint64_t star
     }
 }
 
+// The wave's tiles that have a step outside the range fold_row_piped is exact in, decoded
+// again in the plain form.
+template <int RMODE, int W0, int WR>
+__device__ __forceinline__ void redo_out_of_range(ChainArgsPtr a, uint32_t first, uint32_t stride,
+                                                           uint32_t tiles_all, int lane)
+{
+    const uint32_t W = a->W, tpb = a->tl.tiles_per_bucket;
+    const bool one_bucket = a->tl.bucket_len == a->tl.n;
+    const float* my_steps = a->w[(uint32_t)lane < W ? (uint32_t)lane : W - 1u].steps;
+    for (uint32_t tile = first; tile < tiles_all; tile += stride) {
+        const uint32_t bucket = one_bucket ? 0u : tile / tpb;
+        if (__builtin_amdgcn_ballot_w64(step_out_of_range(my_steps[bucket])) == 0) continue;
+        const uint64_t start = (uint64_t)tile * kChainTile;
+        const uint64_t left = a->tl.n - start;
+        stream_ragged_tile<RMODE, W0, WR>(a, start, left < kChainTile ? (uint32_t)left : kChainTile, bucket, lane);
+    }
+}
+
 // RAGGED: the vector ends in a ragged tile.  An instantiation of its own, because the mere
 // presence of that code in the kernel measured 6 % on the main loop (config 5, which has
 // no ragged tile: 215 against 203 us) although the loop's instructions are the same.
@@ -688,7 +761,7 @@ __device__ __forceinline__ void stream_ragged_tile(ChainArgsPtr a, uint64_t star
 // (206 us at n = 2^27; 105 us when every store writes 1 KB of consecutive bytes).  The tile
 // therefore leaves through the wave's 4 KB of LDS as four stores of consecutive bytes.
 // (2) stream_fold_piped: the fold's instructions in a fixed order with the next row's Philox
-// block advanced in between (7 % fewer issue cycles; hidden behind the stores until (1)).
+// block advanced in between.
 // It starts one extra Philox block per wave, which only a wave with many tiles amortises,
 // and the LDS round trip costs a one-tile wave more than the stores do, so launches of one
 // tile per wave keep the plain form.
@@ -701,6 +774,8 @@ __attribute__((amdgpu_waves_per_eu(PIPED ? NDQ_CHAIN_PIPED_WAVES : kChainStreamW
 void chain_stream_kernel(ChainArgs a_by_value)
 {
     constexpr bool TAIL = RAGGED && PIPED;     // the ragged tile runs through the main loop
+    constexpr bool SCALED = PIPED && RowScaled<RMODE, WR>::value;
+    constexpr float kM = RMODE == kDq ? 1.0f : (float)(1u << WR), kInvM = 1.0f / kM;
     const ChainArgsPtr a = (ChainArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
     const int lane = threadIdx.x & (kWave - 1);
     const uint32_t stride = gridDim.x * kWavesPerBlock;
@@ -745,8 +820,7 @@ void chain_stream_kernel(ChainArgs a_by_value)
     // PIPED: the dither of the row after the current one is always in flight; here the first row's
     PhiloxFlight fl;
     if (PIPED) {
-        const DitherStream ds = {a->w[0].ds.key0, a->w[0].ds.key1, a->w[0].ds.step, a->w[0].ds.worker};
-        fl.start(ds, ((a->w[0].index0 + (uint64_t)first * kChainTile) >> 3) + (uint32_t)lane);
+        fl.start(uniform_keys(a, 0u), block_low(a->w[0].index0, (uint64_t)first * kChainTile, lane));
         fl.run();
     }
     // Lane w looks after worker w's step: one load and ONE correctly rounded division per tile
@@ -755,6 +829,7 @@ void chain_stream_kernel(ChainArgs a_by_value)
     const uint32_t my_worker = (uint32_t)lane < W ? (uint32_t)lane : W - 1u;
     const float* my_steps = a->w[my_worker].steps;
     float steps_ahead = my_steps[one_bucket ? 0u : first / tpb];
+    bool out_of_range = false;
     for (uint32_t tile = first; tile < tiles_all; tile += stride) {
         const uint64_t start = (uint64_t)tile * kChainTile;
         // where the dither after this tile's last row belongs: past the end after the last tile (unused)
@@ -766,7 +841,12 @@ void chain_stream_kernel(ChainArgs a_by_value)
             const uint32_t nt = tile + stride < tiles_all ? tile + stride : tile;
             steps_ahead = my_steps[one_bucket ? 0u : nt / tpb];
         }
-        const float invs_here = inv_step(steps_here);
+        float invs_here = inv_step(steps_here), scaled_here = steps_here;
+        if (SCALED) {
+            invs_here = invs_here * kInvM;
+            scaled_here = steps_here * kM;
+            out_of_range = out_of_range || step_out_of_range(steps_here);
+        }
         auto from_lane = [](float x, uint32_t w) __attribute__((always_inline)) {
             return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(x), (int)w));
         };
@@ -780,14 +860,14 @@ void chain_stream_kernel(ChainArgs a_by_value)
             nxt = tmp;
         }
         {
-            const DitherStream ds = {a->w[0].ds.key0, a->w[0].ds.key1, a->w[0].ds.step, a->w[0].ds.worker};
             if (PIPED) {
                 const uint32_t wn = W > 1u ? 1u : 0u;
-                const DitherStream dn = {a->w[wn].ds.key0, a->w[wn].ds.key1, a->w[wn].ds.step, a->w[wn].ds.worker};
-                stream_fold_piped<kDq, W0, true>(ds, ((a->w[0].index0 + start) >> 3) + (uint32_t)lane, dn,
-                                                 ((a->w[wn].index0 + (W > 1u ? start : next_start)) >> 3) + (uint32_t)lane,
-                                                 (float)a->w[0].q_min, 0.0f, cur, from_lane(steps_here, 0u), 0.0f, S, fl);
+                stream_fold_piped<kDq, W0, true>(
+                    uniform_keys(a, 0u), block_low(a->w[0].index0, start, lane), uniform_keys(a, wn),
+                    block_low(a->w[wn].index0, W > 1u ? start : next_start, lane), a->w[0].q_min, 0.0f, cur,
+                    from_lane(steps_here, 0u), 0.0f, S, fl);
             } else {
+                const DitherStream ds = {a->w[0].ds.key0, a->w[0].ds.key1, a->w[0].ds.step, a->w[0].ds.worker};
                 stream_fold<kDq, W0, true>(ds, (a->w[0].index0 + start) >> 3, (float)a->w[0].q_min, 0.0f, cur,
                                            from_lane(steps_here, 0u), 0.0f, lane, S);
             }
@@ -803,16 +883,16 @@ void chain_stream_kernel(ChainArgs a_by_value)
                 stream_fetch<W0>(a->w[0].codes, (uint64_t)nt * kChainTile, lane, tmp, limit_for(nt, limit0));
                 nxt = tmp;
             }
-            const DitherStream ds = {a->w[w].ds.key0, a->w[w].ds.key1, a->w[w].ds.step, a->w[w].ds.worker};
             if (PIPED) {
                 const bool last = w + 1u == W;
                 const uint32_t wn = last ? 0u : w + 1u;
-                const DitherStream dn = {a->w[wn].ds.key0, a->w[wn].ds.key1, a->w[wn].ds.step, a->w[wn].ds.worker};
-                stream_fold_piped<RMODE, WR, false>(ds, ((a->w[w].index0 + start) >> 3) + (uint32_t)lane, dn,
-                                                    ((a->w[wn].index0 + (last ? next_start : start)) >> 3) + (uint32_t)lane,
-                                                    (float)a->w[w].q_min, a->w[w].side_scale, cur,
-                                                    from_lane(steps_here, w), from_lane(invs_here, w), S, fl);
+                const uint32_t here = block_low(a->w[w].index0, start, lane);
+                const uint32_t next = block_low(a->w[wn].index0, last ? next_start : start, lane);
+                stream_fold_piped<RMODE, WR, false>(uniform_keys(a, w), here, uniform_keys(a, wn), next, a->w[w].q_min,
+                                                    a->w[w].side_scale, cur, from_lane(scaled_here, w),
+                                                    from_lane(invs_here, w), S, fl);
             } else {
+                const DitherStream ds = {a->w[w].ds.key0, a->w[w].ds.key1, a->w[w].ds.step, a->w[w].ds.worker};
                 stream_fold<RMODE, WR, false>(ds, (a->w[w].index0 + start) >> 3, (float)a->w[w].q_min,
                                               a->w[w].side_scale, cur, from_lane(steps_here, w),
                                               from_lane(invs_here, w), lane, S);
@@ -867,6 +947,8 @@ void chain_stream_kernel(ChainArgs a_by_value)
         else if (quarter == 2u) __builtin_amdgcn_s_setprio(1);
         else if (quarter >= 3u) __builtin_amdgcn_s_setprio(0);
     }
+    if (SCALED && __builtin_amdgcn_ballot_w64(out_of_range) != 0)
+        redo_out_of_range<RMODE, W0, WR>(a, first, stride, tiles_all, lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -1026,6 +1108,9 @@ static int try_chain_stream(ChainArgs a, uint32_t bucket, hipStream_t s)
         for (uint32_t j = 2; j < a.W; ++j)
             if (a.w[j].mode != rmode || a.w[j].bits != wr) return 1;
     }
+    // the high word of the dither's block number is the same for the whole call (it changes every 2^35 elements)
+    for (uint32_t j = 0; j < a.W; ++j)
+        if ((a.w[j].index0 >> 35) != ((a.w[j].index0 + a.tl.n - 1u) >> 35)) return 1;
     const uint32_t full = (uint32_t)(a.tl.n / kChainTile);
     if (full == 0u) return 1;
     ChainArgs b = a;
@@ -1159,6 +1244,7 @@ int ndq_decode_chain(const ndq_worker* workers, uint32_t W, size_t n, uint32_t b
                               : (!is_pow2(wk.levels_or_M) ? kNestedAnyM
                                  : (wk.alpha == 1.0f ? kNestedPow2 : kNestedPow2Shrink));
             cw.first = (p0 + j) == 0u;
+            cw.keys = philox_uniform(cw.ds, (uint32_t)((cw.index0 >> 3) >> 32));
         }
         bool any_m = false;
         for (uint32_t j = 0; j < a.W; ++j) any_m = any_m || a.w[j].mode == kNestedAnyM;

@@ -77,17 +77,47 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
 // the order of the program.
 #define NDQ_PIN() __builtin_amdgcn_sched_barrier(0)
 
+// What the ten rounds of a block do with wave-uniform operands only, done once on the host:
+// the second counter pair (step, worker) and the high word of the block number are the same
+// for a whole call (see the caller), so the first round has one multiply and one xor that
+// depend on the lane, the second round one multiply and two xors.
+struct PhiloxUniform {
+    uint32_t c2;          // first round:  c2 = high(p0) ^ this
+    uint32_t c0, c2b;     // second round: c0 = high(p1) ^ c0, c2 = c3 ^ c2b
+    uint32_t c3;          // third round:  c2 = high(p0) ^ c3
+    uint32_t key0, key1;  // keys of the third round
+};
+
+inline PhiloxUniform philox_uniform(const DitherStream& s, uint32_t block_high)
+{
+    const uint64_t p1 = (uint64_t)0xCD9E8D57u * s.step;
+    const uint64_t p0 = (uint64_t)0xD2511F53u * ((uint32_t)(p1 >> 32) ^ block_high ^ s.key0);
+    PhiloxUniform u;
+    u.c2 = s.worker ^ s.key1;
+    u.c0 = (uint32_t)p1 ^ (s.key0 + 0x9E3779B9u);
+    u.c2b = (uint32_t)(p0 >> 32) ^ (s.key1 + 0xBB67AE85u);
+    u.key0 = s.key0 + 2u * 0x9E3779B9u;
+    u.key1 = s.key1 + 2u * 0xBB67AE85u;
+    u.c3 = (uint32_t)p0 ^ u.key1;
+    return u;
+}
+
 // One Philox block advanced a piece at a time, so that the caller can place other
-// work between the pieces: a round is mul0, mul1, mix0, mix1, next_round in that
-// order (each mix needs both products' owner words untouched: mul0 before mix0,
-// mul1 before mix1).  After ten rounds words() are those of philox4x32_10.
+// work between the pieces: 18 multiplies and 19 xors, in the order
+//   mul xor | mul xor xor | eight times: mul mul xor xor
+// After the last the words() are those of philox4x32_10.
 struct PhiloxFlight {
-    uint32_t c0, c1, c2, c3, k0, k1;
+    uint32_t c0, c1, c2, c3;
     uint64_t p0, p1;
-    __device__ __forceinline__ void start(const DitherStream& s, uint64_t block)
+    PhiloxUniform u;
+    uint32_t k0, k1;
+    int muls, xors;       // pieces done: known at compile time once everything is unrolled
+    __device__ __forceinline__ void start(const PhiloxUniform& uniform, uint32_t block_low)
     {
-        c0 = (uint32_t)block; c1 = (uint32_t)(block >> 32); c2 = s.step; c3 = s.worker;
-        k0 = s.key0; k1 = s.key1;
+        u = uniform;
+        c0 = block_low;
+        k0 = u.key0; k1 = u.key1;
+        muls = 0; xors = 0;
     }
     // the 32x32->64 multiply as the one instruction it is (left to the compiler it becomes a
     // high and a low multiply once the two halves are used in different pinned regions)
@@ -97,18 +127,43 @@ struct PhiloxFlight {
         asm("v_mad_u64_u32 %0, vcc, %1, %2, 0" : "=v"(p) : "s"(constant), "v"(x) : "vcc");
         return p;
     }
-    __device__ __forceinline__ void mul0() { p0 = wide_mul(0xD2511F53u, c0); }
-    __device__ __forceinline__ void mul1() { p1 = wide_mul(0xCD9E8D57u, c2); }
-    __device__ __forceinline__ void mix0() { c0 = xor3((uint32_t)(p1 >> 32), c1, k0); c1 = (uint32_t)p1; }
-    __device__ __forceinline__ void mix1() { c2 = xor3((uint32_t)(p0 >> 32), c3, k1); c3 = (uint32_t)p0; }
+    __device__ __forceinline__ void next_multiply()
+    {
+        if ((muls & 1) == 0) p0 = wide_mul(0xD2511F53u, c0);
+        else p1 = wide_mul(0xCD9E8D57u, c2);
+        ++muls;
+    }
+    __device__ __forceinline__ void next_xor()
+    {
+        if (xors == 0) { c2 = (uint32_t)(p0 >> 32) ^ u.c2; c3 = (uint32_t)p0; }
+        else if (xors == 1) { c0 = (uint32_t)(p1 >> 32) ^ u.c0; c1 = (uint32_t)p1; }
+        else if (xors == 2) c2 = c3 ^ u.c2b;
+        else if (xors == 4) { c2 = (uint32_t)(p0 >> 32) ^ u.c3; c3 = (uint32_t)p0; next_round(); }
+        else if ((xors & 1) != 0) { c0 = xor3((uint32_t)(p1 >> 32), c1, k0); c1 = (uint32_t)p1; }
+        else { c2 = xor3((uint32_t)(p0 >> 32), c3, k1); c3 = (uint32_t)p0; next_round(); }
+        ++xors;
+    }
     __device__ __forceinline__ void next_round() { k0 += 0x9E3779B9u; k1 += 0xBB67AE85u; }
     __device__ __forceinline__ void run()
     {
+        next_multiply(); next_xor();
+        next_multiply(); next_xor(); next_xor();
 #pragma unroll
-        for (int round = 0; round < 10; ++round) { mul0(); mul1(); mix0(); mix1(); next_round(); }
+        for (int round = 2; round < 10; ++round) { next_multiply(); next_multiply(); next_xor(); next_xor(); }
     }
     __device__ __forceinline__ void words(uint32_t (&r)[4]) const { r[0] = c0; r[1] = c1; r[2] = c2; r[3] = c3; }
 };
+
+// The bits of 64 + 2^-17 plus twice a 16-bit dither cell are the float 64 + (cell + 1/2) 2^-16,
+// i.e. the unit dither + 64.5 (other `bits`: another integer in place of 64, or all of it
+// divided by a power of two).  v_mad_u32_u16 takes the low half of `word`.
+constexpr uint32_t kDitherBits = 0x42800001u;
+__device__ __forceinline__ float dither_raised(uint32_t word, uint32_t bits)
+{
+    uint32_t x;
+    asm("v_mad_u32_u16 %0, %1, 2, %2" : "=v"(x) : "v"(word), "s"(bits));
+    return __uint_as_float(x);
+}
 
 // Mid-point of cell `cell` of 2^16 equal cells of [-1/2, 1/2): exact in binary32.
 __device__ __forceinline__ float unit_dither(uint32_t cell)

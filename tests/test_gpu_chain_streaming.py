@@ -1,0 +1,60 @@
+"""The persistent chain decoder at its real grid size, against the oracle bit for bit, at inputs
+where its rearranged arithmetic has to give way: steps outside the range in which the fold
+divided by M is exact, and dither indices whose block number crosses a 32-bit word."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from oracle import pipeline as opipe
+from paper_1904_01197_amd import ndq
+
+pytestmark = pytest.mark.gpu
+
+F = np.float32
+TILES = 2 * 6144                     # tiles of 1,024 elements from which the persistent launch is used
+
+
+def _check(plan, fine, bucket, host, offset, scale=1.0):
+    n, W = host[0].size, len(plan)
+    seeds = [11 + w for w in range(W)]
+    ds = opipe.dithers(W, seeds, step=9, offset=offset)
+    codes, steps, _ = opipe.encode_all(plan, fine, bucket, False, host, ds)
+    ref = opipe.decode_chain(plan, bucket, n, codes, steps, ds, scale)
+    workers = [(torch.from_numpy(codes[w]).cuda(), torch.from_numpy(steps[w]).cuda(),
+                ndq.NDQ_WORKER_DQ if kind == "dq" else ndq.NDQ_WORKER_NESTED, arg,
+                ndq.ndq_dither(seeds[w], 9, w, offset)) for w, (kind, arg) in enumerate(plan)]
+    out = ndq.ndq_decode_chain(workers, n, bucket, scale).cpu().numpy()
+    assert np.array_equal(out, ref), np.nonzero(out != ref)[0][:5]
+
+
+def _gradients(W, n, seed):
+    rng = np.random.default_rng(seed)
+    common = rng.standard_normal(n, dtype=F)
+    return [common + F(0.3) * rng.standard_normal(n, dtype=F) for _ in range(W)]
+
+
+@pytest.mark.parametrize("M", [2, 4])
+@pytest.mark.parametrize("tail", [0, 517])
+def test_steps_of_any_magnitude(M, tail):
+    n, bucket = TILES * 1024 + tail, 4096
+    host = _gradients(3, n, 3 + M)
+    scale = np.ones(n // bucket + 1, dtype=F)
+    scale[1::7] = F(2.0 ** 49)       # just inside and just outside of the exact range, and far outside
+    scale[2::7] = F(2.0 ** 52)
+    scale[3::7] = F(2.0 ** 120)
+    scale[4::7] = F(2.0 ** -61)
+    scale[5::7] = F(2.0 ** -95)
+    scale[6::21] = F(0.0)
+    for w, g in enumerate(host):
+        g *= np.repeat(scale, bucket)[:n]
+        g[7 * bucket * (w + 1):7 * bucket * (w + 1) + bucket] *= F(2.0 ** 70)    # one worker's step alone
+    _check((("dq", 4), ("nested", M), ("nested", M)), 4, bucket, host, 64)
+
+
+@pytest.mark.parametrize("n,offset", [
+    (TILES * 1024 + 1024, 5 << 35),                 # a high word that is not zero
+    (TILES * 1024 + 8, (1 << 35) - 8 * 4096),       # the block number's low word wraps inside the call
+    (5000, (1 << 35) - 2048), (4096, (1 << 35) - 4096), (1024, (3 << 35) - 1032)])
+def test_dither_indices_beyond_32_bits(n, offset):
+    _check((("dq", 4), ("nested", 2), ("nested", 2)), 4, 0, _gradients(3, n, 8), offset, 0.5)
