@@ -1,4 +1,4 @@
-"""Builds libndq.so (HIP kernels + C ABI) for gfx950, in-tree."""
+"""Builds libndq.so (HIP kernels + C ABI) for gfx950 and the Python binding, in-tree."""
 import os
 import subprocess
 from concurrent.futures import ThreadPoolExecutor
@@ -68,13 +68,36 @@ def build_probes(verbose=False):
     return out
 
 
+BINDING = os.path.join(HERE, "_native.so")
+BINDING_SOURCE = os.path.join(CSRC, "ndq_python.cpp")
+
+
+def build_binding(verbose=False):
+    """Compiles the native half of the Python binding (host code only) against torch."""
+    import sysconfig
+    import torch
+    root = os.path.dirname(torch.__file__)
+    cxx = os.environ.get("CXX", "g++")
+    _run([cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-fvisibility=hidden",
+          "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+          "-I", os.path.join(ROOT, "include"), "-isystem", os.path.join(root, "include"),
+          "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
+          "-isystem", sysconfig.get_paths()["include"], BINDING_SOURCE, "-o", BINDING,
+          "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10",
+          "-Wl,-rpath," + os.path.join(root, "lib")], verbose)
+    return BINDING
+
+
 def ensure_built():
-    """Builds the library only if no built one is there (a fresh checkout)."""
+    """Builds the library and its binding only where a built one is missing (a fresh checkout)."""
     if not os.path.exists(SO):
         build_library(force=True)
+    if not os.path.exists(BINDING):
+        build_binding()
     return SO
 
 
 if __name__ == "__main__":
     print(build_library(force=True, verbose=True))
+    print(build_binding(verbose=True))
     print("\n".join(build_probes(verbose=True)))
