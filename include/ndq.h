@@ -278,6 +278,14 @@ typedef struct {
 int ndq_decode_chain(const ndq_worker* workers, uint32_t W, size_t n, uint32_t bucket,
                      float scale, float* out, void* stream);
 
+/* Server side of Algorithm 1 as printed, in one pass: decoded[w][i] = g~_w,i for every
+ * worker (as ndq_dq_decode) and out_i = scale * sum_w g~_w,i, summed in ascending w (as
+ * ndq_aggregate): the same values as those calls, without reading the reconstructions back.
+ * workers: HOST array of W DQSG workers (1 <= W <= 1024) that share n and bucket; decoded:
+ * HOST array of W device pointers, n floats each (16-byte aligned).  out must not be one of them. */
+int ndq_decode_mean(const ndq_worker* workers, float* const* decoded, uint32_t W, size_t n,
+                    uint32_t bucket, float scale, float* out, void* stream);
+
 /* Dense base-L stream.  Table 1 (Sec. 4) counts log2(L) bits per index (1.585 for
  * three levels); the fixed-width stream spends ceil(log2 L).  The dense stream
  * stores k = ndq_dense_group(L) = max{k : L^k <= 2^32} indices per 32-bit word as

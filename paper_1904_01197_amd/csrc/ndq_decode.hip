@@ -996,6 +996,133 @@ __global__ __launch_bounds__(kBlock) void aggregate_kernel(AggArgs a)
 }
 
 // ---------------------------------------------------------------------------
+// Algorithm 1's server as printed, in one pass: every DQSG worker's gradient is
+// reconstructed and kept, and their sum leaves with them.  Bound by the memory it writes, 4 (W + 1)
+// bytes per element; decoding and then aggregating reads the 4 W bytes back (W = 4 at
+// 1.66 M elements: 4 x 3.9 + 8.2 us, here 10.4; W = 2 at 37 M: 2 x 25 + 71, here 82 = 5.5 TB/s).  A lane owns four consecutive elements per row like the single
+// decoders (16-byte stores of consecutive addresses), and the sum stays in its registers.
+// ---------------------------------------------------------------------------
+constexpr uint32_t kMeanMax = 32;      // workers per launch
+constexpr int kMeanRows = 2;           // (1.66 M x 4 / 37 M x 2 elements: 1 row 11.5 / 87, 2 rows 10.4 / 82, 4 rows 10.7 / 79 us)
+constexpr uint32_t kMeanTile = kWave * 4 * kMeanRows;
+struct MeanWorker {
+    const unsigned char* codes;
+    const float* steps;
+    float* decoded;
+    uint64_t index0;
+    DitherStream ds;
+    int32_t q_min;
+    uint32_t bits;
+};
+struct MeanArgs {
+    MeanWorker w[kMeanMax];
+    float* out;
+    Tiling tl;
+    uint32_t W;
+    int continue_sum, finish;
+    float scale;
+};
+typedef const __attribute__((address_space(4))) MeanArgs* MeanArgsPtr;
+
+// the words that hold a lane's four codes of every row (a ragged tail only counts its valid codes)
+template <bool FULL>
+__device__ __forceinline__ void mean_fetch(MeanArgsPtr a, uint32_t w, const TileRef& t, int lane,
+                                           uint64_t (&window)[kMeanRows], float& step)
+{
+    const uint32_t bits = a->w[w].bits;
+    const uint32_t* codes32 = (const uint32_t*)(a->w[w].codes + (t.start >> 3) * bits);
+#pragma unroll
+    for (int r = 0; r < kMeanRows; ++r) {
+        const uint32_t o = (uint32_t)(r * kWave + lane) * 4u;
+        window[r] = 0;
+        if (FULL || o < t.len) {
+            const uint32_t ncodes = FULL ? 4u : (t.len - o < 4u ? t.len - o : 4u);
+            const uint32_t word = (o * bits) >> 5, sh = (o * bits) & 31u;
+            window[r] = codes32[word];
+            if (sh + ncodes * bits > 32u) window[r] |= (uint64_t)codes32[word + 1] << 32;
+        }
+    }
+    step = a->w[w].steps[t.bucket];
+}
+
+template <bool FULL>
+__device__ __forceinline__ void mean_tile(MeanArgsPtr a, const TileRef& t, int lane)
+{
+    const uint32_t W = a->W;
+    float acc[kMeanRows][4];
+#pragma unroll
+    for (int r = 0; r < kMeanRows; ++r)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t e = (uint32_t)(r * kWave + lane) * 4u + k;
+            acc[r][k] = (a->continue_sum && (FULL || e < t.len)) ? a->out[t.start + e] : 0.0f;
+        }
+    uint64_t window[kMeanRows], ahead[kMeanRows];
+    float step, step_ahead = 0.0f;
+    mean_fetch<FULL>(a, 0u, t, lane, window, step);
+    for (uint32_t w = 0; w < W; ++w) {
+        if (w + 1u < W) mean_fetch<FULL>(a, w + 1u, t, lane, ahead, step_ahead);
+        const DitherStream ds = {a->w[w].ds.key0, a->w[w].ds.key1, a->w[w].ds.step, a->w[w].ds.worker};
+        const uint64_t quad0 = (a->w[w].index0 + t.start) >> 2;
+        const uint32_t bits = a->w[w].bits;
+        const int32_t q_min = a->w[w].q_min;
+        float* decoded = a->w[w].decoded + t.start;
+#pragma unroll
+        for (int r = 0; r < kMeanRows; ++r) {
+            const uint32_t o = (uint32_t)(r * kWave + lane) * 4u;
+            const uint32_t packed = (uint32_t)(window[r] >> ((o * bits) & 31u));
+            float v[4], res[4];
+            dither4(ds, quad0 + (o >> 2), v);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const uint32_t c = __builtin_amdgcn_ubfe(packed, k * bits, bits);
+                res[k] = index_value((float)((int32_t)c + q_min), step, v[k]);
+                acc[r][k] = acc[r][k] + res[k];
+            }
+            if (FULL || o + 4u <= t.len) {
+                store_streaming(decoded + o, res[0], res[1], res[2], res[3]);
+            } else {
+#pragma unroll
+                for (uint32_t k = 0; k < 4; ++k)
+                    if (o + k < t.len) decoded[o + k] = res[k];
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < kMeanRows; ++r) window[r] = ahead[r];
+        step = step_ahead;
+    }
+    float* out = a->out + t.start;
+    const float scale = a->scale;
+    const bool finish = a->finish != 0;
+#pragma unroll
+    for (int r = 0; r < kMeanRows; ++r) {
+        const uint32_t o = (uint32_t)(r * kWave + lane) * 4u;
+        float res[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) res[k] = finish ? scale * acc[r][k] : acc[r][k];
+        if (FULL || o + 4u <= t.len) {
+            store_streaming(out + o, res[0], res[1], res[2], res[3]);
+        } else {
+#pragma unroll
+            for (uint32_t k = 0; k < 4; ++k)
+                if (o + k < t.len) out[o + k] = res[k];
+        }
+    }
+}
+
+__global__ __launch_bounds__(kBlock) void decode_mean_kernel(MeanArgs by_value)
+{
+    const MeanArgsPtr a = (MeanArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
+    const Tiling tl = {a->tl.n, a->tl.bucket_len, a->tl.tiles_per_bucket, a->tl.total_tiles};
+    const int lane = threadIdx.x & (kWave - 1);
+    const uint32_t tile_id =
+        blockIdx.x * kWavesPerBlock + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const TileRef t = locate_tile(tl, tile_id, kMeanTile);
+    if (t.len == kMeanTile) mean_tile<true>(a, t, lane);
+    else if (t.len != 0) mean_tile<false>(a, t, lane);
+}
+
+// ---------------------------------------------------------------------------
 // Host side: dispatch
 // ---------------------------------------------------------------------------
 template <int MODE, int ACC, bool STRADDLE>
@@ -1183,6 +1310,44 @@ int ndq_aggregate(const float* const* gs, uint32_t W, size_t n, float scale, flo
         a.finish = w0 + kAggMax >= W;
         a.scale = scale;
         if (launch(aggregate_kernel, dim3((uint32_t)blocks), dim3(kBlock), (hipStream_t)stream, a) != NDQ_OK)
+            return NDQ_ELAUNCH;
+    }
+    return NDQ_OK;
+}
+
+int ndq_decode_mean(const ndq_worker* workers, float* const* decoded, uint32_t W, size_t n, uint32_t bucket,
+                    float scale, float* out, void* stream)
+{
+    using namespace ndq;
+    if (!workers || !decoded || W < 1u || W > 1024u) return NDQ_EINVAL;
+    for (uint32_t p = 0; p < W; ++p)
+        if (workers[p].kind != NDQ_WORKER_DQ || workers[p].levels_or_M < 2u || workers[p].levels_or_M > 256u)
+            return NDQ_EINVAL;
+    if (n == 0) return NDQ_OK;
+    if (!out) return NDQ_EINVAL;
+    if (n >= kMaxN) return NDQ_EUNSUPPORTED;
+    if (!aligned16(out) || bucket % 64u != 0u) return NDQ_EALIGN;
+    for (uint32_t p = 0; p < W; ++p) {
+        const ndq_worker& wk = workers[p];
+        if (!wk.codes || !wk.steps || !decoded[p]) return NDQ_EINVAL;
+        if (!aligned16(wk.codes) || !aligned16(decoded[p]) || !aligned4(wk.steps) || (wk.dither.offset & 7u) != 0u)
+            return NDQ_EALIGN;
+    }
+    MeanArgs a;
+    const int rc = make_tiling(n, bucket, kMeanTile, &a.tl);
+    if (rc != NDQ_OK) return rc;
+    a.out = out;
+    a.scale = scale;
+    for (uint32_t p0 = 0; p0 < W; p0 += kMeanMax) {
+        a.W = (W - p0 < kMeanMax) ? W - p0 : kMeanMax;
+        a.continue_sum = p0 != 0u;
+        a.finish = p0 + kMeanMax >= W;
+        for (uint32_t j = 0; j < a.W; ++j) {
+            const ndq_worker& wk = workers[p0 + j];
+            a.w[j] = {(const unsigned char*)wk.codes, wk.steps, decoded[p0 + j], wk.dither.offset,
+                      make_stream(&wk.dither), -(int32_t)(wk.levels_or_M / 2u), code_bits(wk.levels_or_M)};
+        }
+        if (launch(decode_mean_kernel, dim3(blocks_for(a.tl.total_tiles)), dim3(kBlock), (hipStream_t)stream, a) != NDQ_OK)
             return NDQ_ELAUNCH;
     }
     return NDQ_OK;

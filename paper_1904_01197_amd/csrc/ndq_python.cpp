@@ -30,6 +30,7 @@ struct Library {
     decltype(&ndq_nested_decode) nested_decode;
     decltype(&ndq_aggregate) aggregate;
     decltype(&ndq_decode_chain) decode_chain;
+    decltype(&ndq_decode_mean) decode_mean;
     decltype(&ndq_code_entropy) code_entropy;
     decltype(&ndq_dense_pack) dense_pack;
     decltype(&ndq_dense_unpack) dense_unpack;
@@ -412,7 +413,49 @@ NDQ_METHOD(aggregate, 3)
     return status([&] { return lib.aggregate(list.data(), (uint32_t)W, n, scale, (float*)address(out), s); });
 }
 
-// workers of (codes, steps, kind, levels_or_M, d[, alpha]), n, bucket, scale, out
+// (codes, steps, kind, levels_or_M, d[, alpha])
+ndq_worker worker_message(PyObject* entry, size_t n, uint32_t bucket)
+{
+    Sequence f(entry);
+    if (f.size() < 5u) fail(PyExc_ValueError, "a worker has at least five entries");
+    const at::Tensor &codes = tensor(f[0], "codes"), &steps = tensor(f[1], "steps");
+    ndq_worker wk;
+    wk.kind = (uint32_t)integer(f[2]);
+    wk.levels_or_M = (uint32_t)integer(f[3]);
+    wk.alpha = f.size() > 5u ? real(f[5]) : 1.0f;
+    wk.dither = dither(f[4]);
+    check_message(codes, steps, n, code_bits(wk.levels_or_M), bucket);
+    wk.codes = address(codes);
+    wk.steps = (const float*)address(steps);
+    return wk;
+}
+
+// workers, decoded, n, bucket, scale, out
+NDQ_METHOD(decode_mean, 6)
+{
+    Sequence workers(v[0]), decoded(v[1]);
+    const size_t W = workers.size();
+    if (decoded.size() != W) fail(PyExc_ValueError, "one decoded vector per worker");
+    const size_t n = integer(v[2]);
+    const uint32_t bucket = (uint32_t)integer(v[3]);
+    const float scale = real(v[4]);
+    Few<ndq_worker, 32> list(W);
+    Few<float*, 32> values(W);
+    for (size_t w = 0; w < W; ++w) {
+        list[w] = worker_message(workers[w], n, bucket);
+        const at::Tensor& t = tensor(decoded[w], "decoded[w]");
+        check_values(t, n, "decoded[w] must hold n float32");
+        values[w] = (float*)address(t);
+    }
+    const at::Tensor& out = tensor(v[5], "out");
+    check_values(out, n, "out must hold n float32");
+    void* s = current_stream();
+    return status([&] {
+        return lib.decode_mean(list.data(), values.data(), (uint32_t)W, n, bucket, scale, (float*)address(out), s);
+    });
+}
+
+// workers, n, bucket, scale, out
 NDQ_METHOD(decode_chain, 5)
 {
     Sequence workers(v[0]);
@@ -421,19 +464,7 @@ NDQ_METHOD(decode_chain, 5)
     const uint32_t bucket = (uint32_t)integer(v[2]);
     const float scale = real(v[3]);
     Few<ndq_worker, 32> list(W);
-    for (size_t w = 0; w < W; ++w) {
-        Sequence f(workers[w]);
-        if (f.size() < 5u) fail(PyExc_ValueError, "a worker has at least five entries");
-        const at::Tensor &codes = tensor(f[0], "codes"), &steps = tensor(f[1], "steps");
-        ndq_worker& wk = list[w];
-        wk.kind = (uint32_t)integer(f[2]);
-        wk.levels_or_M = (uint32_t)integer(f[3]);
-        wk.alpha = f.size() > 5u ? real(f[5]) : 1.0f;
-        wk.dither = dither(f[4]);
-        check_message(codes, steps, n, code_bits(wk.levels_or_M), bucket);
-        wk.codes = address(codes);
-        wk.steps = (const float*)address(steps);
-    }
+    for (size_t w = 0; w < W; ++w) list[w] = worker_message(workers[w], n, bucket);
     const at::Tensor& out = tensor(v[4], "out");
     check_values(out, n, "out must hold n float32");
     void* s = current_stream();
@@ -544,7 +575,7 @@ PyObject* bind(PyObject*, PyObject* const* v, Py_ssize_t n)
         !take(v[0], "ndq_encode_workers", &l.encode_workers) || !take(v[0], "ndq_dq_decode", &l.dq_decode) ||
         !take(v[0], "ndq_dq_decode_half", &l.dq_decode_half) || !take(v[0], "ndq_nested_decode", &l.nested_decode) ||
         !take(v[0], "ndq_aggregate", &l.aggregate) || !take(v[0], "ndq_decode_chain", &l.decode_chain) ||
-        !take(v[0], "ndq_code_entropy", &l.code_entropy) || !take(v[0], "ndq_dense_pack", &l.dense_pack) ||
+        !take(v[0], "ndq_decode_mean", &l.decode_mean) || !take(v[0], "ndq_code_entropy", &l.code_entropy) || !take(v[0], "ndq_dense_pack", &l.dense_pack) ||
         !take(v[0], "ndq_dense_unpack", &l.dense_unpack) || !take(v[0], "ndq_dense_bytes", &l.dense_bytes) || !take(v[0], "ndq_sqdiff", &l.sqdiff) ||
         !take(v[0], "ndq_sqdiff_static", &l.sqdiff_static))
         return nullptr;
@@ -559,7 +590,7 @@ PyObject* bind(PyObject*, PyObject* const* v, Py_ssize_t n)
 PyMethodDef methods[] = {
     NDQ_ENTRY(bind), NDQ_ENTRY(absmax), NDQ_ENTRY(dq_encode), NDQ_ENTRY(dq_encode_with_step),
     NDQ_ENTRY(nested_encode), NDQ_ENTRY(nested_encode_with_step), NDQ_ENTRY(encode_workers), NDQ_ENTRY(dq_decode),
-    NDQ_ENTRY(dq_decode_half), NDQ_ENTRY(nested_decode), NDQ_ENTRY(aggregate), NDQ_ENTRY(decode_chain),
+    NDQ_ENTRY(dq_decode_half), NDQ_ENTRY(nested_decode), NDQ_ENTRY(aggregate), NDQ_ENTRY(decode_chain), NDQ_ENTRY(decode_mean),
     NDQ_ENTRY(code_entropy), NDQ_ENTRY(dense_pack), NDQ_ENTRY(dense_unpack), NDQ_ENTRY(sqdiff),
     NDQ_ENTRY(sqdiff_static), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_native", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};

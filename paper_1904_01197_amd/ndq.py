@@ -22,7 +22,7 @@ NDQ_OK, NDQ_EINVAL, NDQ_EALIGN, NDQ_EUNSUPPORTED, NDQ_ELAUNCH = 0, -1, -2, -3, -
 EXPORTS = ("ndq_code_bits", "ndq_packed_bytes", "ndq_num_buckets", "ndq_absmax", "ndq_dq_encode",
            "ndq_dq_encode_with_step", "ndq_nested_encode_with_step", "ndq_encode_workers",
            "ndq_dq_decode", "ndq_dq_decode_half", "ndq_nested_encode", "ndq_nested_decode", "ndq_aggregate",
-           "ndq_decode_chain", "ndq_code_entropy", "ndq_dense_group", "ndq_dense_bytes",
+           "ndq_decode_chain", "ndq_decode_mean", "ndq_code_entropy", "ndq_dense_group", "ndq_dense_bytes",
            "ndq_dense_pack", "ndq_dense_unpack", "ndq_alpha_for_equal_variance",
            "ndq_decode_error_bound", "ndq_nesting_ratio_for_error", "ndq_sqdiff_workspace", "ndq_sqdiff", "ndq_sqdiff_static",
            "ndq_strerror")
@@ -99,6 +99,8 @@ def lib():
         L.ndq_aggregate.argtypes, L.ndq_aggregate.restype = [vp, u32, sz, f32, vp, vp], ci
         L.ndq_decode_chain.argtypes = [C.POINTER(ndq_worker), u32, sz, u32, f32, vp, vp]
         L.ndq_decode_chain.restype = ci
+        L.ndq_decode_mean.argtypes = [C.POINTER(ndq_worker), vp, u32, sz, u32, f32, vp, vp]
+        L.ndq_decode_mean.restype = ci
         L.ndq_alpha_for_equal_variance.argtypes = [C.c_double, C.c_double]
         L.ndq_alpha_for_equal_variance.restype = C.c_double
         L.ndq_decode_error_bound.argtypes = [C.c_double, u32, C.c_double, C.c_double]
@@ -242,6 +244,14 @@ def ndq_decode_chain(workers, n, bucket, scale=1.0, out=None):
     order; alpha (nested workers only) defaults to 1."""
     out = _values(out, n, workers[0][0])
     _check(_ready().decode_chain(workers, n, bucket, scale, out), "ndq_decode_chain")
+    return out
+
+
+def ndq_decode_mean(workers, decoded, n, bucket, scale=1.0, out=None):
+    """workers: as in ndq_decode_chain, all DQSG; decoded: one float32 tensor per worker for its
+    reconstruction; -> out, scale times their sum."""
+    out = _values(out, n, workers[0][0])
+    _check(_ready().decode_mean(workers, decoded, n, bucket, scale, out), "ndq_decode_mean")
     return out
 
 

@@ -90,10 +90,10 @@ def decode_chain_fused(wl: Workload, n: int, bufs: Buffers, ds):
 def decode_separately(wl: Workload, n: int, bufs: Buffers, ds):
     """Server side of Algorithm 1 as printed: reconstruct every worker's gradient,
     then average them (all-DQSG workloads only)."""
-    for w, (kind, arg) in enumerate(wl.plan):
-        assert kind == "dq"
-        ndq.ndq_dq_decode(bufs.codes[w], n, arg, wl.bucket, bufs.steps[w], ds[w], bufs.decoded[w])
-    return ndq.ndq_aggregate(bufs.decoded, wl.out_scale, bufs.total)
+    assert all(kind == "dq" for kind, _ in wl.plan)
+    workers = [(bufs.codes[w], bufs.steps[w], ndq.NDQ_WORKER_DQ, arg, ds[w])
+               for w, (_, arg) in enumerate(wl.plan)]
+    return ndq.ndq_decode_mean(workers, bufs.decoded, n, wl.bucket, wl.out_scale, bufs.total)
 
 
 def step(wl: Workload, grads, bufs: Buffers, ds, preset_step: float = 0.0):

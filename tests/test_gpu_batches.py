@@ -111,3 +111,29 @@ def test_bad_workers_are_reported_and_nothing_is_launched():
         assert e.value.rc == ndq.NDQ_EINVAL
     torch.cuda.synchronize()
     assert steps.item() == -1.0 and (codes == 7).all()
+
+
+@pytest.mark.parametrize("W", [1, 3, 33, 70])
+def test_decode_mean_keeps_every_reconstruction_and_their_sum(W):
+    # tile edges (512 elements), partial vectors of four, levels of every code width, more workers
+    # than one launch holds; sums in the same order as the oracle's, so bit for bit
+    levels = [3, 5, 16, 2, 100, 256, 9]
+    for n, bucket in ((1, 0), (511, 0), (513, 64), (2048 + 6, 512), (20000, 2112)):
+        seeds = list(range(W))
+        msgs, decoded = [], [torch.full((n,), 7.0, device="cuda") for _ in range(W)]
+        host = _host(W, n, "f32", n)
+        refs = []
+        for w in range(W):
+            d = oracle.dither(seeds[w], 2, w, 64)
+            c, s = oracle.dq_encode(host[w], 0.0, levels[w % 7], bucket, d)
+            refs.append(oracle.dq_decode(c, n, levels[w % 7], bucket, s, d))
+            msgs.append((torch.from_numpy(c).cuda(), torch.from_numpy(s).cuda(), ndq.NDQ_WORKER_DQ, levels[w % 7],
+                         ndq.ndq_dither(seeds[w], 2, w, 64)))
+        out = ndq.ndq_decode_mean(msgs, decoded, n, bucket, 1.0 / W)
+        for w in range(W):
+            assert np.array_equal(decoded[w].cpu().numpy(), refs[w]), (n, bucket, w)
+        assert np.array_equal(out.cpu().numpy(), oracle.aggregate(refs, 1.0 / W)), (n, bucket)
+    bad = list(msgs[0])
+    bad[2] = ndq.NDQ_WORKER_NESTED
+    with pytest.raises(ndq.NdqError):
+        ndq.ndq_decode_mean([tuple(bad)], decoded[:1], n, bucket)
