@@ -159,6 +159,11 @@ constexpr uint32_t kChainMax = 32;    // workers per launch
 #endif
 constexpr int kChainRows = NDQ_CHAIN_ROWS;   // rows of 8 elements per lane and tile
 constexpr uint32_t kChainTile = kWave * kLaneElems * kChainRows;
+// Below these numbers of tiles a wave takes one row: two waves per SIMD then hide each other's
+// latency where one would wait.  chain_kernel (4 DQSG + 4 nested M = 3: 0.27 M elements 9.8 against
+// 12.2 us, 1 M 10.9 / 12.8, 2 M 14.6 / 16.6, 4 M 20.6 / 20.1), chain_stream_kernel (4 workers: 1 M 5.6
+// against 6.4, 2 M 8.1 / 8.4, 4 M 12.4 / 10.7).
+constexpr uint32_t kShortGeneralTiles = 4096, kShortTiles = 2048;
 
 struct ChainWorker {
     const unsigned char* codes;
@@ -189,60 +194,48 @@ struct ChainArgs {
     uint32_t tile_begin;  // chain_kernel: first tile of this launch; chain_stream_kernel: tiles it owns
 };
 
-// What is prefetched per worker: the step and, per row, the words holding the
-// lane's eight codes (8*bits bits starting at a multiple of 8 bits).
-struct ChainFetch {
-    uint32_t w0[kChainRows], w1[kChainRows], w2[kChainRows];
-    float step[kChainRows];
+// What is prefetched per worker and row: the step, and a lane's eight codes -- `bits` bytes of
+// the stream at any byte address -- as one 64-bit load from there, whatever the code width.
+template <int ROWS> struct ChainFetch {
+    uint64_t codes[ROWS];
+    float step[ROWS];
 };
 
-// Code widths 1, 2 and 4: a lane's eight codes are exactly 1, 2 or 4 bytes at a
-// multiple of their size, so in a full tile one narrow load fetches them with
-// nothing to shift or join afterwards.
-__device__ __forceinline__ bool chain_aligned(uint32_t bits) { return bits == 1u || bits == 2u || bits == 4u; }
-
 // ROWB: a bucket is one row of the tile (the tiling is by tile and every row has
-// its own step); otherwise one step serves the tile.
-template <bool FULL, bool ROWB>
+// its own step); otherwise one step serves the tile.  FULL: every element of the tile is
+// valid and the stream goes on for at least eight bytes after it; else lanes near the end
+// load the stream's last eight bytes and shift (it has at least eight from a tile's start on:
+// its size is a multiple of 16 and a tile starts at a multiple of 8).
+template <bool FULL, bool ROWB, int ROWS>
 __device__ __forceinline__ void chain_fetch(const ChainArgs& a, const ChainWorker& cw, const TileRef& t,
-                                            int lane, ChainFetch& f)
+                                            int lane, ChainFetch<ROWS>& f)
 {
     const uint32_t bits = cw.bits;
-    const uint32_t* codes32 = (const uint32_t*)(cw.codes + (t.start >> 3) * bits);
+    const unsigned char* tile = cw.codes + (t.start >> 3) * bits;
     if (ROWB) {
 #pragma unroll
-        for (int r = 0; r < kChainRows; ++r) {
-            const uint32_t b = t.bucket * kChainRows + r;          // rows past the last bucket get 0
+        for (int r = 0; r < ROWS; ++r) {
+            const uint32_t b = t.bucket * ROWS + r;                // rows past the last bucket get 0
             f.step[r] = b < a.num_buckets ? cw.steps[b] : 0.0f;
         }
     } else {
         f.step[0] = cw.steps[t.bucket];
     }
-    if (FULL && chain_aligned(bits)) {
-        const unsigned char* mine = (const unsigned char*)codes32 + (uint32_t)lane * bits;
 #pragma unroll
-        for (int r = 0; r < kChainRows; ++r) {
-            const unsigned char* p = mine + (uint32_t)(r * kWave) * bits;
-            f.w0[r] = bits == 1u ? (uint32_t)*p : bits == 2u ? (uint32_t)*(const uint16_t*)p : *(const uint32_t*)p;
-            f.w1[r] = 0; f.w2[r] = 0;
+    for (int r = 0; r < ROWS; ++r) {
+        uint32_t off = (uint32_t)(r * kWave + lane) * bits, shift = 0u;
+        if (!FULL) {
+            const uint64_t total = (((a.tl.n * bits + 7u) >> 3) + 15u) & ~(uint64_t)15u;
+            const uint64_t left = total - (t.start >> 3) * bits - 8u;
+            const uint32_t limit = left < 0xFFFFu ? (uint32_t)left : 0xFFFFu;   // (a tile has at most 1,024 bytes)
+            if (off > limit) {
+                shift = (off - limit) * 8u;
+                off = limit;
+            }
         }
-        return;
-    }
-#pragma unroll
-    for (int r = 0; r < kChainRows; ++r) {
-        const uint32_t o = (uint32_t)(r * kWave + lane) * kLaneElems;
-        f.w0[r] = 0; f.w1[r] = 0; f.w2[r] = 0;
-        if (FULL || o < t.len) {
-            const uint32_t bit = o * bits;                     // multiple of 8
-            const uint32_t w = bit >> 5, sh = bit & 31u;
-            // bits used from word w on; a ragged tail only counts its valid codes so
-            // that no word past the stream is touched
-            const uint32_t ncodes = FULL ? 8u : (t.len - o < 8u ? t.len - o : 8u);
-            const uint32_t end = sh + ncodes * bits;
-            f.w0[r] = codes32[w];
-            if (end > 32u) f.w1[r] = codes32[w + 1];
-            if (end > 64u) f.w2[r] = codes32[w + 2];
-        }
+        __builtin_memcpy(&f.codes[r], tile + off, 8);
+        // lanes past the end shift by 64 or more: what they decode is never stored
+        if (!FULL) f.codes[r] >>= shift & 63u;
     }
 }
 
@@ -270,42 +263,27 @@ __device__ __forceinline__ bool chain_row(const ChainWorker& cw, const Quant& qp
     return near_tie;
 }
 
-// Folds one worker into the running sum S of a tile.  WIDTH: 1, 2, 4 = that many
-// code bits, fetched by chain_fetch's aligned path (full tiles only); -1 = any
-// width up to kFieldAsFloatMaxBits; 0 = any width.  All but 0 turn the codes into
-// floats with FieldAsFloat.  FIRST: the running sum starts with this worker.
-template <int MODE, int WIDTH, bool FIRST, bool ROWB>
-__device__ __forceinline__ void chain_fold(const ChainWorker& cw, const ChainFetch& f,
-                                           uint64_t block0, int lane, float (&S)[kChainRows][8])
+// Folds one worker into the running sum S of a tile.  NARROW: codes of at most
+// kFieldAsFloatMaxBits bits, turned into floats with FieldAsFloat.  FIRST: the running sum
+// starts with this worker.
+template <int MODE, bool NARROW, bool FIRST, bool ROWB, int ROWS>
+__device__ __forceinline__ void chain_fold(const ChainWorker& cw, const ChainFetch<ROWS>& f,
+                                           uint64_t block0, int lane, float (&S)[ROWS][8])
 {
-    constexpr bool ALIGNED = WIDTH > 0;
-    constexpr int NF = (WIDTH == 1 || WIDTH == 2) ? 8 : 4;     // fields taken from one 32-bit group
-    const uint32_t bits = ALIGNED ? (uint32_t)WIDTH : cw.bits;
-    const FieldAsFloat<NF> field(WIDTH != 0 ? bits : 1u, MODE == kDq ? (float)cw.q_min : 0.0f);
-    float inv_row[kChainRows];
+    const uint32_t bits = cw.bits;
+    const FieldAsFloat<4> field(NARROW ? bits : 1u, MODE == kDq ? (float)cw.q_min : 0.0f);
+    float inv_row[ROWS];
 #pragma unroll
-    for (int r = 0; r < kChainRows; ++r)
+    for (int r = 0; r < ROWS; ++r)
         inv_row[r] = (ROWB || r == 0) ? cw.alpha * inv_step(f.step[ROWB ? r : 0]) : inv_row[0];
     Quant qp;
     qp.M = cw.M; qp.M_f = cw.M_f; qp.inv_M_f = cw.inv_M_f; qp.q_min = cw.q_min;
     qp.alpha = cw.alpha; qp.beta = cw.beta;
 #pragma unroll
-    for (int r = 0; r < kChainRows; ++r) {
+    for (int r = 0; r < ROWS; ++r) {
         const uint32_t o = (uint32_t)(r * kWave + lane) * kLaneElems;
         const float step = f.step[ROWB ? r : 0], inv = inv_row[r];
-        uint32_t half[2];
-        if (ALIGNED) {
-            half[0] = f.w0[r];
-            half[1] = NF == 8 ? f.w0[r] : f.w0[r] >> (4u * bits);
-        } else {
-            const uint32_t sh = (o * bits) & 31u;
-            // the lane's 8*bits code bits, in two halves of four codes
-            const uint64_t low = (((uint64_t)f.w1[r] << 32) | f.w0[r]) >> sh;
-            const uint64_t high = sh ? ((uint64_t)f.w2[r] << (64u - sh)) : 0u;
-            const uint64_t chunk = low | high;
-            half[0] = (uint32_t)chunk;
-            half[1] = (uint32_t)(chunk >> (4u * bits));
-        }
+        const uint32_t half[2] = {(uint32_t)f.codes[r], (uint32_t)(f.codes[r] >> (4u * bits))};
         float v[8];
         dither8(cw.ds, block0 + (o >> 3), v);
         if (MODE == kNestedAnyM) {
@@ -314,7 +292,7 @@ __device__ __forceinline__ void chain_fold(const ChainWorker& cw, const ChainFet
             float c_f[8];
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
-                if (WIDTH != 0) c_f[k] = NF == 8 ? field.get(half[0], k) : field.get(half[k >> 2], k & 3);
+                if (NARROW) c_f[k] = field.get(half[k >> 2], k & 3);
                 else c_f[k] = (float)__builtin_amdgcn_ubfe(half[k >> 2], (k & 3) * bits, bits);
             }
             float next[8];
@@ -328,8 +306,8 @@ __device__ __forceinline__ void chain_fold(const ChainWorker& cw, const ChainFet
             for (int k = 0; k < 8; ++k) {
                 // the code as a float: plus q_min for DQSG, as it is for a nested worker
                 float c_f;
-                if (WIDTH != 0) {
-                    c_f = NF == 8 ? field.get(half[0], k) : field.get(half[k >> 2], k & 3);
+                if (NARROW) {
+                    c_f = field.get(half[k >> 2], k & 3);
                 } else {
                     const uint32_t c = __builtin_amdgcn_ubfe(half[k >> 2], (k & 3) * bits, bits);
                     c_f = MODE == kDq ? (float)((int32_t)c + qp.q_min) : (float)c;
@@ -349,26 +327,21 @@ __device__ __forceinline__ void chain_fold(const ChainWorker& cw, const ChainFet
     }
 }
 
-// Picks the instantiation for a worker's code width.
-template <int MODE, bool FULL, bool FIRST, bool ROWB>
-__device__ __forceinline__ void chain_fold_width(const ChainWorker& cw, const ChainFetch& f,
-                                                 uint64_t block0, int lane, float (&S)[kChainRows][8])
+template <int MODE, bool FIRST, bool ROWB, int ROWS>
+__device__ __forceinline__ void chain_fold_width(const ChainWorker& cw, const ChainFetch<ROWS>& f,
+                                                 uint64_t block0, int lane, float (&S)[ROWS][8])
 {
-    const uint32_t bits = cw.bits;
-    if (FULL && bits == 1u) chain_fold<MODE, 1, FIRST, ROWB>(cw, f, block0, lane, S);
-    else if (FULL && bits == 2u) chain_fold<MODE, 2, FIRST, ROWB>(cw, f, block0, lane, S);
-    else if (FULL && bits == 4u) chain_fold<MODE, 4, FIRST, ROWB>(cw, f, block0, lane, S);
-    else if (bits <= kFieldAsFloatMaxBits) chain_fold<MODE, -1, FIRST, ROWB>(cw, f, block0, lane, S);
-    else chain_fold<MODE, 0, FIRST, ROWB>(cw, f, block0, lane, S);
+    if (cw.bits <= kFieldAsFloatMaxBits) chain_fold<MODE, true, FIRST, ROWB, ROWS>(cw, f, block0, lane, S);
+    else chain_fold<MODE, false, FIRST, ROWB, ROWS>(cw, f, block0, lane, S);
 }
 
-template <bool FULL, bool ROWB, bool ANYM>
+template <bool FULL, bool ROWB, bool ANYM, int ROWS>
 __device__ __forceinline__ void chain_tile(const ChainArgs& a, const TileRef& t, int lane)
 {
-    float S[kChainRows][8];
+    float S[ROWS][8];
     float* out = a.out + t.start;
 #pragma unroll
-    for (int r = 0; r < kChainRows; ++r) {
+    for (int r = 0; r < ROWS; ++r) {
         const uint32_t o = (uint32_t)(r * kWave + lane) * kLaneElems;
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
@@ -376,27 +349,27 @@ __device__ __forceinline__ void chain_tile(const ChainArgs& a, const TileRef& t,
             if (a.continue_sum && (FULL || o + k < t.len)) S[r][k] = out[o + k];
         }
     }
-    ChainFetch cur;
-    chain_fetch<FULL, ROWB>(a, a.w[0], t, lane, cur);
-    ChainFetch nxt = cur;
+    ChainFetch<ROWS> cur;
+    chain_fetch<FULL, ROWB, ROWS>(a, a.w[0], t, lane, cur);
+    ChainFetch<ROWS> nxt = cur;
     for (uint32_t w = 0; w < a.W; ++w) {
         const ChainWorker& cw = a.w[w];
-        if (w + 1 < a.W) chain_fetch<FULL, ROWB>(a, a.w[w + 1], t, lane, nxt);
+        if (w + 1 < a.W) chain_fetch<FULL, ROWB, ROWS>(a, a.w[w + 1], t, lane, nxt);
         const uint64_t block0 = (cw.index0 + t.start) >> 3;
         if (cw.mode == kDq) {
-            if (cw.first) chain_fold_width<kDq, FULL, true, ROWB>(cw, cur, block0, lane, S);
-            else chain_fold_width<kDq, FULL, false, ROWB>(cw, cur, block0, lane, S);
+            if (cw.first) chain_fold_width<kDq, true, ROWB, ROWS>(cw, cur, block0, lane, S);
+            else chain_fold_width<kDq, false, ROWB, ROWS>(cw, cur, block0, lane, S);
         } else if (cw.mode == kNestedPow2) {
-            chain_fold_width<kNestedPow2, FULL, false, ROWB>(cw, cur, block0, lane, S);
+            chain_fold_width<kNestedPow2, false, ROWB, ROWS>(cw, cur, block0, lane, S);
         } else if (cw.mode == kNestedPow2Shrink) {
-            chain_fold_width<kNestedPow2Shrink, FULL, false, ROWB>(cw, cur, block0, lane, S);
+            chain_fold_width<kNestedPow2Shrink, false, ROWB, ROWS>(cw, cur, block0, lane, S);
         } else if (ANYM) {
-            chain_fold_width<kNestedAnyM, FULL, false, ROWB>(cw, cur, block0, lane, S);
+            chain_fold_width<kNestedAnyM, false, ROWB, ROWS>(cw, cur, block0, lane, S);
         }
         cur = nxt;
     }
 #pragma unroll
-    for (int r = 0; r < kChainRows; ++r) {
+    for (int r = 0; r < ROWS; ++r) {
         const uint32_t o = (uint32_t)(r * kWave + lane) * kLaneElems;
         float res[8];
 #pragma unroll
@@ -420,17 +393,18 @@ __device__ __forceinline__ void chain_tile(const ChainArgs& a, const TileRef& t,
 // ANYM: some worker's nesting ratio is not a power of two.  Those workers take
 // the two-pass rows of chain_fold, which need more registers: that instantiation
 // runs four waves per SIMD, and the common one does not carry their code at all.
-template <bool ROWB, bool ANYM>
+template <bool ROWB, bool ANYM, int ROWS>
 __global__ __launch_bounds__(kBlock)
 __attribute__((amdgpu_waves_per_eu(ANYM ? 4 : NDQ_CHAIN_WAVES_PER_EU)))
 void chain_kernel(ChainArgs a)
 {
+    constexpr uint32_t TILE = kWave * kLaneElems * ROWS;
     const int lane = threadIdx.x & (kWave - 1);
     const uint32_t tile_id =
         a.tile_begin + blockIdx.x * kWavesPerBlock + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const TileRef t = locate_tile(a.tl, tile_id, kChainTile);
-    if (t.len == kChainTile) chain_tile<true, ROWB, ANYM>(a, t, lane);
-    else if (t.len != 0) chain_tile<false, ROWB, ANYM>(a, t, lane);
+    const TileRef t = locate_tile(a.tl, tile_id, TILE);
+    if (t.len == TILE && t.start + TILE + 64u <= a.tl.n) chain_tile<true, ROWB, ANYM, ROWS>(a, t, lane);
+    else if (t.len != 0) chain_tile<false, ROWB, ANYM, ROWS>(a, t, lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -461,20 +435,30 @@ constexpr int kChainStreamWaves = NDQ_CHAIN_STREAM_WAVES;
 // space, indexed by the loop variable (scalar loads, no copy of the arguments)
 typedef const __attribute__((address_space(4))) ChainArgs* ChainArgsPtr;
 
-struct ChainCodes { uint32_t w[kChainRows]; float step; };
+// The forms of the kernel (launch_chain_stream has the rule): persistent waves with the
+// hand-ordered fold, or one tile per wave -- of two rows, or of one where the vector is so short
+// that a wave's own latency is the launch's time (4 workers of 1 M elements: 5.6 us
+// against 6.4; 8: 7.3 against 8.4).
+enum ChainForm { kPiped = 0, kOneTile = 1, kOneRow = 2 };
+template <int FORM> struct ChainStreamTile {
+    static constexpr int ROWS = FORM == kOneRow ? 1 : kChainRows;
+    static constexpr uint32_t N = kWave * kLaneElems * ROWS;
+};
+
+template <int ROWS> struct ChainCodes { uint32_t w[ROWS]; float step; };
 
 // a lane's eight codes of a row: `WIDTH` bytes at a multiple of WIDTH (full tiles).
 // `limit`: the largest byte offset inside the tile's codes that may be read (a multiple of
 // WIDTH); lanes past it read there instead.  Whole tiles pass 0xFFFFFFFF; for the vector's
 // ragged last tile it is the stream's last WIDTH bytes, so that the tile can be fetched and
 // folded like a whole one (what lanes past the end compute is never stored).
-template <int WIDTH>
-__device__ __forceinline__ void stream_fetch(const unsigned char* codes, uint64_t start, int lane, ChainCodes& f,
+template <int WIDTH, int ROWS>
+__device__ __forceinline__ void stream_fetch(const unsigned char* codes, uint64_t start, int lane, ChainCodes<ROWS>& f,
                                              uint32_t limit = 0xFFFFFFFFu)
 {
     const unsigned char* tile = codes + (start >> 3) * WIDTH;
 #pragma unroll
-    for (int r = 0; r < kChainRows; ++r) {
+    for (int r = 0; r < ROWS; ++r) {
         uint32_t off = (uint32_t)(r * kWave + lane) * WIDTH;
         off = off < limit ? off : limit;
         const unsigned char* p = tile + off;
@@ -486,13 +470,13 @@ __device__ __forceinline__ void stream_fetch(const unsigned char* codes, uint64_
 // The same for the vector's ragged last tile of `len` elements: a lane fetches its bytes
 // only if its first code exists (they then lie inside the stream, whose size is padded to
 // a multiple of 16 bytes: (o/8 + 1) * WIDTH <= the padded size of the tile's codes).
-template <int WIDTH>
+template <int WIDTH, int ROWS>
 __device__ __forceinline__ void stream_fetch_ragged(const unsigned char* codes, const float* steps, uint64_t start,
-                                                    uint32_t len, uint32_t bucket, int lane, ChainCodes& f)
+                                                    uint32_t len, uint32_t bucket, int lane, ChainCodes<ROWS>& f)
 {
     const unsigned char* mine = codes + (start >> 3) * WIDTH + (uint32_t)lane * WIDTH;
 #pragma unroll
-    for (int r = 0; r < kChainRows; ++r) {
+    for (int r = 0; r < ROWS; ++r) {
         const unsigned char* p = mine + (uint32_t)(r * kWave) * WIDTH;
         f.w[r] = 0u;
         if ((uint32_t)(r * kWave + lane) * kLaneElems < len)
@@ -501,10 +485,10 @@ __device__ __forceinline__ void stream_fetch_ragged(const unsigned char* codes, 
     f.step = steps[bucket];
 }
 
-template <int MODE, int WIDTH, bool FIRST>
+template <int MODE, int WIDTH, bool FIRST, int ROWS>
 __device__ __forceinline__ void stream_fold(const DitherStream& ds, uint64_t block0, float q_min_f,
-                                            float side_scale, const ChainCodes& f, float step, float inv,
-                                            int lane, float (&S)[kChainRows][8])
+                                            float side_scale, const ChainCodes<ROWS>& f, float step, float inv,
+                                            int lane, float (&S)[ROWS][8])
 {
     constexpr int NF = WIDTH == 4 ? 4 : 8;
     // a power-of-two nesting ratio is 2^(code width): M and 1/M are compile-time constants
@@ -514,7 +498,7 @@ __device__ __forceinline__ void stream_fold(const DitherStream& ds, uint64_t blo
     // v - q_min is exact for |q_min| <= 8 (code widths up to 4 bits).  Nested: m' = c / M.
     const FieldScaled<NF> field((uint32_t)WIDTH, MODE == kDq ? 0u : (uint32_t)WIDTH);
 #pragma unroll
-    for (int r = 0; r < kChainRows; ++r) {
+    for (int r = 0; r < ROWS; ++r) {
         const uint32_t o = (uint32_t)(r * kWave + lane) * kLaneElems;
         float v[8];
         if (MODE == kDq) dither8_shifted(ds, block0 + (o >> 3), -q_min_f, v);
@@ -678,7 +662,7 @@ __device__ __forceinline__ void fold_row_piped(const uint32_t (&words)[4], uint3
 template <int MODE, int WIDTH, bool FIRST>
 __device__ __forceinline__ void stream_fold_piped(const PhiloxUniform& keys, uint32_t block0, const PhiloxUniform& keys_next,
                                                   uint32_t block_next, int32_t q_min, float side_scale,
-                                                  const ChainCodes& f, float step, float inv,
+                                                  const ChainCodes<kChainRows>& f, float step, float inv,
                                                   float (&S)[kChainRows][8], PhiloxFlight& fl)
 {
 #pragma unroll
@@ -692,26 +676,26 @@ __device__ __forceinline__ void stream_fold_piped(const PhiloxUniform& keys, uin
 }
 
 // The ragged last tile with the same folds: lanes past the end decode zeros and store nothing.
-template <int RMODE, int W0, int WR>
+template <int RMODE, int W0, int WR, int ROWS>
 __device__ __forceinline__ void stream_ragged_tile(ChainArgsPtr a, uint64_t start, uint32_t len, uint32_t bucket,
                                                    int lane)
 {
     const uint32_t W = a->W;
-    float S[kChainRows][8];
-    ChainCodes cur, nxt;
-    stream_fetch_ragged<W0>(a->w[0].codes, a->w[0].steps, start, len, bucket, lane, cur);
+    float S[ROWS][8];
+    ChainCodes<ROWS> cur, nxt;
+    stream_fetch_ragged<W0, ROWS>(a->w[0].codes, a->w[0].steps, start, len, bucket, lane, cur);
     nxt = cur;
-    if (W > 1u) stream_fetch_ragged<WR>(a->w[1].codes, a->w[1].steps, start, len, bucket, lane, nxt);
+    if (W > 1u) stream_fetch_ragged<WR, ROWS>(a->w[1].codes, a->w[1].steps, start, len, bucket, lane, nxt);
     {
         const DitherStream ds = {a->w[0].ds.key0, a->w[0].ds.key1, a->w[0].ds.step, a->w[0].ds.worker};
-        stream_fold<kDq, W0, true>(ds, (a->w[0].index0 + start) >> 3, (float)a->w[0].q_min, 0.0f, cur, cur.step,
+        stream_fold<kDq, W0, true, ROWS>(ds, (a->w[0].index0 + start) >> 3, (float)a->w[0].q_min, 0.0f, cur, cur.step,
                                    inv_step(cur.step), lane, S);
     }
     cur = nxt;
     for (uint32_t w = 1; w < W; ++w) {
-        if (w + 1u < W) stream_fetch_ragged<WR>(a->w[w + 1u].codes, a->w[w + 1u].steps, start, len, bucket, lane, nxt);
+        if (w + 1u < W) stream_fetch_ragged<WR, ROWS>(a->w[w + 1u].codes, a->w[w + 1u].steps, start, len, bucket, lane, nxt);
         const DitherStream ds = {a->w[w].ds.key0, a->w[w].ds.key1, a->w[w].ds.step, a->w[w].ds.worker};
-        stream_fold<RMODE, WR, false>(ds, (a->w[w].index0 + start) >> 3, (float)a->w[w].q_min, a->w[w].side_scale,
+        stream_fold<RMODE, WR, false, ROWS>(ds, (a->w[w].index0 + start) >> 3, (float)a->w[w].q_min, a->w[w].side_scale,
                                       cur, cur.step, inv_step(cur.step), lane, S);
         cur = nxt;
     }
@@ -719,7 +703,7 @@ __device__ __forceinline__ void stream_ragged_tile(ChainArgsPtr a, uint64_t star
     const float scale = a->scale;
     const bool apply_scale = a->apply_scale != 0;
 #pragma unroll
-    for (int r = 0; r < kChainRows; ++r) {
+    for (int r = 0; r < ROWS; ++r) {
         const uint32_t o = (uint32_t)(r * kWave + lane) * kLaneElems;
 #pragma unroll
         for (uint32_t k = 0; k < 8; ++k)
@@ -741,7 +725,8 @@ __device__ __forceinline__ void redo_out_of_range(ChainArgsPtr a, uint32_t first
         if (__builtin_amdgcn_ballot_w64(step_out_of_range(my_steps[bucket])) == 0) continue;
         const uint64_t start = (uint64_t)tile * kChainTile;
         const uint64_t left = a->tl.n - start;
-        stream_ragged_tile<RMODE, W0, WR>(a, start, left < kChainTile ? (uint32_t)left : kChainTile, bucket, lane);
+        stream_ragged_tile<RMODE, W0, WR, kChainRows>(a, start, left < kChainTile ? (uint32_t)left : kChainTile, bucket,
+                                                      lane);
     }
 }
 
@@ -768,12 +753,15 @@ __device__ __forceinline__ void redo_out_of_range(ChainArgsPtr a, uint32_t first
 #ifndef NDQ_CHAIN_PIPED_WAVES
 #define NDQ_CHAIN_PIPED_WAVES NDQ_CHAIN_STREAM_WAVES
 #endif
-template <int RMODE, int W0, int WR, bool RAGGED, bool PIPED>
+template <int RMODE, int W0, int WR, bool RAGGED, int FORM>
 __global__ __launch_bounds__(kBlock)
-__attribute__((amdgpu_waves_per_eu(PIPED ? NDQ_CHAIN_PIPED_WAVES : kChainStreamWaves, PIPED ? NDQ_CHAIN_PIPED_WAVES : kChainStreamWaves)))
+__attribute__((amdgpu_waves_per_eu(FORM == kPiped ? NDQ_CHAIN_PIPED_WAVES : kChainStreamWaves, FORM == kPiped ? NDQ_CHAIN_PIPED_WAVES : kChainStreamWaves)))
 void chain_stream_kernel(ChainArgs a_by_value)
 {
+    constexpr bool PIPED = FORM == kPiped;
     constexpr bool TAIL = RAGGED && PIPED;     // the ragged tile runs through the main loop
+    constexpr int ROWS = ChainStreamTile<FORM>::ROWS;
+    constexpr uint32_t TILE = ChainStreamTile<FORM>::N;
     constexpr bool SCALED = PIPED && RowScaled<RMODE, WR>::value;
     constexpr float kM = RMODE == kDq ? 1.0f : (float)(1u << WR), kInvM = 1.0f / kM;
     const ChainArgsPtr a = (ChainArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
@@ -781,7 +769,7 @@ void chain_stream_kernel(ChainArgs a_by_value)
     const uint32_t stride = gridDim.x * kWavesPerBlock;
     const uint32_t wave_in_block = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const uint32_t first = blockIdx.x * kWavesPerBlock + wave_in_block;
-    __shared__ __align__(16) float out_stage_all[PIPED ? kWavesPerBlock : 1][PIPED ? kChainTile : 4];
+    __shared__ __align__(16) float out_stage_all[PIPED ? kWavesPerBlock : 1][PIPED ? TILE : 4];
     float* out_stage = out_stage_all[PIPED ? wave_in_block : 0u];
     const uint32_t tiles = a->tile_begin;                  // whole tiles: ids 0 .. tiles-1
     const uint32_t tiles_all = TAIL ? tiles + 1u : tiles;  // TAIL: and the ragged one, id `tiles`
@@ -794,9 +782,9 @@ void chain_stream_kernel(ChainArgs a_by_value)
     // The ragged last tile goes first, to a wave that has no whole tile if the grid has one
     // (one tile per wave), else to wave 0: at the start every SIMD is full and hides its
     // latencies; as a kernel of its own, or at the end, it would run alone at a fifth of the rate.
-    const uint64_t whole = (uint64_t)tiles * kChainTile;
+    const uint64_t whole = (uint64_t)tiles * TILE;
     if (RAGGED && !PIPED && whole < a->tl.n && first == (stride > tiles ? tiles : 0u))
-        stream_ragged_tile<RMODE, W0, WR>(a, whole, (uint32_t)(a->tl.n - whole), one_bucket ? 0u : tiles / tpb, lane);
+        stream_ragged_tile<RMODE, W0, WR, ROWS>(a, whole, (uint32_t)(a->tl.n - whole), one_bucket ? 0u : tiles / tpb, lane);
     if (first >= tiles_all) return;
     const uint32_t my_tiles = (tiles_all - first + stride - 1u) / stride;
     // TAIL: elements of the ragged tile, and per code width the last byte offset inside its
@@ -815,12 +803,12 @@ void chain_stream_kernel(ChainArgs a_by_value)
     uint32_t done = 0;
     if (my_tiles > 1u) __builtin_amdgcn_s_setprio(3);
 
-    ChainCodes cur;
-    stream_fetch<W0>(a->w[0].codes, (uint64_t)first * kChainTile, lane, cur, limit_for(first, limit0));
+    ChainCodes<ROWS> cur;
+    stream_fetch<W0, ROWS>(a->w[0].codes, (uint64_t)first * TILE, lane, cur, limit_for(first, limit0));
     // PIPED: the dither of the row after the current one is always in flight; here the first row's
     PhiloxFlight fl;
     if (PIPED) {
-        fl.start(uniform_keys(a, 0u), block_low(a->w[0].index0, (uint64_t)first * kChainTile, lane));
+        fl.start(uniform_keys(a, 0u), block_low(a->w[0].index0, (uint64_t)first * TILE, lane));
         fl.run();
     }
     // Lane w looks after worker w's step: one load and ONE correctly rounded division per tile
@@ -831,11 +819,11 @@ void chain_stream_kernel(ChainArgs a_by_value)
     float steps_ahead = my_steps[one_bucket ? 0u : first / tpb];
     bool out_of_range = false;
     for (uint32_t tile = first; tile < tiles_all; tile += stride) {
-        const uint64_t start = (uint64_t)tile * kChainTile;
+        const uint64_t start = (uint64_t)tile * TILE;
         // where the dither after this tile's last row belongs: past the end after the last tile (unused)
-        const uint64_t next_start = start + (uint64_t)stride * kChainTile;
-        float S[kChainRows][8];
-        ChainCodes nxt;
+        const uint64_t next_start = start + (uint64_t)stride * TILE;
+        float S[ROWS][8];
+        ChainCodes<ROWS> nxt;
         const float steps_here = steps_ahead;
         {
             const uint32_t nt = tile + stride < tiles_all ? tile + stride : tile;
@@ -852,15 +840,15 @@ void chain_stream_kernel(ChainArgs a_by_value)
         };
         // first worker: DQSG, starts the sum; meanwhile the second worker's codes (or the next tile's)
         if (W > 1u) {
-            stream_fetch<WR>(a->w[1].codes, start, lane, nxt, limit_for(tile, limitr));
+            stream_fetch<WR, ROWS>(a->w[1].codes, start, lane, nxt, limit_for(tile, limitr));
         } else {
             const uint32_t nt = tile + stride < tiles_all ? tile + stride : tile;
-            ChainCodes tmp;
-            stream_fetch<W0>(a->w[0].codes, (uint64_t)nt * kChainTile, lane, tmp, limit_for(nt, limit0));
+            ChainCodes<ROWS> tmp;
+            stream_fetch<W0, ROWS>(a->w[0].codes, (uint64_t)nt * TILE, lane, tmp, limit_for(nt, limit0));
             nxt = tmp;
         }
         {
-            if (PIPED) {
+            if constexpr (PIPED) {
                 const uint32_t wn = W > 1u ? 1u : 0u;
                 stream_fold_piped<kDq, W0, true>(
                     uniform_keys(a, 0u), block_low(a->w[0].index0, start, lane), uniform_keys(a, wn),
@@ -868,7 +856,7 @@ void chain_stream_kernel(ChainArgs a_by_value)
                     from_lane(steps_here, 0u), 0.0f, S, fl);
             } else {
                 const DitherStream ds = {a->w[0].ds.key0, a->w[0].ds.key1, a->w[0].ds.step, a->w[0].ds.worker};
-                stream_fold<kDq, W0, true>(ds, (a->w[0].index0 + start) >> 3, (float)a->w[0].q_min, 0.0f, cur,
+                stream_fold<kDq, W0, true, ROWS>(ds, (a->w[0].index0 + start) >> 3, (float)a->w[0].q_min, 0.0f, cur,
                                            from_lane(steps_here, 0u), 0.0f, lane, S);
             }
         }
@@ -876,14 +864,14 @@ void chain_stream_kernel(ChainArgs a_by_value)
         for (uint32_t w = 1; w < W; ++w) {
             // the codes of worker w are in `cur`; fetch worker w+1's, or the first worker's of the next tile
             if (w + 1u < W) {
-                stream_fetch<WR>(a->w[w + 1u].codes, start, lane, nxt, limit_for(tile, limitr));
+                stream_fetch<WR, ROWS>(a->w[w + 1u].codes, start, lane, nxt, limit_for(tile, limitr));
             } else {
                 const uint32_t nt = tile + stride < tiles_all ? tile + stride : tile;
-                ChainCodes tmp;
-                stream_fetch<W0>(a->w[0].codes, (uint64_t)nt * kChainTile, lane, tmp, limit_for(nt, limit0));
+                ChainCodes<ROWS> tmp;
+                stream_fetch<W0, ROWS>(a->w[0].codes, (uint64_t)nt * TILE, lane, tmp, limit_for(nt, limit0));
                 nxt = tmp;
             }
-            if (PIPED) {
+            if constexpr (PIPED) {
                 const bool last = w + 1u == W;
                 const uint32_t wn = last ? 0u : w + 1u;
                 const uint32_t here = block_low(a->w[w].index0, start, lane);
@@ -893,7 +881,7 @@ void chain_stream_kernel(ChainArgs a_by_value)
                                                     from_lane(invs_here, w), S, fl);
             } else {
                 const DitherStream ds = {a->w[w].ds.key0, a->w[w].ds.key1, a->w[w].ds.step, a->w[w].ds.worker};
-                stream_fold<RMODE, WR, false>(ds, (a->w[w].index0 + start) >> 3, (float)a->w[w].q_min,
+                stream_fold<RMODE, WR, false, ROWS>(ds, (a->w[w].index0 + start) >> 3, (float)a->w[w].q_min,
                                               a->w[w].side_scale, cur, from_lane(steps_here, w),
                                               from_lane(invs_here, w), lane, S);
             }
@@ -901,7 +889,7 @@ void chain_stream_kernel(ChainArgs a_by_value)
         }
         float* out = out_base + start;
 #pragma unroll
-        for (int r = 0; r < kChainRows; ++r) {
+        for (int r = 0; r < ROWS; ++r) {
             const uint32_t o = (uint32_t)(r * kWave + lane) * kLaneElems;
             if (apply_scale) {       // wave-uniform
 #pragma unroll
@@ -919,7 +907,7 @@ void chain_stream_kernel(ChainArgs a_by_value)
             wave_lds_sync();
             if (TAIL && tile == tiles) {       // the ragged tile: only the elements that exist
 #pragma unroll
-                for (int j = 0; j < (int)(kChainTile / (kWave * 4)); ++j) {
+                for (int j = 0; j < (int)(TILE / (kWave * 4)); ++j) {
                     const uint32_t e = (uint32_t)(j * (kWave * 4) + lane * 4);
                     const float4 x = *(const float4*)(out_stage + e);
                     if (e + 4u <= tail_len) {
@@ -932,7 +920,7 @@ void chain_stream_kernel(ChainArgs a_by_value)
                 }
             } else {
 #pragma unroll
-                for (int j = 0; j < (int)(kChainTile / (kWave * 4)); ++j) {
+                for (int j = 0; j < (int)(TILE / (kWave * 4)); ++j) {
                     const float4 x = *(const float4*)(out_stage + j * (kWave * 4) + lane * 4);
                     store_streaming(out + j * (kWave * 4) + lane * 4, x.x, x.y, x.z, x.w);
                 }
@@ -1189,29 +1177,45 @@ static int decode_common(const void* codes, size_t n, uint32_t levels, uint32_t 
 }
 
 template <int RMODE, int W0, int WR>
-static int launch_chain_stream(const ChainArgs& a, hipStream_t s)
+static int launch_chain_stream(ChainArgs& a, hipStream_t s)
 {
     // Long vectors: persistent waves, kChainStreamWaves on every SIMD, every wave with the same
     // number of tiles (give or take one).  Otherwise one tile per wave: with only a few tiles
     // per wave a fixed share would leave SIMDs idle at the end.
-    const uint32_t tiles = a.tile_begin, slots = 1024u * kChainStreamWaves;
-    const bool ragged = (uint64_t)tiles * kChainTile < a.tl.n;     // one more wave takes the ragged last tile
-    // (the more workers a tile folds in, the earlier a persistent wave pays: W = 16 gains 3-4 % at
-    // one and a half tiles per wave slot, where W = 4 still loses 4 %)
+    // Persistent waves, kChainStreamWaves on every SIMD, from one tile per wave slot on (6.3 M elements;
+    // measured there to 12 M, against one tile per wave: 1 worker 7.0-10.4 against 8.9-15.5 us,
+    // 4 nested 15-21 against 15-23, 16 nested 45-73 against 50-82; 4 and 8 DQSG between 6 % slower
+    // and 9 % faster).  From 2,048 tiles on for one worker, which is bound by its stores (4 M: 6.0
+    // against 6.7 us), and for eight or more nested ones (16: 29.8 against 31.8); the others are 0-11 %
+    // faster with one tile per wave there.
+    const uint32_t slots = 1024u * kChainStreamWaves;
+    const uint32_t full = (uint32_t)(a.tl.n / kChainTile);
     const StreamTuning& tuning = stream_tuning();
-    const bool persistent = tiles >= tuning.chain_min_tiles_per_wave * slots ||
-                            (!tuning.threshold_from_env && a.W >= 8u && 2u * (uint64_t)tiles >= 3u * (uint64_t)slots);
-    const uint32_t blocks = persistent ? persistent_blocks(tiles + (ragged ? 1u : 0u), 1024u * NDQ_CHAIN_PIPED_WAVES)
-                                       : blocks_for(tiles + (ragged ? 1u : 0u));
-    if (persistent && ragged)
-        return launch((chain_stream_kernel<RMODE, W0, WR, true, true>), dim3(blocks), dim3(kBlock), s, a);
-    if (ragged) return launch((chain_stream_kernel<RMODE, W0, WR, true, false>), dim3(blocks), dim3(kBlock), s, a);
-    if (persistent) return launch((chain_stream_kernel<RMODE, W0, WR, false, true>), dim3(blocks), dim3(kBlock), s, a);
-    return launch((chain_stream_kernel<RMODE, W0, WR, false, false>), dim3(blocks), dim3(kBlock), s, a);
+    const bool persistent =
+        full != 0u && (full >= tuning.chain_min_tiles_per_wave * slots ||
+                       (!tuning.threshold_from_env && full >= kShortTiles &&
+                        (a.W == 1u || (a.W >= 8u && RMODE != kDq))));
+    const bool short_vector = !persistent && full < kShortTiles;
+    const uint32_t tile = short_vector ? ChainStreamTile<kOneRow>::N : kChainTile;
+    const uint32_t tiles = (uint32_t)(a.tl.n / tile);
+    if (tiles == 0u) return 1;
+    a.tile_begin = tiles;
+    if (a.tl.bucket_len != a.tl.n) a.tl.tiles_per_bucket = (uint32_t)(a.tl.bucket_len / tile);
+    const bool ragged = (uint64_t)tiles * tile < a.tl.n;     // one more wave takes the ragged last tile
+    const uint32_t all = tiles + (ragged ? 1u : 0u);
+    const dim3 grid(persistent ? persistent_blocks(all, 1024u * NDQ_CHAIN_PIPED_WAVES) : blocks_for(all)), block(kBlock);
+    if (persistent)
+        return ragged ? launch((chain_stream_kernel<RMODE, W0, WR, true, kPiped>), grid, block, s, a)
+                      : launch((chain_stream_kernel<RMODE, W0, WR, false, kPiped>), grid, block, s, a);
+    if (short_vector)
+        return ragged ? launch((chain_stream_kernel<RMODE, W0, WR, true, kOneRow>), grid, block, s, a)
+                      : launch((chain_stream_kernel<RMODE, W0, WR, false, kOneRow>), grid, block, s, a);
+    return ragged ? launch((chain_stream_kernel<RMODE, W0, WR, true, kOneTile>), grid, block, s, a)
+                  : launch((chain_stream_kernel<RMODE, W0, WR, false, kOneTile>), grid, block, s, a);
 }
 
 template <int RMODE, int W0>
-static int launch_chain_stream_w(const ChainArgs& a, uint32_t wr, hipStream_t s)
+static int launch_chain_stream_w(ChainArgs& a, uint32_t wr, hipStream_t s)
 {
     if (wr == 1u) return launch_chain_stream<RMODE, W0, 1>(a, s);
     if (wr == 2u) return launch_chain_stream<RMODE, W0, 2>(a, s);
@@ -1238,10 +1242,7 @@ static int try_chain_stream(ChainArgs a, uint32_t bucket, hipStream_t s)
     // the high word of the dither's block number is the same for the whole call (it changes every 2^35 elements)
     for (uint32_t j = 0; j < a.W; ++j)
         if ((a.w[j].index0 >> 35) != ((a.w[j].index0 + a.tl.n - 1u) >> 35)) return 1;
-    const uint32_t full = (uint32_t)(a.tl.n / kChainTile);
-    if (full == 0u) return 1;
     ChainArgs b = a;
-    b.tile_begin = full;
     int rc;
     if (rmode == kDq) {
         rc = w0 == 1u ? launch_chain_stream_w<kDq, 1>(b, wr, s) : w0 == 2u ? launch_chain_stream_w<kDq, 2>(b, wr, s)
@@ -1381,6 +1382,9 @@ int ndq_decode_chain(const ndq_worker* workers, uint32_t W, size_t n, uint32_t b
     a.num_buckets = a.row_buckets ? (uint32_t)ndq_num_buckets(n, bucket) : 0u;   // n < 2^40: fits
     int rc = make_tiling(n, a.row_buckets ? kChainTile : bucket, kChainTile, &a.tl);
     if (rc != NDQ_OK) return rc;
+    const bool short_vector = a.tl.total_tiles < kShortGeneralTiles;
+    Tiling short_tl = a.tl;
+    if (short_vector && (rc = make_tiling(n, bucket, kWave * kLaneElems, &short_tl)) != NDQ_OK) return rc;
     a.out = out;
     a.scale = scale;
     for (uint32_t p0 = 0; p0 < W; p0 += kChainMax) {
@@ -1421,12 +1425,18 @@ int ndq_decode_chain(const ndq_worker* workers, uint32_t W, size_t n, uint32_t b
             if (rc_stream != 1) return rc_stream;
         }
 #endif
+        if (short_vector) {
+            a.tl = short_tl;
+            a.row_buckets = 0u;
+        }
         const dim3 grid(blocks_for(a.tl.total_tiles)), block(kBlock);
         int rc_launch;
-        if (a.row_buckets && any_m) rc_launch = launch((chain_kernel<true, true>), grid, block, hs, a);
-        else if (a.row_buckets) rc_launch = launch((chain_kernel<true, false>), grid, block, hs, a);
-        else if (any_m) rc_launch = launch((chain_kernel<false, true>), grid, block, hs, a);
-        else rc_launch = launch((chain_kernel<false, false>), grid, block, hs, a);
+        if (short_vector && any_m) rc_launch = launch((chain_kernel<false, true, 1>), grid, block, hs, a);
+        else if (short_vector) rc_launch = launch((chain_kernel<false, false, 1>), grid, block, hs, a);
+        else if (a.row_buckets && any_m) rc_launch = launch((chain_kernel<true, true, kChainRows>), grid, block, hs, a);
+        else if (a.row_buckets) rc_launch = launch((chain_kernel<true, false, kChainRows>), grid, block, hs, a);
+        else if (any_m) rc_launch = launch((chain_kernel<false, true, kChainRows>), grid, block, hs, a);
+        else rc_launch = launch((chain_kernel<false, false, kChainRows>), grid, block, hs, a);
         if (rc_launch != NDQ_OK) return NDQ_ELAUNCH;
     }
     return NDQ_OK;

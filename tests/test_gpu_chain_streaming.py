@@ -58,3 +58,16 @@ def test_steps_of_any_magnitude(M, tail):
     (5000, (1 << 35) - 2048), (4096, (1 << 35) - 4096), (1024, (3 << 35) - 1032)])
 def test_dither_indices_beyond_32_bits(n, offset):
     _check((("dq", 4), ("nested", 2), ("nested", 2)), 4, 0, _gradients(3, n, 8), offset, 0.5)
+
+
+@pytest.mark.parametrize("plan,fine,bucket", [
+    ((("dq", 8), ("nested", 4), ("nested", 3), ("dq", 256), ("nested", 100)), 8, 0),    # every fetch width of the general kernel
+    ((("dq", 4), ("nested", 2), ("nested", 2)), 4, 0),
+    ((("dq", 16),) * 3, 16, 1024),
+    ((("dq", 3),), 3, 512)])
+def test_short_vectors_take_one_row_per_wave(plan, fine, bucket):
+    # edges of a row (512 elements) and of the 64-bit code loads at the stream's end, and the
+    # lengths at which the tile grows from one row to two (2,048 and 4,096 tiles of 1,024)
+    for n in (1, 7, 8, 63, 511, 512, 513, 520, 575, 1024 + 65, 2047 * 1024 + 1023, 2048 * 1024, 4096 * 1024 - 8,
+              4096 * 1024 + 1):
+        _check(plan, fine, bucket, _gradients(len(plan), n, n), 8 * (n % 513), 0.25)
