@@ -1333,6 +1333,8 @@ int ndq_decode_mean(const ndq_worker* workers, float* const* decoded, uint32_t W
         if (!wk.codes || !wk.steps || !decoded[p]) return NDQ_EINVAL;
         if (!aligned16(wk.codes) || !aligned16(decoded[p]) || !aligned4(wk.steps) || (wk.dither.offset & 7u) != 0u)
             return NDQ_EALIGN;
+        // a partial sum waits in `out` between launches (one launch: a lane writes `out` last)
+        if (W > kMeanMax && decoded[p] == out) return NDQ_EINVAL;
     }
     MeanArgs a;
     const int rc = make_tiling(n, bucket, kMeanTile, &a.tl);

@@ -306,7 +306,10 @@ NDQ_METHOD(nested_encode_with_step, 7)
     });
 }
 
-// jobs of (g, kind, levels, M, alpha, d, codes_out, steps_out, step_in or None), delta, bucket
+// jobs of (g, kind, levels, M, alpha, d, codes_out, steps_out, step_in or None), delta, bucket.
+// A library call takes vectors of one length and type, and a handed-over step belongs to the
+// whole vector whatever the bucket: consecutive jobs that agree in these share a call.
+struct EncodeCall { size_t first, jobs, n; int dt; uint32_t bucket; };
 NDQ_METHOD(encode_workers, 3)
 {
     Sequence jobs(v[0]);
@@ -315,29 +318,40 @@ NDQ_METHOD(encode_workers, 3)
     const float delta = real(v[1]);
     const uint32_t bucket = (uint32_t)integer(v[2]);
     Few<ndq_encode_job, 32> list(W);
-    size_t n = 0;
-    int dt = 0;
+    Few<EncodeCall, 4> calls(W);
+    size_t num_calls = 0;
+    constexpr size_t kMaxJobs = 1024;      // of the library call
     for (size_t w = 0; w < W; ++w) {
         Sequence f(jobs[w]);
         if (f.size() != 9u) fail(PyExc_ValueError, "a job has nine entries");
         const at::Tensor &g = tensor(f[0], "g"), &codes = tensor(f[6], "codes_out"), &steps = tensor(f[7], "steps_out");
-        if (w == 0) { n = count(g); dt = gradient_type(g); }
-        else if (count(g) != n || gradient_type(g) != dt)
-            fail(PyExc_ValueError, "all gradients must have one length and type");
         ndq_encode_job& job = list[w];
         job.kind = (uint32_t)integer(f[1]);
         job.levels = (uint32_t)integer(f[2]);
         job.M = (uint32_t)integer(f[3]);
         job.alpha = real(f[4]);
         job.dither = dither(f[5]);
-        check_outputs(n, code_bits(job.kind == NDQ_WORKER_NESTED ? job.M : job.levels), bucket, codes, steps);
         job.g = address(g);
         job.codes_out = address(codes);
         job.steps_out = (float*)address(steps);
         job.step_in = f[8] == Py_None ? nullptr : one_step(f[8]);
+        const size_t n = count(g);
+        const int dt = gradient_type(g);
+        const uint32_t job_bucket = job.step_in ? 0u : bucket;
+        check_outputs(n, code_bits(job.kind == NDQ_WORKER_NESTED ? job.M : job.levels), job_bucket, codes, steps);
+        const EncodeCall* last = num_calls ? &calls[num_calls - 1u] : nullptr;
+        if (!last || last->n != n || last->dt != dt || last->bucket != job_bucket || last->jobs == kMaxJobs)
+            calls[num_calls++] = {w, 0u, n, dt, job_bucket};
+        ++calls[num_calls - 1u].jobs;
     }
     void* s = current_stream();
-    return status([&] { return lib.encode_workers(list.data(), (uint32_t)W, dt, n, delta, bucket, s); });
+    return status([&] {
+        int rc = NDQ_OK;
+        for (size_t c = 0; c < num_calls && rc == NDQ_OK; ++c)
+            rc = lib.encode_workers(&list[calls[c].first], (uint32_t)calls[c].jobs, calls[c].dt, calls[c].n, delta,
+                                    calls[c].bucket, s);
+        return rc;
+    });
 }
 
 // codes, n, levels, bucket, steps, d, out, accumulate

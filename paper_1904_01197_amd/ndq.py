@@ -199,9 +199,10 @@ def ndq_nested_encode_with_step(g, step_in, M, alpha, d, codes_out=None, steps_o
 
 
 def ndq_encode_workers(jobs, delta, bucket):
-    """jobs: sequence of (g, kind, levels, M, alpha, ndq_dither, codes_out, steps_out, step_in) with
-    vectors of one length and type; M and alpha count for nested workers, step_in is None or a
-    device tensor holding one float32 step (bucket 0)."""
+    """jobs: sequence of (g, kind, levels, M, alpha, ndq_dither, codes_out, steps_out, step_in);
+    M and alpha count for nested workers, step_in is None or a device tensor holding one
+    float32 step for the whole vector (`bucket` is then not used).  Neighbours of one length and
+    type share a library call."""
     _check(_ready().encode_workers(jobs, delta, bucket), "ndq_encode_workers")
 
 

@@ -159,3 +159,15 @@ def test_header_is_plain_c99(tmp_path):
     subprocess.check_call(["gcc", "-std=c99", "-I", os.path.join(ROOT, "include"), str(src), "-o", str(exe),
                            "-L", libdir, "-l:libndq.so", "-Wl,-rpath," + libdir])
     assert subprocess.call([str(exe)]) == 0
+
+
+def test_decode_mean_of_several_launches_refuses_a_sum_that_is_also_a_reconstruction():
+    lib = ndq.lib()
+    W = 33
+    workers = (ndq.ndq_worker * W)()
+    for wk in workers:
+        wk.codes, wk.steps, wk.kind, wk.levels_or_M = 0x1000, 0x2000, ndq.NDQ_WORKER_DQ, 4
+    decoded = (C.c_void_p * W)(*[0x10000 + 0x1000 * w for w in range(W)])
+    out = C.c_void_p(0x10000 + 0x1000 * 7)
+    # aligned, never dereferenced: the call fails first
+    assert lib.ndq_decode_mean(workers, C.cast(decoded, C.c_void_p), W, 64, 0, 1.0, out, None) == ndq.NDQ_EINVAL

@@ -105,10 +105,9 @@ def test_bad_workers_are_reported_and_nothing_is_launched():
     d = ndq.ndq_dither(1, 1, 1, 0)
     good = (g, ndq.NDQ_WORKER_DQ, 4, 0, 1.0, d, codes, steps, None)
     bad_M = (g, ndq.NDQ_WORKER_NESTED, 4, 1, 1.0, d, codes, steps, None)
-    for jobs, bucket in (([good, bad_M], 0), ([good, good[:8] + (steps,)], 4096)):
-        with pytest.raises(ndq.NdqError) as e:
-            ndq.ndq_encode_workers(jobs, 0.0, bucket)
-        assert e.value.rc == ndq.NDQ_EINVAL
+    with pytest.raises(ndq.NdqError) as e:
+        ndq.ndq_encode_workers([good, bad_M], 0.0, 0)
+    assert e.value.rc == ndq.NDQ_EINVAL
     torch.cuda.synchronize()
     assert steps.item() == -1.0 and (codes == 7).all()
 
@@ -137,3 +136,25 @@ def test_decode_mean_keeps_every_reconstruction_and_their_sum(W):
     bad[2] = ndq.NDQ_WORKER_NESTED
     with pytest.raises(ndq.NdqError):
         ndq.ndq_decode_mean([tuple(bad)], decoded[:1], n, bucket)
+
+
+def test_workers_of_different_length_type_and_bucket():
+    # neighbours that do not agree are encoded by calls of their own: mixed types and lengths, and
+    # handed-over steps (one for the whole vector) among bucketed vectors
+    bucket = 2048
+    host = [_host(1, n, dtype, n)[0] for n, dtype in ((9001, "f32"), (9001, "f32"), (9001, "bf16"), (70, "bf16"),
+                                                      (70, "f32"))]
+    outs, jobs, refs = [], [], []
+    for w, g in enumerate(host):
+        handed = w in (1, 4)
+        codes = torch.full((ndq.ndq_packed_bytes(g.size, 4),), 0xA5, dtype=torch.uint8, device="cuda")
+        steps = torch.full((1 if handed else ndq.ndq_num_buckets(g.size, bucket),), -1.0, device="cuda")
+        outs.append((codes, steps))
+        jobs.append((_dev(g), ndq.NDQ_WORKER_DQ, 16, 0, 1.0, ndq.ndq_dither(w, 3, w, 0), codes, steps,
+                     outs[0][1][:1] if handed else None))
+        d = oracle.dither(w, 3, w)
+        refs.append(oracle.dq_encode(g, float(refs[0][1][0]) if handed else 0.0, 16, 0 if handed else bucket, d))
+    ndq.ndq_encode_workers(jobs, 0.0, bucket)
+    for w, (codes, steps) in enumerate(outs):
+        assert np.array_equal(steps.cpu().numpy(), refs[w][1]), w
+        assert codes.cpu().numpy().tobytes() == refs[w][0].tobytes(), w
