@@ -809,6 +809,21 @@ def test_code_histogram_ignores_what_lies_in_the_padding(bits):
         assert np.array_equal(hist.cpu().numpy().astype(np.uint64), ref_h), (bits, n)
 
 
+@pytest.mark.parametrize("bits", [3, 4])
+@pytest.mark.parametrize("n", [1, 2, 31, 33, 32 * 1024 + 1, 32 * 1024 * 256 + 63])
+def test_histogram_of_paired_codes_tells_low_from_high(bits, n):
+    """Codes that alternate, so that every pair has different halves: a lone last code, one
+    workgroup and a little, and every workgroup with a second round for some."""
+    dev = _gpu()
+    codes = ((np.arange(n) % 2) * ((1 << bits) - 2) + 1).astype(np.uint32)
+    codes[n // 2] = 0
+    packed = oracle.pack(codes, bits)
+    hist, ent = ndq.ndq_code_entropy(torch.from_numpy(packed).to(dev), n, bits)
+    ref = oracle.code_histogram(packed, n, bits)
+    assert np.array_equal(hist.cpu().numpy().astype(np.uint64), ref)
+    assert abs(float(ent.item()) - oracle.entropy_bits(ref)) <= 1e-9
+
+
 def test_entropy_of_the_benchmark_code_streams():
     """Entropy of the actual DQSG / nested index streams of config 5 (reduced size):
     GPU histogram against the oracle's, bit-exact."""
