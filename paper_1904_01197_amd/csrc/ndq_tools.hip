@@ -106,7 +106,7 @@ __device__ __forceinline__ void load_unit(const uint32_t* __restrict__ words, ui
 
 // Codes of 3 and 4 bits are counted two at a time, by the value of the pair: half the LDS
 // additions, which bound long streams (call of 134 M codes 29.4 -> 22.4 us, of 25.6 M 14.9 -> 14.2
-// us at 4 bits, 29.5 -> 21.6 and 14.7 -> 13.6 at 3).  Pairs of wider codes would need 128 KB of
+// us at 4 bits, 29.5 -> 21.6 and 14.7 -> 13.6 at 3, on the full grid).  Pairs of wider codes would need 128 KB of
 // LDS or more.
 template <int BITS>
 __global__ __launch_bounds__(kHistThreads) void histogram_kernel(const uint32_t* __restrict__ words, uint64_t n,
@@ -706,6 +706,13 @@ int ndq_code_entropy(const void* codes, size_t n, uint32_t bits, uint64_t* hist_
     }
     const uint64_t units = (uint64_t)n >> 5;
     uint64_t blocks = (units + kHistThreads - 1) / kHistThreads;
+    if (bits <= 4u && blocks < (uint64_t)kHistBlocks * kHistBlocks) {
+        // Paired codes: a workgroup's closing atomics cost the call 25 ns, a round of units about
+        // 0.6 us, so 0.025 B + 0.6 blocks / B is smallest at B = sqrt(24 blocks).  4-bit calls
+        // against the full grid: 4 M codes 9.3 -> 8.2 us, 25.6 M 14.2 -> 12.1, 134 M 22.4 both.
+        uint64_t fewer = (uint64_t)sqrt(24.0 * (double)blocks);
+        if (fewer < blocks) blocks = fewer;
+    }
     if (blocks > kHistBlocks) blocks = kHistBlocks;
     if (blocks == 0u) blocks = 1u;
     const dim3 grid((uint32_t)blocks), block(kHistThreads);
