@@ -115,7 +115,8 @@ int ndq_absmax(const void* g, int dt, size_t n, uint32_t bucket, float* kappa_ou
  *   bucket == 0, delta > 0 : one preset step delta (Algorithm 1 initialisation)
  *   bucket == 0, delta <= 0: one step 2 max|g| / (levels-1) for the whole vector
  *   bucket  > 0            : one step per bucket from the bucket's own max-norm
- * codes_out: ndq_packed_bytes(n, ndq_code_bits(levels)) bytes, fully written.
+ * codes_out: ndq_packed_bytes(n, ndq_code_bits(levels)) bytes, fully written (a call
+ * that reads g twice first keeps intermediate maxima there).
  * (Every bucket size gives the same bytes; speed differs.  One pass over g:
  * buckets of 512, 1024, 2048, 4096 or 8192 elements (bfloat16: also 16384), and
  * a preset step.  Other sizes, and bucket == 0 without a preset step, read g

@@ -495,6 +495,7 @@ struct AbsmaxBatch {
     float* parts[kEncJobs];         // absmax_span_kernel: K * blocks_per_bucket floats each; null: atomics
     Tiling tl;
     uint64_t K;                     // buckets per vector
+    uint64_t parts_bytes;           // memory behind each of `parts`
     uint32_t blocks_per_bucket;     // absmax_span_kernel
 };
 typedef const __attribute__((address_space(4))) AbsmaxBatch* AbsmaxBatchPtr;
@@ -607,19 +608,23 @@ __global__ __launch_bounds__(kBlock) void absmax_finish_kernel(AbsmaxBatch by_va
 template <int DT>
 static int run_absmax(AbsmaxBatch& b, uint32_t jobs, hipStream_t s)
 {
-    // many tiles per bucket: workgroups that stride over one.  With memory for the parts (4 bytes
-    // per workgroup, and a workgroup has at least one tile: 256 bytes of 1-bit codes) a full chip
-    // of waves; with atomics one workgroup per compute unit.
+    // many tiles per bucket: workgroups that stride over one.  With memory for the parts a full chip
+    // of waves; with atomics one workgroup per compute unit.  What counts are the tiles that hold
+    // elements: a bucket may be longer than the whole vector.
     constexpr uint32_t kSpanMinTiles = 16, kSpanMaxBuckets = 2048;
     const uint32_t target = b.parts[0] ? 2048u : 256u;
-    const bool span = b.tl.tiles_per_bucket >= kSpanMinTiles && b.K * jobs <= kSpanMaxBuckets;
+    const uint64_t tiles = b.K == 1u ? (b.tl.n + EncTile<DT>::N - 1u) / EncTile<DT>::N : b.tl.tiles_per_bucket;
+    const bool span = tiles >= kSpanMinTiles && b.K * jobs <= kSpanMaxBuckets;
     const bool fill = !(span && b.parts[0]);
     if (fill && launch(fill_zero_kernel, dim3((uint32_t)((b.K + 255) / 256), jobs), dim3(256), s, b) != NDQ_OK)
         return NDQ_ELAUNCH;
     if (span) {
         uint32_t per_bucket = target / (uint32_t)(b.K * jobs);
-        const uint32_t most = blocks_for(b.tl.tiles_per_bucket);
+        const uint32_t most = blocks_for((uint32_t)tiles);
         if (per_bucket > most) per_bucket = most;
+        // a part is 4 bytes.  A workgroup has a tile, 256 bytes of 1-bit codes, so the parts always fit
+        // (K >= 2: only the last bucket is short, and the others have 16 tiles); no plan may write past them
+        if (b.parts[0] && per_bucket > b.parts_bytes / (4u * b.K)) per_bucket = (uint32_t)(b.parts_bytes / (4u * b.K));
         if (per_bucket < 1u) per_bucket = 1u;
         b.blocks_per_bucket = per_bucket;
         if (launch(absmax_span_kernel<DT>, dim3((uint32_t)b.K * per_bucket, jobs), dim3(kBlock), s, b) != NDQ_OK)
@@ -627,7 +632,7 @@ static int run_absmax(AbsmaxBatch& b, uint32_t jobs, hipStream_t s)
         if (!b.parts[0]) return NDQ_OK;
         return launch(absmax_finish_kernel, dim3((uint32_t)b.K, jobs), dim3(kBlock), s, b);
     }
-    return launch(absmax_kernel<DT>, dim3(blocks_for(b.tl.total_tiles), jobs), dim3(kBlock), s, b);
+    return launch(absmax_kernel<DT>, dim3(blocks_for((uint32_t)(tiles * b.K)), jobs), dim3(kBlock), s, b);
 }
 
 // Waves of the streaming kernel: kStreamWaves on each of the 1,024 SIMDs.
@@ -803,6 +808,7 @@ static int run_plans(const EncodePlan* plans, uint32_t jobs, int dt, uint32_t bu
         m.kappa_bits[need] = (uint32_t*)plans[j].a.steps;
         m.levels[need] = plans[j].a.qp.levels;
         m.parts[need] = (float*)plans[j].a.codes;
+        m.parts_bytes = need == 0u || plans[j].a.total_bytes < m.parts_bytes ? plans[j].a.total_bytes : m.parts_bytes;
         ++need;
     }
     if (need != 0u) {
@@ -872,6 +878,7 @@ int ndq_absmax(const void* g, int dt, size_t n, uint32_t bucket, float* kappa_ou
     b.kappa_bits[0] = (uint32_t*)kappa_out;
     b.levels[0] = 0u;
     b.parts[0] = nullptr;
+    b.parts_bytes = 0;
     b.K = bucket ? (n + bucket - 1) / bucket : 1;
     if (n == 0) {   // one (empty) bucket: its max-norm is 0
         if (bucket != 0u) return NDQ_OK;

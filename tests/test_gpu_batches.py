@@ -67,6 +67,31 @@ def test_several_workers_in_one_call_match_oracle(dtype, bucket, shared):
         _compare(plan, 7, bucket, shared, _host(len(plan), n, dtype, n))
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_vectors_much_shorter_than_their_bucket_stay_inside_their_streams(dtype):
+    # the max-norm pass keeps its parts in the code stream: 1-bit codes are the least memory there is
+    guard = 1 << 14
+    for n, bucket in ((64, 65536), (1000, 1 << 20), (5000, 1 << 24), (16 * 4096 + 5, 1 << 17), (65600, 1 << 20)):
+        host = _host(3, n, dtype, n)
+        size = ndq.ndq_packed_bytes(n, 1)
+        for together in (False, True):
+            codes = [torch.full((size + guard,), 0xA5, dtype=torch.uint8, device="cuda") for _ in host]
+            steps = [torch.full((1,), -1.0, device="cuda") for _ in host]
+            ds = [ndq.ndq_dither(7 + w, 3, w, 0) for w in range(3)]
+            if together:
+                ndq.ndq_encode_workers([(_dev(host[w]), ndq.NDQ_WORKER_DQ, 2, 0, 1.0, ds[w], codes[w], steps[w], None)
+                                        for w in range(3)], 0.0, bucket)
+            else:
+                for w in range(3):
+                    ndq.ndq_dq_encode(_dev(host[w]), 0.0, 2, bucket, ds[w], codes[w], steps[w])
+            for w in range(3):
+                ref, s_ref = oracle.dq_encode(host[w], 0.0, 2, bucket, oracle.dither(7 + w, 3, w))
+                got = codes[w].cpu().numpy()
+                assert steps[w].item() == s_ref[0], (n, bucket, w)
+                assert got[:size].tobytes() == ref.tobytes(), (n, bucket, w)
+                assert (got[size:] == 0xA5).all(), "written past the stream"
+
+
 @pytest.mark.parametrize("preset", [0.0, 0.004])
 def test_more_workers_than_one_launch_holds_and_a_step_from_an_earlier_worker(preset):
     # preset: the shared step exists only after the first worker's encoder, not after a max-norm pass
