@@ -8,6 +8,7 @@
 // into an exception.  The library's entry points arrive as addresses (bind()), so that
 // whatever build ndq.py has loaded is the one that is called.  Nothing is kept between calls.
 #define PY_SSIZE_T_CLEAN
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <cstdint>
@@ -190,13 +191,25 @@ void check_values(const at::Tensor& out, size_t n, const char* text)
     if (!is_f32(out) || count(out) < n) fail(PyExc_ValueError, text);
 }
 
-// The GIL is released while the library enqueues, as ctypes does.
-template <class F> PyObject* status(F call)
+// The GIL is released while the library enqueues, as ctypes does.  Only the library's C function
+// may run here: whatever can throw (reading a tensor's address does, for a tensor without
+// storage) belongs before it, and is done while the GIL is held.
+class WithoutGil {
+public:
+    WithoutGil() : state_(PyEval_SaveThread()) {}
+    ~WithoutGil() { PyEval_RestoreThread(state_); }
+    WithoutGil(const WithoutGil&) = delete;
+    WithoutGil& operator=(const WithoutGil&) = delete;
+private:
+    PyThreadState* state_;
+};
+template <class R, class... P, class... A> PyObject* status(R (*function)(P...), A... arguments)
 {
-    int rc;
-    Py_BEGIN_ALLOW_THREADS
-    rc = call();
-    Py_END_ALLOW_THREADS
+    R rc;
+    {
+        WithoutGil released;
+        rc = function(arguments...);
+    }
     return PyLong_FromLong(rc);
 }
 
@@ -210,8 +223,8 @@ template <class F> PyObject* guarded(F body)
         return body();
     } catch (const Failed&) {
         return nullptr;
-    } catch (const std::exception& e) {
-        PyErr_SetString(PyExc_RuntimeError, e.what());
+    } catch (...) {
+        torch::translate_exception_to_python(std::current_exception());    // as torch's own functions do
         return nullptr;
     }
 }
@@ -236,7 +249,7 @@ NDQ_METHOD(absmax, 3)
     const size_t n = count(g);
     const uint32_t bucket = (uint32_t)integer(v[1]);
     void* s = current_stream();
-    return status([&] { return lib.absmax(address(g), dt, n, bucket, (float*)address(out), s); });
+    return status(lib.absmax, address(g), dt, n, bucket, (float*)address(out), s);
 }
 
 // g, delta, levels, bucket, d, codes_out, steps_out
@@ -250,9 +263,8 @@ NDQ_METHOD(dq_encode, 7)
     const ndq_dither d = dither(v[4]);
     check_outputs(n, code_bits(levels), bucket, codes, steps);
     void* s = current_stream();
-    return status([&] {
-        return lib.dq_encode(address(g), dt, n, delta, levels, bucket, &d, address(codes), (float*)address(steps), s);
-    });
+    return status(lib.dq_encode, address(g), dt, n, delta, levels, bucket, &d, address(codes),
+                  (float*)address(steps), s);
 }
 
 // g, step_in, levels, d, codes_out, steps_out
@@ -266,9 +278,8 @@ NDQ_METHOD(dq_encode_with_step, 6)
     const ndq_dither d = dither(v[3]);
     check_outputs(n, code_bits(levels), 0u, codes, steps);
     void* s = current_stream();
-    return status([&] {
-        return lib.dq_encode_with_step(address(g), dt, n, step_in, levels, &d, address(codes), (float*)address(steps), s);
-    });
+    return status(lib.dq_encode_with_step, address(g), dt, n, step_in, levels, &d, address(codes),
+                  (float*)address(steps), s);
 }
 
 // g, delta, levels, M, alpha, bucket, d, codes_out, steps_out
@@ -282,10 +293,8 @@ NDQ_METHOD(nested_encode, 9)
     const ndq_dither d = dither(v[6]);
     check_outputs(n, code_bits(M), bucket, codes, steps);
     void* s = current_stream();
-    return status([&] {
-        return lib.nested_encode(address(g), dt, n, delta, levels, M, alpha, bucket, &d, address(codes),
-                                 (float*)address(steps), s);
-    });
+    return status(lib.nested_encode, address(g), dt, n, delta, levels, M, alpha, bucket, &d, address(codes),
+                  (float*)address(steps), s);
 }
 
 // g, step_in, M, alpha, d, codes_out, steps_out
@@ -300,16 +309,22 @@ NDQ_METHOD(nested_encode_with_step, 7)
     const ndq_dither d = dither(v[4]);
     check_outputs(n, code_bits(M), 0u, codes, steps);
     void* s = current_stream();
-    return status([&] {
-        return lib.nested_encode_with_step(address(g), dt, n, step_in, M, alpha, &d, address(codes),
-                                           (float*)address(steps), s);
-    });
+    return status(lib.nested_encode_with_step, address(g), dt, n, step_in, M, alpha, &d, address(codes),
+                  (float*)address(steps), s);
 }
 
 // jobs of (g, kind, levels, M, alpha, d, codes_out, steps_out, step_in or None), delta, bucket.
 // A library call takes vectors of one length and type, and a handed-over step belongs to the
 // whole vector whatever the bucket: consecutive jobs that agree in these share a call.
 struct EncodeCall { size_t first, jobs, n; int dt; uint32_t bucket; };
+int encode_calls(const ndq_encode_job* jobs, const EncodeCall* calls, size_t num_calls, float delta, void* s)
+{
+    int rc = NDQ_OK;
+    for (size_t c = 0; c < num_calls && rc == NDQ_OK; ++c)
+        rc = lib.encode_workers(jobs + calls[c].first, (uint32_t)calls[c].jobs, calls[c].dt, calls[c].n, delta,
+                                calls[c].bucket, s);
+    return rc;
+}
 NDQ_METHOD(encode_workers, 3)
 {
     Sequence jobs(v[0]);
@@ -345,13 +360,7 @@ NDQ_METHOD(encode_workers, 3)
         ++calls[num_calls - 1u].jobs;
     }
     void* s = current_stream();
-    return status([&] {
-        int rc = NDQ_OK;
-        for (size_t c = 0; c < num_calls && rc == NDQ_OK; ++c)
-            rc = lib.encode_workers(&list[calls[c].first], (uint32_t)calls[c].jobs, calls[c].dt, calls[c].n, delta,
-                                    calls[c].bucket, s);
-        return rc;
-    });
+    return status(encode_calls, list.data(), calls.data(), num_calls, delta, s);
 }
 
 // codes, n, levels, bucket, steps, d, out, accumulate
@@ -365,10 +374,8 @@ NDQ_METHOD(dq_decode, 8)
     check_values(out, n, "out must hold n float32");
     const int add = truth(v[7]);
     void* s = current_stream();
-    return status([&] {
-        return lib.dq_decode(address(codes), n, levels, bucket, (const float*)address(steps), &d, (float*)address(out),
-                             add, s);
-    });
+    return status(lib.dq_decode, address(codes), n, levels, bucket, (const float*)address(steps), &d,
+                  (float*)address(out), add, s);
 }
 
 // codes, n, levels, bucket, steps, out, accumulate
@@ -381,10 +388,8 @@ NDQ_METHOD(dq_decode_half, 7)
     check_values(out, n, "out must hold n float32");
     const int add = truth(v[6]);
     void* s = current_stream();
-    return status([&] {
-        return lib.dq_decode_half(address(codes), n, levels, bucket, (const float*)address(steps), (float*)address(out),
-                                  add, s);
-    });
+    return status(lib.dq_decode_half, address(codes), n, levels, bucket, (const float*)address(steps),
+                  (float*)address(out), add, s);
 }
 
 // codes, n, M, alpha, bucket, steps, d, side, side_scale, out, accumulate
@@ -401,10 +406,8 @@ NDQ_METHOD(nested_decode, 11)
     check_values(side, n, "out and side must hold n float32");
     const int add = truth(v[10]);
     void* s = current_stream();
-    return status([&] {
-        return lib.nested_decode(address(codes), n, M, alpha, bucket, (const float*)address(steps), &d,
-                                 (const float*)address(side), side_scale, (float*)address(out), add, s);
-    });
+    return status(lib.nested_decode, address(codes), n, M, alpha, bucket, (const float*)address(steps), &d,
+                  (const float*)address(side), side_scale, (float*)address(out), add, s);
 }
 
 // gs, scale, out
@@ -424,7 +427,7 @@ NDQ_METHOD(aggregate, 3)
     const float scale = real(v[1]);
     const at::Tensor& out = tensor(v[2], "out");
     void* s = current_stream();
-    return status([&] { return lib.aggregate(list.data(), (uint32_t)W, n, scale, (float*)address(out), s); });
+    return status(lib.aggregate, list.data(), (uint32_t)W, n, scale, (float*)address(out), s);
 }
 
 // (codes, steps, kind, levels_or_M, d[, alpha])
@@ -464,9 +467,8 @@ NDQ_METHOD(decode_mean, 6)
     const at::Tensor& out = tensor(v[5], "out");
     check_values(out, n, "out must hold n float32");
     void* s = current_stream();
-    return status([&] {
-        return lib.decode_mean(list.data(), values.data(), (uint32_t)W, n, bucket, scale, (float*)address(out), s);
-    });
+    return status(lib.decode_mean, list.data(), values.data(), (uint32_t)W, n, bucket, scale, (float*)address(out),
+                  s);
 }
 
 // workers, n, bucket, scale, out
@@ -482,7 +484,7 @@ NDQ_METHOD(decode_chain, 5)
     const at::Tensor& out = tensor(v[4], "out");
     check_values(out, n, "out must hold n float32");
     void* s = current_stream();
-    return status([&] { return lib.decode_chain(list.data(), (uint32_t)W, n, bucket, scale, (float*)address(out), s); });
+    return status(lib.decode_chain, list.data(), (uint32_t)W, n, bucket, scale, (float*)address(out), s);
 }
 
 // codes (or None for n == 0), n, bits, hist_out, entropy_out or None
@@ -500,7 +502,7 @@ NDQ_METHOD(code_entropy, 5)
     const at::Tensor& hist = tensor(v[3], "hist_out");
     double* entropy = v[4] == Py_None ? nullptr : (double*)address(tensor(v[4], "entropy_out"));
     void* s = current_stream();
-    return status([&] { return lib.code_entropy(codes, n, bits, (uint64_t*)address(hist), entropy, s); });
+    return status(lib.code_entropy, codes, n, bits, (uint64_t*)address(hist), entropy, s);
 }
 
 // codes, n, levels, dense_out
@@ -511,7 +513,7 @@ NDQ_METHOD(dense_pack, 4)
     const uint32_t levels = (uint32_t)integer(v[2]);
     if (out.nbytes() < lib.dense_bytes(n, levels)) fail(PyExc_ValueError, "dense_out too small");
     void* s = current_stream();
-    return status([&] { return lib.dense_pack(address(in), n, levels, address(out), s); });
+    return status(lib.dense_pack, address(in), n, levels, address(out), s);
 }
 
 // dense, n, levels, codes_out
@@ -522,7 +524,7 @@ NDQ_METHOD(dense_unpack, 4)
     const uint32_t levels = (uint32_t)integer(v[2]);
     if (out.nbytes() < packed_bytes(n, code_bits(levels))) fail(PyExc_ValueError, "codes_out too small");
     void* s = current_stream();
-    return status([&] { return lib.dense_unpack(address(in), n, levels, address(out), s); });
+    return status(lib.dense_unpack, address(in), n, levels, address(out), s);
 }
 
 void check_pair(const at::Tensor& a, const at::Tensor& b)
@@ -539,10 +541,8 @@ NDQ_METHOD(sqdiff, 4)
     check_pair(a, b);
     const size_t n = count(a);
     void* s = current_stream();
-    return status([&] {
-        return lib.sqdiff((const float*)address(a), (const float*)address(b), n, (double*)address(work),
-                          (double*)address(out), s);
-    });
+    return status(lib.sqdiff, (const float*)address(a), (const float*)address(b), n, (double*)address(work),
+                  (double*)address(out), s);
 }
 
 // a, b, out
@@ -553,9 +553,7 @@ NDQ_METHOD(sqdiff_static, 3)
     if (!is_f64(out) || count(out) < 1u) fail(PyExc_ValueError, "out must hold one float64");
     const size_t n = count(a);
     void* s = current_stream();
-    return status([&] {
-        return lib.sqdiff_static((const float*)address(a), (const float*)address(b), n, (double*)address(out), s);
-    });
+    return status(lib.sqdiff_static, (const float*)address(a), (const float*)address(b), n, (double*)address(out), s);
 }
 
 template <class F> bool take(PyObject* addresses, const char* name, F* slot)

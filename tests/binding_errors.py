@@ -1,0 +1,70 @@
+"""Calls of the binding that must raise, run in a process of their own by test_binding.py
+(a failure of this kind can end the process).  There is no GPU: tensors are fake ones on the device,
+and torch's current device and stream are stood in for, so that a call gets as far as
+the addresses of its tensors."""
+import sys
+
+import torch
+from torch._subclasses.fake_tensor import FakeTensorMode
+
+torch._C._cuda_getDevice = lambda: 0
+torch._C._cuda_getCurrentRawStream = lambda device: 0
+
+from paper_1904_01197_amd import ndq  # noqa: E402
+
+ndq.lib()
+N, W = 64, 3
+
+
+def every_call():
+    """(name, function of a gradient, codes, steps, values and a binary64 number)"""
+    d = ndq.ndq_dither(1, 1, 1, 0)
+    job = lambda g, c, s: (g, ndq.NDQ_WORKER_DQ, 4, 0, 1.0, d, c, s, None)
+    message = lambda c, s: (c, s, ndq.NDQ_WORKER_DQ, 4, d)
+    return [
+        ("absmax", lambda g, c, s, o, e, h: ndq.ndq_absmax(g, 0, s)),
+        ("dq_encode", lambda g, c, s, o, e, h: ndq.ndq_dq_encode(g, 0.0, 4, 0, d, c, s)),
+        ("dq_encode_with_step", lambda g, c, s, o, e, h: ndq.ndq_dq_encode_with_step(g, s, 4, d, c, s)),
+        ("nested_encode", lambda g, c, s, o, e, h: ndq.ndq_nested_encode(g, 0.0, 4, 4, 1.0, 0, d, c, s)),
+        ("nested_encode_with_step", lambda g, c, s, o, e, h: ndq.ndq_nested_encode_with_step(g, s, 4, 1.0, d, c, s)),
+        ("encode_workers", lambda g, c, s, o, e, h: ndq.ndq_encode_workers([job(g, c, s)], 0.0, 0)),
+        ("dq_decode", lambda g, c, s, o, e, h: ndq.ndq_dq_decode(c, N, 4, 0, s, d, o)),
+        ("dq_decode_half", lambda g, c, s, o, e, h: ndq.ndq_dq_decode_half(c, N, 4, 0, s, o)),
+        ("nested_decode", lambda g, c, s, o, e, h: ndq.ndq_nested_decode(c, N, 4, 1.0, 0, s, d, o, 1.0, o)),
+        ("aggregate", lambda g, c, s, o, e, h: ndq.ndq_aggregate([g], 1.0, o)),
+        ("decode_chain", lambda g, c, s, o, e, h: ndq.ndq_decode_chain([message(c, s)], N, 0, 1.0, o)),
+        ("decode_mean", lambda g, c, s, o, e, h: ndq.ndq_decode_mean([message(c, s)], [o], N, 0, 1.0, g)),
+        ("code_entropy", lambda g, c, s, o, e, h: ndq.ndq_code_entropy(c, N, 2, h, e)),
+        ("dense_pack", lambda g, c, s, o, e, h: ndq.ndq_dense_pack(c, N, 4, c)),
+        ("dense_unpack", lambda g, c, s, o, e, h: ndq.ndq_dense_unpack(c, N, 4, c)),
+        ("sqdiff", lambda g, c, s, o, e, h: ndq.ndq_sqdiff(g, o, e, e)),
+        ("sqdiff_static", lambda g, c, s, o, e, h: ndq.ndq_sqdiff_static(g, o, e)),
+    ]
+
+
+def tensors_without_storage():
+    with FakeTensorMode():
+        args = (torch.empty(W, N, device="cuda"), torch.empty(W, 64, dtype=torch.uint8, device="cuda"),
+                torch.empty(W, 1, device="cuda"), torch.empty(W, N, device="cuda"),
+                torch.empty(W, 1, dtype=torch.float64, device="cuda"),
+                torch.empty(W, 4, dtype=torch.int64, device="cuda"))
+        for name, call in every_call():
+            print(name, flush=True)
+
+            def one(g, c, s, o, e, h):
+                call(g, c, s, o, e, h)
+                return g
+
+            try:
+                torch.vmap(one)(*args)
+            except RuntimeError as error:
+                assert "data pointer" in str(error) and "#1 " not in str(error), str(error)
+            else:
+                raise AssertionError("%s took a tensor without storage" % name)
+            # the interpreter is still whole
+            assert sum(i * i for i in range(1000)) == 332833500
+
+
+if __name__ == "__main__":
+    {"storage": tensors_without_storage}[sys.argv[1]]()
+    print("BINDING_ERRORS_OK", flush=True)
