@@ -176,7 +176,8 @@ int ndq_nested_encode_with_step(const void* g, int dt, size_t n, const float* st
  *   kind, levels, M, alpha, dither: the worker's quantizer, as in ndq_dq_encode /
  *     ndq_nested_encode (M and alpha: nested workers only)
  *   step_in: NULL, or -- bucket == 0 only -- one step in device memory, as in the
- *     _with_step calls; it may be the steps_out of an earlier worker of this call
+ *     _with_step calls; it may be the steps_out of another worker of this call: of an
+ *     earlier one, whose step it then is, or of a later one, which then writes over it
  * delta and bucket as in ndq_dq_encode (workers with a step_in do not use delta).
  * jobs: HOST array of W entries (1 <= W <= 1024).  Apart from step_in no worker may read
  * what another one writes. */

@@ -721,6 +721,7 @@ struct EncodePlan {
     int mode;
     bool fused, multi;
     bool two_pass;       // the steps come from a max-norm pass of their own
+    bool handed;         // the step is read from memory the caller named
 };
 
 static bool same_launch(const EncodePlan& p, const EncodePlan& q)
@@ -772,6 +773,7 @@ static int plan_encode(const ndq_encode_job& job, int dt, size_t n, float delta,
     plan->multi = multi;
     plan->fused = (bucket != 0u && bucket <= tile) || block_fused;   // (multi implies fused)
     plan->two_pass = !job.step_in && !plan->fused && a.preset_step == 0.0f;
+    plan->handed = job.step_in != nullptr;
 #ifndef NDQ_NARROW_MAX_BITS
 #define NDQ_NARROW_MAX_BITS 6u
 #endif
@@ -833,6 +835,38 @@ static int run_plans(const EncodePlan* plans, uint32_t jobs, int dt, uint32_t bu
         if (rc != NDQ_OK) return rc;
     }
     return NDQ_OK;
+}
+
+// What a worker writes: its steps and its code stream.
+struct Written {
+    uintptr_t steps, steps_end, codes, codes_end;
+    bool changes_steps;      // false: the step handed over is the one it would write
+};
+static Written written(const EncodePlan& p)
+{
+    const uintptr_t steps = (uintptr_t)p.a.steps, codes = (uintptr_t)p.a.codes;
+    return {steps, steps + 4u * (uintptr_t)p.a.num_buckets, codes, codes + (uintptr_t)p.a.total_bytes,
+            !(p.handed && p.a.step_in == p.a.steps)};
+}
+static bool inside(uintptr_t x, uintptr_t begin, uintptr_t end) { return x + 4u > begin && x < end; }
+
+// run_plans makes the max-norm passes of all its vectors first and one launch of many encoders;
+// the bytes have to be those of one call after the other.  True: `later` must not share a
+// run_plans with `earlier`, because one of them reads a step the other one writes (a step from a
+// max-norm pass is there before every encoder) or both write the same memory.
+static bool must_wait(const EncodePlan& earlier, const EncodePlan& later)
+{
+    const Written a = written(earlier), b = written(later);
+    const uintptr_t reads_a = (uintptr_t)earlier.a.step_in, reads_b = (uintptr_t)later.a.step_in;
+    if (later.handed && ((inside(reads_b, a.steps, a.steps_end) && a.changes_steps && !earlier.two_pass) ||
+                         inside(reads_b, a.codes, a.codes_end)))
+        return true;
+    if (earlier.handed && ((inside(reads_a, b.steps, b.steps_end) && b.changes_steps) ||
+                           inside(reads_a, b.codes, b.codes_end)))
+        return true;
+    return (b.changes_steps && a.steps < b.steps_end && b.steps < a.steps_end) ||
+           (a.codes < b.codes_end && b.codes < a.codes_end) || (a.steps < b.codes_end && b.codes < a.steps_end) ||
+           (b.changes_steps && a.codes < b.steps_end && b.steps < a.codes_end);
 }
 
 // one vector
@@ -905,19 +939,13 @@ int ndq_encode_workers(const ndq_encode_job* jobs, uint32_t W, int dt, size_t n,
         if (rc != NDQ_OK) return rc;
     }
     if (n == 0) return NDQ_OK;
-    const uint64_t K = bucket ? (n + bucket - 1) / bucket : 1;
     for (uint32_t w0 = 0; w0 < W;) {
         uint32_t count = 0;
         for (; w0 + count < W && count < kEncJobs; ++count) {
-            const ndq_encode_job& job = jobs[w0 + count];
-            // a step handed over by an earlier worker of this call: there after the max-norm
-            // passes, or else only after that worker's encoder, which then has to be enqueued first
+            plan_encode(jobs[w0 + count], dt, n, delta, bucket, &plans[count]);
             bool waits = false;
-            for (uint32_t k = 0; k < count && job.step_in; ++k)
-                waits = waits || (!plans[k].two_pass && job.step_in >= plans[k].a.steps &&
-                                  job.step_in < plans[k].a.steps + K);
+            for (uint32_t k = 0; k < count; ++k) waits = waits || must_wait(plans[k], plans[count]);
             if (waits) break;
-            plan_encode(job, dt, n, delta, bucket, &plans[count]);
         }
         const int rc = run_plans(plans, count, dt, bucket, (hipStream_t)stream);
         if (rc != NDQ_OK) return rc;

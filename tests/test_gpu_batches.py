@@ -116,6 +116,29 @@ def test_more_workers_than_one_launch_holds_and_a_step_from_an_earlier_worker(pr
         assert codes[w].cpu().numpy()[:ref.size].tobytes() == ref.tobytes(), w
 
 
+@pytest.mark.parametrize("preset", [0.0, 0.02])
+def test_a_step_that_a_later_worker_writes_over(preset):
+    # (steps_out, step_in) as indices into the steps: the bytes are those of one call after the other
+    n = 70001
+    for workers in ([(1, 0), (0, None)], [(0, None), (0, None), (1, 0)], [(2, 3), (1, 0), (0, 3), (3, None), (2, 3)],
+                    [(0, None), (1, 0), (0, 1), (0, None), (2, 0), (2, 2)]):
+        host = _host(len(workers), n, "f32", 3)
+        first = [0.01, 0.02, 0.03, 0.04]
+        steps, codes, jobs = torch.tensor(first, device="cuda"), [], []
+        for w, (to, given) in enumerate(workers):
+            codes.append(torch.empty(ndq.ndq_packed_bytes(n, 4), dtype=torch.uint8, device="cuda"))
+            jobs.append((_dev(host[w]), ndq.NDQ_WORKER_DQ, 16, 0, 1.0, ndq.ndq_dither(w, 3, w, 0), codes[w],
+                         steps[to:to + 1], None if given is None else steps[given:given + 1]))
+        ndq.ndq_encode_workers(jobs, preset, 0)
+        held = list(first)
+        for w, (to, given) in enumerate(workers):
+            ref, s_ref = oracle.dq_encode(host[w], preset if given is None else float(F(held[given])), 16, 0,
+                                          oracle.dither(w, 3, w))
+            held[to] = float(s_ref[0])
+            assert codes[w].cpu().numpy().tobytes() == ref.tobytes(), (workers, w)
+        assert steps.cpu().numpy().tolist() == [float(F(x)) for x in held], workers
+
+
 @pytest.mark.parametrize("bucket,shared", [(4096, False), (0, True)])
 def test_streaming_encoder_over_several_vectors(bucket, shared):
     # together two tiles per wave slot (8,192 tiles of 4,096 elements) and a ragged end each:

@@ -45,3 +45,45 @@ def test_the_max_norm_pass_keeps_its_parts_inside_the_code_stream(recorder, dt):
                 spans += 1
                 assert 4 * x <= oracle.packed_bytes(n, 1), (n, bucket, W, x)
     assert spans > 20                                 # (the sizes do reach that form)
+
+
+def _kinds(launches):
+    """A letter per launch: the max-norm pass (any of its kernels: m), an encoder (its number of vectors)."""
+    text = ""
+    for name, _, y in launches:
+        if "absmax" in name or "fill_zero" in name:
+            text += "" if text.endswith("m") else "m"
+        else:
+            assert "encode" in name
+            text += str(y)
+    return text
+
+
+# steps of the workers: S[w]; a worker is (its steps_out, the step it is handed or None)
+ORDERS = [
+    # every worker handed the first one's step, which a max-norm pass finds: one batch
+    ([(0, None), (1, 0), (2, 0)], 0.0, "m12"),
+    # the same where every worker keeps it in place
+    ([(0, None), (0, 0), (0, 0)], 0.0, "m12"),
+    # a preset step is there only after its worker's encoder
+    ([(0, None), (1, 0), (2, 0)], 0.5, "12"),
+    # handed over along a chain
+    ([(0, None), (1, 0), (2, 1)], 0.0, "m111"),
+    # a LATER worker writes over the step an earlier one was handed: by its max-norm pass, by its encoder
+    ([(1, 0), (0, None)], 0.0, "1m1"),
+    ([(1, 0), (0, None)], 0.5, "11"),
+    ([(2, 3), (1, 0), (0, 3)], 0.0, "21"),
+    # two workers leave their steps in the same place
+    ([(0, None), (0, None), (1, 0)], 0.0, "m1m11"),
+    ([(0, None), (0, None)], 0.5, "11"),
+]
+
+
+@pytest.mark.parametrize("workers,preset,expected", ORDERS)
+def test_workers_that_share_a_step_are_launched_in_the_order_given(recorder, workers, preset, expected):
+    for n in (1000, 70000):
+        jobs = [_job(codes_out=0x20000000 + 0x100000 * w, levels=16, steps_out=0x30000000 + 4 * out,
+                     step_in=None if handed is None else 0x30000000 + 4 * handed)
+                for w, (out, handed) in enumerate(workers)]
+        (rc, launches), = lr.record(recorder, [["ndq_encode_workers", jobs, len(jobs), 0, n, preset, 0, None]])
+        assert rc == 0 and _kinds(launches) == expected, launches
