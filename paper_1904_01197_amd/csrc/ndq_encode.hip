@@ -421,10 +421,12 @@ void encode_stream_kernel(EncodeBatch by_value, uint32_t full_tiles)
     const uint32_t first = blockIdx.x * kWavesPerBlock + wave;
     const uint32_t jobs = batch->jobs;
     const uint32_t all_tiles = jobs * full_tiles;      // job after job: tile `t` of job j is j * full_tiles + t
-    if (!FUSED && first < jobs) {                      // the transmitted step of one vector
-        select_job(a, batch, first);
-        const float step = a.preset_step > 0.0f ? a.preset_step : a.step_in[0];
-        if (lane == 0) a.steps[0] = step;
+    if constexpr (!FUSED) {                            // the transmitted step of every vector
+        for (uint32_t j = first; j < jobs; j += stride) {
+            select_job(a, batch, j);
+            const float step = a.preset_step > 0.0f ? a.preset_step : a.step_in[0];
+            if (lane == 0) a.steps[0] = step;
+        }
     }
     if (first < all_tiles) {
         // Every pass over a tile issues exactly one load per row, also the last one (then of the

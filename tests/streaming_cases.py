@@ -89,6 +89,28 @@ def encoder_cases():
     return count
 
 
+def batch_cases():
+    """More vectors in one launch than the grid has waves (twelve): each one's step and codes."""
+    count = 0
+    for n in (4096 * 3, 4096 * 2 + 1000):
+        host = [make(n, "bf16", seed=100 + w) for w in range(16)]
+        dev = [to_dev(g) for g in host]
+        for preset, handed in ((0.001, False), (0.0, True), (0.0, False)):
+            print("batch", n, preset, handed, flush=True)
+            given = torch.tensor([0.002], dtype=torch.float32, device="cuda") if handed else None
+            codes = [torch.empty(ndq.ndq_packed_bytes(n, 4), dtype=torch.uint8, device="cuda") for _ in host]
+            steps = [torch.full((1,), -1.0, device="cuda") for _ in host]
+            ndq.ndq_encode_workers([(dev[w], ndq.NDQ_WORKER_DQ, 16, 0, 1.0, ndq.ndq_dither(w, 3, w, 0), codes[w],
+                                     steps[w], given) for w in range(16)], preset, 0)
+            for w in range(16):
+                c_ref, s_ref = oracle.dq_encode(host[w], float(F(0.002)) if handed else preset, 16, 0,
+                                                oracle.dither(w, 3, w))
+                assert steps[w].item() == s_ref[0], (n, preset, handed, w)
+                assert codes[w].cpu().numpy().tobytes() == c_ref.tobytes(), (n, preset, handed, w)
+                count += 1
+    return count
+
+
 def chain_cases():
     count = 0
     plans = [
@@ -126,6 +148,7 @@ if __name__ == "__main__":
     assert os.environ.get("NDQ_STREAM_MIN_TILES_PER_WAVE") == "0"
     assert torch.cuda.is_available()
     torch.cuda.set_device(0)
+    b = batch_cases()
     e = encoder_cases()
     c = chain_cases()
-    print("STREAMING_CASES_OK encoder=%d chain=%d" % (e, c), flush=True)
+    print("STREAMING_CASES_OK batch=%d encoder=%d chain=%d" % (b, e, c), flush=True)
