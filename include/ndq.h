@@ -196,6 +196,12 @@ typedef struct {
 int ndq_encode_workers(const ndq_encode_job* jobs, uint32_t W, int dt, size_t n, float delta,
                        uint32_t bucket, void* stream);
 
+/* What ndq_encode_workers would answer to these arguments (apart from NDQ_ELAUNCH), without
+ * enqueuing anything: for a caller that makes several such calls and wants none of them
+ * to run when one is refused. */
+int ndq_encode_check(const ndq_encode_job* jobs, uint32_t W, int dt, size_t n, float delta,
+                     uint32_t bucket);
+
 /* Server side of Algorithm 2 for a worker of group P2 (eq. (8)).
  * The side information is y_i = side[i] * side_scale, so `side` may be the
  * running SUM of the gradients decoded so far and side_scale = 1/count (the

@@ -928,18 +928,27 @@ int ndq_absmax(const void* g, int dt, size_t n, uint32_t bucket, float* kappa_ou
     return dt == NDQ_F32 ? run_absmax<0>(b, 1u, s) : run_absmax<1>(b, 1u, s);
 }
 
+int ndq_encode_check(const ndq_encode_job* jobs, uint32_t W, int dt, size_t n, float delta, uint32_t bucket)
+{
+    using namespace ndq;
+    if (!jobs || W < 1u || W > 1024u) return NDQ_EINVAL;
+    EncodePlan plan;
+    for (uint32_t w = 0; w < W; ++w) {
+        if (jobs[w].kind != NDQ_WORKER_DQ && jobs[w].kind != NDQ_WORKER_NESTED) return NDQ_EINVAL;
+        if (jobs[w].step_in && bucket != 0u) return NDQ_EINVAL;     // one step belongs to one bucket
+        const int rc = plan_encode(jobs[w], dt, n, delta, bucket, &plan);
+        if (rc != NDQ_OK) return rc;
+    }
+    return NDQ_OK;
+}
+
 int ndq_encode_workers(const ndq_encode_job* jobs, uint32_t W, int dt, size_t n, float delta, uint32_t bucket,
                        void* stream)
 {
     using namespace ndq;
-    if (!jobs || W < 1u || W > 1024u) return NDQ_EINVAL;
+    const int rc_check = ndq_encode_check(jobs, W, dt, n, delta, bucket);
+    if (rc_check != NDQ_OK) return rc_check;
     EncodePlan plans[kEncJobs];
-    for (uint32_t w = 0; w < W; ++w) {
-        if (jobs[w].kind != NDQ_WORKER_DQ && jobs[w].kind != NDQ_WORKER_NESTED) return NDQ_EINVAL;
-        if (jobs[w].step_in && bucket != 0u) return NDQ_EINVAL;     // one step belongs to one bucket
-        const int rc = plan_encode(jobs[w], dt, n, delta, bucket, &plans[0]);
-        if (rc != NDQ_OK) return rc;
-    }
     if (n == 0) return NDQ_OK;
     for (uint32_t w0 = 0; w0 < W;) {
         uint32_t count = 0;

@@ -26,6 +26,7 @@ struct Library {
     decltype(&ndq_nested_encode) nested_encode;
     decltype(&ndq_nested_encode_with_step) nested_encode_with_step;
     decltype(&ndq_encode_workers) encode_workers;
+    decltype(&ndq_encode_check) encode_check;
     decltype(&ndq_dq_decode) dq_decode;
     decltype(&ndq_dq_decode_half) dq_decode_half;
     decltype(&ndq_nested_decode) nested_decode;
@@ -320,6 +321,10 @@ struct EncodeCall { size_t first, jobs, n; int dt; uint32_t bucket; };
 int encode_calls(const ndq_encode_job* jobs, const EncodeCall* calls, size_t num_calls, float delta, void* s)
 {
     int rc = NDQ_OK;
+    // a call checks its own jobs before it enqueues; several have to be checked before the first does
+    for (size_t c = 0; c < num_calls && rc == NDQ_OK && num_calls > 1u; ++c)
+        rc = lib.encode_check(jobs + calls[c].first, (uint32_t)calls[c].jobs, calls[c].dt, calls[c].n, delta,
+                              calls[c].bucket);
     for (size_t c = 0; c < num_calls && rc == NDQ_OK; ++c)
         rc = lib.encode_workers(jobs + calls[c].first, (uint32_t)calls[c].jobs, calls[c].dt, calls[c].n, delta,
                                 calls[c].bucket, s);
@@ -584,7 +589,7 @@ PyObject* bind(PyObject*, PyObject* const* v, Py_ssize_t n)
         !take(v[0], "ndq_dq_encode_with_step", &l.dq_encode_with_step) ||
         !take(v[0], "ndq_nested_encode", &l.nested_encode) ||
         !take(v[0], "ndq_nested_encode_with_step", &l.nested_encode_with_step) ||
-        !take(v[0], "ndq_encode_workers", &l.encode_workers) || !take(v[0], "ndq_dq_decode", &l.dq_decode) ||
+        !take(v[0], "ndq_encode_workers", &l.encode_workers) || !take(v[0], "ndq_encode_check", &l.encode_check) || !take(v[0], "ndq_dq_decode", &l.dq_decode) ||
         !take(v[0], "ndq_dq_decode_half", &l.dq_decode_half) || !take(v[0], "ndq_nested_decode", &l.nested_decode) ||
         !take(v[0], "ndq_aggregate", &l.aggregate) || !take(v[0], "ndq_decode_chain", &l.decode_chain) ||
         !take(v[0], "ndq_decode_mean", &l.decode_mean) || !take(v[0], "ndq_code_entropy", &l.code_entropy) || !take(v[0], "ndq_dense_pack", &l.dense_pack) ||

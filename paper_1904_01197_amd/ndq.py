@@ -20,7 +20,7 @@ NDQ_F32, NDQ_BF16 = 0, 1
 NDQ_OK, NDQ_EINVAL, NDQ_EALIGN, NDQ_EUNSUPPORTED, NDQ_ELAUNCH = 0, -1, -2, -3, -4
 
 EXPORTS = ("ndq_code_bits", "ndq_packed_bytes", "ndq_num_buckets", "ndq_absmax", "ndq_dq_encode",
-           "ndq_dq_encode_with_step", "ndq_nested_encode_with_step", "ndq_encode_workers",
+           "ndq_dq_encode_with_step", "ndq_nested_encode_with_step", "ndq_encode_workers", "ndq_encode_check",
            "ndq_dq_decode", "ndq_dq_decode_half", "ndq_nested_encode", "ndq_nested_decode", "ndq_aggregate",
            "ndq_decode_chain", "ndq_decode_mean", "ndq_code_entropy", "ndq_dense_group", "ndq_dense_bytes",
            "ndq_dense_pack", "ndq_dense_unpack", "ndq_alpha_for_equal_variance",
@@ -94,6 +94,8 @@ def lib():
         L.ndq_nested_encode_with_step.restype = ci
         L.ndq_encode_workers.argtypes = [C.POINTER(ndq_encode_job), u32, ci, sz, f32, u32, vp]
         L.ndq_encode_workers.restype = ci
+        L.ndq_encode_check.argtypes = [C.POINTER(ndq_encode_job), u32, ci, sz, f32, u32]
+        L.ndq_encode_check.restype = ci
         L.ndq_nested_decode.argtypes = [vp, sz, u32, f32, u32, vp, dp, vp, f32, vp, ci, vp]
         L.ndq_nested_decode.restype = ci
         L.ndq_aggregate.argtypes, L.ndq_aggregate.restype = [vp, u32, sz, f32, vp, vp], ci
@@ -202,7 +204,7 @@ def ndq_encode_workers(jobs, delta, bucket):
     """jobs: sequence of (g, kind, levels, M, alpha, ndq_dither, codes_out, steps_out, step_in);
     M and alpha count for nested workers, step_in is None or a device tensor holding one
     float32 step for the whole vector (`bucket` is then not used).  Neighbours of one length and
-    type share a library call."""
+    type share a library call; when one is refused, nothing is enqueued."""
     _check(_ready().encode_workers(jobs, delta, bucket), "ndq_encode_workers")
 
 

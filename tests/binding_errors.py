@@ -65,6 +65,51 @@ def tensors_without_storage():
             assert sum(i * i for i in range(1000)) == 332833500
 
 
+def a_refused_job_among_several_calls():
+    """The binding over stand-ins for the library's functions: jobs of two lengths need two calls, the
+    second of which is refused; the first must not have been made."""
+    import ctypes as C
+    made = []
+
+    def answer(jobs, W, *rest):
+        return ndq.NDQ_EINVAL if any(jobs[i].M == 1 for i in range(W)) else ndq.NDQ_OK
+
+    @C.CFUNCTYPE(C.c_int, C.POINTER(ndq.ndq_encode_job), C.c_uint32, C.c_int, C.c_size_t, C.c_float, C.c_uint32,
+                 C.c_void_p)
+    def workers(jobs, W, *rest):
+        rc = answer(jobs, W)
+        if rc == ndq.NDQ_OK:
+            made.append(W)
+        return rc
+
+    @C.CFUNCTYPE(C.c_int, C.POINTER(ndq.ndq_encode_job), C.c_uint32, C.c_int, C.c_size_t, C.c_float, C.c_uint32)
+    def check(jobs, W, *rest):
+        return answer(jobs, W)
+
+    lib = ndq.lib()
+    addresses = {name: C.cast(getattr(lib, name), C.c_void_p).value for name in ndq.EXPORTS}
+    addresses["ndq_encode_workers"] = C.cast(workers, C.c_void_p).value
+    addresses["ndq_encode_check"] = C.cast(check, C.c_void_p).value
+    ndq._native.bind(addresses, ndq.ndq_dither, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+    with FakeTensorMode():
+        d = ndq.ndq_dither(1, 1, 1, 0)
+
+        def job(n, M):
+            return (torch.empty(n, device="cuda"), ndq.NDQ_WORKER_NESTED, 4, M, 1.0, d,
+                    torch.empty(n, dtype=torch.uint8, device="cuda"), torch.empty(1, device="cuda"), None)
+
+        ndq.ndq_encode_workers([job(64, 4), job(64, 4), job(128, 4)], 0.0, 0)
+        assert made == [2, 1], made
+        for jobs in ([job(64, 4), job(128, 1)], [job(64, 4)] * 1024 + [job(64, 1)], [job(64, 1)]):
+            del made[:]
+            try:
+                ndq.ndq_encode_workers(jobs, 0.0, 0)
+            except ndq.NdqError as error:
+                assert error.rc == ndq.NDQ_EINVAL and made == [], made
+            else:
+                raise AssertionError("the refusal was lost")
+
+
 if __name__ == "__main__":
-    {"storage": tensors_without_storage}[sys.argv[1]]()
+    {"storage": tensors_without_storage, "refused": a_refused_job_among_several_calls}[sys.argv[1]]()
     print("BINDING_ERRORS_OK", flush=True)

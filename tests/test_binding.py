@@ -16,3 +16,7 @@ def _run(case):
 
 def test_a_tensor_without_storage_raises_and_the_process_goes_on():
     _run("storage")
+
+
+def test_nothing_is_enqueued_when_one_of_several_calls_is_refused():
+    _run("refused")

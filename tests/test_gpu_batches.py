@@ -153,11 +153,13 @@ def test_bad_workers_are_reported_and_nothing_is_launched():
     d = ndq.ndq_dither(1, 1, 1, 0)
     good = (g, ndq.NDQ_WORKER_DQ, 4, 0, 1.0, d, codes, steps, None)
     bad_M = (g, ndq.NDQ_WORKER_NESTED, 4, 1, 1.0, d, codes, steps, None)
-    with pytest.raises(ndq.NdqError) as e:
-        ndq.ndq_encode_workers([good, bad_M], 0.0, 0)
-    assert e.value.rc == ndq.NDQ_EINVAL
-    torch.cuda.synchronize()
-    assert steps.item() == -1.0 and (codes == 7).all()
+    other = (g[:1024], ndq.NDQ_WORKER_NESTED, 4, 1, 1.0, d, codes, steps, None)     # needs a library call of its own
+    for jobs in ([good, bad_M], [good, other]):
+        with pytest.raises(ndq.NdqError) as e:
+            ndq.ndq_encode_workers(jobs, 0.0, 0)
+        assert e.value.rc == ndq.NDQ_EINVAL
+        torch.cuda.synchronize()
+        assert steps.item() == -1.0 and (codes == 7).all()
 
 
 @pytest.mark.parametrize("W", [1, 3, 33, 70])
