@@ -290,7 +290,9 @@ int ndq_decode_chain(const ndq_worker* workers, uint32_t W, size_t n, uint32_t b
  * worker (as ndq_dq_decode) and out_i = scale * sum_w g~_w,i, summed in ascending w (as
  * ndq_aggregate): the same values as those calls, without reading the reconstructions back.
  * workers: HOST array of W DQSG workers (1 <= W <= 1024) that share n and bucket; decoded:
- * HOST array of W device pointers, n floats each (16-byte aligned).  out must not be one of them. */
+ * HOST array of W device pointers, n floats each (16-byte aligned).  out may be one of them
+ * only if W <= 32 (the sum then takes that reconstruction's place), and the same vector may serve
+ * several workers (the last one's values stay); vectors that overlap otherwise are NDQ_EINVAL. */
 int ndq_decode_mean(const ndq_worker* workers, float* const* decoded, uint32_t W, size_t n,
                     uint32_t bucket, float scale, float* out, void* stream);
 

@@ -2,6 +2,7 @@
 // Algorithm 2, aggregation.  See include/ndq.h for the contract.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <utility>
 
 #include "ndq.h"
@@ -1336,6 +1337,13 @@ int ndq_decode_mean(const ndq_worker* workers, float* const* decoded, uint32_t W
         // a partial sum waits in `out` between launches (one launch: a lane writes `out` last)
         if (W > kMeanMax && decoded[p] == out) return NDQ_EINVAL;
     }
+    // vectors that overlap by a part would race between waves (the same vector twice: a lane writes it in order)
+    uintptr_t begin[1025];
+    for (uint32_t p = 0; p < W; ++p) begin[p] = (uintptr_t)decoded[p];
+    begin[W] = (uintptr_t)out;
+    std::sort(begin, begin + W + 1u);
+    for (uint32_t p = 0; p < W; ++p)
+        if (begin[p] != begin[p + 1u] && begin[p + 1u] - begin[p] < 4u * n) return NDQ_EINVAL;
     MeanArgs a;
     const int rc = make_tiling(n, bucket, kMeanTile, &a.tl);
     if (rc != NDQ_OK) return rc;

@@ -182,6 +182,11 @@ def test_decode_mean_keeps_every_reconstruction_and_their_sum(W):
         for w in range(W):
             assert np.array_equal(decoded[w].cpu().numpy(), refs[w]), (n, bucket, w)
         assert np.array_equal(out.cpu().numpy(), oracle.aggregate(refs, 1.0 / W)), (n, bucket)
+    if W <= 32:      # the sum in the place of one reconstruction; the others stay
+        total = ndq.ndq_decode_mean(msgs, decoded, n, bucket, 1.0 / W, decoded[W // 2])
+        assert np.array_equal(total.cpu().numpy(), oracle.aggregate(refs, 1.0 / W))
+        for w in range(W):
+            assert w == W // 2 or np.array_equal(decoded[w].cpu().numpy(), refs[w])
     bad = list(msgs[0])
     bad[2] = ndq.NDQ_WORKER_NESTED
     with pytest.raises(ndq.NdqError):

@@ -87,3 +87,19 @@ def test_workers_that_share_a_step_are_launched_in_the_order_given(recorder, wor
                 for w, (out, handed) in enumerate(workers)]
         (rc, launches), = lr.record(recorder, [["ndq_encode_workers", jobs, len(jobs), 0, n, preset, 0, None]])
         assert rc == 0 and _kinds(launches) == expected, launches
+
+
+# byte offsets of out and of the reconstructions; n = 1000 floats are 4,000 bytes
+@pytest.mark.parametrize("out,decoded,accepted", [
+    (0, [4000], True), (0, [0], True), (4000, [0, 8000, 12000], True), (8000, [0, 8000, 12000], True),
+    (0, [4000, 4000], True), (0, [3984], False), (3984, [0], False), (16000, [0, 8000, 11984], False),
+    (8016, [0, 8000, 12000], False), (0, [4000 * (w + 1) for w in range(33)], True),
+    (4000 * 7, [4000 * (w + 1) for w in range(33)], False), (4000 * 32, [4000 * w for w in range(32)], True),
+    (4000 * 34, [4000 * w for w in range(32)] + [4000 * 32 - 16], False)])
+def test_the_mean_refuses_vectors_that_overlap_by_a_part(recorder, out, decoded, accepted):
+    base = 0x10000000
+    workers = [{"codes": 0x20000000, "steps": 0x30000000, "kind": 0, "levels_or_M": 4, "alpha": 1.0,
+                "dither": [1, 2, 3, 0]}] * len(decoded)
+    (rc, launches), = lr.record(recorder, [["ndq_decode_mean", workers, [base + x for x in decoded], len(decoded), 1000,
+                                            0, 1.0, base + out, None]])
+    assert rc == (0 if accepted else -1) and len(launches) == ((len(decoded) + 31) // 32 if accepted else 0)
