@@ -121,6 +121,23 @@ ndq_dither dither(PyObject* o)
     return d;
 }
 
+// A worker's message may also carry its dither as a tuple of the fields (missing ones are 0).
+ndq_dither dither_or_fields(PyObject* o)
+{
+    if (!PyTuple_Check(o)) return dither(o);
+    PyObject* made = PyObject_Call(dither_type, o, nullptr);
+    if (!made) throw Failed();
+    ndq_dither d;
+    try {
+        d = dither(made);
+    } catch (...) {
+        Py_DECREF(made);
+        throw;
+    }
+    Py_DECREF(made);
+    return d;
+}
+
 void* current_stream()
 {
     PyObject* device = PyObject_CallNoArgs(get_device);
@@ -445,7 +462,7 @@ ndq_worker worker_message(PyObject* entry, size_t n, uint32_t bucket)
     wk.kind = (uint32_t)integer(f[2]);
     wk.levels_or_M = (uint32_t)integer(f[3]);
     wk.alpha = f.size() > 5u ? real(f[5]) : 1.0f;
-    wk.dither = dither(f[4]);
+    wk.dither = dither_or_fields(f[4]);
     check_message(codes, steps, n, code_bits(wk.levels_or_M), bucket);
     wk.codes = address(codes);
     wk.steps = (const float*)address(steps);

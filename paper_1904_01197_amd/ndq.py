@@ -245,7 +245,8 @@ def ndq_aggregate(gs, scale=1.0, out=None):
 def ndq_decode_chain(workers, n, bucket, scale=1.0, out=None):
     """workers: sequence of (codes, steps, kind, levels_or_M, ndq_dither[, alpha]) in decoding
     order; alpha (nested workers only) defaults to 1."""
-    out = _values(out, n, workers[0][0])
+    if out is None:
+        out = _values(None, n, workers[0][0])
     _check(_ready().decode_chain(workers, n, bucket, scale, out), "ndq_decode_chain")
     return out
 
@@ -253,7 +254,8 @@ def ndq_decode_chain(workers, n, bucket, scale=1.0, out=None):
 def ndq_decode_mean(workers, decoded, n, bucket, scale=1.0, out=None):
     """workers: as in ndq_decode_chain, all DQSG; decoded: one float32 tensor per worker for its
     reconstruction; -> out, scale times their sum."""
-    out = _values(out, n, workers[0][0])
+    if out is None:
+        out = _values(None, n, workers[0][0])
     _check(_ready().decode_mean(workers, decoded, n, bucket, scale, out), "ndq_decode_mean")
     return out
 

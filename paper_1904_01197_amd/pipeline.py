@@ -46,8 +46,8 @@ def allocate(wl: Workload, n: int, device="cuda", separate=False) -> Buffers:
 
 
 def encode_all(wl: Workload, grads, bufs: Buffers, ds, preset_step: float = 0.0):
-    """Worker side, all workers in one library call.  With wl.shared_step and no preset, worker 0 chooses the step and
-    the other workers read it from worker 0's steps in device memory (Algorithm 1,
+    """Worker side, all workers in one library call.  With wl.shared_step and no preset, worker 0
+    chooses the step and the other workers read it from worker 0's steps in device memory (Algorithm 1,
     initialisation: one Delta for all): no host round trip between the calls."""
     jobs = []
     for w, (kind, arg) in enumerate(wl.plan):
@@ -57,7 +57,8 @@ def encode_all(wl: Workload, grads, bufs: Buffers, ds, preset_step: float = 0.0)
         else:
             jobs.append((grads[w], ndq.NDQ_WORKER_NESTED, wl.fine_levels, arg, 1.0, ds[w], bufs.codes[w],
                          bufs.steps[w], step_in))
-    ndq.ndq_encode_workers(jobs, preset_step, wl.bucket)
+    if jobs:
+        ndq.ndq_encode_workers(jobs, preset_step, wl.bucket)
 
 
 def decode_chain(wl: Workload, n: int, bufs: Buffers, ds):

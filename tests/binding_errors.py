@@ -110,6 +110,44 @@ def a_refused_job_among_several_calls():
                 raise AssertionError("the refusal was lost")
 
 
+def forms_of_a_message():
+    """What a server may pass as a worker's message, over a stand-in for the library's function."""
+    import ctypes as C
+    seen = []
+
+    @C.CFUNCTYPE(C.c_int, C.POINTER(ndq.ndq_worker), C.c_uint32, C.c_size_t, C.c_uint32, C.c_float, C.c_void_p,
+                 C.c_void_p)
+    def chain(workers, W, *rest):
+        seen.append([(w.kind, w.levels_or_M, w.alpha, w.dither.seed, w.dither.step, w.dither.worker, w.dither.offset)
+                     for w in workers[:W]])
+        return ndq.NDQ_OK if W else ndq.NDQ_EINVAL
+
+    lib = ndq.lib()
+    addresses = {name: C.cast(getattr(lib, name), C.c_void_p).value for name in ndq.EXPORTS}
+    addresses["ndq_decode_chain"] = C.cast(chain, C.c_void_p).value
+    ndq._native.bind(addresses, ndq.ndq_dither, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+    with FakeTensorMode():
+        c, s = torch.empty(64, dtype=torch.uint8, device="cuda"), torch.empty(1, device="cuda")
+        out = torch.empty(N, device="cuda")
+        d = ndq.ndq_dither(1 << 40, 2, 3, 64)
+        for message in ((c, s, 0, 4, d), [c, s, 0, 4, d], (c, s, 0, 4, (1 << 40, 2, 3, 64)), (c, s, 0, 4, d, 1.0, "more")):
+            ndq.ndq_decode_chain([message], N, 0, 1.0, out)
+            assert seen.pop() == [(0, 4, 1.0, 1 << 40, 2, 3, 64)], message
+        ndq.ndq_decode_chain([(c, s, 0, 4, (9,)), (c, s, 1, 3, d, 0.5)], N, 0, 1.0, out)
+        assert seen.pop() == [(0, 4, 1.0, 9, 0, 0, 0), (1, 3, 0.5, 1 << 40, 2, 3, 64)]
+        for workers, kind in (([], ndq.NdqError), ([(c, s, 0, 4, [1, 2, 3, 0])], TypeError),
+                              ([(c, s, 0, 4, (1, 2, 3, 0, 5))], TypeError), ([(c, s, 0, 4, None)], TypeError)):
+            try:
+                ndq.ndq_decode_chain(workers, N, 0, 1.0, out)
+            except kind:
+                continue
+            raise AssertionError(workers)
+        from paper_1904_01197_amd import pipeline, workloads
+        wl = workloads.CONFIGS[1]
+        empty = type(wl)(**dict(vars(wl), plan=(), W=0))
+        pipeline.encode_all(empty, [], None, [])       # nobody to encode for: nothing happens
+
+
 if __name__ == "__main__":
-    {"storage": tensors_without_storage, "refused": a_refused_job_among_several_calls}[sys.argv[1]]()
+    {"messages": forms_of_a_message, "storage": tensors_without_storage, "refused": a_refused_job_among_several_calls}[sys.argv[1]]()
     print("BINDING_ERRORS_OK", flush=True)

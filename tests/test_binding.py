@@ -20,3 +20,7 @@ def test_a_tensor_without_storage_raises_and_the_process_goes_on():
 
 def test_nothing_is_enqueued_when_one_of_several_calls_is_refused():
     _run("refused")
+
+
+def test_the_forms_of_a_workers_message():
+    _run("messages")
