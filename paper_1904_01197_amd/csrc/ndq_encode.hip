@@ -519,7 +519,7 @@ __device__ __forceinline__ uint32_t absmax_word(float m, uint32_t levels)
     return __float_as_uint(levels ? step_from_kappa(m, levels) : m);
 }
 
-template <int DT>
+template <int DT, bool KEEP>
 __global__ __launch_bounds__(kBlock) void absmax_kernel(AbsmaxBatch by_value)
 {
     constexpr uint32_t TILE = EncTile<DT>::N;
@@ -532,8 +532,8 @@ __global__ __launch_bounds__(kBlock) void absmax_kernel(AbsmaxBatch by_value)
     const TileRef t = locate_tile(tl, tile_id, TILE);
     if (t.len == 0) return;
     TileRegs<DT> regs;
-    if (t.len == TILE) load_tile<DT, true, true>(g, t, lane, regs);
-    else load_tile<DT, false, true>(g, t, lane, regs);
+    if (t.len == TILE) load_tile<DT, true, KEEP>(g, t, lane, regs);
+    else load_tile<DT, false, KEEP>(g, t, lane, regs);
     const float m = tile_max<DT>(regs);
     if (lane == 0) atomicMax(b->kappa_bits[blockIdx.y] + t.bucket, absmax_word(m, b->levels[blockIdx.y]));
 }
@@ -546,7 +546,7 @@ __global__ __launch_bounds__(kBlock) void absmax_kernel(AbsmaxBatch by_value)
 // encoder's pass stores its parts and absmax_finish_kernel reduces them; the parts
 // lie in the vector's code stream, which the encoder overwrites afterwards.
 // ndq_absmax has no such memory: few workgroups, one atomic each.
-template <int DT>
+template <int DT, bool KEEP>
 __global__ __launch_bounds__(kBlock) void absmax_span_kernel(AbsmaxBatch by_value)
 {
     using T = Elem<DT>;
@@ -566,8 +566,8 @@ __global__ __launch_bounds__(kBlock) void absmax_span_kernel(AbsmaxBatch by_valu
         const TileRef t = locate_tile(tl, bucket * tl.tiles_per_bucket + j, TILE);
         if (t.len == 0) break;   // past the end of the vector: so are this wave's later tiles
         TileRegs<DT> regs;
-        if (t.len == TILE) load_tile<DT, true, true>(g, t, lane, regs);
-        else load_tile<DT, false, true>(g, t, lane, regs);
+        if (t.len == TILE) load_tile<DT, true, KEEP>(g, t, lane, regs);
+        else load_tile<DT, false, KEEP>(g, t, lane, regs);
         acc = lane_max<DT>(acc, regs);
     }
     const float m = wave_max(T::max_final(acc));
@@ -578,8 +578,10 @@ __global__ __launch_bounds__(kBlock) void absmax_span_kernel(AbsmaxBatch by_valu
 #pragma unroll
         for (int w = 1; w < kWavesPerBlock; ++w) all = __builtin_fmaxf(all, part[w]);
         float* parts = b->parts[blockIdx.y];
-        if (parts) parts[blockIdx.x] = all;
-        else atomicMax(b->kappa_bits[blockIdx.y] + bucket, absmax_word(all, b->levels[blockIdx.y]));
+        uint32_t* word = b->kappa_bits[blockIdx.y] + bucket;
+        if (blocks_per_bucket == 1u) *word = absmax_word(all, b->levels[blockIdx.y]);
+        else if (parts) parts[blockIdx.x] = all;
+        else atomicMax(word, absmax_word(all, b->levels[blockIdx.y]));
     }
 }
 
@@ -606,22 +608,36 @@ __global__ __launch_bounds__(kBlock) void absmax_finish_kernel(AbsmaxBatch by_va
 // ---------------------------------------------------------------------------
 // Host side: dispatch
 // ---------------------------------------------------------------------------
-// b: vectors, words, levels, tiling and (for an encoder) memory for the parts are set.
+// Whether the pass leaves its lines in the caches for the encoder (its loads are cached instead of
+// streaming).  `bytes`: the vectors of the launch, all of which are read before the first encoder runs.
+// binary32 (steps for the whole vector): 25.6 M elements 37.2 us against 42.7 streaming, 8 x 11 M 124.5 /
+// 137, 16 x 8 M (512 MiB) 191.5 / 200.5, 200 M (763 MiB) 285 / 290; beyond that the cached loads themselves are
+// the slower ones: 300 M 442 / 433, 16 x 25 M 605 / 585, 393 M in 3,000 buckets 585 / 572.
+// bfloat16: 11 M (22 MB, within the L2s) 14.8 / 15.7, 25.6 M 27.9 / 25.3, 4 x 11 M 41.4 / 38.7, 300 M 238 / 217.
+// ndq_absmax, which no encoder follows: at 2^27 binary32 elements, buckets of 2,048, 89.4 / 86.9.
 template <int DT>
-static int run_absmax(AbsmaxBatch& b, uint32_t jobs, hipStream_t s)
+static bool absmax_keeps(uint64_t bytes, bool encoder_follows)
 {
-    // many tiles per bucket: workgroups that stride over one.  With memory for the parts a full chip
-    // of waves; with atomics one workgroup per compute unit.  What counts are the tiles that hold
-    // elements: a bucket may be longer than the whole vector.
-    constexpr uint32_t kSpanMinTiles = 16, kSpanMaxBuckets = 2048;
-    const uint32_t target = b.parts[0] ? 2048u : 256u;
+    const uint64_t most = DT == 1 ? (uint64_t)32 << 20 : encoder_follows ? (uint64_t)768 << 20 : (uint64_t)256 << 20;
+    return bytes <= most;
+}
+
+// b: vectors, words, levels, tiling and (for an encoder) memory for the parts are set.
+template <int DT, bool KEEP>
+static int run_absmax_loads(AbsmaxBatch& b, uint32_t jobs, hipStream_t s)
+{
+    // Many tiles per bucket: workgroups that stride over one, at any number of buckets (3,000 buckets of
+    // 64 tiles, binary32: 572 us against 602 with an atomic per tile, of 32 tiles 288 / 298).  With
+    // memory for the parts a full chip of waves; with atomics one workgroup per compute unit; a workgroup that
+    // has a bucket to itself writes its word.  What counts are the tiles that hold elements: a bucket may
+    // be longer than the whole vector.
+    constexpr uint32_t kSpanMinTiles = 16;
+    // (binary32 with streaming loads is the only one to gain from twice the workgroups: 250 M elements 366 ->
+    // 361 us, 16 x 25 M 595 -> 585; cached, 25.6 M 37.2 -> 38.9; bfloat16, 60 M 50.5 -> 52.1)
+    const uint32_t target = !b.parts[0] ? 256u : DT == 0 && !KEEP ? 4096u : 2048u;
     const uint64_t tiles = b.K == 1u ? (b.tl.n + EncTile<DT>::N - 1u) / EncTile<DT>::N : b.tl.tiles_per_bucket;
-    const bool span = tiles >= kSpanMinTiles && b.K * jobs <= kSpanMaxBuckets;
-    const bool fill = !(span && b.parts[0]);
-    if (fill && launch(fill_zero_kernel, dim3((uint32_t)((b.K + 255) / 256), jobs), dim3(256), s, b) != NDQ_OK)
-        return NDQ_ELAUNCH;
-    if (span) {
-        uint32_t per_bucket = target / (uint32_t)(b.K * jobs);
+    if (tiles >= kSpanMinTiles) {
+        uint32_t per_bucket = (uint32_t)(target / (b.K * jobs));
         const uint32_t most = blocks_for((uint32_t)tiles);
         if (per_bucket > most) per_bucket = most;
         // a part is 4 bytes.  A workgroup has a tile, 256 bytes of 1-bit codes, so the parts always fit
@@ -629,12 +645,24 @@ static int run_absmax(AbsmaxBatch& b, uint32_t jobs, hipStream_t s)
         if (b.parts[0] && per_bucket > b.parts_bytes / (4u * b.K)) per_bucket = (uint32_t)(b.parts_bytes / (4u * b.K));
         if (per_bucket < 1u) per_bucket = 1u;
         b.blocks_per_bucket = per_bucket;
-        if (launch(absmax_span_kernel<DT>, dim3((uint32_t)b.K * per_bucket, jobs), dim3(kBlock), s, b) != NDQ_OK)
+        const bool parts = b.parts[0] && per_bucket > 1u, atomics = !b.parts[0] && per_bucket > 1u;
+        if (atomics && launch(fill_zero_kernel, dim3((uint32_t)((b.K + 255) / 256), jobs), dim3(256), s, b) != NDQ_OK)
             return NDQ_ELAUNCH;
-        if (!b.parts[0]) return NDQ_OK;
-        return launch(absmax_finish_kernel, dim3((uint32_t)b.K, jobs), dim3(kBlock), s, b);
+        if (launch((absmax_span_kernel<DT, KEEP>), dim3((uint32_t)b.K * per_bucket, jobs), dim3(kBlock), s, b) != NDQ_OK)
+            return NDQ_ELAUNCH;
+        return parts ? launch(absmax_finish_kernel, dim3((uint32_t)b.K, jobs), dim3(kBlock), s, b) : NDQ_OK;
     }
-    return launch(absmax_kernel<DT>, dim3(blocks_for((uint32_t)(tiles * b.K)), jobs), dim3(kBlock), s, b);
+    if (launch(fill_zero_kernel, dim3((uint32_t)((b.K + 255) / 256), jobs), dim3(256), s, b) != NDQ_OK)
+        return NDQ_ELAUNCH;
+    return launch((absmax_kernel<DT, KEEP>), dim3(blocks_for((uint32_t)(tiles * b.K)), jobs), dim3(kBlock), s, b);
+}
+
+template <int DT>
+static int run_absmax(AbsmaxBatch& b, uint32_t jobs, hipStream_t s)
+{
+    const uint64_t bytes = b.tl.n * sizeof(typename Elem<DT>::scalar) * jobs;
+    return absmax_keeps<DT>(bytes, b.parts[0] != nullptr) ? run_absmax_loads<DT, true>(b, jobs, s)
+                                                          : run_absmax_loads<DT, false>(b, jobs, s);
 }
 
 // Waves of the streaming kernel: kStreamWaves on each of the 1,024 SIMDs.

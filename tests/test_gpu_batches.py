@@ -213,3 +213,53 @@ def test_workers_of_different_length_type_and_bucket():
     for w, (codes, steps) in enumerate(outs):
         assert np.array_equal(steps.cpu().numpy(), refs[w][1]), w
         assert codes.cpu().numpy().tobytes() == refs[w][0].tobytes(), w
+
+
+def _bucket_maxima(g, bucket):
+    g = g.float().abs()
+    if bucket == 0:
+        return g.max().reshape(1)
+    whole = g.numel() // bucket * bucket
+    parts = [g[:whole].view(-1, bucket).amax(1)] if whole else []
+    return torch.cat(parts + ([g[whole:].max().reshape(1)] if whole < g.numel() else []))
+
+
+# every form of the max-norm pass: an atomic per tile (under 16 tiles per bucket), per workgroup, a
+# workgroup with a bucket to itself (129 buckets on), a bucket longer than the vector; cached loads and
+# streaming ones (binary32 from 256 MB, bfloat16 from 32 MB on)
+@pytest.mark.parametrize("dtype,n,bucket", [
+    ("f32", 70001, 0), ("f32", 70001, 1 << 20), ("f32", 300007, 2048 * 15), ("f32", 128 * 32768, 32768),
+    ("f32", 129 * 32768 - 5, 32768), ("f32", 700 * 32768 + 1, 32768), ("f32", (1 << 26) + 5, 0),
+    ("f32", (1 << 26) + 5, 2048), ("bf16", 129 * 65536 + 9, 65536), ("bf16", (1 << 24) + 1, 0),
+    ("bf16", 300 * 65536 + 3, 65536), ("bf16", (1 << 24) + 1, 4096)])
+def test_max_norms_are_exact_in_every_form(dtype, n, bucket):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n)
+    g = torch.randn(n, device="cuda", generator=gen)
+    g = g.to(torch.bfloat16) if dtype == "bf16" else g
+    kappa = torch.full((ndq.ndq_num_buckets(n, bucket),), -1.0, device="cuda")
+    ndq.ndq_absmax(g, bucket, kappa)
+    assert torch.equal(kappa, _bucket_maxima(g, bucket))
+
+
+@pytest.mark.parametrize("dtype,W,n,bucket", [
+    ("f32", 16, 65 * 32768 + 77, 32768),      # more buckets in the batch than workgroups: one each
+    ("f32", 3, 4 * 32768 + 77, 32768),        # parts, reduced by a kernel of their own
+    ("bf16", 4, (1 << 22) + 9, 0),            # together above 32 MB: streaming loads
+    ("f32", 2, 101000003, 0)])                # together above 768 MiB
+def test_steps_of_a_batch_in_every_form_of_the_max_norm_pass(dtype, W, n, bucket):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n)
+    grads = [torch.randn(n, device="cuda", generator=gen) for _ in range(W)]
+    grads = [g.to(torch.bfloat16) if dtype == "bf16" else g for g in grads]
+    codes = [torch.empty(ndq.ndq_packed_bytes(n, 1), dtype=torch.uint8, device="cuda") for _ in grads]
+    steps = [torch.full((ndq.ndq_num_buckets(n, bucket),), -1.0, device="cuda") for _ in grads]
+    ndq.ndq_encode_workers([(grads[w], ndq.NDQ_WORKER_DQ, 2, 0, 1.0, ndq.ndq_dither(w, 3, w, 0), codes[w], steps[w],
+                             None) for w in range(W)], 0.0, bucket)
+    for w in range(W):       # two levels: Delta = 2 kappa, exactly
+        assert torch.equal(steps[w], 2.0 * _bucket_maxima(grads[w], bucket)), w
+    m = min(n, 1 << 20)      # the codes of the first elements
+    ref, _ = oracle.dq_encode(grads[W - 1][:m].float().cpu().numpy(), steps[W - 1][0].item(), 2, 0,
+                              oracle.dither(W - 1, 3, W - 1))
+    if bucket == 0:
+        assert codes[W - 1][:m // 8].cpu().numpy().tobytes() == ref[:m // 8].tobytes()
