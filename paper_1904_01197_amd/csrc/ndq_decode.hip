@@ -1010,13 +1010,20 @@ struct MeanArgs {
     uint32_t W;
     int continue_sum, finish;
     float scale;
+    uint32_t bucket_blocks, last_bucket;    // SMALL: 64-element blocks per bucket; index of the last bucket
 };
 typedef const __attribute__((address_space(4))) MeanArgs* MeanArgsPtr;
 
-// the words that hold a lane's four codes of every row (a ragged tail only counts its valid codes)
-template <bool FULL>
+// SMALL: buckets shorter than a tile.  The tiles then run over the whole vector, and a lane reads the
+// step of its own bucket for every row (its four elements lie in one: a bucket is a multiple of 64):
+// with a tile per bucket most lanes have nothing to do (buckets of 64, 11 M elements, one worker / four:
+// 67 / 196 us, so 16 / 42; buckets of 320, 30 M x 4: 134 / 108).
+//
+// the words that hold a lane's four codes of every row (a ragged tail only counts its valid codes), and the steps
+template <bool FULL, bool SMALL>
 __device__ __forceinline__ void mean_fetch(MeanArgsPtr a, uint32_t w, const TileRef& t, int lane,
-                                           uint64_t (&window)[kMeanRows], float& step)
+                                           const uint32_t (&bucket)[kMeanRows], uint64_t (&window)[kMeanRows],
+                                           float (&step)[kMeanRows])
 {
     const uint32_t bits = a->w[w].bits;
     const uint32_t* codes32 = (const uint32_t*)(a->w[w].codes + (t.start >> 3) * bits);
@@ -1031,13 +1038,25 @@ __device__ __forceinline__ void mean_fetch(MeanArgsPtr a, uint32_t w, const Tile
             if (sh + ncodes * bits > 32u) window[r] |= (uint64_t)codes32[word + 1] << 32;
         }
     }
-    step = a->w[w].steps[t.bucket];
+    const float* steps = a->w[w].steps;
+#pragma unroll
+    for (int r = 0; r < kMeanRows; ++r) step[r] = (SMALL || r == 0) ? steps[bucket[r]] : step[0];
 }
 
-template <bool FULL>
-__device__ __forceinline__ void mean_tile(MeanArgsPtr a, const TileRef& t, int lane)
+template <bool FULL, bool SMALL>
+__device__ __forceinline__ void mean_tile(MeanArgsPtr a, const TileRef& t, uint32_t tile_id, int lane)
 {
     const uint32_t W = a->W;
+    uint32_t bucket[kMeanRows];
+#pragma unroll
+    for (int r = 0; r < kMeanRows; ++r) {
+        if (!SMALL) {
+            bucket[r] = t.bucket;
+            continue;
+        }
+        const uint32_t b = (tile_id * (kMeanTile / 64u) + (uint32_t)(r * kWave + lane) / 16u) / a->bucket_blocks;
+        bucket[r] = FULL || b < a->last_bucket ? b : a->last_bucket;       // lanes past the end: any step will do
+    }
     float acc[kMeanRows][4];
 #pragma unroll
     for (int r = 0; r < kMeanRows; ++r)
@@ -1047,10 +1066,10 @@ __device__ __forceinline__ void mean_tile(MeanArgsPtr a, const TileRef& t, int l
             acc[r][k] = (a->continue_sum && (FULL || e < t.len)) ? a->out[t.start + e] : 0.0f;
         }
     uint64_t window[kMeanRows], ahead[kMeanRows];
-    float step, step_ahead = 0.0f;
-    mean_fetch<FULL>(a, 0u, t, lane, window, step);
+    float step[kMeanRows], step_ahead[kMeanRows] = {};
+    mean_fetch<FULL, SMALL>(a, 0u, t, lane, bucket, window, step);
     for (uint32_t w = 0; w < W; ++w) {
-        if (w + 1u < W) mean_fetch<FULL>(a, w + 1u, t, lane, ahead, step_ahead);
+        if (w + 1u < W) mean_fetch<FULL, SMALL>(a, w + 1u, t, lane, bucket, ahead, step_ahead);
         const DitherStream ds = {a->w[w].ds.key0, a->w[w].ds.key1, a->w[w].ds.step, a->w[w].ds.worker};
         const uint64_t quad0 = (a->w[w].index0 + t.start) >> 2;
         const uint32_t bits = a->w[w].bits;
@@ -1065,7 +1084,7 @@ __device__ __forceinline__ void mean_tile(MeanArgsPtr a, const TileRef& t, int l
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const uint32_t c = __builtin_amdgcn_ubfe(packed, k * bits, bits);
-                res[k] = index_value((float)((int32_t)c + q_min), step, v[k]);
+                res[k] = index_value((float)((int32_t)c + q_min), step[r], v[k]);
                 acc[r][k] = acc[r][k] + res[k];
             }
             if (FULL || o + 4u <= t.len) {
@@ -1077,8 +1096,7 @@ __device__ __forceinline__ void mean_tile(MeanArgsPtr a, const TileRef& t, int l
             }
         }
 #pragma unroll
-        for (int r = 0; r < kMeanRows; ++r) window[r] = ahead[r];
-        step = step_ahead;
+        for (int r = 0; r < kMeanRows; ++r) { window[r] = ahead[r]; step[r] = step_ahead[r]; }
     }
     float* out = a->out + t.start;
     const float scale = a->scale;
@@ -1099,6 +1117,7 @@ __device__ __forceinline__ void mean_tile(MeanArgsPtr a, const TileRef& t, int l
     }
 }
 
+template <bool SMALL>
 __global__ __launch_bounds__(kBlock) void decode_mean_kernel(MeanArgs by_value)
 {
     const MeanArgsPtr a = (MeanArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
@@ -1107,8 +1126,8 @@ __global__ __launch_bounds__(kBlock) void decode_mean_kernel(MeanArgs by_value)
     const uint32_t tile_id =
         blockIdx.x * kWavesPerBlock + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const TileRef t = locate_tile(tl, tile_id, kMeanTile);
-    if (t.len == kMeanTile) mean_tile<true>(a, t, lane);
-    else if (t.len != 0) mean_tile<false>(a, t, lane);
+    if (t.len == kMeanTile) mean_tile<true, SMALL>(a, t, tile_id, lane);
+    else if (t.len != 0) mean_tile<false, SMALL>(a, t, tile_id, lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -1345,8 +1364,15 @@ int ndq_decode_mean(const ndq_worker* workers, float* const* decoded, uint32_t W
     for (uint32_t p = 0; p < W; ++p)
         if (begin[p] != begin[p + 1u] && begin[p + 1u] - begin[p] < 4u * n) return NDQ_EINVAL;
     MeanArgs a;
-    const int rc = make_tiling(n, bucket, kMeanTile, &a.tl);
+    // (tiles of the whole vector: their 64-element blocks are numbered in 32 bits.  One worker alone is bound
+    // by its stores, and with three quarters of its lanes busy does no worse: 384 elements, 30 M 37.6 us
+    // against 43.5; two workers or more gain, four 116 -> 108)
+    const bool small = bucket != 0u && bucket < kMeanTile && (W > 1u || bucket < 384u) && n < ((uint64_t)1 << 37);
+    int rc = make_tiling(n, bucket, kMeanTile, &a.tl);
+    if (rc == NDQ_OK && small) rc = make_tiling(n, 0u, kMeanTile, &a.tl);
     if (rc != NDQ_OK) return rc;
+    a.bucket_blocks = small ? bucket / 64u : 1u;
+    a.last_bucket = small ? (uint32_t)((n + bucket - 1u) / bucket) - 1u : 0u;
     a.out = out;
     a.scale = scale;
     for (uint32_t p0 = 0; p0 < W; p0 += kMeanMax) {
@@ -1358,7 +1384,9 @@ int ndq_decode_mean(const ndq_worker* workers, float* const* decoded, uint32_t W
             a.w[j] = {(const unsigned char*)wk.codes, wk.steps, decoded[p0 + j], wk.dither.offset,
                       make_stream(&wk.dither), -(int32_t)(wk.levels_or_M / 2u), code_bits(wk.levels_or_M)};
         }
-        if (launch(decode_mean_kernel, dim3(blocks_for(a.tl.total_tiles)), dim3(kBlock), (hipStream_t)stream, a) != NDQ_OK)
+        const dim3 grid(blocks_for(a.tl.total_tiles)), block(kBlock);
+        if ((small ? launch(decode_mean_kernel<true>, grid, block, (hipStream_t)stream, a)
+                   : launch(decode_mean_kernel<false>, grid, block, (hipStream_t)stream, a)) != NDQ_OK)
             return NDQ_ELAUNCH;
     }
     return NDQ_OK;

@@ -167,7 +167,8 @@ def test_decode_mean_keeps_every_reconstruction_and_their_sum(W):
     # tile edges (512 elements), partial vectors of four, levels of every code width, more workers
     # than one launch holds; sums in the same order as the oracle's, so bit for bit
     levels = [3, 5, 16, 2, 100, 256, 9]
-    for n, bucket in ((1, 0), (511, 0), (513, 64), (2048 + 6, 512), (20000, 2112)):
+    for n, bucket in ((1, 0), (511, 0), (1, 64), (513, 64), (513, 320), (4097, 192), (20001, 448), (2048 + 6, 512),
+                      (20000, 2112), (1000, 1 << 20)):
         seeds = list(range(W))
         msgs, decoded = [], [torch.full((n,), 7.0, device="cuda") for _ in range(W)]
         host = _host(W, n, "f32", n)
