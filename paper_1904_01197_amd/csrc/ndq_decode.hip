@@ -1196,25 +1196,41 @@ static int decode_common(const void* codes, size_t n, uint32_t levels, uint32_t 
     return run_decode<kNestedAnyM>(a, n, bucket, acc, s);
 }
 
+// Tiles (of 1,024 elements) from which the persistent form of chain_stream_kernel is taken, for `slots`
+// wave slots.  With only a few tiles per wave a fixed share leaves SIMDs idle at the end; the hand-ordered fold makes
+// up for it the sooner the more there is to fold.  Persistent time over one tile per wave's, three
+// runs each, at 2.1 / 3.2 / 4.2 / 5.2 / 7.5 / 8.5 / 10.5 / 12.5 / 18 M elements:
+//   1 DQSG    0.98 0.95 0.94 0.90 0.75 0.73 0.68 0.75 0.70   bound by its stores (5.7 to 7.0 us up to 5.2 M)
+//   2 DQSG    1.21 1.11 1.16 1.08 0.95 0.96 0.80 0.95 0.79
+//   3 DQSG    1.22 1.11 1.18 1.12 1.12 1.06 1.02 0.98 0.93
+//   4 DQSG    1.15 1.03 1.13 1.14 1.08 1.03 0.99 0.99 0.94
+//   8 DQSG    1.04 0.99 1.04 1.06 1.00 0.98 0.96 0.96 0.94
+//   2 (1 nested) 1.22 1.11 1.23 1.16 1.10 1.06 1.04 1.07 1.07
+//   3 (2 nested) 1.16 1.07 1.15 1.12 1.05 1.04 1.01 1.01 0.96
+//   4 (3 nested) 1.10 1.03 1.08 1.07 1.03 1.01 0.96 0.96 0.94   (1-bit: 0.97 at 7.5 M)
+//   8 (7 nested) 1.02 0.97 0.99 0.97 0.95 0.92 0.91 0.92 0.90
+//   16 (15 nested) 0.96 0.92 0.93 0.94 0.90 0.90 0.88 0.89 0.87
+// Just above one tile per slot every plan takes it: a second round of one-tile waves would be
+// nearly empty (6.4 M: 0.82 to 1.00).
+static uint32_t persistent_from(uint32_t W, bool all_dq, uint32_t slots)
+{
+    if (W == 1u) return kShortTiles;
+    if (all_dq) return W == 2u || W >= 8u ? slots : slots / 2u * 3u;
+    return W <= 3u ? 2u * slots : W < 8u ? slots : kShortTiles;
+}
+
 template <int RMODE, int W0, int WR>
 static int launch_chain_stream(ChainArgs& a, hipStream_t s)
 {
-    // Long vectors: persistent waves, kChainStreamWaves on every SIMD, every wave with the same
-    // number of tiles (give or take one).  Otherwise one tile per wave: with only a few tiles
-    // per wave a fixed share would leave SIMDs idle at the end.
-    // Persistent waves, kChainStreamWaves on every SIMD, from one tile per wave slot on (6.3 M elements;
-    // measured there to 12 M, against one tile per wave: 1 worker 7.0-10.4 against 8.9-15.5 us,
-    // 4 nested 15-21 against 15-23, 16 nested 45-73 against 50-82; 4 and 8 DQSG between 6 % slower
-    // and 9 % faster).  From 2,048 tiles on for one worker, which is bound by its stores (4 M: 6.0
-    // against 6.7 us), and for eight or more nested ones (16: 29.8 against 31.8); the others are 0-11 %
-    // faster with one tile per wave there.
+    // Persistent waves, kChainStreamWaves on every SIMD, every wave with the same number of tiles (give or
+    // take one), or one tile per wave: see persistent_from.
     const uint32_t slots = 1024u * kChainStreamWaves;
     const uint32_t full = (uint32_t)(a.tl.n / kChainTile);
     const StreamTuning& tuning = stream_tuning();
     const bool persistent =
-        full != 0u && (full >= tuning.chain_min_tiles_per_wave * slots ||
-                       (!tuning.threshold_from_env && full >= kShortTiles &&
-                        (a.W == 1u || (a.W >= 8u && RMODE != kDq))));
+        full != 0u && (tuning.threshold_from_env ? full >= tuning.chain_min_tiles_per_wave * slots
+                                                 : full >= persistent_from(a.W, RMODE == kDq, slots) ||
+                                                       (full >= slots && full < slots + slots / 16u));
     const bool short_vector = !persistent && full < kShortTiles;
     const uint32_t tile = short_vector ? ChainStreamTile<kOneRow>::N : kChainTile;
     const uint32_t tiles = (uint32_t)(a.tl.n / tile);

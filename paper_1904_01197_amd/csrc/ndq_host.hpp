@@ -118,8 +118,9 @@ inline const StreamTuning& stream_tuning()
 {
     static const StreamTuning t = [] {
         // measured over vector lengths, each kernel in both forms in one run: the persistent bfloat16
-        // encoders win by 3-9 % from two tiles per wave slot on; the chain decoder: see launch_chain_stream
-        StreamTuning v = {2u, 1u, 0u, false};
+        // encoders win by 3-9 % from two tiles per wave slot on (the chain decoder's own rule, used unless the
+        // threshold comes from the environment, is persistent_from)
+        StreamTuning v = {2u, 0u, 0u, false};
         if (const char* e = getenv("NDQ_STREAM_MIN_TILES_PER_WAVE")) {
             v.enc_min_tiles_per_wave = v.chain_min_tiles_per_wave = (uint32_t)strtoul(e, nullptr, 10);
             v.threshold_from_env = true;

@@ -103,3 +103,23 @@ def test_the_mean_refuses_vectors_that_overlap_by_a_part(recorder, out, decoded,
     (rc, launches), = lr.record(recorder, [["ndq_decode_mean", workers, [base + x for x in decoded], len(decoded), 1000,
                                             0, 1.0, base + out, None]])
     assert rc == (0 if accepted else -1) and len(launches) == ((len(decoded) + 31) // 32 if accepted else 0)
+
+
+# form of the chain decoder: 0 persistent, 1 one tile (two rows) per wave, 2 one row per wave; lines in
+# tiles of 1,024 elements (6,144 wave slots), DQSG workers and nested ones
+@pytest.mark.parametrize("dq,nested,lines", [
+    (1, 0, [(2047, 2), (2048, 0)]), (2, 0, [(2047, 2), (2048, 1), (6143, 1), (6144, 0)]),
+    (3, 0, [(6143, 1), (6144, 0), (6527, 0), (6528, 1), (9215, 1), (9216, 0)]),
+    (7, 0, [(6528, 1), (9216, 0)]), (8, 0, [(6143, 1), (6144, 0), (7000, 0)]),
+    (1, 1, [(2048, 1), (6144, 0), (6528, 1), (12287, 1), (12288, 0)]), (1, 2, [(12287, 1), (12288, 0)]),
+    (1, 3, [(6143, 1), (6144, 0), (7000, 0)]), (1, 7, [(2047, 2), (2048, 0)]), (1, 31, [(2047, 2), (2048, 0)])])
+def test_form_of_the_chain_decoder(recorder, dq, nested, lines):
+    worker = {"codes": 0x20000000, "steps": 0x30000000, "kind": 0, "levels_or_M": 16, "alpha": 1.0,
+              "dither": [1, 2, 3, 0]}
+    workers = [worker] * dq + [dict(worker, kind=1, levels_or_M=4)] * nested
+    calls = [["ndq_decode_chain", workers, len(workers), 1024 * tiles + 1023, 0, 1.0, 0x40000000, None]
+             for tiles, _ in lines]
+    for (tiles, form), (rc, launches) in zip(lines, lr.record(recorder, calls)):
+        assert rc == 0 and len(launches) == 1
+        assert launches[0][0].startswith("_ZN3ndq19chain_stream_kernel"), launches
+        assert launches[0][0].endswith("ELi%dEEEvNS_9ChainArgsE" % form), (tiles, form, launches)
