@@ -20,6 +20,9 @@
 namespace {
 
 struct Library {
+    decltype(&ndq_code_bits) code_bits;
+    decltype(&ndq_packed_bytes) packed_bytes;
+    decltype(&ndq_num_buckets) num_buckets;
     decltype(&ndq_absmax) absmax;
     decltype(&ndq_dq_encode) dq_encode;
     decltype(&ndq_dq_encode_with_step) dq_encode_with_step;
@@ -44,17 +47,6 @@ Library lib = {};
 PyObject* dither_type = nullptr;       // ctypes mirror of ndq_dither
 PyObject* get_device = nullptr;        // torch's current device, and its current stream there
 PyObject* get_raw_stream = nullptr;
-
-// The size rules of the interface.
-uint32_t code_bits(uint32_t x)
-{
-    uint32_t b = 0;
-    if (x < 2u || x > 256u) return 0u;
-    while ((1u << b) < x) ++b;
-    return b;
-}
-size_t packed_bytes(size_t n, uint32_t bits) { return ((n * bits + 7u) / 8u + 15u) / 16u * 16u; }
-size_t num_buckets(size_t n, uint32_t bucket) { return bucket ? (n + bucket - 1u) / bucket : 1u; }
 
 struct Failed {};      // a Python exception is set
 
@@ -184,16 +176,16 @@ private:
 
 void check_outputs(size_t n, uint32_t bits, uint32_t bucket, const at::Tensor& codes, const at::Tensor& steps)
 {
-    if (codes.nbytes() < packed_bytes(n, bits)) fail(PyExc_ValueError, "codes_out too small");
-    if (count(steps) < num_buckets(n, bucket)) fail(PyExc_ValueError, "steps_out too small");
+    if (codes.nbytes() < lib.packed_bytes(n, bits)) fail(PyExc_ValueError, "codes_out too small");
+    if (count(steps) < lib.num_buckets(n, bucket)) fail(PyExc_ValueError, "steps_out too small");
 }
 
 // A worker's message must be as large as the call will read.
 void check_message(const at::Tensor& codes, const at::Tensor& steps, size_t n, uint32_t bits, uint32_t bucket)
 {
-    if (codes.nbytes() < packed_bytes(n, bits))
+    if (codes.nbytes() < lib.packed_bytes(n, bits))
         fail(PyExc_ValueError, "codes hold fewer than ndq_packed_bytes(n, bits) bytes");
-    if (!is_f32(steps) || count(steps) < num_buckets(n, bucket))
+    if (!is_f32(steps) || count(steps) < lib.num_buckets(n, bucket))
         fail(PyExc_ValueError, "steps must hold ndq_num_buckets(n, bucket) float32");
 }
 
@@ -279,7 +271,7 @@ NDQ_METHOD(dq_encode, 7)
     const float delta = real(v[1]);
     const uint32_t levels = (uint32_t)integer(v[2]), bucket = (uint32_t)integer(v[3]);
     const ndq_dither d = dither(v[4]);
-    check_outputs(n, code_bits(levels), bucket, codes, steps);
+    check_outputs(n, lib.code_bits(levels), bucket, codes, steps);
     void* s = current_stream();
     return status(lib.dq_encode, address(g), dt, n, delta, levels, bucket, &d, address(codes),
                   (float*)address(steps), s);
@@ -294,7 +286,7 @@ NDQ_METHOD(dq_encode_with_step, 6)
     const float* step_in = one_step(v[1]);
     const uint32_t levels = (uint32_t)integer(v[2]);
     const ndq_dither d = dither(v[3]);
-    check_outputs(n, code_bits(levels), 0u, codes, steps);
+    check_outputs(n, lib.code_bits(levels), 0u, codes, steps);
     void* s = current_stream();
     return status(lib.dq_encode_with_step, address(g), dt, n, step_in, levels, &d, address(codes),
                   (float*)address(steps), s);
@@ -309,7 +301,7 @@ NDQ_METHOD(nested_encode, 9)
     const float delta = real(v[1]), alpha = real(v[4]);
     const uint32_t levels = (uint32_t)integer(v[2]), M = (uint32_t)integer(v[3]), bucket = (uint32_t)integer(v[5]);
     const ndq_dither d = dither(v[6]);
-    check_outputs(n, code_bits(M), bucket, codes, steps);
+    check_outputs(n, lib.code_bits(M), bucket, codes, steps);
     void* s = current_stream();
     return status(lib.nested_encode, address(g), dt, n, delta, levels, M, alpha, bucket, &d, address(codes),
                   (float*)address(steps), s);
@@ -325,7 +317,7 @@ NDQ_METHOD(nested_encode_with_step, 7)
     const uint32_t M = (uint32_t)integer(v[2]);
     const float alpha = real(v[3]);
     const ndq_dither d = dither(v[4]);
-    check_outputs(n, code_bits(M), 0u, codes, steps);
+    check_outputs(n, lib.code_bits(M), 0u, codes, steps);
     void* s = current_stream();
     return status(lib.nested_encode_with_step, address(g), dt, n, step_in, M, alpha, &d, address(codes),
                   (float*)address(steps), s);
@@ -375,7 +367,7 @@ NDQ_METHOD(encode_workers, 3)
         const size_t n = count(g);
         const int dt = gradient_type(g);
         const uint32_t job_bucket = job.step_in ? 0u : bucket;
-        check_outputs(n, code_bits(job.kind == NDQ_WORKER_NESTED ? job.M : job.levels), job_bucket, codes, steps);
+        check_outputs(n, lib.code_bits(job.kind == NDQ_WORKER_NESTED ? job.M : job.levels), job_bucket, codes, steps);
         const EncodeCall* last = num_calls ? &calls[num_calls - 1u] : nullptr;
         if (!last || last->n != n || last->dt != dt || last->bucket != job_bucket || last->jobs == kMaxJobs)
             calls[num_calls++] = {w, 0u, n, dt, job_bucket};
@@ -392,7 +384,7 @@ NDQ_METHOD(dq_decode, 8)
     const uint32_t levels = (uint32_t)integer(v[2]), bucket = (uint32_t)integer(v[3]);
     const at::Tensor &codes = tensor(v[0], "codes"), &steps = tensor(v[4], "steps"), &out = tensor(v[6], "out");
     const ndq_dither d = dither(v[5]);
-    check_message(codes, steps, n, code_bits(levels), bucket);
+    check_message(codes, steps, n, lib.code_bits(levels), bucket);
     check_values(out, n, "out must hold n float32");
     const int add = truth(v[7]);
     void* s = current_stream();
@@ -406,7 +398,7 @@ NDQ_METHOD(dq_decode_half, 7)
     const size_t n = integer(v[1]);
     const uint32_t levels = (uint32_t)integer(v[2]), bucket = (uint32_t)integer(v[3]);
     const at::Tensor &codes = tensor(v[0], "codes"), &steps = tensor(v[4], "steps"), &out = tensor(v[5], "out");
-    check_message(codes, steps, n, code_bits(levels), bucket);
+    check_message(codes, steps, n, lib.code_bits(levels), bucket);
     check_values(out, n, "out must hold n float32");
     const int add = truth(v[6]);
     void* s = current_stream();
@@ -423,7 +415,7 @@ NDQ_METHOD(nested_decode, 11)
     const at::Tensor &codes = tensor(v[0], "codes"), &steps = tensor(v[5], "steps"), &side = tensor(v[7], "side"),
                      &out = tensor(v[9], "out");
     const ndq_dither d = dither(v[6]);
-    check_message(codes, steps, n, code_bits(M), bucket);
+    check_message(codes, steps, n, lib.code_bits(M), bucket);
     check_values(out, n, "out and side must hold n float32");
     check_values(side, n, "out and side must hold n float32");
     const int add = truth(v[10]);
@@ -463,7 +455,7 @@ ndq_worker worker_message(PyObject* entry, size_t n, uint32_t bucket)
     wk.levels_or_M = (uint32_t)integer(f[3]);
     wk.alpha = f.size() > 5u ? real(f[5]) : 1.0f;
     wk.dither = dither_or_fields(f[4]);
-    check_message(codes, steps, n, code_bits(wk.levels_or_M), bucket);
+    check_message(codes, steps, n, lib.code_bits(wk.levels_or_M), bucket);
     wk.codes = address(codes);
     wk.steps = (const float*)address(steps);
     return wk;
@@ -517,7 +509,7 @@ NDQ_METHOD(code_entropy, 5)
     const void* codes = nullptr;
     if (n) {
         const at::Tensor& t = tensor(v[0], "codes");
-        if (t.nbytes() < packed_bytes(n, bits))
+        if (t.nbytes() < lib.packed_bytes(n, bits))
             fail(PyExc_ValueError, "codes hold fewer than ndq_packed_bytes(n, bits) bytes");
         codes = address(t);
     }
@@ -544,7 +536,7 @@ NDQ_METHOD(dense_unpack, 4)
     const at::Tensor &in = tensor(v[0], "dense"), &out = tensor(v[3], "codes_out");
     const size_t n = integer(v[1]);
     const uint32_t levels = (uint32_t)integer(v[2]);
-    if (out.nbytes() < packed_bytes(n, code_bits(levels))) fail(PyExc_ValueError, "codes_out too small");
+    if (out.nbytes() < lib.packed_bytes(n, lib.code_bits(levels))) fail(PyExc_ValueError, "codes_out too small");
     void* s = current_stream();
     return status(lib.dense_unpack, address(in), n, levels, address(out), s);
 }
@@ -602,16 +594,19 @@ PyObject* bind(PyObject*, PyObject* const* v, Py_ssize_t n)
         return nullptr;
     }
     Library l = {};
-    if (!take(v[0], "ndq_absmax", &l.absmax) || !take(v[0], "ndq_dq_encode", &l.dq_encode) ||
+    if (!take(v[0], "ndq_code_bits", &l.code_bits) || !take(v[0], "ndq_packed_bytes", &l.packed_bytes) ||
+        !take(v[0], "ndq_num_buckets", &l.num_buckets) || !take(v[0], "ndq_absmax", &l.absmax) ||
+        !take(v[0], "ndq_dq_encode", &l.dq_encode) ||
         !take(v[0], "ndq_dq_encode_with_step", &l.dq_encode_with_step) ||
         !take(v[0], "ndq_nested_encode", &l.nested_encode) ||
         !take(v[0], "ndq_nested_encode_with_step", &l.nested_encode_with_step) ||
-        !take(v[0], "ndq_encode_workers", &l.encode_workers) || !take(v[0], "ndq_encode_check", &l.encode_check) || !take(v[0], "ndq_dq_decode", &l.dq_decode) ||
-        !take(v[0], "ndq_dq_decode_half", &l.dq_decode_half) || !take(v[0], "ndq_nested_decode", &l.nested_decode) ||
-        !take(v[0], "ndq_aggregate", &l.aggregate) || !take(v[0], "ndq_decode_chain", &l.decode_chain) ||
-        !take(v[0], "ndq_decode_mean", &l.decode_mean) || !take(v[0], "ndq_code_entropy", &l.code_entropy) || !take(v[0], "ndq_dense_pack", &l.dense_pack) ||
-        !take(v[0], "ndq_dense_unpack", &l.dense_unpack) || !take(v[0], "ndq_dense_bytes", &l.dense_bytes) || !take(v[0], "ndq_sqdiff", &l.sqdiff) ||
-        !take(v[0], "ndq_sqdiff_static", &l.sqdiff_static))
+        !take(v[0], "ndq_encode_workers", &l.encode_workers) || !take(v[0], "ndq_encode_check", &l.encode_check) ||
+        !take(v[0], "ndq_dq_decode", &l.dq_decode) || !take(v[0], "ndq_dq_decode_half", &l.dq_decode_half) ||
+        !take(v[0], "ndq_nested_decode", &l.nested_decode) || !take(v[0], "ndq_aggregate", &l.aggregate) ||
+        !take(v[0], "ndq_decode_chain", &l.decode_chain) || !take(v[0], "ndq_decode_mean", &l.decode_mean) ||
+        !take(v[0], "ndq_code_entropy", &l.code_entropy) || !take(v[0], "ndq_dense_pack", &l.dense_pack) ||
+        !take(v[0], "ndq_dense_unpack", &l.dense_unpack) || !take(v[0], "ndq_dense_bytes", &l.dense_bytes) ||
+        !take(v[0], "ndq_sqdiff", &l.sqdiff) || !take(v[0], "ndq_sqdiff_static", &l.sqdiff_static))
         return nullptr;
     Py_INCREF(v[1]); Py_XSETREF(dither_type, v[1]);
     Py_INCREF(v[2]); Py_XSETREF(get_device, v[2]);

@@ -148,6 +148,85 @@ def forms_of_a_message():
         pipeline.encode_all(empty, [], None, [])       # nobody to encode for: nothing happens
 
 
+def refusals():
+    """What the binding checks before the library is called: tensors on the device, contiguous, of the
+    right type and large enough (the library never learns their sizes)."""
+    d = ndq.ndq_dither(1, 1, 1, 0)
+    with FakeTensorMode():
+        n = 130                                                     # 130 codes of 2 bits: 33 bytes, so 48
+        g, c, s = torch.empty(n, device="cuda"), torch.empty(48, dtype=torch.uint8, device="cuda"), \
+            torch.empty(3, device="cuda")                           # three buckets of 64
+        o, e = torch.empty(n, device="cuda"), torch.empty(1, dtype=torch.float64, device="cuda")
+        host, strided = torch.empty(n), torch.empty(n, 2, device="cuda")[:, 0]
+        job = lambda g=g, c=c, s=s, step=None, d=d, M=4: (g, ndq.NDQ_WORKER_NESTED, 4, M, 1.0, d, c, s, step)
+        enc = lambda g=g, c=c, s=s, d=d: ndq.ndq_dq_encode(g, 0.0, 4, 64, d, c, s)
+        nes = lambda g=g, c=c, s=s, d=d: ndq.ndq_nested_encode(g, 0.0, 4, 4, 1.0, 64, d, c, s)
+        dec = lambda c=c, s=s, o=o, d=d: ndq.ndq_dq_decode(c, n, 4, 64, s, d, o)
+        half = lambda c=c, s=s, o=o: ndq.ndq_dq_decode_half(c, n, 4, 64, s, o)
+        ndec = lambda c=c, s=s, o=o, side=o, d=d: ndq.ndq_nested_decode(c, n, 4, 1.0, 64, s, d, side, 1.0, o)
+        msg = lambda c=c, s=s, d=d: (c, s, ndq.NDQ_WORKER_DQ, 4, d)
+        chain = lambda *m, o=o: ndq.ndq_decode_chain(list(m), n, 64, 1.0, o)
+        mean = lambda m, dec, o=o: ndq.ndq_decode_mean(m, dec, n, 64, 1.0, o)
+        workers = lambda *j: ndq.ndq_encode_workers(list(j), 0.0, 64)
+        small_c, small_s, small_o = c[:32], s[:2], o[:129]
+        cases = []
+        for f in (enc, nes, lambda **k: workers(job(**k))):
+            cases += [(TypeError, lambda f=f: f(g=host)), (TypeError, lambda f=f: f(g=strided)),
+                      (TypeError, lambda f=f: f(g=[1.0])), (TypeError, lambda f=f: f(g=g.double())),
+                      (TypeError, lambda f=f: f(c=c.cpu())), (TypeError, lambda f=f: f(s=s.cpu())),
+                      (ValueError, lambda f=f: f(c=small_c)), (ValueError, lambda f=f: f(s=small_s)),
+                      (TypeError, lambda f=f: f(d=(1, 1, 1, 0))), (TypeError, lambda f=f: f(d=None))]
+        for f in (dec, ndec, half, lambda **k: chain(msg(**{x: k[x] for x in k if x != "o"}), o=k.get("o", o)),
+                  lambda **k: mean([msg(**{x: k[x] for x in k if x != "o"})], [o], k.get("o", o)),
+                  lambda **k: mean([msg(**{x: k[x] for x in k if x != "o"})], [k.get("o", o)])):
+            cases += [(TypeError, lambda f=f: f(c=c.cpu())), (TypeError, lambda f=f: f(s=s.cpu())),
+                      (TypeError, lambda f=f: f(o=o.cpu())), (TypeError, lambda f=f: f(o=strided)),
+                      (ValueError, lambda f=f: f(c=small_c)), (ValueError, lambda f=f: f(s=small_s)),
+                      (ValueError, lambda f=f: f(s=s.double())), (ValueError, lambda f=f: f(o=small_o)),
+                      (ValueError, lambda f=f: f(o=o.double()))]
+            if f is not half:
+                cases.append((TypeError, lambda f=f: f(d=7)))
+        cases += [
+            (ValueError, lambda: workers()), (ValueError, lambda: workers(job()[:8])), (TypeError, lambda: workers(5)),
+            (ValueError, lambda: workers(job(step=s.double()))), (ValueError, lambda: workers(job(step=s[:0]))),
+            (ValueError, lambda: ndq.ndq_dq_encode_with_step(g, s.double(), 4, d, c, s)),
+            (ValueError, lambda: ndq.ndq_nested_encode_with_step(g, s[:0], 4, 1.0, d, c, s)),
+            (ValueError, lambda: ndq.ndq_nested_encode_with_step(g, s, 4, 1.0, d, small_c, s)),
+            (ValueError, lambda: ndec(side=small_o)), (ValueError, lambda: ndec(side=o.double())),
+            (TypeError, lambda: ndec(side=host)),
+            (ValueError, lambda: chain(msg()[:4])), (ValueError, lambda: chain(msg(), msg(c=small_c))),
+            (ValueError, lambda: mean([msg()], [])), (ValueError, lambda: mean([msg(), msg()], [o])),
+            (ValueError, lambda: ndq.ndq_dq_decode(c, n, 4, 64, s, d, None, True)),
+            (TypeError, lambda: ndq.ndq_absmax(host, 64, s)), (TypeError, lambda: ndq.ndq_absmax(g, 64, s.cpu())),
+            (TypeError, lambda: ndq.ndq_absmax(g.half(), 64, s)), (TypeError, lambda: ndq.ndq_absmax(g, 64.0, s)),
+            (ValueError, lambda: ndq.ndq_aggregate([g, g[:64]], 1.0, o)),
+            (ValueError, lambda: ndq.ndq_aggregate([g.double()], 1.0, o)),
+            (TypeError, lambda: ndq.ndq_aggregate([host], 1.0, o)), (TypeError, lambda: ndq.ndq_aggregate([g], "x", o)),
+            (ValueError, lambda: ndq.ndq_code_entropy(small_c, n, 2)),
+            (TypeError, lambda: ndq.ndq_code_entropy(c.cpu(), n, 2)),
+            (ValueError, lambda: ndq.ndq_dense_pack(c, n, 3, c[:8])),
+            (ValueError, lambda: ndq.ndq_dense_unpack(c, n, 3, small_c)),
+            (ValueError, lambda: ndq.ndq_sqdiff(g, o[:64], e, e)), (ValueError, lambda: ndq.ndq_sqdiff(g, e, e, e)),
+            (ValueError, lambda: ndq.ndq_sqdiff_static(g, o, s)), (ValueError, lambda: ndq.ndq_sqdiff_static(g, o, e[:0])),
+        ]
+        for i, (kind, call) in enumerate(cases):
+            try:
+                call()
+            except kind as error:
+                assert type(error) is kind, (i, error)
+                continue
+            raise AssertionError("case %d was not refused" % i)
+        # what passes these checks reaches the library, which refuses the null addresses of fake tensors
+        for call in (enc, nes, dec, half, ndec, lambda: chain(msg()), lambda: mean([msg()], [o]),
+                     lambda: workers(job())):
+            try:
+                call()
+            except ndq.NdqError as error:
+                assert error.rc == ndq.NDQ_EINVAL
+                continue
+            raise AssertionError("null addresses were accepted")
+
+
 if __name__ == "__main__":
-    {"messages": forms_of_a_message, "storage": tensors_without_storage, "refused": a_refused_job_among_several_calls}[sys.argv[1]]()
+    {"refusals": refusals, "messages": forms_of_a_message, "storage": tensors_without_storage, "refused": a_refused_job_among_several_calls}[sys.argv[1]]()
     print("BINDING_ERRORS_OK", flush=True)

@@ -24,3 +24,7 @@ def test_nothing_is_enqueued_when_one_of_several_calls_is_refused():
 
 def test_the_forms_of_a_workers_message():
     _run("messages")
+
+
+def test_tensors_of_the_wrong_kind_or_size_are_refused():
+    _run("refusals")
