@@ -233,28 +233,45 @@ def main():
     step_ms = sorted(step_marks[i].elapsed_time(step_marks[i + 1]) for i in range(len(step_marks) - 1))
     ms_per_step_event_median = step_ms[len(step_ms) // 2]
 
-    # ---- per-kernel durations, in place: events on the launch stream around
-    # every library call of the step, averaged over --kernel-reps further steps ----
+    # ---- per-kernel durations, in place: events on the launch stream around the step's launches,
+    # averaged over --kernel-reps further steps.  pipeline.encode_all is one library call, which makes one
+    # launch for all workers that share a quantizer: here such a group is a call of its own. ----
     bf16 = wl.dtype == "bf16"
     calls = []   # (kernel key, function, algorithmic bytes, algorithmic lane-ops)
+    groups = []  # workers of a kind, in the order of their first one
+    for w, entry in enumerate(wl.plan):
+        if entry not in [g[0] for g in groups]:
+            groups.append((entry, []))
+        next(g for g in groups if g[0] == entry)[1].append(w)
+
+    def encode_job(entry, src, w, codes, steps):
+        kind, arg = entry
+        return (dev[src], ndq.NDQ_WORKER_DQ if kind == "dq" else ndq.NDQ_WORKER_NESTED,
+                arg if kind == "dq" else wl.fine_levels, arg, 1.0, ds[w], codes, steps, None)
+
+    own_step = wl.bucket != 0 or preset == 0.0
+    for entry, members in groups:
+        kind, arg = entry
+        bits = ndq.ndq_code_bits(arg)
+        k = len(members)
+        jobs = [encode_job(entry, w, w, bufs.codes[w], bufs.steps[w]) for w in members]
+        enc_ops = OPS["nested_encode" if (kind != "dq" and arg & (arg - 1) == 0 and own_step) else "dq_encode"](bf16)
+        calls.append(("%s_encode_%s_b%d%s" % (kind, wl.dtype, bits, "_x%d" % k if k > 1 else ""),
+                      lambda jobs=jobs: ndq.ndq_encode_workers(jobs, preset, wl.bucket),
+                      k * algorithmic_bytes("encode", n, bits, K, s_in), tuple(k * n * x for x in enc_ops)))
+    # a step that is not preset and not found inside the encoder: two kernels of max-norm before it
+    max_norm_launches = 2 if wl.bucket == 0 and preset == 0.0 else 0
     count = 0
     chain_bytes, chain_ops = 4 * n, (0.0, 0.0)
     decs = []
     for w, (kind, arg) in enumerate(wl.plan):
         bits = ndq.ndq_code_bits(arg)
         if kind == "dq":
-            enc_key, enc = "dq_encode_%s_b%d" % (wl.dtype, bits), (
-                lambda w=w, arg=arg: ndq.ndq_dq_encode(dev[w], preset, arg, wl.bucket, ds[w],
-                                                       bufs.codes[w], bufs.steps[w]))
             dkind = "dq_decode_accumulate" if count > 0 else "dq_decode_store"
             dec_key, dec = "%s_b%d" % (dkind, bits), (
                 lambda w=w, arg=arg, c=count: ndq.ndq_dq_decode(
                     bufs.codes[w], n, arg, wl.bucket, bufs.steps[w], ds[w], bufs.total, c > 0))
         else:
-            enc_key, enc = "nested_encode_%s_b%d" % (wl.dtype, bits), (
-                lambda w=w, arg=arg: ndq.ndq_nested_encode(dev[w], preset, wl.fine_levels, arg,
-                                                           1.0, wl.bucket, ds[w], bufs.codes[w],
-                                                           bufs.steps[w]))
             dkind = "nested_decode"
             dec_key, dec = "nested_decode_inplace_b%d" % bits, (
                 lambda w=w, arg=arg, c=count: ndq.ndq_nested_decode(
@@ -264,10 +281,6 @@ def main():
         chain_bytes += (n * bits + 7) // 8 + 4 * K
         dec_ops = tuple(n * x for x in OPS[dkind](bf16))
         chain_ops = (chain_ops[0] + dec_ops[0], chain_ops[1] + dec_ops[1])
-        own_step = wl.bucket != 0 or preset == 0.0
-        enc_ops = tuple(n * x for x in OPS["nested_encode" if (kind != "dq" and arg & (arg - 1) == 0 and own_step)
-                                           else "dq_encode"](bf16))
-        calls.append((enc_key, enc, algorithmic_bytes("encode", n, bits, K, s_in), enc_ops))
         decs.append((dec_key, dec, algorithmic_bytes(dkind, n, bits, K, s_in), dec_ops))
     enc_bytes = sum(c[2] for c in calls)
     serial_bytes = enc_bytes + sum(d[2] for d in decs) + (8 * n if wl.out_scale != 1.0 else 0)
@@ -331,16 +344,14 @@ def main():
     alone_reps = max(4, min(args.kernel_reps, 24))
     for rec in kernels:
         group = [c for c in calls if c[0] == rec["kernel"]]
-        if rec["kernel"].startswith(("dq_encode", "nested_encode")):
-            w0 = next(w for w, c in enumerate(calls[:wl.W]) if c[0] == rec["kernel"])
-            arg = wl.plan[w0][1]
-            out_c, out_s = torch.empty_like(bufs.codes[w0]), torch.empty_like(bufs.steps[w0])
-            if wl.plan[w0][0] == "dq":
-                fns = [lambda w=w: ndq.ndq_dq_encode(dev[w], preset, arg, wl.bucket, ds[w0], out_c, out_s)
-                       for w in range(wl.W)]
-            else:
-                fns = [lambda w=w: ndq.ndq_nested_encode(dev[w], preset, wl.fine_levels, arg, 1.0, wl.bucket,
-                                                         ds[w0], out_c, out_s) for w in range(wl.W)]
+        at = next(i for i, c in enumerate(calls) if c[0] == rec["kernel"])
+        if at < len(groups):
+            entry, members = groups[at]
+            out_c = [torch.empty_like(bufs.codes[w]) for w in members]
+            out_s = [torch.empty_like(bufs.steps[w]) for w in members]
+            turns = [[encode_job(entry, (w + t) % wl.W, w, out_c[i], out_s[i]) for i, w in enumerate(members)]
+                     for t in range(wl.W)]
+            fns = [lambda jobs=jobs: ndq.ndq_encode_workers(jobs, preset, wl.bucket) for jobs in turns]
         else:
             fns = [c[1] for c in group]
         turn = [0]
@@ -555,7 +566,7 @@ def main():
         "scaling": "weak", "vs_baseline": None, "dtype": "f32", "data": "synthetic",
         "config": {"workload": wl.name, "W": wl.W, "n_per_worker": n, "input_dtype": wl.dtype,
                    "bucket": wl.bucket, "schedule": args.schedule, "hip_graph": bool(args.graph), "plan": ["%s%d" % p for p in wl.plan],
-                   "launches_per_step": sum(r["launches_per_step"] for r in kernels)},
+                   "launches_per_step": sum(r["launches_per_step"] for r in kernels) + max_norm_launches},
         "gelem_per_s": round(wl.W * n / (ms_per_step * 1e-3) / 1e9, 3),
         "step_algorithmic_bytes": step_bytes,
         "step_hbm_frac_of_peak": round(step_bytes / (ms_per_step * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
