@@ -13,8 +13,8 @@
  *
  * Conventions for every entry point
  *   - All data pointers are DEVICE pointers owned by the caller; `d` (the dither
- *     descriptor) and the pointer array of ndq_aggregate are HOST pointers, read
- *     before the call returns.
+ *     descriptor), the pointer arrays of ndq_aggregate and ndq_decode_mean and the arrays of
+ *     jobs and workers are HOST memory, read before the call returns.
  *   - The library never allocates, frees, retains or synchronises.  A call only
  *     enqueues kernels on `stream` (a hipStream_t passed as void*; NULL = the
  *     default stream) and returns.
@@ -22,9 +22,9 @@
  *     checked before anything is launched: with NDQ_EINVAL, NDQ_EALIGN or
  *     NDQ_EUNSUPPORTED nothing has been enqueued.  NDQ_ELAUNCH comes from the
  *     runtime's launch call itself; calls made of several kernels (a max-norm
- *     pass or a step copy before the encoder, ndq_code_entropy, ndq_sqdiff, more than 32 workers
- *     in ndq_decode_chain / ndq_aggregate) may then already have enqueued their
- *     first kernels, and the outputs are unspecified.  n == 0 is a successful no-op.
+ *     pass before the encoder, ndq_absmax, ndq_encode_workers, ndq_code_entropy, ndq_sqdiff, more than
+ *     32 workers in ndq_decode_chain / ndq_decode_mean / ndq_aggregate) may then already have enqueued
+ *     their first kernels, and the outputs are unspecified.  n == 0 is a successful no-op.
  *   - g, codes, out and side must be 16-byte aligned; steps 4-byte aligned.
  *     bucket must be 0 or a multiple of 64; d->offset a multiple of 8 (and of
  *     bucket when a slice of a bucketed vector is processed).

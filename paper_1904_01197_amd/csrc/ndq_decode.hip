@@ -436,7 +436,7 @@ constexpr int kChainStreamWaves = NDQ_CHAIN_STREAM_WAVES;
 // space, indexed by the loop variable (scalar loads, no copy of the arguments)
 typedef const __attribute__((address_space(4))) ChainArgs* ChainArgsPtr;
 
-// The forms of the kernel (launch_chain_stream has the rule): persistent waves with the
+// The forms of the kernel (persistent_from has the rule): persistent waves with the
 // hand-ordered fold, or one tile per wave -- of two rows, or of one where the vector is so short
 // that a wave's own latency is the launch's time (4 workers of 1 M elements: 5.6 us
 // against 6.4; 8: 7.3 against 8.4).
@@ -748,9 +748,9 @@ __device__ __forceinline__ void redo_out_of_range(ChainArgsPtr a, uint32_t first
 // therefore leaves through the wave's 4 KB of LDS as four stores of consecutive bytes.
 // (2) stream_fold_piped: the fold's instructions in a fixed order with the next row's Philox
 // block advanced in between.
-// It starts one extra Philox block per wave, which only a wave with many tiles amortises,
-// and the LDS round trip costs a one-tile wave more than the stores do, so launches of one
-// tile per wave keep the plain form.
+// It starts one extra Philox block per wave, which a wave with several tiles or many workers to
+// fold amortises, and the LDS round trip costs a one-tile wave more than the stores do: the one-tile
+// forms keep the plain fold, and persistent_from says from where on this one is taken.
 #ifndef NDQ_CHAIN_PIPED_WAVES
 #define NDQ_CHAIN_PIPED_WAVES NDQ_CHAIN_STREAM_WAVES
 #endif

@@ -545,7 +545,8 @@ __global__ __launch_bounds__(kBlock) void absmax_kernel(AbsmaxBatch by_value)
 // 18 and 27 us with 512, 1,024 and 1,365, which is the number that streams fastest), so an
 // encoder's pass stores its parts and absmax_finish_kernel reduces them; the parts
 // lie in the vector's code stream, which the encoder overwrites afterwards.
-// ndq_absmax has no such memory: few workgroups, one atomic each.
+// ndq_absmax has no such memory: few workgroups, one atomic each.  A workgroup with a bucket to itself
+// writes the word.
 template <int DT, bool KEEP>
 __global__ __launch_bounds__(kBlock) void absmax_span_kernel(AbsmaxBatch by_value)
 {
