@@ -1020,10 +1020,11 @@ typedef const __attribute__((address_space(4))) MeanArgs* MeanArgsPtr;
 // 67 / 196 us, so 16 / 42; buckets of 320, 30 M x 4: 134 / 108).
 //
 // the words that hold a lane's four codes of every row (a ragged tail only counts its valid codes), and the steps
+template <bool SMALL> struct MeanSteps { static constexpr int N = SMALL ? kMeanRows : 1; };    // per row, or one
 template <bool FULL, bool SMALL>
 __device__ __forceinline__ void mean_fetch(MeanArgsPtr a, uint32_t w, const TileRef& t, int lane,
-                                           const uint32_t (&bucket)[kMeanRows], uint64_t (&window)[kMeanRows],
-                                           float (&step)[kMeanRows])
+                                           const uint32_t (&bucket)[MeanSteps<SMALL>::N],
+                                           uint64_t (&window)[kMeanRows], float (&step)[MeanSteps<SMALL>::N])
 {
     const uint32_t bits = a->w[w].bits;
     const uint32_t* codes32 = (const uint32_t*)(a->w[w].codes + (t.start >> 3) * bits);
@@ -1038,24 +1039,24 @@ __device__ __forceinline__ void mean_fetch(MeanArgsPtr a, uint32_t w, const Tile
             if (sh + ncodes * bits > 32u) window[r] |= (uint64_t)codes32[word + 1] << 32;
         }
     }
-    const float* steps = a->w[w].steps;
 #pragma unroll
-    for (int r = 0; r < kMeanRows; ++r) step[r] = (SMALL || r == 0) ? steps[bucket[r]] : step[0];
+    for (int r = 0; r < MeanSteps<SMALL>::N; ++r) step[r] = a->w[w].steps[bucket[r]];
 }
 
 template <bool FULL, bool SMALL>
 __device__ __forceinline__ void mean_tile(MeanArgsPtr a, const TileRef& t, uint32_t tile_id, int lane)
 {
     const uint32_t W = a->W;
-    uint32_t bucket[kMeanRows];
+    constexpr int STEPS = MeanSteps<SMALL>::N;
+    uint32_t bucket[STEPS];
+    if constexpr (SMALL) {
 #pragma unroll
-    for (int r = 0; r < kMeanRows; ++r) {
-        if (!SMALL) {
-            bucket[r] = t.bucket;
-            continue;
+        for (int r = 0; r < STEPS; ++r) {
+            const uint32_t b = (tile_id * (kMeanTile / 64u) + (uint32_t)(r * kWave + lane) / 16u) / a->bucket_blocks;
+            bucket[r] = FULL || b < a->last_bucket ? b : a->last_bucket;       // lanes past the end: any step will do
         }
-        const uint32_t b = (tile_id * (kMeanTile / 64u) + (uint32_t)(r * kWave + lane) / 16u) / a->bucket_blocks;
-        bucket[r] = FULL || b < a->last_bucket ? b : a->last_bucket;       // lanes past the end: any step will do
+    } else {
+        bucket[0] = t.bucket;
     }
     float acc[kMeanRows][4];
 #pragma unroll
@@ -1066,7 +1067,7 @@ __device__ __forceinline__ void mean_tile(MeanArgsPtr a, const TileRef& t, uint3
             acc[r][k] = (a->continue_sum && (FULL || e < t.len)) ? a->out[t.start + e] : 0.0f;
         }
     uint64_t window[kMeanRows], ahead[kMeanRows];
-    float step[kMeanRows], step_ahead[kMeanRows] = {};
+    float step[STEPS], step_ahead[STEPS] = {};
     mean_fetch<FULL, SMALL>(a, 0u, t, lane, bucket, window, step);
     for (uint32_t w = 0; w < W; ++w) {
         if (w + 1u < W) mean_fetch<FULL, SMALL>(a, w + 1u, t, lane, bucket, ahead, step_ahead);
@@ -1084,7 +1085,7 @@ __device__ __forceinline__ void mean_tile(MeanArgsPtr a, const TileRef& t, uint3
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const uint32_t c = __builtin_amdgcn_ubfe(packed, k * bits, bits);
-                res[k] = index_value((float)((int32_t)c + q_min), step[r], v[k]);
+                res[k] = index_value((float)((int32_t)c + q_min), step[SMALL ? r : 0], v[k]);
                 acc[r][k] = acc[r][k] + res[k];
             }
             if (FULL || o + 4u <= t.len) {
@@ -1096,7 +1097,9 @@ __device__ __forceinline__ void mean_tile(MeanArgsPtr a, const TileRef& t, uint3
             }
         }
 #pragma unroll
-        for (int r = 0; r < kMeanRows; ++r) { window[r] = ahead[r]; step[r] = step_ahead[r]; }
+        for (int r = 0; r < kMeanRows; ++r) window[r] = ahead[r];
+#pragma unroll
+        for (int r = 0; r < STEPS; ++r) step[r] = step_ahead[r];
     }
     float* out = a->out + t.start;
     const float scale = a->scale;
