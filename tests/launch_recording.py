@@ -1,7 +1,7 @@
 """The launches a library call makes, recorded on the CPU (see launch_recorder.cpp).
 
-    with Recorder(tmp_path) as r:           # in the test: compiles the recorder
-        rc, launches = r.call("dq_encode", ...)
+    recorder = build(tmp_path)
+    (rc, launches), ... = record(recorder, [["ndq_dq_encode", arguments...], ...])
 
 The calls run in a process of their own, because the library of this process has long been
 bound to the real runtime; device pointers are plain numbers that nobody dereferences."""
@@ -12,7 +12,7 @@ import subprocess
 import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-LIBRARY = os.path.join(os.path.dirname(HERE), "paper_1904_01197_amd", "libndq.so")
+LIBRARY = os.environ.get("NDQ_LIBRARY", os.path.join(os.path.dirname(HERE), "paper_1904_01197_amd", "libndq.so"))
 
 
 class Dither(C.Structure):
