@@ -2,6 +2,7 @@
 source.  A workgroup's ticket says that its additions to the bins are done, and one thread's fence
 before the ticket waits for the additions of that thread's wave only (a barrier does not wait for
 atomics without a result): the first wave has to have made them all."""
+import os
 import re
 import subprocess
 
@@ -14,7 +15,7 @@ from paper_1904_01197_amd import build
 def kernels(tmp_path_factory):
     out = str(tmp_path_factory.mktemp("asm") / "tools.s")
     source = next(s for s in build.SOURCES if s.endswith("ndq_tools.hip"))
-    subprocess.check_call(["/opt/rocm/bin/hipcc"] + build.HIPCC_FLAGS +
+    subprocess.check_call([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")] + build.HIPCC_FLAGS +
                           ["-I", build.ROOT + "/include", "-I", build.CSRC, "--cuda-device-only", "-S", source,
                            "-o", out], stderr=subprocess.DEVNULL)
     text = open(out).read()
