@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 #include <utility>
 
 #include "ndq.h"
@@ -179,10 +180,9 @@ struct ChainWorker {
     uint32_t bits;
     uint32_t mode;        // Mode
     uint32_t first;       // S <- value instead of S + value
-    PhiloxUniform keys;   // chain_stream_kernel
 };
 
-struct ChainArgs {
+struct GeneralChainArgs {
     ChainWorker w[kChainMax];
     float* out;
     Tiling tl;
@@ -192,7 +192,6 @@ struct ChainArgs {
     float scale;
     uint32_t row_buckets; // 1: a bucket is one row of a tile (tiling is by tile, a step per row)
     uint32_t num_buckets; // with row_buckets: steps per worker (rows past them decode with step 0)
-    uint32_t tile_begin;  // chain_kernel: first tile of this launch; chain_stream_kernel: tiles it owns
 };
 
 // What is prefetched per worker and row: the step, and a lane's eight codes -- `bits` bytes of
@@ -208,7 +207,7 @@ template <int ROWS> struct ChainFetch {
 // load the stream's last eight bytes and shift (it has at least eight from a tile's start on:
 // its size is a multiple of 16 and a tile starts at a multiple of 8).
 template <bool FULL, bool ROWB, int ROWS>
-__device__ __forceinline__ void chain_fetch(const ChainArgs& a, const ChainWorker& cw, const TileRef& t,
+__device__ __forceinline__ void chain_fetch(const GeneralChainArgs& a, const ChainWorker& cw, const TileRef& t,
                                             int lane, ChainFetch<ROWS>& f)
 {
     const uint32_t bits = cw.bits;
@@ -337,7 +336,7 @@ __device__ __forceinline__ void chain_fold_width(const ChainWorker& cw, const Ch
 }
 
 template <bool FULL, bool ROWB, bool ANYM, int ROWS>
-__device__ __forceinline__ void chain_tile(const ChainArgs& a, const TileRef& t, int lane)
+__device__ __forceinline__ void chain_tile(const GeneralChainArgs& a, const TileRef& t, int lane)
 {
     float S[ROWS][8];
     float* out = a.out + t.start;
@@ -397,12 +396,12 @@ __device__ __forceinline__ void chain_tile(const ChainArgs& a, const TileRef& t,
 template <bool ROWB, bool ANYM, int ROWS>
 __global__ __launch_bounds__(kBlock)
 __attribute__((amdgpu_waves_per_eu(ANYM ? 4 : NDQ_CHAIN_WAVES_PER_EU)))
-void chain_kernel(ChainArgs a)
+void chain_kernel(GeneralChainArgs a)
 {
     constexpr uint32_t TILE = kWave * kLaneElems * ROWS;
     const int lane = threadIdx.x & (kWave - 1);
     const uint32_t tile_id =
-        a.tile_begin + blockIdx.x * kWavesPerBlock + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+        blockIdx.x * kWavesPerBlock + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const TileRef t = locate_tile(a.tl, tile_id, TILE);
     if (t.len == TILE && t.start + TILE + 64u <= a.tl.n) chain_tile<true, ROWB, ANYM, ROWS>(a, t, lane);
     else if (t.len != 0) chain_tile<false, ROWB, ANYM, ROWS>(a, t, lane);
@@ -432,9 +431,45 @@ void chain_kernel(ChainArgs a)
 #endif
 constexpr int kChainStreamWaves = NDQ_CHAIN_STREAM_WAVES;
 
-// per-worker parameters as the kernel reads them: through the constant address
-// space, indexed by the loop variable (scalar loads, no copy of the arguments)
+// Per-worker parameters as the kernel reads them: through the constant address space (scalar
+// loads, no copy of the arguments), with everything that does not depend on the tile worked out
+// by the host, and no more than that: a worker is 40 bytes.  A short launch waits for every cache line of its
+// arguments (16 workers of 65,536 elements: 11.1 us, with 112 bytes a worker 14.1), a long one spends
+// fewer vector instructions on addresses (4 x 2^27: 187 -> 182 us, 16 x 11.2 M: 66.6 -> 65, 8 DQSG workers of 25.6 M:
+// 57.5 -> 55, and the plain fold of the one-tile forms, which takes the same dither, 8 x 4.2 M: 15.2 -> 14.0).
+struct StreamWorker {
+    const unsigned char* codes;
+    uint32_t block;       // low word of the number of its first Philox block
+    uint32_t extra;       // nested: side_scale, 1/(workers folded in before it), as bits; DQSG: q_min
+    PhiloxUniform keys;
+};
+struct ChainArgs {
+    StreamWorker w[kChainMax];
+    const float* steps[kChainMax];
+    float* out;
+    uint64_t n;
+    uint64_t bucket_magic;    // bucket of tile t: t * bucket_magic >> bucket_shift (one bucket: 0)
+    uint32_t bucket_shift;
+    uint32_t tiles;           // whole tiles
+    uint32_t W;
+    int apply_scale;
+    float scale;
+};
+static_assert(sizeof(ChainArgs) <= 4096, "kernel arguments");
 typedef const __attribute__((address_space(4))) ChainArgs* ChainArgsPtr;
+typedef const __attribute__((address_space(4))) StreamWorker* StreamWorkerPtr;
+
+// t * magic >> shift is t / d for every t < 2^31: with l = ceil(log2 d) and magic =
+// ceil(2^(31 + l) / d) the excess of magic * d over 2^(31 + l) is at most 2^l.
+__device__ __forceinline__ uint32_t bucket_of(ChainArgsPtr a, uint32_t tile)
+{
+    return (uint32_t)((tile * a->bucket_magic) >> a->bucket_shift);
+}
+
+__device__ __forceinline__ PhiloxUniform uniform_keys(StreamWorkerPtr w)
+{
+    return {w->keys.c2, w->keys.c0, w->keys.c2b, w->keys.c3, w->keys.key0, w->keys.key1};
+}
 
 // The forms of the kernel (persistent_from has the rule): persistent waves with the
 // hand-ordered fold, or one tile per wave -- of two rows, or of one where the vector is so short
@@ -486,37 +521,45 @@ __device__ __forceinline__ void stream_fetch_ragged(const unsigned char* codes, 
     f.step = steps[bucket];
 }
 
+// `block`: low word of the number of the lane's first block (the high word is the same for the whole
+// call and part of the keys).
 template <int MODE, int WIDTH, bool FIRST, int ROWS>
-__device__ __forceinline__ void stream_fold(const DitherStream& ds, uint64_t block0, float q_min_f,
-                                            float side_scale, const ChainCodes<ROWS>& f, float step, float inv,
-                                            int lane, float (&S)[ROWS][8])
+__device__ __forceinline__ void stream_fold(const PhiloxUniform& keys, uint32_t block, uint32_t extra,
+                                            const ChainCodes<ROWS>& f, float step, float inv, float (&S)[ROWS][8])
 {
     constexpr int NF = WIDTH == 4 ? 4 : 8;
     // a power-of-two nesting ratio is 2^(code width): M and 1/M are compile-time constants
     constexpr float M_f = (float)(1u << WIDTH), inv_M_f = 1.0f / M_f;
     // DQSG: the code c itself, the index offset q_min going into the dither instead:
     // (c + q_min) - v and c - (v - q_min) are the same exact value rounded once, and
-    // v - q_min is exact for |q_min| <= 8 (code widths up to 4 bits).  Nested: m' = c / M.
-    const FieldScaled<NF> field((uint32_t)WIDTH, MODE == kDq ? 0u : (uint32_t)WIDTH);
+    // v - q_min is exact for |q_min| <= 8 (code widths up to 4 bits); raised by 64.5, the dither
+    // leaves c + 64.5 to subtract it from.  Nested: m' = c / M.
+    const FieldScaled<NF> field((uint32_t)WIDTH, MODE == kDq ? 0u : (uint32_t)WIDTH, MODE == kDq ? 64.5f : 0.0f);
+    const uint32_t dither_bits = MODE == kDq ? kDitherBits - (extra << 17) : kDitherBits;
+    const float side_scale = __uint_as_float(extra);
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) {
-        const uint32_t o = (uint32_t)(r * kWave + lane) * kLaneElems;
-        float v[8];
-        if (MODE == kDq) dither8_shifted(ds, block0 + (o >> 3), -q_min_f, v);
-        else dither8(ds, block0 + (o >> 3), v);
+        PhiloxFlight fl;
+        fl.start(keys, block + (uint32_t)(r * kWave));
+        fl.run();
+        uint32_t words[4];
+        fl.words(words);
         const uint32_t lo = f.w[r], hi = WIDTH == 4 ? f.w[r] >> 16 : f.w[r];
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
+            const float x = (k & 1) ? dither_raised<true>(words[k >> 1], dither_bits)
+                                    : dither_raised<false>(words[k >> 1], dither_bits);
             const float c_f = NF == 8 ? field.get(lo, k) : field.get(k < 4 ? lo : hi, k & 3);
             float val;
             if (MODE == kDq) {
-                val = index_value(c_f, step, v[k]);
+                val = step * (c_f - x);
             } else {
+                const float v = x - 64.5f;
                 const float y = S[r][k] * side_scale;
-                const float c = __builtin_fmaf(y, inv, v[k]);
+                const float c = __builtin_fmaf(y, inv, v);
                 const float kk = __builtin_rintf(__builtin_fmaf(c, inv_M_f, -c_f));
                 const float qs = kk + c_f;
-                const float centred = __builtin_fmaf(qs, M_f, -v[k]);
+                const float centred = __builtin_fmaf(qs, M_f, -v);
                 val = step * centred;
             }
             S[r][k] = FIRST ? val : S[r][k] + val;
@@ -530,7 +573,8 @@ __device__ __forceinline__ void stream_fold(const DitherStream& ds, uint64_t blo
 // multiply 4.6; round-to-integer, conversions, 16-bit multiply 4.2, and a binary32 operation
 // beside one of these is almost free unless it is a sub-dword (SDWA) form).  133
 // vector instructions per row and nested 1-bit worker, 143 before; 4 workers of 2^27
-// elements: 204 -> 188 us, 16 workers of 11.2 M: 76 -> 69 us, and no more register spills:
+// elements: 204 -> 188 us, 16 workers of 11.2 M: 76 -> 69 us, and no more register spills (with the worker's
+// parameters worked out by the host, see StreamWorker, 181 and 65):
 // - The dither goes through the mantissa: the bits of 64 + 2^-17 plus twice the cell are
 //   the float 64 + (cell + 1/2) 2^-16 (v_mad_u32_u16, which takes the low half of a word; the
 //   half-word conversions it replaces are SDWA), and an exact subtraction follows.  DQSG:
@@ -549,17 +593,6 @@ __device__ __forceinline__ void stream_fold(const DitherStream& ds, uint64_t blo
 __device__ __forceinline__ bool step_out_of_range(float step)
 {
     return step > 0x1p50f || (step < 0x1p-60f && step != 0.0f);
-}
-
-// Low word of the number of the Philox block of this lane's elements in the first row.
-__device__ __forceinline__ uint32_t block_low(uint64_t index0, uint64_t start, int lane)
-{
-    return (uint32_t)((index0 + start) >> 3) + (uint32_t)lane;
-}
-
-__device__ __forceinline__ PhiloxUniform uniform_keys(ChainArgsPtr a, uint32_t w)
-{
-    return {a->w[w].keys.c2, a->w[w].keys.c0, a->w[w].keys.c2b, a->w[w].keys.c3, a->w[w].keys.key0, a->w[w].keys.key1};
 }
 
 // The order of a row's instructions, made at compile time: element k runs through its
@@ -628,7 +661,7 @@ struct RowFold {
         constexpr uint32_t base = (150u - j * WIDTH - (MODE == kDq ? 0u : WIDTH)) << 23;
         if constexpr (op == 'm') fl.next_multiply();
         if constexpr (op == 'X') fl.next_xor();
-        if constexpr (op == 'x') x[k] = dither_raised((k & 1) ? words[k >> 1] >> 16 : words[k >> 1], dither_bits);
+        if constexpr (op == 'x') x[k] = dither_raised<(k & 1) != 0>(words[k >> 1], dither_bits);
         if constexpr (op == 'v') v[k] = x[k] - (BIT ? 64.5f * inv_M_f : 64.5f);
         if constexpr (op == 'a' && BIT) m[k] = __uint_as_float(code & (1u << (23 + k)));
         if constexpr (op == 'a' && !BIT)
@@ -650,19 +683,22 @@ struct RowFold {
 
 template <int MODE, int WIDTH, bool FIRST>
 __device__ __forceinline__ void fold_row_piped(const uint32_t (&words)[4], uint32_t code, float step, float inv,
-                                               float side_scale, int32_t q_min, float (&S)[8], PhiloxFlight& fl)
+                                               uint32_t extra, float (&S)[8], PhiloxFlight& fl)
 {
     using Fold = RowFold<MODE, WIDTH, FIRST>;
     // raised dither: v + 64 (DQSG: v - q_min + 64, so that c minus it is (c + q_min) - v; nested: divided by M)
-    const uint32_t dither_bits = MODE == kDq ? kDitherBits - ((uint32_t)q_min << 17)
+    const uint32_t dither_bits = MODE == kDq ? kDitherBits - (extra << 17)
                                              : Fold::BIT ? kDitherBits - ((uint32_t)WIDTH << 23) : kDitherBits;
-    Fold f = {words, Fold::BIT ? code << 23 : code, code >> 16, dither_bits, step, inv, side_scale, S, fl, {}, {}, {}, {}};
+    Fold f = {words, Fold::BIT ? code << 23 : code, code >> 16, dither_bits, step, inv, __uint_as_float(extra), S, fl,
+              {}, {}, {}, {}};
     f.run_all(std::make_integer_sequence<int, RowOrder<MODE, WIDTH, FIRST>::program.n>());
 }
 
+// Folds a worker's two rows.  While a row is folded the Philox block of the next one is on its
+// way: the second row's with this worker's keys, then the next worker's first with its keys.
 template <int MODE, int WIDTH, bool FIRST>
-__device__ __forceinline__ void stream_fold_piped(const PhiloxUniform& keys, uint32_t block0, const PhiloxUniform& keys_next,
-                                                  uint32_t block_next, int32_t q_min, float side_scale,
+__device__ __forceinline__ void stream_fold_piped(const PhiloxUniform& keys, uint32_t block, const PhiloxUniform& keys_next,
+                                                  uint32_t block_next, uint32_t extra,
                                                   const ChainCodes<kChainRows>& f, float step, float inv,
                                                   float (&S)[kChainRows][8], PhiloxFlight& fl)
 {
@@ -670,9 +706,9 @@ __device__ __forceinline__ void stream_fold_piped(const PhiloxUniform& keys, uin
     for (int r = 0; r < kChainRows; ++r) {
         uint32_t words[4];
         fl.words(words);
-        if (r + 1 < kChainRows) fl.start(keys, block0 + (uint32_t)((r + 1) * kWave));
+        if (r + 1 < kChainRows) fl.start(keys, block + (uint32_t)((r + 1) * kWave));
         else fl.start(keys_next, block_next);
-        fold_row_piped<MODE, WIDTH, FIRST>(words, f.w[r], step, inv, side_scale, q_min, S[r], fl);
+        fold_row_piped<MODE, WIDTH, FIRST>(words, f.w[r], step, inv, extra, S[r], fl);
     }
 }
 
@@ -682,22 +718,18 @@ __device__ __forceinline__ void stream_ragged_tile(ChainArgsPtr a, uint64_t star
                                                    int lane)
 {
     const uint32_t W = a->W;
+    const uint32_t block = (uint32_t)(start >> 3) + (uint32_t)lane;
     float S[ROWS][8];
     ChainCodes<ROWS> cur, nxt;
-    stream_fetch_ragged<W0, ROWS>(a->w[0].codes, a->w[0].steps, start, len, bucket, lane, cur);
+    stream_fetch_ragged<W0, ROWS>(a->w[0].codes, a->steps[0], start, len, bucket, lane, cur);
     nxt = cur;
-    if (W > 1u) stream_fetch_ragged<WR, ROWS>(a->w[1].codes, a->w[1].steps, start, len, bucket, lane, nxt);
-    {
-        const DitherStream ds = {a->w[0].ds.key0, a->w[0].ds.key1, a->w[0].ds.step, a->w[0].ds.worker};
-        stream_fold<kDq, W0, true, ROWS>(ds, (a->w[0].index0 + start) >> 3, (float)a->w[0].q_min, 0.0f, cur, cur.step,
-                                   inv_step(cur.step), lane, S);
-    }
+    if (W > 1u) stream_fetch_ragged<WR, ROWS>(a->w[1].codes, a->steps[1], start, len, bucket, lane, nxt);
+    stream_fold<kDq, W0, true, ROWS>(uniform_keys(&a->w[0]), a->w[0].block + block, a->w[0].extra, cur, cur.step, 0.0f, S);
     cur = nxt;
     for (uint32_t w = 1; w < W; ++w) {
-        if (w + 1u < W) stream_fetch_ragged<WR, ROWS>(a->w[w + 1u].codes, a->w[w + 1u].steps, start, len, bucket, lane, nxt);
-        const DitherStream ds = {a->w[w].ds.key0, a->w[w].ds.key1, a->w[w].ds.step, a->w[w].ds.worker};
-        stream_fold<RMODE, WR, false, ROWS>(ds, (a->w[w].index0 + start) >> 3, (float)a->w[w].q_min, a->w[w].side_scale,
-                                      cur, cur.step, inv_step(cur.step), lane, S);
+        if (w + 1u < W) stream_fetch_ragged<WR, ROWS>(a->w[w + 1u].codes, a->steps[w + 1u], start, len, bucket, lane, nxt);
+        stream_fold<RMODE, WR, false, ROWS>(uniform_keys(&a->w[w]), a->w[w].block + block, a->w[w].extra, cur, cur.step,
+                                            inv_step(cur.step), S);
         cur = nxt;
     }
     float* out = a->out + start;
@@ -718,14 +750,13 @@ template <int RMODE, int W0, int WR>
 __device__ __forceinline__ void redo_out_of_range(ChainArgsPtr a, uint32_t first, uint32_t stride,
                                                            uint32_t tiles_all, int lane)
 {
-    const uint32_t W = a->W, tpb = a->tl.tiles_per_bucket;
-    const bool one_bucket = a->tl.bucket_len == a->tl.n;
-    const float* my_steps = a->w[(uint32_t)lane < W ? (uint32_t)lane : W - 1u].steps;
+    const uint32_t W = a->W;
+    const float* my_steps = a->steps[(uint32_t)lane < W ? (uint32_t)lane : W - 1u];
     for (uint32_t tile = first; tile < tiles_all; tile += stride) {
-        const uint32_t bucket = one_bucket ? 0u : tile / tpb;
+        const uint32_t bucket = bucket_of(a, tile);
         if (__builtin_amdgcn_ballot_w64(step_out_of_range(my_steps[bucket])) == 0) continue;
         const uint64_t start = (uint64_t)tile * kChainTile;
-        const uint64_t left = a->tl.n - start;
+        const uint64_t left = a->n - start;
         stream_ragged_tile<RMODE, W0, WR, kChainRows>(a, start, left < kChainTile ? (uint32_t)left : kChainTile, bucket,
                                                       lane);
     }
@@ -772,11 +803,9 @@ void chain_stream_kernel(ChainArgs a_by_value)
     const uint32_t first = blockIdx.x * kWavesPerBlock + wave_in_block;
     __shared__ __align__(16) float out_stage_all[PIPED ? kWavesPerBlock : 1][PIPED ? TILE : 4];
     float* out_stage = out_stage_all[PIPED ? wave_in_block : 0u];
-    const uint32_t tiles = a->tile_begin;                  // whole tiles: ids 0 .. tiles-1
+    const uint32_t tiles = a->tiles;                       // whole tiles: ids 0 .. tiles-1
     const uint32_t tiles_all = TAIL ? tiles + 1u : tiles;  // TAIL: and the ragged one, id `tiles`
     const uint32_t W = a->W;
-    const uint32_t tpb = a->tl.tiles_per_bucket;
-    const bool one_bucket = a->tl.bucket_len == a->tl.n;   // bucket == 0
     float* out_base = a->out;
     const float scale = a->scale;
     const bool apply_scale = __builtin_amdgcn_readfirstlane(a->apply_scale) != 0;
@@ -784,16 +813,16 @@ void chain_stream_kernel(ChainArgs a_by_value)
     // (one tile per wave), else to wave 0: at the start every SIMD is full and hides its
     // latencies; as a kernel of its own, or at the end, it would run alone at a fifth of the rate.
     const uint64_t whole = (uint64_t)tiles * TILE;
-    if (RAGGED && !PIPED && whole < a->tl.n && first == (stride > tiles ? tiles : 0u))
-        stream_ragged_tile<RMODE, W0, WR, ROWS>(a, whole, (uint32_t)(a->tl.n - whole), one_bucket ? 0u : tiles / tpb, lane);
+    if (RAGGED && !PIPED && whole < a->n && first == (stride > tiles ? tiles : 0u))
+        stream_ragged_tile<RMODE, W0, WR, ROWS>(a, whole, (uint32_t)(a->n - whole), bucket_of(a, tiles), lane);
     if (first >= tiles_all) return;
     const uint32_t my_tiles = (tiles_all - first + stride - 1u) / stride;
     // TAIL: elements of the ragged tile, and per code width the last byte offset inside its
     // codes that a lane may read: the stream is padded to a multiple of 16 bytes, the tile
     // starts at one, so at least 16 bytes of it exist
-    const uint32_t tail_len = TAIL ? (uint32_t)(a->tl.n - whole) : 0u;
+    const uint32_t tail_len = TAIL ? (uint32_t)(a->n - whole) : 0u;
     auto tail_limit = [&](uint32_t width) __attribute__((always_inline)) {
-        const uint64_t total = ((((uint64_t)a->tl.n * width + 7u) >> 3) + 15u) & ~(uint64_t)15u;
+        const uint64_t total = ((((uint64_t)a->n * width + 7u) >> 3) + 15u) & ~(uint64_t)15u;
         return (uint32_t)(total - (whole >> 3) * width) - width;
     };
     const uint32_t limit0 = TAIL ? tail_limit((uint32_t)W0) : 0xFFFFFFFFu;
@@ -801,35 +830,36 @@ void chain_stream_kernel(ChainArgs a_by_value)
     auto limit_for = [&](uint32_t tile_id, uint32_t tail) __attribute__((always_inline)) {
         return (TAIL && tile_id == tiles) ? tail : 0xFFFFFFFFu;
     };
+    // a wave's priority (see the end of the loop) steps down at these numbers of tiles done
+    const uint32_t lower2 = (my_tiles + 3u) / 4u, lower1 = (my_tiles + 1u) / 2u, lower0 = (3u * my_tiles + 3u) / 4u;
     uint32_t done = 0;
     if (my_tiles > 1u) __builtin_amdgcn_s_setprio(3);
 
+    const StreamWorkerPtr first_worker = &a->w[0], end_worker = &a->w[W];
     ChainCodes<ROWS> cur;
-    stream_fetch<W0, ROWS>(a->w[0].codes, (uint64_t)first * TILE, lane, cur, limit_for(first, limit0));
+    stream_fetch<W0, ROWS>(first_worker->codes, (uint64_t)first * TILE, lane, cur, limit_for(first, limit0));
     // PIPED: the dither of the row after the current one is always in flight; here the first row's
+    PhiloxUniform keys = uniform_keys(first_worker);
     PhiloxFlight fl;
     if (PIPED) {
-        fl.start(uniform_keys(a, 0u), block_low(a->w[0].index0, (uint64_t)first * TILE, lane));
+        fl.start(keys, first_worker->block + first * (TILE / kLaneElems) + (uint32_t)lane);
         fl.run();
     }
     // Lane w looks after worker w's step: one load and ONE correctly rounded division per tile
     // for all workers (at most 32, one per lane), instead of one per worker in every lane; a
     // worker's step and reciprocal are then read from its lane into scalar registers.
-    const uint32_t my_worker = (uint32_t)lane < W ? (uint32_t)lane : W - 1u;
-    const float* my_steps = a->w[my_worker].steps;
-    float steps_ahead = my_steps[one_bucket ? 0u : first / tpb];
+    const float* my_steps = a->steps[(uint32_t)lane < W ? (uint32_t)lane : W - 1u];
+    float steps_ahead = my_steps[bucket_of(a, first)];
     bool out_of_range = false;
     for (uint32_t tile = first; tile < tiles_all; tile += stride) {
         const uint64_t start = (uint64_t)tile * TILE;
-        // where the dither after this tile's last row belongs: past the end after the last tile (unused)
-        const uint64_t next_start = start + (uint64_t)stride * TILE;
+        // the wave's next tile (after the last one: this one again, unused)
+        const uint32_t next = tile + stride < tiles_all ? tile + stride : tile;
+        const uint32_t block_here = tile * (TILE / kLaneElems) + (uint32_t)lane;
+        const uint32_t block_ahead = next * (TILE / kLaneElems) + (uint32_t)lane;
         float S[ROWS][8];
-        ChainCodes<ROWS> nxt;
         const float steps_here = steps_ahead;
-        {
-            const uint32_t nt = tile + stride < tiles_all ? tile + stride : tile;
-            steps_ahead = my_steps[one_bucket ? 0u : nt / tpb];
-        }
+        steps_ahead = my_steps[bucket_of(a, next)];
         float invs_here = inv_step(steps_here), scaled_here = steps_here;
         if (SCALED) {
             invs_here = invs_here * kInvM;
@@ -839,55 +869,30 @@ void chain_stream_kernel(ChainArgs a_by_value)
         auto from_lane = [](float x, uint32_t w) __attribute__((always_inline)) {
             return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(x), (int)w));
         };
-        // first worker: DQSG, starts the sum; meanwhile the second worker's codes (or the next tile's)
-        if (W > 1u) {
-            stream_fetch<WR, ROWS>(a->w[1].codes, start, lane, nxt, limit_for(tile, limitr));
-        } else {
-            const uint32_t nt = tile + stride < tiles_all ? tile + stride : tile;
-            ChainCodes<ROWS> tmp;
-            stream_fetch<W0, ROWS>(a->w[0].codes, (uint64_t)nt * TILE, lane, tmp, limit_for(nt, limit0));
-            nxt = tmp;
-        }
-        {
-            if constexpr (PIPED) {
-                const uint32_t wn = W > 1u ? 1u : 0u;
-                stream_fold_piped<kDq, W0, true>(
-                    uniform_keys(a, 0u), block_low(a->w[0].index0, start, lane), uniform_keys(a, wn),
-                    block_low(a->w[wn].index0, W > 1u ? start : next_start, lane), a->w[0].q_min, 0.0f, cur,
-                    from_lane(steps_here, 0u), 0.0f, S, fl);
-            } else {
-                const DitherStream ds = {a->w[0].ds.key0, a->w[0].ds.key1, a->w[0].ds.step, a->w[0].ds.worker};
-                stream_fold<kDq, W0, true, ROWS>(ds, (a->w[0].index0 + start) >> 3, (float)a->w[0].q_min, 0.0f, cur,
-                                           from_lane(steps_here, 0u), 0.0f, lane, S);
-            }
-        }
-        cur = nxt;
-        for (uint32_t w = 1; w < W; ++w) {
-            // the codes of worker w are in `cur`; fetch worker w+1's, or the first worker's of the next tile
-            if (w + 1u < W) {
-                stream_fetch<WR, ROWS>(a->w[w + 1u].codes, start, lane, nxt, limit_for(tile, limitr));
-            } else {
-                const uint32_t nt = tile + stride < tiles_all ? tile + stride : tile;
-                ChainCodes<ROWS> tmp;
-                stream_fetch<W0, ROWS>(a->w[0].codes, (uint64_t)nt * TILE, lane, tmp, limit_for(nt, limit0));
-                nxt = tmp;
-            }
-            if constexpr (PIPED) {
-                const bool last = w + 1u == W;
-                const uint32_t wn = last ? 0u : w + 1u;
-                const uint32_t here = block_low(a->w[w].index0, start, lane);
-                const uint32_t next = block_low(a->w[wn].index0, last ? next_start : start, lane);
-                stream_fold_piped<RMODE, WR, false>(uniform_keys(a, w), here, uniform_keys(a, wn), next, a->w[w].q_min,
-                                                    a->w[w].side_scale, cur, from_lane(scaled_here, w),
-                                                    from_lane(invs_here, w), S, fl);
-            } else {
-                const DitherStream ds = {a->w[w].ds.key0, a->w[w].ds.key1, a->w[w].ds.step, a->w[w].ds.worker};
-                stream_fold<RMODE, WR, false, ROWS>(ds, (a->w[w].index0 + start) >> 3, (float)a->w[w].q_min,
-                                              a->w[w].side_scale, cur, from_lane(steps_here, w),
-                                              from_lane(invs_here, w), lane, S);
-            }
+        // Folds worker `w`, whose codes are in `cur`, and fetches the next worker's, or the first
+        // worker's of the next tile.
+        auto fold = [&](auto mode, auto width, auto is_first, StreamWorkerPtr w, uint32_t index)
+            __attribute__((always_inline)) {
+            constexpr int MODE = decltype(mode)::value, WIDTH = decltype(width)::value;
+            constexpr bool FIRST = decltype(is_first)::value;
+            const bool last = w + 1 == end_worker;
+            const StreamWorkerPtr wn = last ? first_worker : w + 1;
+            const PhiloxUniform keys_next = uniform_keys(wn);
+            const uint32_t extra = w->extra, here = w->block + block_here, ahead = wn->block + (last ? block_ahead : block_here);
+            const unsigned char* codes_next = wn->codes;
+            ChainCodes<ROWS> nxt;
+            if (last) stream_fetch<W0, ROWS>(codes_next, (uint64_t)next * TILE, lane, nxt, limit_for(next, limit0));
+            else stream_fetch<WR, ROWS>(codes_next, start, lane, nxt, limit_for(tile, limitr));
+            const float step = from_lane(FIRST ? steps_here : scaled_here, index), inv = FIRST ? 0.0f : from_lane(invs_here, index);
+            if constexpr (PIPED) stream_fold_piped<MODE, WIDTH, FIRST>(keys, here, keys_next, ahead, extra, cur, step, inv, S, fl);
+            else stream_fold<MODE, WIDTH, FIRST, ROWS>(keys, here, extra, cur, step, inv, S);
+            keys = keys_next;
             cur = nxt;
-        }
+        };
+        fold(std::integral_constant<int, kDq>{}, std::integral_constant<int, W0>{}, std::true_type{}, first_worker, 0u);
+        uint32_t index = 1u;
+        for (StreamWorkerPtr w = first_worker + 1; w != end_worker; ++w, ++index)
+            fold(std::integral_constant<int, RMODE>{}, std::integral_constant<int, WR>{}, std::false_type{}, w, index);
         float* out = out_base + start;
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) {
@@ -931,10 +936,9 @@ void chain_stream_kernel(ChainArgs a_by_value)
         // the arbiter serves the oldest wave of a SIMD first: lower a wave's priority as it
         // gets ahead, so that the waves of a SIMD finish together
         ++done;
-        const uint32_t quarter = my_tiles > 1u ? 4u * done / my_tiles : 0u;
-        if (quarter == 1u) __builtin_amdgcn_s_setprio(2);
-        else if (quarter == 2u) __builtin_amdgcn_s_setprio(1);
-        else if (quarter >= 3u) __builtin_amdgcn_s_setprio(0);
+        if (done == lower0) __builtin_amdgcn_s_setprio(0);
+        else if (done == lower1) __builtin_amdgcn_s_setprio(1);
+        else if (done == lower2) __builtin_amdgcn_s_setprio(2);
     }
     if (SCALED && __builtin_amdgcn_ballot_w64(out_of_range) != 0)
         redo_out_of_range<RMODE, W0, WR>(a, first, stride, tiles_all, lane);
@@ -1223,12 +1227,12 @@ static uint32_t persistent_from(uint32_t W, bool all_dq, uint32_t slots)
 }
 
 template <int RMODE, int W0, int WR>
-static int launch_chain_stream(ChainArgs& a, hipStream_t s)
+static int launch_chain_stream(ChainArgs& a, uint64_t bucket_len, hipStream_t s)
 {
     // Persistent waves, kChainStreamWaves on every SIMD, every wave with the same number of tiles (give or
     // take one), or one tile per wave: see persistent_from.
     const uint32_t slots = 1024u * kChainStreamWaves;
-    const uint32_t full = (uint32_t)(a.tl.n / kChainTile);
+    const uint32_t full = (uint32_t)(a.n / kChainTile);
     const StreamTuning& tuning = stream_tuning();
     const bool persistent =
         full != 0u && (tuning.threshold_from_env ? full >= tuning.chain_min_tiles_per_wave * slots
@@ -1236,11 +1240,16 @@ static int launch_chain_stream(ChainArgs& a, hipStream_t s)
                                                        (full >= slots && full < slots + slots / 16u));
     const bool short_vector = !persistent && full < kShortTiles;
     const uint32_t tile = short_vector ? ChainStreamTile<kOneRow>::N : kChainTile;
-    const uint32_t tiles = (uint32_t)(a.tl.n / tile);
+    const uint32_t tiles = (uint32_t)(a.n / tile);
     if (tiles == 0u) return 1;
-    a.tile_begin = tiles;
-    if (a.tl.bucket_len != a.tl.n) a.tl.tiles_per_bucket = (uint32_t)(a.tl.bucket_len / tile);
-    const bool ragged = (uint64_t)tiles * tile < a.tl.n;     // one more wave takes the ragged last tile
+    a.tiles = tiles;
+    // (see bucket_of; a bucket is a multiple of the tile.  A tile's number times the magic stays below 2^63)
+    const uint64_t per_bucket = bucket_len / tile;
+    uint32_t log2 = 0u;
+    while (((uint64_t)1 << log2) < per_bucket) ++log2;
+    a.bucket_shift = 31u + log2;
+    a.bucket_magic = bucket_len == a.n ? 0u : (((uint64_t)1 << a.bucket_shift) + per_bucket - 1u) / per_bucket;
+    const bool ragged = (uint64_t)tiles * tile < a.n;     // one more wave takes the ragged last tile
     const uint32_t all = tiles + (ragged ? 1u : 0u);
     const dim3 grid(persistent ? persistent_blocks(all, 1024u * NDQ_CHAIN_PIPED_WAVES) : blocks_for(all)), block(kBlock);
     if (persistent)
@@ -1254,16 +1263,16 @@ static int launch_chain_stream(ChainArgs& a, hipStream_t s)
 }
 
 template <int RMODE, int W0>
-static int launch_chain_stream_w(ChainArgs& a, uint32_t wr, hipStream_t s)
+static int launch_chain_stream_w(ChainArgs& a, uint64_t bucket_len, uint32_t wr, hipStream_t s)
 {
-    if (wr == 1u) return launch_chain_stream<RMODE, W0, 1>(a, s);
-    if (wr == 2u) return launch_chain_stream<RMODE, W0, 2>(a, s);
-    return launch_chain_stream<RMODE, W0, 4>(a, s);
+    if (wr == 1u) return launch_chain_stream<RMODE, W0, 1>(a, bucket_len, s);
+    if (wr == 2u) return launch_chain_stream<RMODE, W0, 2>(a, bucket_len, s);
+    return launch_chain_stream<RMODE, W0, 4>(a, bucket_len, s);
 }
 
 // Runs the streaming kernel when the plan and the tiling allow it; returns 1 when it
 // does not apply.
-static int try_chain_stream(ChainArgs a, uint32_t bucket, hipStream_t s)
+static int try_chain_stream(const GeneralChainArgs& a, uint32_t bucket, hipStream_t s)
 {
     if (a.row_buckets || a.continue_sum) return 1;
     if (!(bucket == 0u || bucket % kChainTile == 0u)) return 1;
@@ -1281,17 +1290,31 @@ static int try_chain_stream(ChainArgs a, uint32_t bucket, hipStream_t s)
     // the high word of the dither's block number is the same for the whole call (it changes every 2^35 elements)
     for (uint32_t j = 0; j < a.W; ++j)
         if ((a.w[j].index0 >> 35) != ((a.w[j].index0 + a.tl.n - 1u) >> 35)) return 1;
-    ChainArgs b = a;
-    int rc;
-    if (rmode == kDq) {
-        rc = w0 == 1u ? launch_chain_stream_w<kDq, 1>(b, wr, s) : w0 == 2u ? launch_chain_stream_w<kDq, 2>(b, wr, s)
-                                                                            : launch_chain_stream_w<kDq, 4>(b, wr, s);
-    } else {
-        rc = w0 == 1u ? launch_chain_stream_w<kNestedPow2, 1>(b, wr, s)
-                      : w0 == 2u ? launch_chain_stream_w<kNestedPow2, 2>(b, wr, s)
-                                 : launch_chain_stream_w<kNestedPow2, 4>(b, wr, s);
+    ChainArgs b;
+    for (uint32_t j = 0; j < a.W; ++j) {
+        const ChainWorker& cw = a.w[j];
+        StreamWorker& sw = b.w[j];
+        sw.codes = cw.codes;
+        sw.block = (uint32_t)(cw.index0 >> 3);
+        sw.extra = (uint32_t)cw.q_min;
+        if (cw.mode != kDq) __builtin_memcpy(&sw.extra, &cw.side_scale, 4);
+        sw.keys = philox_uniform(cw.ds, (uint32_t)(cw.index0 >> 35));
+        b.steps[j] = cw.steps;
     }
-    return rc;
+    b.out = a.out;
+    b.n = a.tl.n;
+    b.W = a.W;
+    b.apply_scale = a.apply_scale;
+    b.scale = a.scale;
+    // (a bucket that holds the whole vector is no different from none)
+    const uint64_t bucket_len = bucket != 0u && bucket < b.n ? bucket : b.n;
+    if (rmode == kDq)
+        return w0 == 1u ? launch_chain_stream_w<kDq, 1>(b, bucket_len, wr, s)
+                        : w0 == 2u ? launch_chain_stream_w<kDq, 2>(b, bucket_len, wr, s)
+                                   : launch_chain_stream_w<kDq, 4>(b, bucket_len, wr, s);
+    return w0 == 1u ? launch_chain_stream_w<kNestedPow2, 1>(b, bucket_len, wr, s)
+                    : w0 == 2u ? launch_chain_stream_w<kNestedPow2, 2>(b, bucket_len, wr, s)
+                               : launch_chain_stream_w<kNestedPow2, 4>(b, bucket_len, wr, s);
 }
 
 }  // namespace ndq
@@ -1433,7 +1456,7 @@ int ndq_decode_chain(const ndq_worker* workers, uint32_t W, size_t n, uint32_t b
         if (!aligned16(wk.codes) || !aligned4(wk.steps) || (wk.dither.offset & 7u) != 0u)
             return NDQ_EALIGN;
     }
-    ChainArgs a;
+    GeneralChainArgs a;
     // buckets of exactly one row share a tile, each row with its own step
     a.row_buckets = (kChainRows > 1 && bucket == kWave * kLaneElems) ? 1u : 0u;
     a.num_buckets = a.row_buckets ? (uint32_t)ndq_num_buckets(n, bucket) : 0u;   // n < 2^40: fits
@@ -1470,12 +1493,10 @@ int ndq_decode_chain(const ndq_worker* workers, uint32_t W, size_t n, uint32_t b
                               : (!is_pow2(wk.levels_or_M) ? kNestedAnyM
                                  : (wk.alpha == 1.0f ? kNestedPow2 : kNestedPow2Shrink));
             cw.first = (p0 + j) == 0u;
-            cw.keys = philox_uniform(cw.ds, (uint32_t)((cw.index0 >> 3) >> 32));
         }
         bool any_m = false;
         for (uint32_t j = 0; j < a.W; ++j) any_m = any_m || a.w[j].mode == kNestedAnyM;
         hipStream_t hs = (hipStream_t)stream;
-        a.tile_begin = 0u;
 #ifndef NDQ_NO_STREAM_CHAIN
         if (W <= kChainMax) {
             const int rc_stream = try_chain_stream(a, bucket, hs);

@@ -80,11 +80,13 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
 // What the ten rounds of a block do with wave-uniform operands only, done once on the host:
 // the second counter pair (step, worker) and the high word of the block number are the same
 // for a whole call (see the caller), so the first round has one multiply and one xor that
-// depend on the lane, the second round one multiply and two xors.
+// depend on the lane, the second round one multiply and two xors.  (The keys of the later rounds are
+// advanced by scalar additions, which cost nothing beside the vector instructions; reading them
+// instead makes a worker two cache lines, and a short launch waits for each line of its arguments.)
 struct PhiloxUniform {
     uint32_t c2;          // first round:  c2 = high(p0) ^ this
     uint32_t c0, c2b;     // second round: c0 = high(p1) ^ c0, c2 = c3 ^ c2b
-    uint32_t c3;          // third round:  c2 = high(p0) ^ c3
+    uint32_t c3;          // third round:  c2 = high(p0) ^ c3 (the round's second key is part of it)
     uint32_t key0, key1;  // keys of the third round
 };
 
@@ -110,13 +112,11 @@ struct PhiloxFlight {
     uint32_t c0, c1, c2, c3;
     uint64_t p0, p1;
     PhiloxUniform u;
-    uint32_t k0, k1;
     int muls, xors;       // pieces done: known at compile time once everything is unrolled
     __device__ __forceinline__ void start(const PhiloxUniform& uniform, uint32_t block_low)
     {
         u = uniform;
         c0 = block_low;
-        k0 = u.key0; k1 = u.key1;
         muls = 0; xors = 0;
     }
     // the 32x32->64 multiply as the one instruction it is (left to the compiler it becomes a
@@ -138,12 +138,11 @@ struct PhiloxFlight {
         if (xors == 0) { c2 = (uint32_t)(p0 >> 32) ^ u.c2; c3 = (uint32_t)p0; }
         else if (xors == 1) { c0 = (uint32_t)(p1 >> 32) ^ u.c0; c1 = (uint32_t)p1; }
         else if (xors == 2) c2 = c3 ^ u.c2b;
-        else if (xors == 4) { c2 = (uint32_t)(p0 >> 32) ^ u.c3; c3 = (uint32_t)p0; next_round(); }
-        else if ((xors & 1) != 0) { c0 = xor3((uint32_t)(p1 >> 32), c1, k0); c1 = (uint32_t)p1; }
-        else { c2 = xor3((uint32_t)(p0 >> 32), c3, k1); c3 = (uint32_t)p0; next_round(); }
+        else if (xors == 4) { c2 = (uint32_t)(p0 >> 32) ^ u.c3; c3 = (uint32_t)p0; }
+        else if ((xors & 1) != 0) { c0 = xor3((uint32_t)(p1 >> 32), c1, u.key0 + (uint32_t)((xors - 3) >> 1) * 0x9E3779B9u); c1 = (uint32_t)p1; }
+        else { c2 = xor3((uint32_t)(p0 >> 32), c3, u.key1 + (uint32_t)((xors - 4) >> 1) * 0xBB67AE85u); c3 = (uint32_t)p0; }
         ++xors;
     }
-    __device__ __forceinline__ void next_round() { k0 += 0x9E3779B9u; k1 += 0xBB67AE85u; }
     __device__ __forceinline__ void run()
     {
         next_multiply(); next_xor();
@@ -156,12 +155,14 @@ struct PhiloxFlight {
 
 // The bits of 64 + 2^-17 plus twice a 16-bit dither cell are the float 64 + (cell + 1/2) 2^-16,
 // i.e. the unit dither + 64.5 (other `bits`: another integer in place of 64, or all of it
-// divided by a power of two).  v_mad_u32_u16 takes the low half of `word`.
+// divided by a power of two).  v_mad_u32_u16 takes the low half of a word (its op_sel form,
+// which takes the high one, is slower than the shift: 4 workers of 2^27 elements 190 against 185 us, 16 of 11.2 M 75 / 67).
 constexpr uint32_t kDitherBits = 0x42800001u;
+template <bool HIGH>
 __device__ __forceinline__ float dither_raised(uint32_t word, uint32_t bits)
 {
     uint32_t x;
-    asm("v_mad_u32_u16 %0, %1, 2, %2" : "=v"(x) : "v"(word), "s"(bits));
+    asm("v_mad_u32_u16 %0, %1, 2, %2" : "=v"(x) : "v"(HIGH ? word >> 16 : word), "s"(bits));
     return __uint_as_float(x);
 }
 
@@ -183,24 +184,6 @@ __device__ __forceinline__ void dither8(const DitherStream& s, uint64_t block, f
     for (int w = 0; w < 4; ++w) {
         v[2 * w] = unit_dither(r[w] & 0xFFFFu);
         v[2 * w + 1] = unit_dither(r[w] >> 16);
-    }
-}
-
-// The same plus an integer `shift` with |shift| <= 8: v + shift needs at most 21
-// significant bits, so the one fma that forms it is as exact as unit_dither's.
-__device__ __forceinline__ float unit_dither_shifted(uint32_t cell, float centre)   // centre = shift - 1/2 + 2^-17
-{
-    return __builtin_fmaf((float)cell, 0x1p-16f, centre);
-}
-__device__ __forceinline__ void dither8_shifted(const DitherStream& s, uint64_t block, float shift, float (&v)[8])
-{
-    uint32_t r[4];
-    philox4x32_10((uint32_t)block, (uint32_t)(block >> 32), s.step, s.worker, s.key0, s.key1, r);
-    const float centre = shift + (-0.5f + 0x1p-17f);
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-        v[2 * w] = unit_dither_shifted(r[w] & 0xFFFFu, centre);
-        v[2 * w + 1] = unit_dither_shifted(r[w] >> 16, centre);
     }
 }
 
