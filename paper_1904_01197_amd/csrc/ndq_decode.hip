@@ -239,22 +239,22 @@ __device__ __forceinline__ void chain_fetch(const GeneralChainArgs& a, const Cha
     }
 }
 
-// One row of eight elements of one worker: next = S + (this worker's decoded
+// N elements of one worker: next = S + (this worker's decoded
 // values), the side information being S scaled.  Returns whether any element's
 // fast quotient was too close to a rounding tie to be trusted (see Div).
-template <int MODE, bool FIRST, int DIV>
-__device__ __forceinline__ bool chain_row(const ChainWorker& cw, const Quant& qp, const float (&c_f)[8],
-                                          const float (&v)[8], float step, float inv,
-                                          const float (&S)[8], float (&next)[8])
+template <int MODE, bool FIRST, int DIV, int N>
+__device__ __forceinline__ bool chain_row(float side_scale, const Quant& qp, const float (&c_f)[N],
+                                          const float (&v)[N], float step, float inv,
+                                          const float (&S)[N], float (&next)[N])
 {
     bool near_tie = false;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
+    for (int k = 0; k < N; ++k) {
         float q, yk = 0.0f;
         if (MODE == kDq) {
             q = c_f[k];
         } else {
-            yk = S[k] * cw.side_scale;
+            yk = S[k] * side_scale;
             q = coset_index_f<MODE, DIV>(c_f[k], yk, inv, v[k], qp, near_tie);
         }
         const float val = shrink<MODE>(index_value(q, step, v[k]), yk, qp);
@@ -296,9 +296,9 @@ __device__ __forceinline__ void chain_fold(const ChainWorker& cw, const ChainFet
                 else c_f[k] = (float)__builtin_amdgcn_ubfe(half[k >> 2], (k & 3) * bits, bits);
             }
             float next[8];
-            const bool near_tie = chain_row<MODE, FIRST, kDivFast>(cw, qp, c_f, v, step, inv, S[r], next);
+            const bool near_tie = chain_row<MODE, FIRST, kDivFast>(cw.side_scale, qp, c_f, v, step, inv, S[r], next);
             if (__builtin_amdgcn_ballot_w64(near_tie) != 0)
-                chain_row<MODE, FIRST, kDivExact>(cw, qp, c_f, v, step, inv, S[r], next);
+                chain_row<MODE, FIRST, kDivExact>(cw.side_scale, qp, c_f, v, step, inv, S[r], next);
 #pragma unroll
             for (int k = 0; k < 8; ++k) S[r][k] = next[k];
         } else {
@@ -405,6 +405,141 @@ void chain_kernel(GeneralChainArgs a)
     const TileRef t = locate_tile(a.tl, tile_id, TILE);
     if (t.len == TILE && t.start + TILE + 64u <= a.tl.n) chain_tile<true, ROWB, ANYM, ROWS>(a, t, lane);
     else if (t.len != 0) chain_tile<false, ROWB, ANYM, ROWS>(a, t, lane);
+}
+
+// ---------------------------------------------------------------------------
+// Chain decoder for short vectors, any plan.  A wave that folds one worker after the other waits, for
+// each of them, for its arguments, its codes and forty dependent instructions of Philox: a launch of few
+// waves takes W times that, however short the vector.  Here a workgroup takes one row (512 elements) and
+// its four waves first do, side by side, all that does not depend on the running sum -- the workers' Philox
+// blocks (a wave takes every fourth worker), codes, steps and reciprocals -- and leave it in LDS;
+// then a lane folds the workers into two elements, about ten dependent operations each.
+// Twice the instructions of the other forms per element, so only as long as the chip is not full
+// (short_chain_most has the lines).  WMAX: workers the workgroup's LDS holds.
+// ---------------------------------------------------------------------------
+typedef const __attribute__((address_space(4))) GeneralChainArgs* GeneralChainArgsPtr;
+constexpr uint32_t kShortTile = kWave * kLaneElems;
+constexpr uint32_t kShortSteps = kShortTile / 64u;       // buckets a tile can meet: multiples of 64 elements
+constexpr uint32_t kShortCodeWords = kShortTile / 4u;    // 32-bit words of a tile's codes, 8 bits each
+
+template <int MODE, bool FIRST>
+__device__ __forceinline__ void short_fold(float side_scale, const Quant& qp, const float (&c_f)[2], const float (&v)[2],
+                                           float step, float inv, float (&S)[2])
+{
+    float next[2];
+    const bool near_tie = chain_row<MODE, FIRST, kDivFast>(side_scale, qp, c_f, v, step, inv, S, next);
+    if (MODE == kNestedAnyM && __builtin_amdgcn_ballot_w64(near_tie) != 0)
+        chain_row<MODE, FIRST, kDivExact>(side_scale, qp, c_f, v, step, inv, S, next);
+    S[0] = next[0];
+    S[1] = next[1];
+}
+
+template <uint32_t WMAX>
+__global__ __launch_bounds__(kBlock) void chain_short_kernel(GeneralChainArgs by_value)
+{
+    const GeneralChainArgsPtr a = (GeneralChainArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
+    __shared__ __align__(16) uint32_t words_of[WMAX][kBlock];            // Philox words: two elements each
+    __shared__ uint32_t codes_of[WMAX][kShortCodeWords + 4u];            // (a window may reach one word further)
+    __shared__ float step_of[WMAX][kShortSteps], inv_of[WMAX][kShortSteps];
+    constexpr uint32_t MINE = WMAX / kWavesPerBlock;                     // workers a wave prepares
+    const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1u);
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const uint32_t W = a->W, n = (uint32_t)a->tl.n;
+    const uint32_t start = blockIdx.x * kShortTile;
+    const uint32_t bucket_len = a->tl.bucket_len < n ? (uint32_t)a->tl.bucket_len : n;
+    const uint32_t bucket0 = start / bucket_len;
+
+    // lane w holds worker w's parameters: one wait for all of them instead of one per worker
+    const uint32_t mine = lane < W ? lane : 0u;
+    const uint64_t codes_at = (uint64_t)a->w[mine].codes, index0 = a->w[mine].index0;
+    const uint32_t key0 = a->w[mine].ds.key0, key1 = a->w[mine].ds.key1;
+    const uint32_t iteration = a->w[mine].ds.step, number = a->w[mine].ds.worker;
+    const uint32_t bits_of = a->w[mine].bits, mode_of = a->w[mine].mode;
+    const int32_t q_min_of = a->w[mine].q_min;
+    const float M_of = a->w[mine].M_f, inv_M_of = a->w[mine].inv_M_f, alpha_of = a->w[mine].alpha;
+    const float beta_of = a->w[mine].beta, side_of = a->w[mine].side_scale;
+    auto from = [](uint32_t x, uint32_t w) __attribute__((always_inline)) {
+        return (uint32_t)__builtin_amdgcn_readlane((int)x, (int)w);
+    };
+    auto from_f = [&](float x, uint32_t w) __attribute__((always_inline)) {
+        return __uint_as_float(from(__float_as_uint(x), w));
+    };
+
+    // codes: the tile's share of every stream as aligned words, up to the stream's padded end
+    uint32_t code[MINE][2];
+#pragma unroll
+    for (uint32_t i = 0; i < MINE; ++i) {
+        const uint32_t w = i * kWavesPerBlock + wave;
+        code[i][0] = code[i][1] = 0u;
+        if (w < W) {
+            const uint32_t bits = from(bits_of, w);
+            const uint32_t total = ((n * (uint64_t)bits + 7u) / 8u + 15u) / 16u * 16u, byte0 = start / 8u * bits;
+            const uint64_t at = ((uint64_t)from((uint32_t)(codes_at >> 32), w) << 32 | from((uint32_t)codes_at, w)) + byte0;
+            const uint32_t* p = (const uint32_t*)at;
+            const uint32_t share = kShortTile / 32u * bits, left = (total - byte0) / 4u;
+            const uint32_t have = share < left ? share : left;
+            if (lane < have) code[i][0] = p[lane];
+            if (lane + kWave < have) code[i][1] = p[lane + kWave];
+        }
+    }
+    if (tid < W * kShortSteps) {
+        const uint32_t w = tid / kShortSteps, j = tid % kShortSteps, bucket = bucket0 + j;
+        const uint32_t buckets = (n + bucket_len - 1u) / bucket_len;
+        const float step = a->w[w].steps[bucket < buckets ? bucket : buckets - 1u];
+        step_of[w][j] = step;
+        inv_of[w][j] = a->w[w].alpha * inv_step(step);
+    }
+#pragma unroll
+    for (uint32_t i = 0; i < MINE; ++i) {
+        const uint32_t w = i * kWavesPerBlock + wave;
+        if (w < W) {
+            const uint64_t block = (((uint64_t)from((uint32_t)(index0 >> 32), w) << 32 | from((uint32_t)index0, w)) + start) / 8u + lane;
+            uint32_t r[4];
+            philox4x32_10((uint32_t)block, (uint32_t)(block >> 32), from(iteration, w), from(number, w), from(key0, w),
+                          from(key1, w), r);
+            *(uint4*)&words_of[w][lane * 4u] = make_uint4(r[0], r[1], r[2], r[3]);
+            codes_of[w][lane] = code[i][0];
+            codes_of[w][lane + kWave] = code[i][1];
+        }
+    }
+    __syncthreads();
+
+    const uint32_t element = start + 2u * tid;
+    const uint32_t my_bucket = (element < n ? element : n - 1u) / bucket_len - bucket0;
+    float S[2] = {0.0f, 0.0f};
+    for (uint32_t w = 0; w < W; ++w) {
+        const uint32_t bits = from(bits_of, w), mode = from(mode_of, w);
+        const uint32_t bit = 2u * tid * bits;
+        const uint32_t window = __builtin_amdgcn_alignbit(codes_of[w][bit / 32u + 1u], codes_of[w][bit / 32u], bit & 31u);
+        const uint32_t word = words_of[w][tid];
+        const float step = step_of[w][my_bucket], inv = inv_of[w][my_bucket];
+        const float v[2] = {unit_dither(word & 0xFFFFu), unit_dither(word >> 16)};
+        const uint32_t c0 = __builtin_amdgcn_ubfe(window, 0u, bits), c1 = __builtin_amdgcn_ubfe(window, bits, bits);
+        Quant qp;
+        qp.M_f = from_f(M_of, w);
+        qp.inv_M_f = from_f(inv_M_of, w);
+        qp.alpha = from_f(alpha_of, w);
+        qp.beta = from_f(beta_of, w);
+        const float side = from_f(side_of, w);
+        if (mode == kDq) {
+            const int32_t q_min = (int32_t)from((uint32_t)q_min_of, w);
+            const float c_f[2] = {(float)((int32_t)c0 + q_min), (float)((int32_t)c1 + q_min)};
+            if (w == 0u) short_fold<kDq, true>(side, qp, c_f, v, step, inv, S);
+            else short_fold<kDq, false>(side, qp, c_f, v, step, inv, S);
+        } else {
+            const float c_f[2] = {(float)c0, (float)c1};
+            if (mode == kNestedPow2) short_fold<kNestedPow2, false>(side, qp, c_f, v, step, inv, S);
+            else if (mode == kNestedPow2Shrink) short_fold<kNestedPow2Shrink, false>(side, qp, c_f, v, step, inv, S);
+            else short_fold<kNestedAnyM, false>(side, qp, c_f, v, step, inv, S);
+        }
+    }
+    if (a->apply_scale) {
+        S[0] = a->scale * S[0];
+        S[1] = a->scale * S[1];
+    }
+    float* out = a->out;
+    if (element + 1u < n) *(float2*)(out + element) = make_float2(S[0], S[1]);
+    else if (element < n) out[element] = S[0];
 }
 
 // ---------------------------------------------------------------------------
@@ -1270,26 +1405,34 @@ static int launch_chain_stream_w(ChainArgs& a, uint64_t bucket_len, uint32_t wr,
     return launch_chain_stream<RMODE, W0, 4>(a, bucket_len, s);
 }
 
-// Runs the streaming kernel when the plan and the tiling allow it; returns 1 when it
-// does not apply.
-static int try_chain_stream(const GeneralChainArgs& a, uint32_t bucket, hipStream_t s)
+// Whether the streaming kernel has the plan and the tiling; *rmode and *wr are the mode and the code width of
+// the workers after the first.
+static bool chain_streams(const GeneralChainArgs& a, uint32_t bucket, uint32_t* rmode, uint32_t* wr)
 {
-    if (a.row_buckets || a.continue_sum) return 1;
-    if (!(bucket == 0u || bucket % kChainTile == 0u)) return 1;
+    if (a.row_buckets || a.continue_sum) return false;
+    if (!(bucket == 0u || bucket % kChainTile == 0u)) return false;
     const uint32_t w0 = a.w[0].bits;
-    if (a.w[0].mode != kDq || !(w0 == 1u || w0 == 2u || w0 == 4u)) return 1;
-    uint32_t rmode = kDq, wr = w0;
+    if (a.w[0].mode != kDq || !(w0 == 1u || w0 == 2u || w0 == 4u)) return false;
+    *rmode = kDq;
+    *wr = w0;
     if (a.W > 1u) {
-        rmode = a.w[1].mode;
-        wr = a.w[1].bits;
-        if (rmode != kDq && rmode != kNestedPow2) return 1;
-        if (!(wr == 1u || wr == 2u || wr == 4u)) return 1;
+        *rmode = a.w[1].mode;
+        *wr = a.w[1].bits;
+        if (*rmode != kDq && *rmode != kNestedPow2) return false;
+        if (!(*wr == 1u || *wr == 2u || *wr == 4u)) return false;
         for (uint32_t j = 2; j < a.W; ++j)
-            if (a.w[j].mode != rmode || a.w[j].bits != wr) return 1;
+            if (a.w[j].mode != *rmode || a.w[j].bits != *wr) return false;
     }
     // the high word of the dither's block number is the same for the whole call (it changes every 2^35 elements)
     for (uint32_t j = 0; j < a.W; ++j)
-        if ((a.w[j].index0 >> 35) != ((a.w[j].index0 + a.tl.n - 1u) >> 35)) return 1;
+        if ((a.w[j].index0 >> 35) != ((a.w[j].index0 + a.tl.n - 1u) >> 35)) return false;
+    return true;
+}
+
+// Runs the streaming kernel for a plan that chain_streams accepts; returns 1 when the vector holds no whole tile.
+static int run_chain_stream(const GeneralChainArgs& a, uint32_t bucket, uint32_t rmode, uint32_t wr, hipStream_t s)
+{
+    const uint32_t w0 = a.w[0].bits;
     ChainArgs b;
     for (uint32_t j = 0; j < a.W; ++j) {
         const ChainWorker& cw = a.w[j];
@@ -1315,6 +1458,22 @@ static int try_chain_stream(const GeneralChainArgs& a, uint32_t bucket, hipStrea
     return w0 == 1u ? launch_chain_stream_w<kNestedPow2, 1>(b, bucket_len, wr, s)
                     : w0 == 2u ? launch_chain_stream_w<kNestedPow2, 2>(b, bucket_len, wr, s)
                                : launch_chain_stream_w<kNestedPow2, 4>(b, bucket_len, wr, s);
+}
+
+// Longest vector chain_short_kernel takes.  us, this kernel / the other one, at 61 k, 267 k, 530 k, 1.05 M elements:
+//   against chain_stream_kernel                        against chain_kernel
+//   4 DQSG          3.4/3.9   3.9/4.1   5.0/4.3        2 DQSG of 5 levels      3.1/3.7  3.4/3.8   4.2/4.0   5.3/4.6
+//   1 + 3 nested    3.5/4.2   4.1/4.3   5.3/4.7        4 + 4 of ratio 3        4.8/9.5  5.9/9.6   7.8/10.0  10.6/10.5
+//   8 DQSG          4.3/5.8   5.2/5.9   7.1/6.2        16 DQSG of 5 levels     6.6/15.1 8.3/15.3  11.4/15.6 16.0/15.8
+//   1 + 7           4.7/6.4   5.7/6.6   7.7/7.1        8 + 8 nested            7.0/15.6 8.9/15.8  12.0/16.0 17.0/16.3
+//   1 + 15          7.4/11.1  9.2/11.3  12.6/12.2      1 + 15 of ratio 3       8.1/18.5 10.1/18.7 14.1/19.0 19.8/19.3
+// One worker alone has nothing to wait for twice.  (A streaming threshold from the environment means that
+// kernel, whatever the length.)
+static uint32_t short_chain_most(uint32_t W, bool streams)
+{
+    if (W < 2u || (streams && stream_tuning().threshold_from_env)) return 0u;
+    if (streams) return 262144u + 16384u * (W < 16u ? W : 16u);
+    return 131072u * (W < 7u ? W + 1u : 8u);
 }
 
 }  // namespace ndq
@@ -1497,9 +1656,18 @@ int ndq_decode_chain(const ndq_worker* workers, uint32_t W, size_t n, uint32_t b
         bool any_m = false;
         for (uint32_t j = 0; j < a.W; ++j) any_m = any_m || a.w[j].mode == kNestedAnyM;
         hipStream_t hs = (hipStream_t)stream;
+        uint32_t rmode, wr;
+        const bool streams = W <= kChainMax && chain_streams(a, bucket, &rmode, &wr);
+        if (W <= kChainMax && n <= short_chain_most(W, streams)) {
+            a.tl.bucket_len = bucket != 0u ? bucket : n;
+            const dim3 grid((uint32_t)((n + kShortTile - 1u) / kShortTile)), block(kBlock);
+            return W <= 8u ? launch(chain_short_kernel<8>, grid, block, hs, a)
+                           : W <= 16u ? launch(chain_short_kernel<16>, grid, block, hs, a)
+                                      : launch(chain_short_kernel<32>, grid, block, hs, a);
+        }
 #ifndef NDQ_NO_STREAM_CHAIN
-        if (W <= kChainMax) {
-            const int rc_stream = try_chain_stream(a, bucket, hs);
+        if (streams) {
+            const int rc_stream = run_chain_stream(a, bucket, rmode, wr, hs);
             if (rc_stream != 1) return rc_stream;
         }
 #endif
