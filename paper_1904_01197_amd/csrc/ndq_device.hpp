@@ -445,6 +445,7 @@ template <> struct Elem<0> {               // binary32: two 16-byte vectors
         return max4(max4(m, row.v[0]), row.v[1]);
     }
     __device__ static __forceinline__ float max_final(float m) { return m; }
+    __device__ static __forceinline__ float max_merge(float a, float b) { return __builtin_fmaxf(a, b); }
 };
 template <> struct Elem<1> {               // bfloat16, widened exactly: one 16-byte vector
     static constexpr int V = 1;
@@ -471,6 +472,7 @@ template <> struct Elem<1> {               // bfloat16, widened exactly: one 16-
         const u16x2 x = __builtin_bit_cast(u16x2, a), y = __builtin_bit_cast(u16x2, b);
         return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(x, y));
     }
+    __device__ static __forceinline__ uint32_t max_merge(uint32_t a, uint32_t b) { return pk_max(a, b); }
     __device__ static __forceinline__ uint32_t max_update(uint32_t m, const Row& row)
     {
         const uint4& raw = row.v[0];
