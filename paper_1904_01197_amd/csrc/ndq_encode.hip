@@ -13,6 +13,7 @@
 #include <string.h>
 
 #include <type_traits>
+#include <utility>
 
 #include "ndq.h"
 #include "ndq_device.hpp"
@@ -140,7 +141,8 @@ __device__ __forceinline__ float tile_max(const TileRegs<DT>& regs)
 // REFILL: a row's registers are loaded again while the row is processed, with the same row of
 // the whole tile at `refill` (lane `refill_lane`'s share), so that one set of registers holds
 // the current tile and, by the end, the next one.
-template <int DT, int MODE, bool FUSED, bool FULL, bool MULTI, int BITSW = 0, bool REFILL = false>
+// GIVEN: `kappa` is the step itself, and the caller writes it.
+template <int DT, int MODE, bool FUSED, bool FULL, bool MULTI, int BITSW = 0, bool REFILL = false, bool GIVEN = false>
 __device__ __forceinline__ void encode_tile(const EncodeArgs& a, const TileRef& t, uint32_t tile_id,
                                             typename std::conditional<REFILL, TileRegs<DT>, const TileRegs<DT>>::type& regs,
                                             float kappa, bool writes_step, unsigned char* stage, int lane,
@@ -184,7 +186,9 @@ __device__ __forceinline__ void encode_tile(const EncodeArgs& a, const TileRef& 
             inv_row[r] = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(invs), r & ~(int)group_mask));
     } else {
         float step;
-        if (FUSED) {
+        if (GIVEN) {
+            step = kappa;
+        } else if (FUSED) {
             step = step_from_kappa(kappa, a.qp.levels);
             if (REFILL) a.steps[t.bucket] = step;     // every lane, the same value: no branch around the store
             else if (lane == 0 && writes_step) a.steps[t.bucket] = step;
@@ -322,28 +326,17 @@ template <int DT> struct EncWaves { static constexpr int W = DT == 1 ? NDQ_ENC_W
 // 0: any width, read from the arguments.
 // (MULTI reduces a bucket's rows in a lane before it reduces them across the wave, and divides for all buckets
 // of a tile at once: with the known width, 4 x 11.2 M bfloat16 in buckets of 1,024, the iteration 47.4 -> 41.8 us.)
-template <int DT, int MODE, bool FUSED, bool MULTI, bool BLOCK, int BITSW = 0>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(EncWaves<DT>::W)))
-void encode_kernel(EncodeBatch by_value)
+template <int DT, int MODE, bool FUSED, bool MULTI, bool BLOCK, int BITSW>
+__device__ __forceinline__ void encode_wave(const EncodeArgs& a, const TileRef& t, uint32_t tile_id, int wave, int lane,
+                                            unsigned char* stage, float (&part)[kWavesPerBlock])
 {
-    const EncodeBatchPtr batch = (EncodeBatchPtr)__builtin_amdgcn_kernarg_segment_ptr();
-    EncodeArgs a = common_args(batch);
-    select_job(a, batch, blockIdx.y);
     constexpr uint32_t TILE = EncTile<DT>::N;
-    __shared__ __align__(16) unsigned char stage_all[kWavesPerBlock][TILE + 8];
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);   // wave-uniform
-    unsigned char* stage = stage_all[wave];
-
-    const uint32_t tile_id = blockIdx.x * kWavesPerBlock + wave;
-    const TileRef t = locate_tile(a.tl, tile_id, TILE);
     const uint32_t bits = BITSW ? (uint32_t)BITSW : a.qp.bits;
     if (BLOCK) {
         // A bucket of 2 or 4 tiles lies inside one workgroup (tile ids are consecutive
         // and buckets start at multiples of their length): the waves exchange their
         // tile maxima through LDS.  Every wave of the workgroup reaches the barrier,
         // also one whose tile is empty.
-        __shared__ float part[kWavesPerBlock];
         TileRegs<DT> regs;
         if (t.len == TILE) load_tile<DT, true>(a.g, t, lane, regs);
         else if (t.len != 0) load_tile<DT, false>(a.g, t, lane, regs);
@@ -372,6 +365,163 @@ void encode_kernel(EncodeBatch by_value)
     }
     wave_lds_sync();     // a wave copies out only the stage it filled itself
     if (t.len != 0) stage_to_stream(a, t, bits, stage, lane);
+}
+
+template <int DT, int MODE, bool FUSED, bool MULTI, bool BLOCK, int BITSW = 0>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(EncWaves<DT>::W)))
+void encode_kernel(EncodeBatch by_value)
+{
+    const EncodeBatchPtr batch = (EncodeBatchPtr)__builtin_amdgcn_kernarg_segment_ptr();
+    EncodeArgs a = common_args(batch);
+    select_job(a, batch, blockIdx.y);
+    constexpr uint32_t TILE = EncTile<DT>::N;
+    __shared__ __align__(16) unsigned char stage_all[kWavesPerBlock][TILE + 8];
+    __shared__ float part[kWavesPerBlock];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);   // wave-uniform
+    const uint32_t tile_id = blockIdx.x * kWavesPerBlock + wave;
+    const TileRef t = locate_tile(a.tl, tile_id, TILE);
+    encode_wave<DT, MODE, FUSED, MULTI, BLOCK, BITSW>(a, t, tile_id, wave, lane, stage_all[wave], part);
+}
+
+// ---------------------------------------------------------------------------
+// Encoder for short vectors: the vectors of ALL quantizers of a call in one launch (a launch of few
+// waves takes 3 to 5 us whatever it does), each workgroup going by its vector's mode and code width.
+//   FORM  kFormBucket: a bucket is at most a tile   kFormMulti: several share one   kFormBlock: 2 or 4 tiles
+//         kFormVector: one step for the whole vector
+// kFormVector, step from the vector's own max-norm: the workgroup reduces the parts of the max-norm pass by
+// itself, which spares the launch between (absmax_finish_kernel).  The codes will overwrite the parts, so every
+// workgroup has a copy of them to itself, at the start of the codes it is going to write
+// (ShortShare; absmax_copies_kernel writes all the copies).
+// ---------------------------------------------------------------------------
+enum ShortForm { kFormBucket = 0, kFormMulti = 1, kFormBlock = 2, kFormVector = 3 };
+struct ShortJob : EncodeJob {
+    Quant qp;
+    uint64_t total_bytes;
+    float preset_step;
+    uint32_t variant;      // 8 * mode + code width
+    uint32_t parts;        // kFormVector: parts to reduce; 0: the step is preset or in memory
+    uint32_t levels;       // the parts' step: levels of the vector that chose it
+};
+struct ShortBatch {
+    ShortJob job[kEncJobs];
+    Tiling tl;
+    uint32_t rows_log2, num_buckets, waves_log2;
+    uint32_t groups;       // kFormVector: workgroups per vector
+};
+typedef const __attribute__((address_space(4))) ShortBatch* ShortBatchPtr;
+static_assert(sizeof(ShortBatch) <= 4096, "kernel arguments");
+
+// kFormVector: the tiles of workgroup `group` of `groups`, as even as whole tiles go, so that also the last
+// one, which ends with the vector, has codes enough to hold its copy of the parts.
+struct ShortShare {
+    uint32_t first, count;
+    __host__ __device__ __forceinline__ ShortShare(uint32_t tiles, uint32_t groups, uint32_t group)
+    {
+        const uint32_t base = tiles / groups, extra = tiles - base * groups;
+        first = group * base + (group < extra ? group : extra);
+        count = base + (group < extra ? 1u : 0u);
+    }
+};
+
+template <int DT, int FORM, int MODE, int BITSW>
+__device__ __forceinline__ void encode_short(const EncodeArgs& a, const TileRef& t, uint32_t tile_id, int wave, int lane,
+                                             unsigned char* stage, float (&part)[kWavesPerBlock], uint32_t parts,
+                                             uint32_t levels, const float* copy)
+{
+    if constexpr (FORM != kFormVector) {
+        encode_wave<DT, MODE, true, FORM == kFormMulti, FORM == kFormBlock, BITSW>(a, t, tile_id, wave, lane, stage, part);
+    } else {
+        constexpr uint32_t TILE = EncTile<DT>::N;
+        TileRegs<DT> regs;
+        if (t.len == TILE) load_tile<DT, true, true>(a.g, t, lane, regs);
+        else if (t.len != 0) load_tile<DT, false, true>(a.g, t, lane, regs);
+        float step;
+        if (parts != 0u) {
+            const float mine = wave_max((uint32_t)threadIdx.x < parts ? copy[threadIdx.x] : 0.0f);
+            if (lane == 0) part[wave] = mine;
+            __syncthreads();     // and the copy has been read: the codes may take its place
+            float all = part[0];
+#pragma unroll
+            for (int w = 1; w < kWavesPerBlock; ++w) all = __builtin_fmaxf(all, part[w]);
+            step = step_from_kappa(all, levels);
+        } else {
+            step = a.preset_step > 0.0f ? a.preset_step : a.step_in[0];
+        }
+        if (tile_id == 0u && lane == 0) a.steps[0] = step;
+        if (t.len == TILE) encode_tile<DT, MODE, false, true, false, BITSW, false, true>(a, t, tile_id, regs, step, false, stage, lane);
+        else if (t.len != 0) encode_tile<DT, MODE, false, false, false, BITSW, false, true>(a, t, tile_id, regs, step, false, stage, lane);
+        wave_lds_sync();
+        if (t.len != 0) stage_to_stream(a, t, BITSW, stage, lane);
+    }
+}
+
+// The variants a workgroup may meet.  (A step that is not the vector's own comes with kFormVector only.)
+template <int FORM> struct ShortVariants {
+    using list = std::integer_sequence<int, 8 * kDqNarrow + 1, 8 * kDqNarrow + 2, 8 * kDqNarrow + 3, 8 * kDqNarrow + 4,
+                                       8 * kNestedPow2Bounded + 1, 8 * kNestedPow2Bounded + 2, 8 * kNestedPow2Bounded + 3,
+                                       8 * kNestedPow2Bounded + 4, 8 * kNestedAnyMBounded + 2, 8 * kNestedAnyMBounded + 3>;
+};
+template <> struct ShortVariants<kFormVector> {
+    using list = std::integer_sequence<int, 8 * kDqNarrow + 1, 8 * kDqNarrow + 2, 8 * kDqNarrow + 3, 8 * kDqNarrow + 4,
+                                       8 * kNestedPow2Bounded + 1, 8 * kNestedPow2Bounded + 2, 8 * kNestedPow2Bounded + 3,
+                                       8 * kNestedPow2Bounded + 4, 8 * kNestedAnyMBounded + 2, 8 * kNestedAnyMBounded + 3,
+                                       8 * kNestedPow2 + 1, 8 * kNestedPow2 + 2, 8 * kNestedPow2 + 3, 8 * kNestedPow2 + 4>;
+};
+template <int... V>
+constexpr bool short_variant(uint32_t variant, std::integer_sequence<int, V...>) { return ((variant == (uint32_t)V) || ...); }
+
+template <int DT, int FORM, int... V>
+__device__ __forceinline__ void encode_short_any(uint32_t variant, std::integer_sequence<int, V...>, const EncodeArgs& a,
+                                                 const TileRef& t, uint32_t tile_id, int wave, int lane, unsigned char* stage,
+                                                 float (&part)[kWavesPerBlock], uint32_t parts, uint32_t levels,
+                                                 const float* copy)
+{
+    (void)((variant == (uint32_t)V
+                ? (encode_short<DT, FORM, V / 8, V % 8>(a, t, tile_id, wave, lane, stage, part, parts, levels, copy), true)
+                : false) || ...);
+}
+
+template <int DT, int FORM>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(EncWaves<DT>::W)))
+void encode_short_kernel(ShortBatch by_value)
+{
+    const ShortBatchPtr batch = (ShortBatchPtr)__builtin_amdgcn_kernarg_segment_ptr();
+    const __attribute__((address_space(4))) ShortJob* job = &batch->job[blockIdx.y];
+    EncodeArgs a;
+    a.g = job->g;
+    a.codes = job->codes;
+    a.steps = job->steps;
+    a.step_in = job->step_in;
+    a.index0 = job->index0;
+    a.ds.key0 = job->ds.key0; a.ds.key1 = job->ds.key1; a.ds.step = job->ds.step; a.ds.worker = job->ds.worker;
+    a.tl.n = batch->tl.n;
+    a.tl.bucket_len = batch->tl.bucket_len;
+    a.tl.tiles_per_bucket = batch->tl.tiles_per_bucket;
+    a.tl.total_tiles = batch->tl.total_tiles;
+    a.total_bytes = job->total_bytes;
+    a.qp.q_min_f = job->qp.q_min_f; a.qp.q_max_f = job->qp.q_max_f; a.qp.q_min = job->qp.q_min;
+    a.qp.levels = job->qp.levels; a.qp.M = job->qp.M; a.qp.M_f = job->qp.M_f; a.qp.inv_M_f = job->qp.inv_M_f;
+    a.qp.bits = job->qp.bits; a.qp.pack_bias = job->qp.pack_bias; a.qp.alpha = job->qp.alpha; a.qp.beta = job->qp.beta;
+    a.preset_step = job->preset_step;
+    a.rows_log2 = batch->rows_log2;
+    a.num_buckets = batch->num_buckets;
+    a.waves_log2 = batch->waves_log2;
+    constexpr uint32_t TILE = EncTile<DT>::N;
+    __shared__ __align__(16) unsigned char stage_all[kWavesPerBlock][TILE / 2 + 8];      // at most 4 bits a code
+    __shared__ float part[kWavesPerBlock];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    uint32_t tile_id = blockIdx.x * kWavesPerBlock + wave;
+    const float* copy = nullptr;
+    if (FORM == kFormVector) {
+        const ShortShare share(a.tl.total_tiles, batch->groups, blockIdx.x);
+        tile_id = (uint32_t)wave < share.count ? share.first + wave : a.tl.total_tiles;
+        copy = (const float*)(a.codes + (uint64_t)share.first * (TILE / 8u) * a.qp.bits);
+    }
+    const TileRef t = locate_tile(a.tl, tile_id, TILE);
+    encode_short_any<DT, FORM>(job->variant, typename ShortVariants<FORM>::list{}, a, t, tile_id, wave, lane, stage_all[wave],
+                               part, job->parts, job->levels, copy);
 }
 
 // The same for a full tile that is not the vector's last, with the code width known
@@ -522,6 +672,17 @@ struct AbsmaxBatch {
 };
 typedef const __attribute__((address_space(4))) AbsmaxBatch* AbsmaxBatchPtr;
 
+// absmax_copies_kernel
+struct CopiesBatch {
+    const void* g[kEncJobs];           // blockIdx.y: the vectors that choose their step
+    unsigned char* codes[kEncJobs];    // the vectors that quantize with one of those steps, their own included:
+    uint32_t bits[kEncJobs];           // where their workgroups' copies lie follows from their code width
+    uint32_t source[kEncJobs];         // ... and whose parts they are (blockIdx.y)
+    uint32_t users, groups;            // how many such vectors, and workgroups the encoder has for each
+    Tiling tl;
+};
+typedef const __attribute__((address_space(4))) CopiesBatch* CopiesBatchPtr;
+
 __global__ void fill_zero_kernel(AbsmaxBatch by_value)
 {
     const AbsmaxBatchPtr b = (AbsmaxBatchPtr)__builtin_amdgcn_kernarg_segment_ptr();
@@ -603,6 +764,42 @@ __global__ __launch_bounds__(kBlock) void absmax_span_kernel(AbsmaxBatch by_valu
         if (blocks_per_bucket == 1u) *word = absmax_word(all, b->levels[blockIdx.y]);
         else if (parts) parts[blockIdx.x] = all;
         else atomicMax(word, absmax_word(all, b->levels[blockIdx.y]));
+    }
+}
+
+// The same for one bucket per vector whose encoder is encode_short_kernel: the workgroup's part goes to
+// every workgroup of the encoder that needs it.
+template <int DT>
+__global__ __launch_bounds__(kBlock) void absmax_copies_kernel(CopiesBatch by_value)
+{
+    using T = Elem<DT>;
+    constexpr uint32_t TILE = EncTile<DT>::N;
+    const CopiesBatchPtr b = (CopiesBatchPtr)__builtin_amdgcn_kernarg_segment_ptr();
+    const Tiling tl = {b->tl.n, b->tl.bucket_len, b->tl.tiles_per_bucket, b->tl.total_tiles};
+    const void* g = b->g[blockIdx.y];
+    __shared__ float part[kWavesPerBlock];
+    const int lane = threadIdx.x & (kWave - 1);
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    typename T::maxacc acc = T::max_init();
+    for (uint32_t j = blockIdx.x * kWavesPerBlock + wave; j < tl.total_tiles; j += gridDim.x * kWavesPerBlock) {
+        const TileRef t = locate_tile(tl, j, TILE);
+        TileRegs<DT> regs;
+        if (t.len == TILE) load_tile<DT, true, true>(g, t, lane, regs);
+        else load_tile<DT, false, true>(g, t, lane, regs);
+        acc = lane_max<DT>(acc, regs);
+    }
+    const float m = wave_max(T::max_final(acc));
+    if (lane == 0) part[wave] = m;
+    __syncthreads();
+    float all = part[0];
+#pragma unroll
+    for (int w = 1; w < kWavesPerBlock; ++w) all = __builtin_fmaxf(all, part[w]);
+    const uint32_t groups = b->groups;
+    for (uint32_t u = 0; u < b->users; ++u) {
+        if (b->source[u] != blockIdx.y) continue;
+        const uint32_t tile_bytes = TILE / 8u * b->bits[u];
+        for (uint32_t e = threadIdx.x; e < groups; e += kBlock)
+            ((float*)(b->codes[u] + (uint64_t)ShortShare(tl.total_tiles, groups, e).first * tile_bytes))[blockIdx.x] = all;
     }
 }
 
@@ -858,12 +1055,122 @@ static int run_encode_mode(const EncodeBatch& b, const EncodePlan& p, uint32_t b
     return run_encode<DT, kNestedAnyM>(b, p.fused, p.multi, bucket, s);
 }
 
+// Whether encode_short_kernel takes a batch; it then answers *rc.  Worth it while a launch more counts: encoder
+// calls, us, this / a launch per quantizer, W vectors of n elements:
+//   binary32, buckets of 1,024     8 + 8   61 k 5.4/8.9    267 k 7.1/11.4   1.05 M 14.8/17.4   1.66 M 23.3/25.2   3 M 40.5/40.4
+//   bfloat16, buckets of 4,096     8 + 8   61 k 5.3/10.5   267 k 6.9/12.9   1.05 M 10.1/13.4   1.66 M 15.0/19.6   3 M 24.3/27.5
+//   binary32, a step per vector    1 + 1   61 k 9.0/16.0   267 k 9.5/16.0   1.05 M 9.4/15.1
+//                                  4 + 4   61 k 9.0/15.8   267 k 10.4/17.7  1.05 M 13.3/17.9   1.66 M 24.9/27.1   3 M 40.1/38.6
+//                                  16      61 k 9.3/12.6   267 k 10.4/13.5  530 k 14.3/16.0    1.05 M 26.9/24.8
+// so buckets up to 16,384 tiles in all, steps per vector up to 6,144 or, with one quantizer, 4,096.
+constexpr uint32_t kShortBucketTiles = 16384, kShortVectorTiles = 6144, kShortOneQuantizerTiles = 4096;
+// Copies of parts to write, at most: every one is a store to a line of its own.  Iterations of 4 x 1.66 M elements, us, with at
+// most 16 k / 32 k / 64 k / 128 k copies: 22.2-23.7 / 22.1 / 22.8-23.1 / 24.1-24.4, with absmax_finish_kernel 22.2; 4 x 900 k: 14.5-15.6 /
+// 13.9 / 13.5-14.7 / 14.7, 15.1.
+constexpr uint32_t kShortCopies = 32768;
+
+template <int DT>
+static bool run_short(const EncodePlan* plans, uint32_t jobs, uint32_t bucket, hipStream_t s, int* rc)
+{
+    constexpr uint32_t TILE = EncTile<DT>::N;
+    const EncodeArgs& first = plans[0].a;
+    const bool vector = bucket == 0u;
+    const uint64_t all_tiles = (uint64_t)first.tl.total_tiles * jobs;
+    if (all_tiles > (vector ? kShortVectorTiles : kShortBucketTiles)) return false;
+    if (!vector && !plans[0].fused) return false;       // (the form of a bucket is the same for all)
+    bool one_quantizer = true, several = false;
+    uint32_t sources = 0u;
+    for (uint32_t j = 0; j < jobs; ++j) {
+        const uint32_t variant = 8u * (uint32_t)plans[j].mode + plans[j].a.qp.bits;
+        if (!(vector ? short_variant(variant, ShortVariants<kFormVector>::list{})
+                     : short_variant(variant, ShortVariants<kFormBucket>::list{})))
+            return false;
+        one_quantizer = one_quantizer && plans[j].a.qp.M == first.qp.M && plans[j].a.qp.bits == first.qp.bits;
+        several = several || (!same_launch(plans[0], plans[j]) && plans[0].two_pass == plans[j].two_pass);
+        if (vector && plans[j].two_pass) ++sources;
+    }
+    if (sources == 0u && !several) return false;
+    if (vector && one_quantizer && all_tiles > kShortOneQuantizerTiles) return false;
+    ShortBatch b[2];        // the vectors of the first launch, and those of a second one
+    uint32_t count[2] = {0u, 0u};
+    CopiesBatch m;
+    m.users = 0u;
+    uint32_t chosen = 0u, narrow = 4u;
+    for (uint32_t j = 0; j < jobs; ++j) {
+        // A vector that is handed the step of one that chooses it here finds the step itself, from
+        // parts like that one's, if the quantizers differ (the workers of Algorithm 2); the others that have
+        // their step in memory or from the caller wait for a launch of their own where anything chooses.
+        uint32_t source = kEncJobs, k = 0u;
+        if (vector)
+            for (uint32_t i = 0; i < jobs; ++i) {
+                if (!plans[i].two_pass) continue;
+                if (i == j || (!one_quantizer && i < j && plans[j].handed && plans[j].a.step_in == plans[i].a.steps)) source = k;
+                ++k;
+            }
+        const uint32_t launch_of = source == kEncJobs && sources != 0u ? 1u : 0u;
+        ShortJob& job = b[launch_of].job[count[launch_of]++];
+        static_cast<EncodeJob&>(job) = plans[j].a;
+        job.qp = plans[j].a.qp;
+        job.total_bytes = plans[j].a.total_bytes;
+        job.preset_step = plans[j].a.preset_step;
+        job.variant = 8u * (uint32_t)plans[j].mode + plans[j].a.qp.bits;
+        job.parts = 0u;
+        job.levels = 0u;
+        if (source == kEncJobs) continue;
+        if (plans[j].two_pass) {
+            m.g[chosen++] = plans[j].a.g;
+            job.levels = plans[j].a.qp.levels;
+        } else {
+            for (uint32_t u = 0; u < m.users; ++u)
+                if (m.source[u] == source) { job.levels = b[0].job[u].levels; break; }
+        }
+        m.codes[m.users] = plans[j].a.codes;
+        m.bits[m.users] = plans[j].a.qp.bits;
+        m.source[m.users++] = source;
+        if (plans[j].a.qp.bits < narrow) narrow = plans[j].a.qp.bits;
+    }
+    const uint32_t tiles = first.tl.total_tiles, groups = blocks_for(tiles);
+    if (sources != 0u) {
+        // a copy of the parts fits the shortest share of the narrowest codes, the last one's; the
+        // pass keeps a workgroup per compute unit, or one for every four of the encoder's
+        const ShortShare last(tiles, groups, groups - 1u);
+        const uint64_t bytes = packed_bytes(first.tl.n, narrow) - (uint64_t)last.first * (TILE / 8u) * narrow;
+        uint32_t parts = groups < (uint32_t)kBlock ? groups : (uint32_t)kBlock;
+        if (parts > bytes / 4u) parts = (uint32_t)(bytes / 4u);
+        if (parts > kShortCopies / (groups * m.users)) parts = kShortCopies / (groups * m.users);
+        if (parts == 0u || (4u * parts < groups && parts * sources < 256u)) return false;
+        for (uint32_t u = 0; u < m.users; ++u) b[0].job[u].parts = parts;
+        m.tl = first.tl;
+        m.groups = groups;
+        *rc = launch(absmax_copies_kernel<DT>, dim3(parts, sources), dim3(kBlock), s, m);
+        if (*rc != NDQ_OK) return true;
+    }
+    for (uint32_t i = 0; i < 2u; ++i) {
+        if (count[i] == 0u) continue;
+        b[i].tl = first.tl;
+        b[i].rows_log2 = first.rows_log2;
+        b[i].num_buckets = first.num_buckets;
+        b[i].waves_log2 = first.waves_log2;
+        b[i].groups = groups;
+        const dim3 grid(groups, count[i]), block(kBlock);
+        *rc = vector ? launch((encode_short_kernel<DT, kFormVector>), grid, block, s, b[i])
+              : first.waves_log2 != 0u ? launch((encode_short_kernel<DT, kFormBlock>), grid, block, s, b[i])
+              : plans[0].multi ? launch((encode_short_kernel<DT, kFormMulti>), grid, block, s, b[i])
+                               : launch((encode_short_kernel<DT, kFormBucket>), grid, block, s, b[i]);
+        if (*rc != NDQ_OK) return true;
+    }
+    return true;
+}
+
 // Up to kEncJobs planned vectors: first the max-norm passes of those that need one, all in
 // one launch, then the encoders, one launch for all vectors of a kind.  Launches of many
 // vectors instead of one per vector: a launch ramps up and drains once, and the next
 // vector's loads overlap with this one's arithmetic.
 static int run_plans(const EncodePlan* plans, uint32_t jobs, int dt, uint32_t bucket, hipStream_t s)
 {
+    int rc_short;
+    if (dt == NDQ_F32 ? run_short<0>(plans, jobs, bucket, s, &rc_short) : run_short<1>(plans, jobs, bucket, s, &rc_short))
+        return rc_short;
     AbsmaxBatch m;
     uint32_t need = 0;
     for (uint32_t j = 0; j < jobs; ++j) {
