@@ -297,144 +297,72 @@ __global__ void clear_histogram_kernel(unsigned long long* hist, uint32_t nbins,
 }
 
 // ---------------------------------------------------------------------------
-// Dense base-L stream (Sec. 4 Table 1 counts log2 L bits per index): k indices
+// Dense base-L stream (Sec. 4 Table 1 counts log2 L bits per index): K indices
 // per 32-bit word as the number sum_j c_j L^j.  Transcoders between the
-// fixed-width stream and the dense one.  A thread owns 8 dense words = 8k
-// indices = k*bits whole bytes of the fixed-width stream, so no two threads
-// share a byte.
+// fixed-width stream and the dense one.  A thread owns P dense words = P K
+// indices = TB = P K BITS / 8 whole bytes of the fixed-width stream, so no two threads
+// share a byte; they sit in its registers as one bit string with every index at a place known
+// at compile time.  Both streams move between memory and LDS sixteen bytes at a time.
+//
+// Bound by the digits' arithmetic: a digit at a time is a multiply and a shift or two for each of K, so D
+// digits are taken together, through a table of their 2^(D BITS) codes (packing) or L^D values
+// (unpacking) that the workgroup makes first: K / D multiplications or divisions a word.  Four words a
+// thread where that is a whole number of 32-bit words (more waves for the same stream), else eight.
+// us, packing + unpacking, before (a digit at a time; other L than 3 and 5 byte by byte, with eight words a
+// thread) and now: 25.6 M indices of three levels 4.8 + 6.3, 4.1 + 4.3; five 5.2 + 7.3, 5.2 + 6.7; six 12.8 + 15.9,
+// 5.9 + 6.7; 1.5 M of twelve 7.3 + 7.4, 3.1 + 3.1.  (Packing three levels by the table: 4.5.)
 // ---------------------------------------------------------------------------
 struct DenseArgs {
     unsigned char* fixed;     // fixed-width stream (read by pack, written by unpack)
     uint32_t* dense;          // dense stream (written by pack, read by unpack)
     uint64_t n;               // indices
     uint64_t fixed_total;     // its padded size
-    uint64_t dense_valid;     // ceil(n/k) words that hold indices
     uint64_t dense_total;     // padded size in words
-    uint32_t levels, k, bits;
-    // division of a 32-bit number by `levels` through one high multiply (division by
-    // an invariant integer, round-up method): with l = ceil(log2 levels) and
-    // magic = floor(2^32 (2^l - levels) / levels) + 1, for every 32-bit x
-    // x / levels = (t + ((x - t) >> 1)) >> (l - 1), t = high word of x * magic
+    uint32_t levels;
+    uint32_t group;           // levels^D
+    // division of a 32-bit number by `group` through one high multiply (division by
+    // an invariant integer, round-up method): with l = ceil(log2 group) and
+    // magic = floor(2^32 (2^l - group) / group) + 1, for every 32-bit x
+    // x / group = (t + ((x - t) >> 1)) >> (l - 1), t = high word of x * magic
     uint32_t magic, shift;
 };
 
-__device__ __forceinline__ uint32_t divide_by_levels(uint32_t x, const DenseArgs& a)
-{
-    const uint32_t t = __umulhi(x, a.magic);
-    return (t + ((x - t) >> 1)) >> a.shift;
-}
-
-// Both transcoders stage a workgroup's share of the two streams in LDS: a thread's
-// bytes lie k*bits (at most kDenseThreadBytes) apart from its neighbour's, so direct
-// byte accesses would each be a memory transaction of their own; the workgroup's
-// share is contiguous and moves as whole 32-bit words instead.
-constexpr uint32_t kDenseThreadBytes = 40;     // max of k * bits over levels 2..256
 constexpr uint32_t kDenseBlock = 256;
-constexpr uint32_t kDenseWordsPerThread = 8;
 
-struct DenseStage {
-    uint32_t dense[kDenseBlock * kDenseWordsPerThread];
-    uint32_t fixed[kDenseBlock * kDenseThreadBytes / 4];
+// LC: the number of levels when it is known at compile time (the level counts of the paper's own
+// experiments, three and five), else 0.
+template <uint32_t LC, uint32_t K, uint32_t BITS> struct DenseForm {
+    static constexpr uint32_t D = BITS == 1u ? 8u : BITS == 2u ? (K == 20u ? 5u : 4u) : BITS == 3u ? 3u : BITS <= 5u ? 2u : 1u;
+    static constexpr uint32_t G = K / D, R = K % D;                 // whole groups of digits, and digits left over
+    static constexpr uint32_t PACK_D = LC ? 1u : D;                 // (packing: by a constant L a digit is a shift and an addition)
+    static constexpr uint32_t P = K * BITS % 8u == 0u ? 4u : 8u;    // dense words per thread
+    static constexpr uint32_t TB = P * K * BITS / 8u;               // a thread's bytes of the fixed-width stream
+    static constexpr uint32_t NX = (TB + 3u) / 4u;                  // as 32-bit words
+    static constexpr uint32_t NR = TB % 4u == 0u ? NX : TB / 4u + 2u;   // aligned words that cover them at any offset
+    static constexpr uint32_t FIXED_WORDS = kDenseBlock * TB / 4u;  // per workgroup (256 * TB is a multiple of 16)
+    static constexpr uint32_t DENSE_WORDS = kDenseBlock * P;
+    static constexpr uint32_t CODES = 1u << (D * BITS);             // entries of either table: L^D <= CODES
+    static constexpr uint32_t power(uint32_t e) { return e == 0u ? 1u : LC * power(e - 1u); }
+    static_assert(P * K * BITS % 8u == 0u && FIXED_WORDS % 4u == 0u && CODES <= 1024u, "partition");
+    static __device__ __forceinline__ uint32_t group(const DenseArgs& a) { return LC ? power(D) : a.group; }
+    static __device__ __forceinline__ uint32_t divide(uint32_t x, const DenseArgs& a)
+    {
+        if (LC) return x / power(D);
+        const uint32_t t = __umulhi(x, a.magic);
+        return (t + ((x - t) >> 1)) >> a.shift;
+    }
 };
 
-// bytes of the fixed-width stream that belong to this workgroup (a multiple of 4:
-// its first byte is a multiple of 256 and the stream's size one of 16)
+// bytes of the fixed-width stream that belong to this workgroup (a multiple of 16, like its first byte
+// and the stream's size)
+template <uint32_t TB>
 __device__ __forceinline__ uint32_t dense_block_bytes(const DenseArgs& a, uint64_t block_byte0)
 {
-    const uint64_t share = (uint64_t)kDenseBlock * a.k * a.bits;
+    constexpr uint64_t share = (uint64_t)kDenseBlock * TB;
     if (block_byte0 >= a.fixed_total) return 0u;
     const uint64_t left = a.fixed_total - block_byte0;
     return (uint32_t)(left < share ? left : share);
 }
-
-__global__ __launch_bounds__(kDenseBlock) void dense_pack_kernel(DenseArgs a)
-{
-    __shared__ DenseStage st;
-    const uint32_t tid = threadIdx.x;
-    const uint32_t thread_bytes = a.k * a.bits;
-    const uint64_t block_byte0 = (uint64_t)blockIdx.x * kDenseBlock * thread_bytes;
-    const uint64_t block_w0 = (uint64_t)blockIdx.x * kDenseBlock * kDenseWordsPerThread;
-    const uint32_t words_in = dense_block_bytes(a, block_byte0) / 4u;
-    const uint32_t* fixed32 = reinterpret_cast<const uint32_t*>(a.fixed + block_byte0);
-    for (uint32_t i = tid; i < kDenseBlock * thread_bytes / 4u; i += kDenseBlock)
-        st.fixed[i] = i < words_in ? fixed32[i] : 0u;
-    __syncthreads();
-    const unsigned char* mine = reinterpret_cast<const unsigned char*>(st.fixed) + tid * thread_bytes;
-    const uint32_t mask = (1u << a.bits) - 1u;
-    uint32_t buf = 0u, have = 0u, byte = 0u;
-    for (uint32_t j = 0; j < kDenseWordsPerThread; ++j) {
-        const uint64_t w = block_w0 + tid * kDenseWordsPerThread + j;
-        // sum_j c_j L^j <= L^k - 1 < 2^32; the weight may wrap after the last digit, unused
-        uint32_t value = 0u, weight = 1u;
-        for (uint32_t d = 0; d < a.k; ++d) {
-            if (have < a.bits) {
-                buf |= (uint32_t)mine[byte++] << have;
-                have += 8u;
-            }
-            uint32_t c = buf & mask;
-            buf >>= a.bits;
-            have -= a.bits;
-            if (w * a.k + d >= a.n) c = 0u;      // also hides whatever the padding holds
-            value += c * weight;
-            weight *= a.levels;
-        }
-        st.dense[tid * kDenseWordsPerThread + j] = value;
-    }
-    __syncthreads();
-    for (uint32_t i = tid; i < kDenseBlock * kDenseWordsPerThread; i += kDenseBlock)
-        if (block_w0 + i < a.dense_total) a.dense[block_w0 + i] = st.dense[i];
-}
-
-__global__ __launch_bounds__(kDenseBlock) void dense_unpack_kernel(DenseArgs a)
-{
-    __shared__ DenseStage st;
-    const uint32_t tid = threadIdx.x;
-    const uint32_t thread_bytes = a.k * a.bits;
-    const uint64_t block_byte0 = (uint64_t)blockIdx.x * kDenseBlock * thread_bytes;
-    const uint64_t block_w0 = (uint64_t)blockIdx.x * kDenseBlock * kDenseWordsPerThread;
-    for (uint32_t i = tid; i < kDenseBlock * kDenseWordsPerThread; i += kDenseBlock)
-        st.dense[i] = block_w0 + i < a.dense_valid ? a.dense[block_w0 + i] : 0u;
-    __syncthreads();
-    unsigned char* mine = reinterpret_cast<unsigned char*>(st.fixed) + tid * thread_bytes;
-    uint32_t buf = 0u, have = 0u, byte = 0u;
-    for (uint32_t j = 0; j < kDenseWordsPerThread; ++j) {
-        const uint64_t w = block_w0 + tid * kDenseWordsPerThread + j;
-        uint32_t value = st.dense[tid * kDenseWordsPerThread + j];
-        for (uint32_t d = 0; d < a.k; ++d) {
-            const uint32_t q = divide_by_levels(value, a);
-            uint32_t c = value - q * a.levels;
-            value = q;
-            if (w * a.k + d >= a.n) c = 0u;
-            buf |= c << have;
-            have += a.bits;
-            if (have >= 8u) {
-                mine[byte++] = (unsigned char)buf;
-                buf >>= 8;
-                have -= 8u;
-            }
-        }
-    }
-    // 8 k bits per thread are whole bytes: nothing is left in buf
-    __syncthreads();
-    const uint32_t words_out = dense_block_bytes(a, block_byte0) / 4u;
-    uint32_t* fixed32 = reinterpret_cast<uint32_t*>(a.fixed + block_byte0);
-    for (uint32_t i = tid; i < words_out; i += kDenseBlock) fixed32[i] = st.fixed[i];
-}
-
-// The level counts of the paper's own experiments (Sec. 4: three levels, M = 1, and five,
-// M = 2) with everything known at compile time: the same partition as above (a thread
-// owns 8 dense words = 8 K indices = TB = K * BITS bytes of the fixed-width stream), but
-// the thread's bytes sit in registers as one bit string, every index at a fixed
-// position, the digits come and go with constant multipliers, and both streams move
-// between memory and LDS sixteen bytes at a time.
-template <uint32_t L, uint32_t K, uint32_t BITS> struct DenseFixed {
-    static constexpr uint32_t TB = K * BITS;                       // a thread's bytes of the fixed-width stream
-    static constexpr uint32_t NX = (TB + 3u) / 4u;                 // as 32-bit words
-    static constexpr uint32_t NR = TB % 4u == 0u ? NX : TB / 4u + 2u;   // aligned words that cover them at any offset
-    static constexpr uint32_t FIXED_WORDS = kDenseBlock * TB / 4u;  // per workgroup (256 * TB is a multiple of 16)
-    static constexpr uint32_t DENSE_WORDS = kDenseBlock * kDenseWordsPerThread;
-    static_assert(TB <= kDenseThreadBytes && FIXED_WORDS % 4u == 0u, "partition");
-};
 
 // keeps the first `valid_bits` bits of a bit string held in NX words
 template <uint32_t NX>
@@ -448,144 +376,213 @@ __device__ __forceinline__ void keep_bits(uint32_t (&x)[NX], uint32_t valid_bits
 }
 
 // bits of the thread's share that belong to indices below n
-template <uint32_t K, uint32_t BITS>
+template <uint32_t K, uint32_t BITS, uint32_t P>
 __device__ __forceinline__ uint32_t dense_valid_bits(const DenseArgs& a, uint64_t first_word)
 {
     const uint64_t first = first_word * K;
     if (first >= a.n) return 0u;
     const uint64_t left = a.n - first;
-    return left >= 8u * K ? 8u * K * BITS : (uint32_t)left * BITS;
+    return left >= P * K ? P * K * BITS : (uint32_t)left * BITS;
 }
 
-template <uint32_t L, uint32_t K, uint32_t BITS>
-__global__ __launch_bounds__(kDenseBlock) void dense_pack_fixed_kernel(DenseArgs a)
+// the `width` <= 10 bits from `bit` on
+template <uint32_t NX>
+__device__ __forceinline__ uint32_t window_of(const uint32_t (&x)[NX], uint32_t bit, uint32_t width)
 {
-    using D = DenseFixed<L, K, BITS>;
-    __shared__ __align__(16) DenseStage st;
+    const uint32_t k = bit >> 5, sh = bit & 31u;
+    uint32_t c = x[k] >> sh;
+    if (sh + width > 32u) c |= x[k + 1] << (32u - sh);
+    return c & ((1u << width) - 1u);
+}
+
+template <uint32_t LC, uint32_t K, uint32_t BITS>
+__global__ __launch_bounds__(kDenseBlock) void dense_pack_kernel(DenseArgs a)
+{
+    using F = DenseForm<LC, K, BITS>;
+    constexpr uint32_t D = F::PACK_D, G = K / D, R = K % D, CODES = 1u << (D * BITS);
+    __shared__ __align__(16) uint32_t fixed_stage[F::FIXED_WORDS], dense_stage[F::DENSE_WORDS];
+    __shared__ uint16_t value_of[D > 1u ? CODES : 1u];
     const uint32_t tid = threadIdx.x;
-    const uint64_t block_byte0 = (uint64_t)blockIdx.x * kDenseBlock * D::TB;
-    const uint64_t block_w0 = (uint64_t)blockIdx.x * D::DENSE_WORDS;
-    const uint32_t vectors_in = dense_block_bytes(a, block_byte0) / 16u;
+    const uint64_t block_byte0 = (uint64_t)blockIdx.x * kDenseBlock * F::TB;
+    const uint64_t block_w0 = (uint64_t)blockIdx.x * F::DENSE_WORDS;
+    const uint32_t vectors_in = dense_block_bytes<F::TB>(a, block_byte0) / 16u;
     const uint4* fixed128 = reinterpret_cast<const uint4*>(a.fixed + block_byte0);
-    uint4* stage128 = reinterpret_cast<uint4*>(st.fixed);
-    for (uint32_t i = tid; i < D::FIXED_WORDS / 4u; i += kDenseBlock)
+    uint4* stage128 = reinterpret_cast<uint4*>(fixed_stage);
+    for (uint32_t i = tid; i < F::FIXED_WORDS / 4u; i += kDenseBlock)
         stage128[i] = i < vectors_in ? fixed128[i] : make_uint4(0u, 0u, 0u, 0u);
+    if constexpr (D > 1u) {
+        const uint32_t L = LC ? LC : a.levels;
+        for (uint32_t e = tid; e < CODES; e += kDenseBlock) {
+            uint32_t v = 0u;
+#pragma unroll
+            for (int d = (int)D - 1; d >= 0; --d) v = v * L + ((e >> (d * BITS)) & ((1u << BITS) - 1u));
+            value_of[e] = (uint16_t)v;      // (an index that is not below L counts like any other)
+        }
+    }
     __syncthreads();
 
     // the thread's TB bytes, from the aligned words around them
-    const uint32_t byte0 = tid * D::TB;
-    uint32_t r[D::NR], x[D::NX];
+    const uint32_t byte0 = tid * F::TB;
+    uint32_t r[F::NR], x[F::NX];
 #pragma unroll
-    for (uint32_t i = 0; i < D::NR; ++i) {
+    for (uint32_t i = 0; i < F::NR; ++i) {
         const uint32_t w = byte0 / 4u + i;
-        r[i] = w < D::FIXED_WORDS ? st.fixed[w] : 0u;
+        r[i] = F::TB % 4u == 0u || w < F::FIXED_WORDS ? fixed_stage[w] : 0u;
     }
-    if constexpr (D::TB % 4u == 0u) {
+    if constexpr (F::TB % 4u == 0u) {
 #pragma unroll
-        for (uint32_t i = 0; i < D::NX; ++i) x[i] = r[i];
+        for (uint32_t i = 0; i < F::NX; ++i) x[i] = r[i];
     } else {
 #pragma unroll
-        for (uint32_t i = 0; i < D::NX; ++i) x[i] = __builtin_amdgcn_alignbyte(r[i + 1], r[i], byte0 & 3u);
+        for (uint32_t i = 0; i < F::NX; ++i) x[i] = __builtin_amdgcn_alignbyte(r[i + 1], r[i], byte0 & 3u);
     }
     // indices at or beyond n count as digit 0, whatever the padding holds
-    keep_bits<D::NX>(x, dense_valid_bits<K, BITS>(a, block_w0 + (uint64_t)tid * kDenseWordsPerThread));
+    keep_bits<F::NX>(x, dense_valid_bits<K, BITS, F::P>(a, block_w0 + (uint64_t)tid * F::P));
 
-    uint32_t value[kDenseWordsPerThread];
+    const uint32_t group = LC ? F::power(D) : a.group;
+    uint32_t value[F::P];
 #pragma unroll
-    for (uint32_t j = 0; j < kDenseWordsPerThread; ++j) {
+    for (uint32_t j = 0; j < F::P; ++j) {
         uint32_t v = 0u;
+        if (R != 0u) {
+            const uint32_t c = window_of<F::NX>(x, (j * K + G * D) * BITS, R * BITS);
+            v = D > 1u ? value_of[c] : c;
+        }
 #pragma unroll
-        for (int d = (int)K - 1; d >= 0; --d) {       // sum_d c_d L^d, highest digit first
-            constexpr uint32_t MASK = (1u << BITS) - 1u;
-            const uint32_t bit = (j * K + (uint32_t)d) * BITS, k = bit >> 5, sh = bit & 31u;
-            uint32_t c = x[k] >> sh;
-            if (sh + BITS > 32u) c |= x[k + 1] << (32u - sh);
-            v = v * L + (c & MASK);
+        for (int g = (int)G - 1; g >= 0; --g) {        // highest digits first
+            const uint32_t c = window_of<F::NX>(x, (j * K + (uint32_t)g * D) * BITS, D * BITS);
+            v = v * group + (D > 1u ? value_of[c] : c);
         }
         value[j] = v;
     }
-    uint4* mine = reinterpret_cast<uint4*>(st.dense + tid * kDenseWordsPerThread);
-    mine[0] = make_uint4(value[0], value[1], value[2], value[3]);
-    mine[1] = make_uint4(value[4], value[5], value[6], value[7]);
+    uint4* mine = reinterpret_cast<uint4*>(dense_stage + tid * F::P);
+#pragma unroll
+    for (uint32_t j = 0; j < F::P; j += 4u) mine[j / 4u] = make_uint4(value[j], value[j + 1u], value[j + 2u], value[j + 3u]);
     __syncthreads();
-    const uint4* out128 = reinterpret_cast<const uint4*>(st.dense);
+    const uint4* out128 = reinterpret_cast<const uint4*>(dense_stage);
     uint4* dense128 = reinterpret_cast<uint4*>(a.dense + block_w0);
-    for (uint32_t i = tid; i < D::DENSE_WORDS / 4u; i += kDenseBlock)
+    for (uint32_t i = tid; i < F::DENSE_WORDS / 4u; i += kDenseBlock)
         if (block_w0 + 4u * i < a.dense_total) dense128[i] = out128[i];      // dense_total is a multiple of 4
 }
 
-template <uint32_t L, uint32_t K, uint32_t BITS>
-__global__ __launch_bounds__(kDenseBlock) void dense_unpack_fixed_kernel(DenseArgs a)
+template <uint32_t LC, uint32_t K, uint32_t BITS>
+__global__ __launch_bounds__(kDenseBlock) void dense_unpack_kernel(DenseArgs a)
 {
-    using D = DenseFixed<L, K, BITS>;
-    __shared__ __align__(16) DenseStage st;
+    using F = DenseForm<LC, K, BITS>;
+    __shared__ __align__(16) uint32_t fixed_stage[F::FIXED_WORDS], dense_stage[F::DENSE_WORDS];
+    __shared__ uint16_t codes_of[F::D > 1u ? F::CODES : 1u];
     const uint32_t tid = threadIdx.x;
-    const uint64_t block_byte0 = (uint64_t)blockIdx.x * kDenseBlock * D::TB;
-    const uint64_t block_w0 = (uint64_t)blockIdx.x * D::DENSE_WORDS;
+    const uint64_t block_byte0 = (uint64_t)blockIdx.x * kDenseBlock * F::TB;
+    const uint64_t block_w0 = (uint64_t)blockIdx.x * F::DENSE_WORDS;
     const uint4* dense128 = reinterpret_cast<const uint4*>(a.dense + block_w0);
-    uint4* in128 = reinterpret_cast<uint4*>(st.dense);
-    for (uint32_t i = tid; i < D::DENSE_WORDS / 4u; i += kDenseBlock)
+    uint4* in128 = reinterpret_cast<uint4*>(dense_stage);
+    for (uint32_t i = tid; i < F::DENSE_WORDS / 4u; i += kDenseBlock)
         in128[i] = block_w0 + 4u * i < a.dense_total ? dense128[i] : make_uint4(0u, 0u, 0u, 0u);
-    __syncthreads();
-
-    const uint4* mine = reinterpret_cast<const uint4*>(st.dense + tid * kDenseWordsPerThread);
-    const uint4 lo4 = mine[0], hi4 = mine[1];
-    const uint32_t value[kDenseWordsPerThread] = {lo4.x, lo4.y, lo4.z, lo4.w, hi4.x, hi4.y, hi4.z, hi4.w};
-    uint32_t x[D::NX];
+    const uint32_t group = F::group(a);
+    if constexpr (F::D > 1u) {
+        // the codes of every value below L^D, written by the thread that has the codes: no division
+        const uint32_t L = LC ? LC : a.levels;
+        for (uint32_t e = tid; e < F::CODES; e += kDenseBlock) {
+            uint32_t v = 0u;
+            bool below = true;
 #pragma unroll
-    for (uint32_t i = 0; i < D::NX; ++i) x[i] = 0u;
-    auto put = [&](uint32_t index, uint32_t c) __attribute__((always_inline)) {
-        const uint32_t bit = index * BITS, k = bit >> 5, sh = bit & 31u;
-        x[k] |= c << sh;
-        if (sh + BITS > 32u) x[k + 1] |= c >> (32u - sh);
-    };
-#pragma unroll
-    for (uint32_t j = 0; j < kDenseWordsPerThread; ++j) {
-        if constexpr (L == 3u && K == 20u) {
-            // two halves of ten digits, each below 3^10 < 2^16, taken two digits at a time:
-            // y / 9 = (y * 58255) >> 19 exactly for y < 2^16, and for the remainder r in 0..8
-            // the two codes c0 + 4 c1 = r + r / 3 with r / 3 = (r * 11) >> 5.  All factors lie
-            // below 2^24 and the products fit 32 bits, which the compiler sees: it picks
-            // the multiplies of the fast 24-bit kind.
-            const uint32_t top = value[j] / 59049u;
-            uint32_t half[2] = {value[j] - top * 59049u, top};
-#pragma unroll
-            for (uint32_t h = 0; h < 2u; ++h) {
-                uint32_t y = half[h] & 0xffffu;       // (a word that is not a valid number stays in range)
-#pragma unroll
-                for (uint32_t d = 0; d < 10u; d += 2u) {
-                    const uint32_t q = (y * 58255u) >> 19;
-                    const uint32_t r = y - q * 9u;
-                    put(j * K + 10u * h + d, r + ((r * 11u) >> 5));     // an even index: four bits inside one word
-                    y = q;
-                }
+            for (int d = (int)F::D - 1; d >= 0; --d) {
+                const uint32_t c = (e >> (d * BITS)) & ((1u << BITS) - 1u);
+                below = below && c < L;
+                v = v * L + c;
             }
-        } else {
-            uint32_t v = value[j];
-#pragma unroll
-            for (uint32_t d = 0; d < K; ++d) {
-                const uint32_t q = v / L;
-                put(j * K + d, v - q * L);
-                v = q;
-            }
+            if (below) codes_of[v] = (uint16_t)e;
         }
     }
-    keep_bits<D::NX>(x, dense_valid_bits<K, BITS>(a, block_w0 + (uint64_t)tid * kDenseWordsPerThread));
+    __syncthreads();
 
-    const uint32_t byte0 = tid * D::TB;
-    if constexpr (D::TB % 4u == 0u) {
+    uint32_t value[F::P], x[F::NX];
+    const uint4* mine = reinterpret_cast<const uint4*>(dense_stage + tid * F::P);
 #pragma unroll
-        for (uint32_t i = 0; i < D::NX; ++i) st.fixed[byte0 / 4u + i] = x[i];
+    for (uint32_t j = 0; j < F::P; j += 4u) {
+        const uint4 w = mine[j / 4u];
+        value[j] = w.x; value[j + 1u] = w.y; value[j + 2u] = w.z; value[j + 3u] = w.w;
+    }
+#pragma unroll
+    for (uint32_t i = 0; i < F::NX; ++i) x[i] = 0u;
+    auto put = [&](uint32_t bit, uint32_t width, uint32_t c) __attribute__((always_inline)) {
+        const uint32_t k = bit >> 5, sh = bit & 31u;
+        x[k] |= c << sh;
+        if (sh + width > 32u) x[k + 1] |= c >> (32u - sh);
+    };
+#pragma unroll
+    for (uint32_t j = 0; j < F::P; ++j) {
+        uint32_t v = value[j];
+#pragma unroll
+        for (uint32_t g = 0; g < F::G + (F::R != 0u ? 1u : 0u); ++g) {
+            const uint32_t q = F::divide(v, a), rest = v - q * group;       // below L^D whatever the word holds
+            uint32_t c = F::D > 1u ? codes_of[rest] : rest;
+            const uint32_t digits = g < F::G ? F::D : F::R;
+            if (g == F::G) c &= (1u << (F::R * BITS)) - 1u;
+            put((j * K + g * F::D) * BITS, digits * BITS, c);
+            v = q;
+        }
+    }
+    keep_bits<F::NX>(x, dense_valid_bits<K, BITS, F::P>(a, block_w0 + (uint64_t)tid * F::P));
+
+    const uint32_t byte0 = tid * F::TB;
+    if constexpr (F::TB % 4u == 0u) {
+#pragma unroll
+        for (uint32_t i = 0; i < F::NX; ++i) fixed_stage[byte0 / 4u + i] = x[i];
     } else {
-        unsigned char* bytes = reinterpret_cast<unsigned char*>(st.fixed) + byte0;
+        unsigned char* bytes = reinterpret_cast<unsigned char*>(fixed_stage) + byte0;
 #pragma unroll
-        for (uint32_t b = 0; b < D::TB; ++b) bytes[b] = (unsigned char)(x[b / 4u] >> (8u * (b & 3u)));
+        for (uint32_t i = 0; i < F::TB; ++i) bytes[i] = (unsigned char)(x[i / 4u] >> (8u * (i & 3u)));
     }
     __syncthreads();
-    const uint32_t vectors_out = dense_block_bytes(a, block_byte0) / 16u;
-    const uint4* stage128 = reinterpret_cast<const uint4*>(st.fixed);
+    const uint32_t vectors_out = dense_block_bytes<F::TB>(a, block_byte0) / 16u;
+    const uint4* stage128 = reinterpret_cast<const uint4*>(fixed_stage);
     uint4* fixed128 = reinterpret_cast<uint4*>(a.fixed + block_byte0);
     for (uint32_t i = tid; i < vectors_out; i += kDenseBlock) fixed128[i] = stage128[i];
+}
+
+// Launches the transcoder whose level count, or digits per word and code width, are those of the call.
+template <uint32_t LC, uint32_t K, uint32_t BITS>
+static int launch_dense(DenseArgs& a, bool pack, hipStream_t s)
+{
+    using F = DenseForm<LC, K, BITS>;
+    a.group = 1u;
+    for (uint32_t d = 0; d < F::D; ++d) a.group *= a.levels;
+    uint32_t log2 = 0u;
+    while ((1u << log2) < a.group) ++log2;
+    a.magic = (uint32_t)((((uint64_t)1 << 32) * (((uint64_t)1 << log2) - a.group)) / a.group + 1u);
+    a.shift = log2 - 1u;                        // group >= 2
+    const uint64_t blocks = pack ? (a.dense_total + F::DENSE_WORDS - 1u) / F::DENSE_WORDS
+                                 : (a.fixed_total + 4u * F::FIXED_WORDS - 1u) / (4u * F::FIXED_WORDS);
+    if (blocks >= ((uint64_t)1 << 31)) return NDQ_EUNSUPPORTED;
+    const dim3 grid((uint32_t)blocks), block(kDenseBlock);
+    return pack ? launch((dense_pack_kernel<LC, K, BITS>), grid, block, s, a)
+                : launch((dense_unpack_kernel<LC, K, BITS>), grid, block, s, a);
+}
+
+// every (digits per word, code width) that a level count from 2 to 256 has
+static int run_dense(DenseArgs& a, uint32_t k, uint32_t bits, bool pack, hipStream_t s)
+{
+    if (a.levels == 3u) return launch_dense<3, 20, 2>(a, pack, s);
+    if (a.levels == 5u) return launch_dense<5, 13, 3>(a, pack, s);
+    switch (16u * k + bits) {
+    case 16u * 32u + 1u: return launch_dense<0, 32, 1>(a, pack, s);
+    case 16u * 16u + 2u: return launch_dense<0, 16, 2>(a, pack, s);
+    case 16u * 12u + 3u: return launch_dense<0, 12, 3>(a, pack, s);
+    case 16u * 11u + 3u: return launch_dense<0, 11, 3>(a, pack, s);
+    case 16u * 10u + 3u: return launch_dense<0, 10, 3>(a, pack, s);
+    case 16u * 10u + 4u: return launch_dense<0, 10, 4>(a, pack, s);
+    case 16u * 9u + 4u: return launch_dense<0, 9, 4>(a, pack, s);
+    case 16u * 8u + 4u: return launch_dense<0, 8, 4>(a, pack, s);
+    case 16u * 7u + 5u: return launch_dense<0, 7, 5>(a, pack, s);
+    case 16u * 6u + 5u: return launch_dense<0, 6, 5>(a, pack, s);
+    case 16u * 6u + 6u: return launch_dense<0, 6, 6>(a, pack, s);
+    case 16u * 5u + 6u: return launch_dense<0, 5, 6>(a, pack, s);
+    case 16u * 5u + 7u: return launch_dense<0, 5, 7>(a, pack, s);
+    case 16u * 4u + 7u: return launch_dense<0, 4, 7>(a, pack, s);
+    case 16u * 4u + 8u: return launch_dense<0, 4, 8>(a, pack, s);
+    default: return NDQ_EUNSUPPORTED;      // cannot happen
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -762,38 +759,20 @@ static int dense_common(const void* fixed, const void* dense, size_t n, uint32_t
 {
     using namespace ndq;
     DenseArgs a;
-    a.k = ndq_dense_group(levels);
-    if (!a.k) return NDQ_EINVAL;
+    const uint32_t k = ndq_dense_group(levels);
+    if (!k) return NDQ_EINVAL;
     if (n == 0) return NDQ_OK;
     if (!fixed || !dense) return NDQ_EINVAL;
     if (n >= kMaxN) return NDQ_EUNSUPPORTED;
     if (!aligned16(fixed) || !aligned16(dense)) return NDQ_EALIGN;
+    const uint32_t bits = code_bits(levels);
     a.fixed = (unsigned char*)fixed;
     a.dense = (uint32_t*)dense;
     a.n = n;
     a.levels = levels;
-    a.bits = code_bits(levels);
-    a.shift = a.bits - 1u;      // bits = ceil(log2 levels) >= 1
-    a.magic = (uint32_t)((((uint64_t)1 << 32) * (((uint64_t)1 << a.bits) - levels)) / levels + 1u);
-    a.fixed_total = packed_bytes(n, a.bits);
-    a.dense_valid = ((uint64_t)n + a.k - 1u) / a.k;
+    a.fixed_total = packed_bytes(n, bits);
     a.dense_total = ndq_dense_bytes(n, levels) / 4u;
-    const uint64_t per_thread_bytes = (uint64_t)a.k * a.bits;
-    const uint64_t threads = pack ? (a.dense_total + 7u) / 8u
-                                  : (a.fixed_total + per_thread_bytes - 1u) / per_thread_bytes;
-    const uint64_t blocks = (threads + 255u) / 256u;
-    if (blocks >= ((uint64_t)1 << 31)) return NDQ_EUNSUPPORTED;
-    if (per_thread_bytes > kDenseThreadBytes) return NDQ_EUNSUPPORTED;   // cannot happen for levels <= 256
-    const dim3 grid((uint32_t)blocks), block(kDenseBlock);
-    hipStream_t s = (hipStream_t)stream;
-    if (levels == 3u && a.k == 20u && a.bits == 2u)
-        return pack ? launch((dense_pack_fixed_kernel<3, 20, 2>), grid, block, s, a)
-                    : launch((dense_unpack_fixed_kernel<3, 20, 2>), grid, block, s, a);
-    if (levels == 5u && a.k == 13u && a.bits == 3u)
-        return pack ? launch((dense_pack_fixed_kernel<5, 13, 3>), grid, block, s, a)
-                    : launch((dense_unpack_fixed_kernel<5, 13, 3>), grid, block, s, a);
-    if (pack) return launch(dense_pack_kernel, grid, block, s, a);
-    return launch(dense_unpack_kernel, grid, block, s, a);
+    return run_dense(a, k, bits, pack, (hipStream_t)stream);
 }
 
 int ndq_dense_pack(const void* codes, size_t n, uint32_t levels, void* dense_out, void* stream)
