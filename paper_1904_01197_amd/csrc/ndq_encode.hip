@@ -306,7 +306,7 @@ __device__ __forceinline__ void stage_to_stream(const EncodeArgs& a, const TileR
     const uint32_t units = (uint32_t)(nbytes >> 3);
     uint64_t* dst = (uint64_t*)(a.codes + byte0);
     const uint64_t* src = (const uint64_t*)stage;
-    for (uint32_t u = lane; u < units; u += kWave) dst[u] = src[u];
+    for (uint32_t u = lane; u < units; u += kWave) store_through(dst + u, src[u]);
 }
 
 // Occupancy target.  The bfloat16 encoder is bound by instruction issue with a
@@ -536,10 +536,10 @@ __device__ __forceinline__ void stage_to_stream_full(const EncodeArgs& a, const 
     const uint64_t* src = (const uint64_t*)stage;
     if constexpr (units % kWave == 0u) {
 #pragma unroll
-        for (uint32_t u = 0; u < units; u += kWave) dst[u + lane] = src[u + lane];
+        for (uint32_t u = 0; u < units; u += kWave) store_through(dst + u + lane, src[u + lane]);
     } else {
         static_assert(units < (uint32_t)kWave, "a partial store only for less than one unit per lane");
-        if ((uint32_t)lane < units) dst[lane] = src[lane];
+        if ((uint32_t)lane < units) store_through(dst + lane, src[lane]);
     }
 }
 
