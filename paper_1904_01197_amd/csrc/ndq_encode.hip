@@ -394,7 +394,9 @@ void encode_kernel(EncodeBatch by_value)
 // workgroup has a copy of them to itself, at the start of the codes it is going to write
 // (ShortShare; absmax_copies_kernel writes all the copies).
 // ---------------------------------------------------------------------------
-enum ShortForm { kFormBucket = 0, kFormMulti = 1, kFormBlock = 2, kFormVector = 3 };
+//         kFormLong: the same for long binary32 vectors of several quantizers, whose steps are all in memory: what
+//         is spared is the end of one launch and the start of the next (1 + 15 workers of 11.2 M: see run_long)
+enum ShortForm { kFormBucket = 0, kFormMulti = 1, kFormBlock = 2, kFormVector = 3, kFormLong = 4 };
 struct ShortJob : EncodeJob {
     Quant qp;
     uint64_t total_bytes;
@@ -402,6 +404,7 @@ struct ShortJob : EncodeJob {
     uint32_t variant;      // 8 * mode + code width
     uint32_t parts;        // kFormVector: parts to reduce; 0: the step is preset or in memory
     uint32_t levels;       // the parts' step: levels of the vector that chose it
+    uint32_t writes;       // kFormLong: 0 when the step already lies where it would be written
 };
 struct ShortBatch {
     ShortJob job[kEncJobs];
@@ -427,17 +430,17 @@ struct ShortShare {
 template <int DT, int FORM, int MODE, int BITSW>
 __device__ __forceinline__ void encode_short(const EncodeArgs& a, const TileRef& t, uint32_t tile_id, int wave, int lane,
                                              unsigned char* stage, float (&part)[kWavesPerBlock], uint32_t parts,
-                                             uint32_t levels, const float* copy)
+                                             uint32_t levels, uint32_t writes, const float* copy)
 {
-    if constexpr (FORM != kFormVector) {
+    if constexpr (FORM != kFormVector && FORM != kFormLong) {
         encode_wave<DT, MODE, true, FORM == kFormMulti, FORM == kFormBlock, BITSW>(a, t, tile_id, wave, lane, stage, part);
     } else {
         constexpr uint32_t TILE = EncTile<DT>::N;
         TileRegs<DT> regs;
-        if (t.len == TILE) load_tile<DT, true, true>(a.g, t, lane, regs);
-        else if (t.len != 0) load_tile<DT, false, true>(a.g, t, lane, regs);
+        if (t.len == TILE) load_tile<DT, true, FORM == kFormVector>(a.g, t, lane, regs);
+        else if (t.len != 0) load_tile<DT, false, FORM == kFormVector>(a.g, t, lane, regs);
         float step;
-        if (parts != 0u) {
+        if (FORM == kFormVector && parts != 0u) {
             const float mine = wave_max((uint32_t)threadIdx.x < parts ? copy[threadIdx.x] : 0.0f);
             if (lane == 0) part[wave] = mine;
             __syncthreads();     // and the copy has been read: the codes may take its place
@@ -448,7 +451,7 @@ __device__ __forceinline__ void encode_short(const EncodeArgs& a, const TileRef&
         } else {
             step = a.preset_step > 0.0f ? a.preset_step : a.step_in[0];
         }
-        if (tile_id == 0u && lane == 0) a.steps[0] = step;
+        if (tile_id == 0u && lane == 0 && (FORM == kFormVector || writes != 0u)) a.steps[0] = step;
         if (t.len == TILE) encode_tile<DT, MODE, false, true, false, BITSW, false, true>(a, t, tile_id, regs, step, false, stage, lane);
         else if (t.len != 0) encode_tile<DT, MODE, false, false, false, BITSW, false, true>(a, t, tile_id, regs, step, false, stage, lane);
         wave_lds_sync();
@@ -468,6 +471,7 @@ template <> struct ShortVariants<kFormVector> {
                                        8 * kNestedPow2Bounded + 4, 8 * kNestedAnyMBounded + 2, 8 * kNestedAnyMBounded + 3,
                                        8 * kNestedPow2 + 1, 8 * kNestedPow2 + 2, 8 * kNestedPow2 + 3, 8 * kNestedPow2 + 4>;
 };
+template <> struct ShortVariants<kFormLong> : ShortVariants<kFormVector> {};
 template <int... V>
 constexpr bool short_variant(uint32_t variant, std::integer_sequence<int, V...>) { return ((variant == (uint32_t)V) || ...); }
 
@@ -475,10 +479,10 @@ template <int DT, int FORM, int... V>
 __device__ __forceinline__ void encode_short_any(uint32_t variant, std::integer_sequence<int, V...>, const EncodeArgs& a,
                                                  const TileRef& t, uint32_t tile_id, int wave, int lane, unsigned char* stage,
                                                  float (&part)[kWavesPerBlock], uint32_t parts, uint32_t levels,
-                                                 const float* copy)
+                                                 uint32_t writes, const float* copy)
 {
     (void)((variant == (uint32_t)V
-                ? (encode_short<DT, FORM, V / 8, V % 8>(a, t, tile_id, wave, lane, stage, part, parts, levels, copy), true)
+                ? (encode_short<DT, FORM, V / 8, V % 8>(a, t, tile_id, wave, lane, stage, part, parts, levels, writes, copy), true)
                 : false) || ...);
 }
 
@@ -521,7 +525,7 @@ void encode_short_kernel(ShortBatch by_value)
     }
     const TileRef t = locate_tile(a.tl, tile_id, TILE);
     encode_short_any<DT, FORM>(job->variant, typename ShortVariants<FORM>::list{}, a, t, tile_id, wave, lane, stage_all[wave],
-                               part, job->parts, job->levels, copy);
+                               part, job->parts, job->levels, job->writes, copy);
 }
 
 // The same for a full tile that is not the vector's last, with the code width known
@@ -1069,6 +1073,42 @@ constexpr uint32_t kShortBucketTiles = 16384, kShortVectorTiles = 6144, kShortOn
 // 13.9 / 13.5-14.7 / 14.7, 15.1.
 constexpr uint32_t kShortCopies = 32768;
 
+static ShortJob short_job(const EncodePlan& p)
+{
+    ShortJob job;
+    static_cast<EncodeJob&>(job) = p.a;
+    job.qp = p.a.qp;
+    job.total_bytes = p.a.total_bytes;
+    job.preset_step = p.a.preset_step;
+    job.variant = 8u * (uint32_t)p.mode + p.a.qp.bits;
+    job.parts = 0u;
+    job.levels = 0u;
+    job.writes = p.two_pass ? 0u : 1u;
+    return job;
+}
+
+// Long binary32 vectors with one step each, of several quantizers, after the max-norm passes.  Iterations, a launch
+// per quantizer / this: 1 + 15 workers of 11.2 M elements 211 / 208.8 us, 1 + 7 of 4 M 65.4 / 62.2, 1 + 3 39.5 / 34.3, 1 + 1
+// 27.4 / 22.0.  bfloat16 has the streaming kernel.  Whether it applies; it then answers *rc.
+static bool run_long(const EncodePlan* plans, uint32_t jobs, int dt, uint32_t bucket, hipStream_t s, int* rc)
+{
+    if (dt != NDQ_F32 || bucket != 0u) return false;
+    bool one_quantizer = true;
+    for (uint32_t j = 0; j < jobs; ++j) {
+        if (!short_variant(8u * (uint32_t)plans[j].mode + plans[j].a.qp.bits, ShortVariants<kFormLong>::list{})) return false;
+        one_quantizer = one_quantizer && plans[j].a.qp.M == plans[0].a.qp.M && plans[j].a.qp.bits == plans[0].a.qp.bits;
+    }
+    if (one_quantizer) return false;
+    ShortBatch b;
+    for (uint32_t j = 0; j < jobs; ++j) b.job[j] = short_job(plans[j]);
+    b.tl = plans[0].a.tl;
+    b.rows_log2 = b.waves_log2 = 0u;
+    b.num_buckets = 1u;
+    b.groups = blocks_for(b.tl.total_tiles);
+    *rc = launch((encode_short_kernel<0, kFormLong>), dim3(b.groups, jobs), dim3(kBlock), s, b);
+    return true;
+}
+
 template <int DT>
 static bool run_short(const EncodePlan* plans, uint32_t jobs, uint32_t bucket, hipStream_t s, int* rc)
 {
@@ -1109,13 +1149,7 @@ static bool run_short(const EncodePlan* plans, uint32_t jobs, uint32_t bucket, h
             }
         const uint32_t launch_of = source == kEncJobs && sources != 0u ? 1u : 0u;
         ShortJob& job = b[launch_of].job[count[launch_of]++];
-        static_cast<EncodeJob&>(job) = plans[j].a;
-        job.qp = plans[j].a.qp;
-        job.total_bytes = plans[j].a.total_bytes;
-        job.preset_step = plans[j].a.preset_step;
-        job.variant = 8u * (uint32_t)plans[j].mode + plans[j].a.qp.bits;
-        job.parts = 0u;
-        job.levels = 0u;
+        job = short_job(plans[j]);
         if (source == kEncJobs) continue;
         if (plans[j].two_pass) {
             m.g[chosen++] = plans[j].a.g;
@@ -1188,6 +1222,7 @@ static int run_plans(const EncodePlan* plans, uint32_t jobs, int dt, uint32_t bu
         const int rc = dt == NDQ_F32 ? run_absmax<0>(m, need, s) : run_absmax<1>(m, need, s);
         if (rc != NDQ_OK) return rc;
     }
+    if (run_long(plans, jobs, dt, bucket, s, &rc_short)) return rc_short;
     bool done[kEncJobs] = {};
     for (uint32_t j = 0; j < jobs; ++j) {
         if (done[j]) continue;

@@ -80,7 +80,7 @@ def _jobs(plan, shared):
 @pytest.mark.parametrize("plan,n,bucket,shared,expected", [
     ([(0, 3)], 65536, 0, False, "m1"), ([(0, 3)], 4096 * 2048 + 1, 0, False, "mm1"),
     ([(0, 8), (1, 4)], 1 << 20, 0, True, "m2"), ([(0, 8), (1, 4)], 1 << 20, 0, False, "m2"),
-    ([(0, 16)] + [(1, 4)] * 15, 11173962, 0, True, "mm1" + "f"), ([(0, 16), (1, 100)], 70000, 0, False, "mm11"),
+    ([(0, 16)] + [(1, 4)] * 15, 11173962, 0, True, "mm10"), ([(0, 16), (1, 100)], 70000, 0, False, "mm11"),
     ([(0, 5)] * 4 + [(1, 3)] * 4, 266610, 0, False, "m8"), ([(0, 5)] * 4 + [(1, 3)] * 4, 266610, 2048, False, "8"),
     ([(0, 5)] * 4 + [(1, 3)] * 4, 16384 * 256 + 1, 2048, False, "44"), ([(0, 5)] * 8, 266610, 1024, False, "8")])
 def test_launches_of_short_calls(recorder, plan, n, bucket, shared, expected):
