@@ -171,7 +171,8 @@ int ndq_nested_encode_with_step(const void* g, int dt, size_t n, const float* st
 
 /* Several workers' vectors of one length and type, encoded by one call.  The bytes are
  * those of W calls of the functions above in the given order; what is saved is launches:
- * vectors that share a quantizer are one launch (up to 16 of them), the max-norm passes of
+ * vectors that share a quantizer are one launch (up to 16 of them; where the vectors are short, or long
+ * binary32 ones with one step each, those of all quantizers are), the max-norm passes of
  * a group are one launch, and no launch ends with an idle chip W times.
  *   kind, levels, M, alpha, dither: the worker's quantizer, as in ndq_dq_encode /
  *     ndq_nested_encode (M and alpha: nested workers only)
