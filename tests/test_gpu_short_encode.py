@@ -109,3 +109,41 @@ def test_copies_of_the_parts_stay_inside_every_share(recorder):
                 first = (groups - 1) * (tiles // groups) + min(groups - 1, tiles % groups)
                 assert parts[0] <= 256 and 4 * parts[0] <= oracle.packed_bytes(n, bits) - first * tile // 8 * bits, n
     assert seen > 200
+
+
+@pytest.mark.gpu
+def test_a_short_iteration_replayed_from_a_graph():
+    # copies of the parts, encoders of all quantizers and the short chain, with eager work between the replays
+    plan, n = [(DQ, 8), (NESTED, 4), (NESTED, 3)], 70001
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    grads = [torch.empty(n, device="cuda") for _ in plan]
+    codes = [torch.empty(ndq.ndq_packed_bytes(n, ndq.ndq_code_bits(arg)), dtype=torch.uint8, device="cuda") for _, arg in plan]
+    steps = [torch.empty(1, device="cuda") for _ in plan]
+    out = torch.empty(n, device="cuda")
+    ds = [ndq.ndq_dither(w, 1, w, 0) for w in range(3)]
+
+    def iteration():
+        ndq.ndq_encode_workers([(grads[w], kind, arg if kind == DQ else 16, 0 if kind == DQ else arg, 1.0, ds[w], codes[w],
+                                 steps[w], steps[0] if w else None) for w, (kind, arg) in enumerate(plan)], 0.0, 0)
+        ndq.ndq_decode_chain([(codes[w], steps[w], kind, arg, ds[w]) for w, (kind, arg) in enumerate(plan)], n, 0, 0.5, out)
+
+    def draw():
+        for g in grads:
+            g.copy_(torch.randn(n, device="cuda", generator=gen))
+
+    draw()
+    iteration()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        iteration()
+    for _ in range(4):
+        draw()
+        iteration()
+        torch.cuda.synchronize()
+        want = [t.clone() for t in codes + steps + [out]]
+        for t in codes + steps + [out]:
+            t.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(codes + steps + [out], want))
