@@ -1118,6 +1118,8 @@ static bool run_short(const EncodePlan* plans, uint32_t jobs, uint32_t bucket, h
     const uint64_t all_tiles = (uint64_t)first.tl.total_tiles * jobs;
     if (all_tiles > (vector ? kShortVectorTiles : kShortBucketTiles)) return false;
     if (!vector && !plans[0].fused) return false;       // (the form of a bucket is the same for all)
+    // (a streaming threshold from the environment means that kernel, whatever the length: see try_stream)
+    if (DT == 1 && stream_tuning().threshold_from_env && (vector || bucket == TILE)) return false;
     bool one_quantizer = true, several = false;
     uint32_t sources = 0u;
     for (uint32_t j = 0; j < jobs; ++j) {
