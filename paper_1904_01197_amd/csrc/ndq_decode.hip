@@ -1460,20 +1460,29 @@ static int run_chain_stream(const GeneralChainArgs& a, uint32_t bucket, uint32_t
                                : launch_chain_stream_w<kNestedPow2, 4>(b, bucket_len, wr, s);
 }
 
-// Longest vector chain_short_kernel takes.  us, this kernel / the other one, at 61 k, 267 k, 530 k, 1.05 M elements:
-//   against chain_stream_kernel                        against chain_kernel
-//   4 DQSG          3.4/3.9   3.9/4.1   5.0/4.3        2 DQSG of 5 levels      3.1/3.7  3.4/3.8   4.2/4.0   5.3/4.6
-//   1 + 3 nested    3.5/4.2   4.1/4.3   5.3/4.7        4 + 4 of ratio 3        4.8/9.5  5.9/9.6   7.8/10.0  10.6/10.5
-//   8 DQSG          4.3/5.8   5.2/5.9   7.1/6.2        16 DQSG of 5 levels     6.6/15.1 8.3/15.3  11.4/15.6 16.0/15.8
-//   1 + 7           4.7/6.4   5.7/6.6   7.7/7.1        8 + 8 nested            7.0/15.6 8.9/15.8  12.0/16.0 17.0/16.3
-//   1 + 15          7.4/11.1  9.2/11.3  12.6/12.2      1 + 15 of ratio 3       8.1/18.5 10.1/18.7 14.1/19.0 19.8/19.3
+// Longest vector chain_short_kernel takes.  A workgroup keeps all workers of a row in LDS, so a compute unit holds six of
+// them for up to 16 workers and three for more: the lines lie about where these rounds end.  Time over the other kernel's,
+// launches replayed from a graph / one call after the other, at 131 k, 262 k, 393 k, 459 k elements
+//   against chain_stream_kernel   2 workers     1.05/1.03  1.15/1.04  1.14/1.02  1.23/1.05   (3.0 against 2.7 us)
+//                                 3             0.97/1.03  1.05/1.03  1.15/1.06  1.20/1.06
+//                                 4             0.93/0.98  0.98/0.98  1.09/1.02  1.19/1.08
+//                                 8             0.83/0.82  0.90/0.87  1.00/0.94  1.15/1.04
+//                                 16            0.75/0.71  0.80/0.75  0.95/0.85  1.10/0.98
+//                                 20 to 32      0.71/0.64  0.77/0.70  0.88/0.83  1.27/1.19
+// and at 262 k, 393 k, 524 k, 655 k, 786 k, 918 k, 983 k
+//   against chain_kernel          2             0.92/0.99  0.94/0.98  1.02/1.00  1.06/1.01  1.14/1.06  1.17/1.08  1.19/1.10
+//                                 3             0.80/0.89  0.89/0.89  0.97/0.94  1.04/0.97  1.07/1.02  1.13/1.06  1.18/1.07
+//                                 4             0.73/0.79  0.82/0.83  0.89/0.89  0.94/0.92  0.99/0.96  1.06/1.01  1.12/1.04
+//                                 6, 8          0.64/0.66  0.72/0.71  0.81/0.77  0.86/0.84  0.94/0.89  1.02/0.96  1.09/1.03
+//                                 12, 16        0.56/0.51  0.66/0.57  0.76/0.67  0.80/0.76  0.89/0.86  0.98/0.95  1.06/1.03
+//                                 20 to 32      0.53/0.46  0.60/0.54  0.81/0.77  0.86/0.85  0.96/0.95  1.12/1.12  1.19/1.19
 // One worker alone has nothing to wait for twice.  (A streaming threshold from the environment means that
 // kernel, whatever the length.)
 static uint32_t short_chain_most(uint32_t W, bool streams)
 {
-    if (W < 2u || (streams && stream_tuning().threshold_from_env)) return 0u;
-    if (streams) return 262144u + 16384u * (W < 16u ? W : 16u);
-    return 131072u * (W < 7u ? W + 1u : 8u);
+    if (!streams) return W < 2u ? 0u : 131072u * (W > 16u ? 6u : W < 6u ? W + 1u : 7u);
+    if (W < 4u || stream_tuning().threshold_from_env) return 0u;
+    return 196608u + 12288u * (W < 16u ? W : 16u);
 }
 
 }  // namespace ndq

@@ -12,13 +12,16 @@ from paper_1904_01197_amd import ndq
 pytestmark = pytest.mark.gpu
 
 F = np.float32
-# lines: streamable plans 262,144 + 16,384 W elements, others 131,072 (W + 1), both up to a number of workers
+# lines: plans that stream, from four workers on, 196,608 + 12,288 W elements, others 131,072 (W + 1), both up to a
+# number of workers; one or two lengths are further up, where both sides of it go to the same kernel
 PLANS = [
     ((("dq", 4), ("nested", 2)), 4, 0, 0.5, (294912,)),
     ((("dq", 16),) * 3, 16, 1024, 1.0, (311296,)),
+    ((("dq", 4), ("nested", 2), ("nested", 2), ("nested", 2)), 4, 0, 0.25, (245760,)),
+    ((("dq", 16),) + (("nested", 4),) * 7, 16, 1024, 1.0, (294912,)),
     ((("dq", 8), ("nested", 3), ("dq", 256), ("nested", 100), ("nested", 8)), 8, 0, 1.0, (786432,)),
-    ((("dq", 5),) * 4 + (("nested", 3),) * 5, 5, 192, 1.0 / 9, (1048576,)),      # nine workers: sixteen slots
-    ((("dq", 2),) + (("nested", 4),) * 16, 4, 64, 1.0, (524288,)),               # 17: thirty-two slots, every bucket in a row
+    ((("dq", 5),) * 4 + (("nested", 3),) * 5, 5, 192, 1.0 / 9, (917504, 1048576)),      # nine workers: sixteen slots
+    ((("dq", 2),) + (("nested", 4),) * 16, 4, 64, 1.0, (393216, 524288)),               # 17: thirty-two slots, every bucket in a row
     ((("dq", 3),) * 32, 3, 512, 1.0 / 32, ()),
 ]
 

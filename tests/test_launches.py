@@ -142,3 +142,19 @@ def test_a_streaming_threshold_from_the_environment_reaches_the_persistent_encod
     for call, (rc, launches) in zip(calls, lr.record(recorder, calls, env)):
         encoders = [(name, x) for name, x, _ in launches if "absmax" not in name and "fill_zero" not in name]
         assert rc == 0 and encoders and all("encode_stream_kernel" in name and x <= 3 for name, x in encoders), (call, launches)
+
+
+# longest vector that the kernel for short chains takes, by its plan: (kind, levels or M) of every worker
+@pytest.mark.parametrize("plan,most", [
+    ([(0, 16)] * 3, 0), ([(0, 16), (1, 4)], 0), ([(0, 16)] * 4, 245760), ([(0, 4)] + [(1, 2)] * 7, 294912),
+    ([(0, 16)] + [(1, 4)] * 15, 393216), ([(0, 16)] * 32, 393216), ([(0, 5)], 0), ([(0, 8), (1, 4)], 393216),
+    ([(0, 5)] * 2 + [(1, 3)] * 2, 655360), ([(0, 5)] * 5, 786432), ([(0, 16)] * 8 + [(1, 4)] * 8, 917504),
+    ([(0, 8)] + [(1, 8)] * 31, 786432)])
+def test_longest_vector_of_the_short_chain_kernel(recorder, plan, most):
+    workers = [{"codes": 0x20000000, "steps": 0x30000000, "kind": kind, "levels_or_M": arg, "alpha": 1.0,
+                "dither": [1, 2, 3, 0]} for kind, arg in plan]
+    sizes = [most, most + 1] if most else [1, 512, 65536]
+    calls = [["ndq_decode_chain", workers, len(workers), n, 0, 1.0, 0x40000000, None] for n in sizes]
+    for n, (rc, launches) in zip(sizes, lr.record(recorder, calls)):
+        assert rc == 0 and len(launches) == 1
+        assert ("chain_short_kernel" in launches[0][0]) == (n <= most), (n, launches)
