@@ -897,6 +897,33 @@ __device__ __forceinline__ void redo_out_of_range(ChainArgsPtr a, uint32_t first
     }
 }
 
+// The one-tile forms of few workers are bound by their stores: a lane's eight results are 32 bytes, so a store of 16 bytes a
+// lane half-writes every sector (see PIPED below).  Four neighbouring lanes put their results in order first (quad
+// permutations, 24 instructions a row), and the two stores that share 128-byte lines follow each other at once (with the second's
+// permutations between them half of the gain is lost): 2 DQSG workers of 5.2 M elements 7.9 -> 6.2 us, 1 + 1 nested of 8.4 M
+// 10.9 -> 8.8, 3 DQSG of 8.4 M 10.9 -> 10.2; from four workers on (three with nested ones) the
+// instructions cost as much as the stores gain, or 1-2 % more.
+__device__ __forceinline__ void store_row_lines(float* row, int lane, const float (&s)[8])
+{
+    const bool odd = (lane & 1) != 0;
+    float front[4], back[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int lo = (int)__float_as_uint(s[k]), hi = (int)__float_as_uint(s[4 + k]);
+        // quad_perm [0,0,1,1]: the sixteen results of the first two lanes; [2,2,3,3]: of the other two
+        const int fl = __builtin_amdgcn_update_dpp(0, lo, 0x50, 0xF, 0xF, false);
+        const int fh = __builtin_amdgcn_update_dpp(0, hi, 0x50, 0xF, 0xF, false);
+        const int bl = __builtin_amdgcn_update_dpp(0, lo, 0xFA, 0xF, 0xF, false);
+        const int bh = __builtin_amdgcn_update_dpp(0, hi, 0xFA, 0xF, 0xF, false);
+        front[k] = __uint_as_float((uint32_t)(odd ? fh : fl));
+        back[k] = __uint_as_float((uint32_t)(odd ? bh : bl));
+    }
+    float* p = row + (lane & ~3) * 8 + (lane & 3) * 4;
+    __builtin_amdgcn_sched_barrier(0);        // the two stores next to each other: they share their 128-byte lines
+    store_streaming(p, front[0], front[1], front[2], front[3]);
+    store_streaming(p + 16, back[0], back[1], back[2], back[3]);
+}
+
 // RAGGED: the vector ends in a ragged tile.  An instantiation of its own, because the mere
 // presence of that code in the kernel measured 6 % on the main loop (config 5, which has
 // no ragged tile: 215 against 203 us) although the loop's instructions are the same.
@@ -1031,17 +1058,25 @@ void chain_stream_kernel(ChainArgs a_by_value)
         float* out = out_base + start;
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) {
-            const uint32_t o = (uint32_t)(r * kWave + lane) * kLaneElems;
             if (apply_scale) {       // wave-uniform
 #pragma unroll
                 for (int k = 0; k < 8; ++k) S[r][k] = scale * S[r][k];
             }
             if (PIPED) {
+                const uint32_t o = (uint32_t)(r * kWave + lane) * kLaneElems;
                 *(float4*)(out_stage + o) = make_float4(S[r][0], S[r][1], S[r][2], S[r][3]);
                 *(float4*)(out_stage + o + 4) = make_float4(S[r][4], S[r][5], S[r][6], S[r][7]);
-            } else {
-                store_streaming(out + o, S[r][0], S[r][1], S[r][2], S[r][3]);
-                store_streaming(out + o + 4, S[r][4], S[r][5], S[r][6], S[r][7]);
+            }
+        }
+        if (!PIPED && W < (RMODE == kDq ? 4u : 3u)) {
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) store_row_lines(out + r * kWave * kLaneElems, lane, S[r]);
+        } else if (!PIPED) {
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) {
+                float* p = out + (r * kWave + lane) * kLaneElems;
+                store_streaming(p, S[r][0], S[r][1], S[r][2], S[r][3]);
+                store_streaming(p + 4, S[r][4], S[r][5], S[r][6], S[r][7]);
             }
         }
         if (PIPED) {
@@ -1340,20 +1375,20 @@ static int decode_common(const void* codes, size_t n, uint32_t levels, uint32_t 
 
 // Tiles (of 1,024 elements) from which the persistent form of chain_stream_kernel is taken, for `slots`
 // wave slots.  With only a few tiles per wave a fixed share leaves SIMDs idle at the end; the hand-ordered fold makes
-// up for it the sooner the more there is to fold.  Persistent time over one tile per wave's, three
-// runs each, at 2.1 / 3.2 / 4.2 / 5.2 / 7.5 / 8.5 / 10.5 / 12.5 / 18 M elements:
-//   1 DQSG    0.98 0.95 0.94 0.90 0.75 0.73 0.68 0.75 0.70   bound by its stores (5.7 to 7.0 us up to 5.2 M)
-//   2 DQSG    1.21 1.11 1.16 1.08 0.95 0.96 0.80 0.95 0.79
-//   3 DQSG    1.22 1.11 1.18 1.12 1.12 1.06 1.02 0.98 0.93
-//   4 DQSG    1.15 1.03 1.13 1.14 1.08 1.03 0.99 0.99 0.94
-//   8 DQSG    1.04 0.99 1.04 1.06 1.00 0.98 0.96 0.96 0.94
-//   2 (1 nested) 1.22 1.11 1.23 1.16 1.10 1.06 1.04 1.07 1.07
-//   3 (2 nested) 1.16 1.07 1.15 1.12 1.05 1.04 1.01 1.01 0.96
-//   4 (3 nested) 1.10 1.03 1.08 1.07 1.03 1.01 0.96 0.96 0.94   (1-bit: 0.97 at 7.5 M)
-//   8 (7 nested) 1.02 0.97 0.99 0.97 0.95 0.92 0.91 0.92 0.90
-//   16 (15 nested) 0.96 0.92 0.93 0.94 0.90 0.90 0.88 0.89 0.87
-// Just above one tile per slot every plan takes it: a second round of one-tile waves would be
-// nearly empty (6.4 M: 0.82 to 1.00).
+// up for it the sooner the more there is to fold.  Persistent time over one tile per wave's
+// at 2.1 / 3.2 / 4.2 / 5.2 / 7.5 / 8.4 / 10.5 / 12.5 M elements:
+//   1 DQSG    1.14 0.98 0.96 0.87 0.84 0.80 0.76 0.70   bound by its stores
+//   2 DQSG    1.11 1.08 1.14 1.05 0.91 0.95 0.88 0.85
+//   3 DQSG    1.06 1.04 1.06 1.08 1.04 1.07 0.98 0.98
+//   4 DQSG    1.03 1.02 1.05 1.05 1.01 0.97 0.98 0.96
+//   8 DQSG    0.99 1.02 1.01 1.02 1.06 1.01 1.00 0.99
+//   2 (1 nested) 1.13 1.04 1.15 1.15 1.03 1.12 1.00 1.00
+//   3 (2 nested) 1.09 1.05 1.11 1.06 1.05 1.04 1.02 1.00
+//   4 (3 nested) 1.09 1.03 1.10 1.08 1.06 1.04 1.01 0.99
+//   8 (7 nested) 1.02 1.00 1.03 1.03 1.01 1.01 1.00 1.01
+//   16 (15 nested) 0.98 0.98 1.01 1.01 1.00 1.00 1.00 0.99
+// Just above one tile per slot every plan takes it: a second round of one-tile waves is
+// nearly empty (6.4 M: 2 workers 0.93 to 0.99, 3 DQSG 0.99, 4 DQSG 1.02, 4 with nested ones 1.06).
 static uint32_t persistent_from(uint32_t W, bool all_dq, uint32_t slots)
 {
     if (W == 1u) return kShortTiles;

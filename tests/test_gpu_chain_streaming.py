@@ -71,3 +71,21 @@ def test_short_vectors_take_one_row_per_wave(plan, fine, bucket):
     for n in (1, 7, 8, 63, 511, 512, 513, 520, 575, 1024 + 65, 2047 * 1024 + 1023, 2048 * 1024, 4096 * 1024 - 8,
               4096 * 1024 + 1):
         _check(plan, fine, bucket, _gradients(len(plan), n, n), 8 * (n % 513), 0.25)
+
+
+@pytest.mark.parametrize("plan,fine,bucket,sizes", [
+    # one tile per wave, of one row and of two, on both sides of the plans whose lanes put results in order before
+    # the store: whole tiles, a row more, ragged ends
+    ((("dq", 16),), 16, 0, (1024 * 700, 1024 * 700 + 517)),
+    ((("dq", 4), ("dq", 16)), 16, 0, (1, 512, 515, 1024 * 700 + 5, 1024 * 2047 + 513, 1024 * 2100, 1024 * 2100 + 1)),
+    ((("dq", 4), ("nested", 2)), 4, 2048, (7, 513, 1024 * 700 + 520, 1024 * 2100 + 1023)),
+    ((("dq", 16),) * 3, 16, 0, (1024 * 700 + 511, 1024 * 2100 + 512)),
+    ((("dq", 4), ("nested", 4), ("nested", 4)), 16, 0, (1024 * 700 + 8, 1024 * 2100 + 8)),
+    # the general kernel's code loads at the stream's end, a worker of every width it has alone
+    ((("dq", 8),), 8, 0, (1, 7, 8, 63, 511, 513, 520, 575, 1089)), ((("dq", 32),), 32, 0, (1, 7, 8, 63, 511, 513, 520, 575, 1089)),
+    ((("dq", 64),), 64, 0, (1, 7, 8, 63, 511, 513, 520, 575, 1089)), ((("dq", 128),), 128, 0, (1, 7, 8, 63, 511, 513, 520, 575, 1089)),
+    ((("dq", 256),), 256, 0, (1, 7, 8, 63, 511, 513, 520, 575, 1089))])
+def test_few_workers_match_oracle(plan, fine, bucket, sizes):
+    for n in sizes:
+        print(plan, bucket, n, flush=True)
+        _check(plan, fine, bucket, _gradients(len(plan), n, n), 8 * (n % 513), 0.75)
