@@ -512,6 +512,12 @@ __device__ __forceinline__ void store_streaming(float* p, float a, float b, floa
 // leave the L2 at once too, but their lines do not stay in the memory-side cache for the decoder.  us, plain / nontemporal /
 // this: encoders of 8 x 25.6 M binary32, 4-bit codes, 173 / 161 / 162; 16 x 11.2 M 154 / 144 / 144; the iterations
 // 228 / 220 / 219, 220 / 210 / 210, 4 x 2^27 bfloat16 394 / 410 / 386.
+// Codes of 1 and 2 bits of a binary32 tile are only 256 and 512 bytes: plain stores are the better ones there until the
+// gradients are far larger than the caches.  This over plain, encoders of buckets of 2,048: 1 bit, 1 x 11 M 1.05, 1 x 25.6 M 1.09,
+// 4 x 11 M 1.06, 4 x 25.6 M 1.00-1.03, 8 x 25.6 M 0.97; 2 bits, 1 x 11 M 1.04, 1 x 25.6 M 1.07, 4 x 11 M 1.02, 1 x 67 M 0.95, 4 x 25.6 M 0.91;
+// iterations 1.03, 1.02, 1.04, 1.01, 0.97 and 0.99, 1.02, 1.01, 0.95, 0.95.  16 x 4 M 0.98.  So from 120 M bits of codes in a launch on.
+// Persistent bfloat16 encoders with one step for the vector, 1 and 2 bits: 1 x 67 M 1.02-1.05, 4 x 25.6 M 1.01-1.04, iterations
+// 1.00-1.01; with a step per tile 0.95-0.98.
 __device__ __forceinline__ void store_through(uint64_t* p, uint64_t x)
 {
     __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -264,3 +264,31 @@ def test_steps_of_a_batch_in_every_form_of_the_max_norm_pass(dtype, W, n, bucket
                               oracle.dither(W - 1, 3, W - 1))
     if bucket == 0:
         assert codes[W - 1][:m // 8].cpu().numpy().tobytes() == ref[:m // 8].tobytes()
+
+
+@pytest.mark.parametrize("kind,arg,bucket", [("dq", 3, 2048), ("nested", 4, 512), ("dq", 2, 8192), ("dq", 3, 0), ("nested", 2, 0)])
+def test_codes_stored_through_the_cache_or_not_are_the_same(kind, arg, bucket):
+    # narrow codes of binary32 vectors: stored through the L2 when a launch has 120 M bits of them, else plainly; sixteen
+    # vectors in one call against one call each, and the last one against the oracle
+    bits = ndq.ndq_code_bits(arg)
+    n, W = (1 << 23) // bits + 77, 16
+    gen = torch.Generator(device="cuda").manual_seed(arg)
+    grads = [torch.randn(n, device="cuda", generator=gen) for _ in range(W)]
+    ds = [ndq.ndq_dither(w, 3, w, 0) for w in range(W)]
+
+    def encode(which):
+        codes = [torch.full((ndq.ndq_packed_bytes(n, bits),), 0xA5, dtype=torch.uint8, device="cuda") for _ in which]
+        steps = [torch.empty(ndq.ndq_num_buckets(n, bucket), device="cuda") for _ in which]
+        ndq.ndq_encode_workers([(grads[w], ndq.NDQ_WORKER_DQ if kind == "dq" else ndq.NDQ_WORKER_NESTED,
+                                 arg if kind == "dq" else 16, 0 if kind == "dq" else arg, 1.0, ds[w], c, s, None)
+                                for w, c, s in zip(which, codes, steps)], 0.0, bucket)
+        return codes, steps
+
+    codes, steps = encode(range(W))
+    for w in range(W):
+        (c,), (s,) = encode([w])
+        assert torch.equal(codes[w], c) and torch.equal(steps[w], s), w
+    d = oracle.dither(W - 1, 3, W - 1)
+    host = grads[-1].cpu().numpy()
+    ref = oracle.dq_encode(host, 0.0, arg, bucket, d) if kind == "dq" else oracle.nested_encode(host, 0.0, 16, arg, bucket, d)
+    assert codes[-1].cpu().numpy().tobytes() == ref[0].tobytes() and np.array_equal(steps[-1].cpu().numpy(), ref[1])
