@@ -519,7 +519,8 @@ void encode_short_kernel(ShortBatch by_value)
     a.rows_log2 = batch->rows_log2;
     a.num_buckets = batch->num_buckets;
     a.waves_log2 = batch->waves_log2;
-    a.through = job->through;
+    // (short launches: a step per vector 6.3 us through the L2 and 6.5 plainly, 2 x 61 k; buckets 8.4 and 8.1, 4 x 2 M)
+    a.through = FORM == kFormLong ? job->through : FORM == kFormVector ? 1u : 0u;
     constexpr uint32_t TILE = EncTile<DT>::N;
     __shared__ __align__(16) unsigned char stage_all[kWavesPerBlock][TILE / 2 + 8];      // at most 4 bits a code
     __shared__ float part[kWavesPerBlock];
