@@ -1080,11 +1080,27 @@ static int run_encode_mode(const EncodeBatch& b, const EncodePlan& p, uint32_t b
 // calls, us, this / a launch per quantizer, W vectors of n elements:
 //   binary32, buckets of 1,024     8 + 8   61 k 5.4/8.9    267 k 7.1/11.4   1.05 M 14.8/17.4   1.66 M 23.3/25.2   3 M 40.5/40.4
 //   bfloat16, buckets of 4,096     8 + 8   61 k 5.3/10.5   267 k 6.9/12.9   1.05 M 10.1/13.4   1.66 M 15.0/19.6   3 M 24.3/27.5
-//   binary32, a step per vector    1 + 1   61 k 9.0/16.0   267 k 9.5/16.0   1.05 M 9.4/15.1
-//                                  4 + 4   61 k 9.0/15.8   267 k 10.4/17.7  1.05 M 13.3/17.9   1.66 M 24.9/27.1   3 M 40.1/38.6
-//                                  16      61 k 9.3/12.6   267 k 10.4/13.5  530 k 14.3/16.0    1.05 M 26.9/24.8
-// so buckets up to 16,384 tiles in all, steps per vector up to 6,144 or, with one quantizer, 4,096.
-constexpr uint32_t kShortBucketTiles = 16384, kShortVectorTiles = 6144, kShortOneQuantizerTiles = 4096;
+// so buckets up to 16,384 tiles in all.  A step per vector: this over the max-norm pass with its closing kernel and the
+// encoders after it (binary32: one launch of those too, see run_long), and in brackets where it is not taken:
+//   binary32   1        61 k 0.88   267 k 0.89   1.05 M 0.91   1.66 M 0.95  (2.2 M 1.05)
+//              2        61 k 0.84   267 k 0.85   1.05 M 0.89   1.3 M 0.94   1.66 M 1.02
+//              4        61 k 0.87   267 k 0.90   660 k 0.85    800 k 1.04   1.05 M 0.94  (1.3 M 1.09)
+//              8        61 k 0.86   267 k 0.85   530 k 1.02   (800 k 1.08   930 k 1.10)
+//              16       61 k 0.93   267 k 0.92   400 k 0.97   (530 k 1.10)
+//              1 + 1    61 k 0.83   267 k 0.88   1.05 M 0.87   1.66 M 0.98
+//              4 + 4    61 k 0.85   267 k 0.85   530 k 0.99   (800 k 1.04   930 k 1.06)
+//      shared step      61 k 0.97   267 k 0.94   530 k 1.01   (800 k 1.08)
+//      1 + 15 shared   (61 k 1.11   267 k 1.09   530 k 1.10)
+//   bfloat16   1        61 k 0.91   267 k 0.94   1.05 M 0.93   2.2 M 0.96   3 M 0.99     (4.5 M 1.08)
+//              4        61 k 0.91   267 k 0.93   1.05 M 0.91   1.66 M 1.04  (2.2 M 1.03)
+//              16       61 k 0.95   267 k 0.94   530 k 0.98    800 k 1.03   (930 k 1.12)
+//              1 + 1    61 k 0.62   267 k 0.62   1.05 M 0.64   2.2 M 0.72   3 M 0.79
+//              4 + 4    61 k 0.63   267 k 0.62   1.05 M 0.76   1.66 M 0.86
+//      1 + 15 shared    61 k 0.77   267 k 0.72   800 k 0.96    1.05 M 1.07
+// What it costs are the copies: the more of them, the fewer workgroups the pass has (kShortCopies), and where one of those
+// takes the tiles of three workgroups of the encoder, or of two and the others of one, it is what everything waits for.
+constexpr uint32_t kShortBucketTiles = 16384, kShortVectorTiles = 6144;
+template <int DT> constexpr uint32_t kShortOneQuantizerTiles = DT == 0 ? 4096 : 3200;
 // Copies of parts to write, at most: every one is a store to a line of its own.  Iterations of 4 x 1.66 M elements, us, with at
 // most 16 k / 32 k / 64 k / 128 k copies: 22.2-23.7 / 22.1 / 22.8-23.1 / 24.1-24.4, with absmax_finish_kernel 22.2; 4 x 900 k: 14.5-15.6 /
 // 13.9 / 13.5-14.7 / 14.7, 15.1.
@@ -1156,7 +1172,7 @@ static bool run_short(const EncodePlan* plans, uint32_t jobs, uint32_t bucket, h
         if (vector && plans[j].two_pass) ++sources;
     }
     if (sources == 0u && !several) return false;
-    if (vector && one_quantizer && all_tiles > kShortOneQuantizerTiles) return false;
+    if (vector && one_quantizer && all_tiles > kShortOneQuantizerTiles<DT>) return false;
     ShortBatch b[2];        // the vectors of the first launch, and those of a second one
     uint32_t count[2] = {0u, 0u};
     CopiesBatch m;
@@ -1199,6 +1215,10 @@ static bool run_short(const EncodePlan* plans, uint32_t jobs, uint32_t bucket, h
         if (parts > bytes / 4u) parts = (uint32_t)(bytes / 4u);
         if (parts > kShortCopies / (groups * m.users)) parts = kShortCopies / (groups * m.users);
         if (parts == 0u || (4u * parts < groups && parts * sources < 256u)) return false;
+        // no more than two of the encoder's workgroups for one of the pass, unless all have the same number: with one quantizer,
+        // or binary32, a launch is all there is to spare
+        if ((DT == 0 || one_quantizer) && 2u * parts < groups && groups % parts != 0u) return false;
+        if (DT == 0 && m.users > 8u && sources < m.users) return false;
         for (uint32_t u = 0; u < m.users; ++u) b[0].job[u].parts = parts;
         m.tl = first.tl;
         m.groups = groups;

@@ -82,7 +82,11 @@ def _jobs(plan, shared):
     ([(0, 8), (1, 4)], 1 << 20, 0, True, "m2"), ([(0, 8), (1, 4)], 1 << 20, 0, False, "m2"),
     ([(0, 16)] + [(1, 4)] * 15, 11173962, 0, True, "mm10"), ([(0, 16), (1, 100)], 70000, 0, False, "mm11"),
     ([(0, 5)] * 4 + [(1, 3)] * 4, 266610, 0, False, "m8"), ([(0, 5)] * 4 + [(1, 3)] * 4, 266610, 2048, False, "8"),
-    ([(0, 5)] * 4 + [(1, 3)] * 4, 16384 * 256 + 1, 2048, False, "44"), ([(0, 5)] * 8, 266610, 1024, False, "8")])
+    ([(0, 5)] * 4 + [(1, 3)] * 4, 16384 * 256 + 1, 2048, False, "44"), ([(0, 5)] * 8, 266610, 1024, False, "8"),
+    # three workgroups of the encoder for one of the max-norm pass; more than eight vectors that are handed a step
+    ([(0, 3)], 1663370, 0, False, "m1"), ([(0, 3)], 2200000, 0, False, "mm1"), ([(0, 3)] * 4, 800000, 0, False, "m4"),
+    ([(0, 3)] * 4, 1300000, 0, False, "mm4"), ([(0, 3)] * 4, 1 << 20, 0, False, "m4"), ([(0, 16)] * 8, 800000, 0, False, "mm8"),
+    ([(0, 16)] + [(1, 4)] * 7, 266610, 0, True, "m8"), ([(0, 16)] + [(1, 4)] * 8, 266610, 0, True, "mm9")])
 def test_launches_of_short_calls(recorder, plan, n, bucket, shared, expected):
     (rc, launches), = lr.record(recorder, [["ndq_encode_workers", _jobs(plan, shared), len(plan), 0, n, 0.0, bucket, None]])
     text = "".join("m" if "absmax" in name else "%x" % y for name, _, y in launches)
