@@ -158,3 +158,12 @@ def test_longest_vector_of_the_short_chain_kernel(recorder, plan, most):
     for n, (rc, launches) in zip(sizes, lr.record(recorder, calls)):
         assert rc == 0 and len(launches) == 1
         assert ("chain_short_kernel" in launches[0][0]) == (n <= most), (n, launches)
+
+
+@pytest.mark.parametrize("dt,M,bucket,width", [(1, 3, 64, 0), (1, 3, 448, 0), (1, 3, 512, 2), (1, 3, 4096, 2), (1, 7, 64, 3), (0, 3, 64, 2),
+                                               (1, 4, 64, 2)])
+def test_encoders_that_know_their_code_width(recorder, dt, M, bucket, width):
+    call = ["ndq_nested_encode", 0x10000000, dt, 100000, 0.0, 16, M, 1.0, bucket, D, 0x20000000, 0x30000000, None]
+    (rc, launches), = lr.record(recorder, [call])
+    assert rc == 0 and len(launches) == 1
+    assert ("ELi%dEEEvNS_11EncodeBatch" % width) in launches[0][0], launches
