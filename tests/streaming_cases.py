@@ -121,10 +121,15 @@ def chain_cases():
         ((("dq", 3),), 3, 0, 1.0, False),
         ((("dq", 4), ("dq", 2)), 4, 3072, 0.5, False),
     ]
+    # every pair of code widths of the first worker and the others, all DQSG and nested
+    pairs = [((("dq", first),) + ((kind, other),) * 2, 16, 0, 0.5, False)
+             for first in (2, 4, 16) for other in (2, 4, 16) for kind in ("dq", "nested")]
+    plans += pairs
     for plan, fine, bucket, scale, shared in plans:
         # whole tiles only (the hand-ordered fold with results staged through LDS: one, several
         # and unequal numbers of tiles per wave), then ragged ends (the plain fold)
-        for n in (1024 * 12, 1024 * 40, 1024 * 129, 1024 * 37 + 100, 1024 * 150 + 1023, 1024 * 3 + 8):
+        sizes = (1024 * 12, 1024 * 40, 1024 * 129, 1024 * 37 + 100, 1024 * 150 + 1023, 1024 * 3 + 8)
+        for n in sizes[1:5:2] if (plan, fine, bucket, scale, shared) in pairs else sizes:
             print("chain", plan, bucket, n, flush=True)
             rng = np.random.default_rng(n + len(plan))
             common = rng.standard_normal(n) * 0.01

@@ -89,3 +89,18 @@ def test_few_workers_match_oracle(plan, fine, bucket, sizes):
     for n in sizes:
         print(plan, bucket, n, flush=True)
         _check(plan, fine, bucket, _gradients(len(plan), n, n), 8 * (n % 513), 0.75)
+
+
+@pytest.mark.parametrize("kind", ["dq", "nested"])
+@pytest.mark.parametrize("first", [2, 4, 16])
+@pytest.mark.parametrize("other", [2, 4, 16])
+def test_one_tile_forms_of_every_pair_of_widths_match_oracle(kind, first, other):
+    # one row per wave and two, whole tiles and a ragged end
+    for n in (1024 * 700, 1024 * 700 + 517, 1024 * 2100, 1024 * 2100 + 517):
+        print(kind, first, other, n, flush=True)
+        _check((("dq", first),) + ((kind, other),) * 2, 16, 0, _gradients(3, n, n + other), 64, 0.5)
+
+
+def test_buckets_of_a_row_with_a_ratio_that_is_no_power_of_two():
+    n = 2050 * 1024 + 77
+    _check((("dq", 4), ("nested", 3)), 4, 512, _gradients(2, n, 5), 8, 0.5)

@@ -25,7 +25,8 @@ PLANS = {                                                    # (kind, levels or 
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("name", list(PLANS))
-@pytest.mark.parametrize("bucket,shared", [(0, False), (0, True), (512, False), (1024, False), (4096, False), (8192, False)])
+@pytest.mark.parametrize("bucket,shared", [(0, False), (0, True), (512, False), (1024, False), (4096, False), (8192, False),
+                                           (192, False), (2048, False)])
 def test_short_vectors_match_oracle(dtype, name, bucket, shared):
     plan = PLANS[name]
     tile = 2048 if dtype == "f32" else 4096
