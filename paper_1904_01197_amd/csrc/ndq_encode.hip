@@ -43,7 +43,7 @@ struct EncodeArgs : EncodeJob {
     uint32_t rows_log2;    // MULTI: a bucket is 2^rows_log2 rows of a tile
     uint32_t num_buckets;  // MULTI: buckets in the call (steps to write)
     uint32_t waves_log2;   // FUSED, not MULTI: a bucket is 2^waves_log2 tiles of one workgroup
-    uint32_t through;      // binary32: how codes of 1 and 2 bits are stored (codes_through)
+    uint32_t through;      // binary32, buckets: how codes of 1 and 2 bits are stored
 };
 
 // A launch encodes up to kEncJobs vectors of one length, type and quantizer (blockIdx.y, or
@@ -298,8 +298,9 @@ __device__ __forceinline__ void encode_tile(const EncodeArgs& a, const TileRef& 
     if (lane == 0) *(uint64_t*)(stage + (size_t)EncTile<DT>::N / 8 * bits) = 0;  // pad unit
 }
 
-// Copies a tile's packed codes from the wave's stage to the stream, 8 bytes per lane.
-template <int DT>
+// Copies a tile's packed codes from the wave's stage to the stream, 8 bytes per lane.  BUCKETS: a step per bucket
+// (which stores: see store_through).
+template <int DT, bool BUCKETS>
 __device__ __forceinline__ void stage_to_stream(const EncodeArgs& a, const TileRef& t, uint32_t bits,
                                                 const unsigned char* stage, int lane)
 {
@@ -309,7 +310,7 @@ __device__ __forceinline__ void stage_to_stream(const EncodeArgs& a, const TileR
     const uint32_t units = (uint32_t)(nbytes >> 3);
     uint64_t* dst = (uint64_t*)(a.codes + byte0);
     const uint64_t* src = (const uint64_t*)stage;
-    if (DT == 1 || bits > 2u || a.through != 0u) {
+    if (DT == 1 || !BUCKETS || bits > 2u || a.through != 0u) {
         for (uint32_t u = lane; u < units; u += kWave) store_through(dst + u, src[u]);
     } else {
         for (uint32_t u = lane; u < units; u += kWave) dst[u] = src[u];
@@ -371,7 +372,7 @@ __device__ __forceinline__ void encode_wave(const EncodeArgs& a, const TileRef& 
         encode_tile<DT, MODE, FUSED, false, MULTI, BITSW>(a, t, tile_id, regs, kappa, true, stage, lane);
     }
     wave_lds_sync();     // a wave copies out only the stage it filled itself
-    if (t.len != 0) stage_to_stream<DT>(a, t, bits, stage, lane);
+    if (t.len != 0) stage_to_stream<DT, FUSED>(a, t, bits, stage, lane);
 }
 
 template <int DT, int MODE, bool FUSED, bool MULTI, bool BLOCK, int BITSW = 0>
@@ -412,7 +413,6 @@ struct ShortJob : EncodeJob {
     uint32_t parts;        // kFormVector: parts to reduce; 0: the step is preset or in memory
     uint32_t levels;       // the parts' step: levels of the vector that chose it
     uint32_t writes;       // kFormLong: 0 when the step already lies where it would be written
-    uint32_t through;      // binary32: how codes of 1 and 2 bits are stored (codes_through)
 };
 struct ShortBatch {
     ShortJob job[kEncJobs];
@@ -463,7 +463,7 @@ __device__ __forceinline__ void encode_short(const EncodeArgs& a, const TileRef&
         if (t.len == TILE) encode_tile<DT, MODE, false, true, false, BITSW, false, true>(a, t, tile_id, regs, step, false, stage, lane);
         else if (t.len != 0) encode_tile<DT, MODE, false, false, false, BITSW, false, true>(a, t, tile_id, regs, step, false, stage, lane);
         wave_lds_sync();
-        if (t.len != 0) stage_to_stream<DT>(a, t, BITSW, stage, lane);
+        if (t.len != 0) stage_to_stream<DT, false>(a, t, BITSW, stage, lane);
     }
 }
 
@@ -519,8 +519,7 @@ void encode_short_kernel(ShortBatch by_value)
     a.rows_log2 = batch->rows_log2;
     a.num_buckets = batch->num_buckets;
     a.waves_log2 = batch->waves_log2;
-    // (short launches: a step per vector 6.3 us through the L2 and 6.5 plainly, 2 x 61 k; buckets 8.4 and 8.1, 4 x 2 M)
-    a.through = FORM == kFormLong ? job->through : FORM == kFormVector ? 1u : 0u;
+    a.through = 0u;           // (launches of few codes)
     constexpr uint32_t TILE = EncTile<DT>::N;
     __shared__ __align__(16) unsigned char stage_all[kWavesPerBlock][TILE / 2 + 8];      // at most 4 bits a code
     __shared__ float part[kWavesPerBlock];
@@ -672,7 +671,7 @@ void encode_stream_kernel(EncodeBatch by_value, uint32_t full_tiles)
                 wave_lds_sync();
                 encode_tile<DT, MODE, FUSED, false, false, BITSW>(a, t, full_tiles, regs, kappa, true, stage, lane);
                 wave_lds_sync();
-                stage_to_stream<DT>(a, t, BITSW ? (uint32_t)BITSW : a.qp.bits, stage, lane);
+                stage_to_stream<DT, FUSED>(a, t, BITSW ? (uint32_t)BITSW : a.qp.bits, stage, lane);
             }
         }
     }
@@ -1109,16 +1108,9 @@ template <int DT> constexpr uint32_t kShortOneQuantizerTiles = DT == 0 ? 4096 : 
 // 13.9 / 13.5-14.7 / 14.7, 15.1.
 constexpr uint32_t kShortCopies = 32768;
 
-// How an encoder of `jobs` vectors like this one stores narrow codes: straight through the L2, or not (see store_through).
-static uint32_t codes_through(const EncodeArgs& a, uint32_t jobs)
-{
-    return a.tl.n * jobs * a.qp.bits >= 120000000u ? 1u : 0u;
-}
-
-static ShortJob short_job(const EncodePlan& p, uint32_t jobs)
+static ShortJob short_job(const EncodePlan& p)
 {
     ShortJob job;
-    job.through = codes_through(p.a, jobs);
     static_cast<EncodeJob&>(job) = p.a;
     job.qp = p.a.qp;
     job.total_bytes = p.a.total_bytes;
@@ -1143,7 +1135,7 @@ static bool run_long(const EncodePlan* plans, uint32_t jobs, int dt, uint32_t bu
     }
     if (one_quantizer) return false;
     ShortBatch b;
-    for (uint32_t j = 0; j < jobs; ++j) b.job[j] = short_job(plans[j], jobs);
+    for (uint32_t j = 0; j < jobs; ++j) b.job[j] = short_job(plans[j]);
     b.tl = plans[0].a.tl;
     b.rows_log2 = b.waves_log2 = 0u;
     b.num_buckets = 1u;
@@ -1194,7 +1186,7 @@ static bool run_short(const EncodePlan* plans, uint32_t jobs, uint32_t bucket, h
             }
         const uint32_t launch_of = source == kEncJobs && sources != 0u ? 1u : 0u;
         ShortJob& job = b[launch_of].job[count[launch_of]++];
-        job = short_job(plans[j], jobs);
+        job = short_job(plans[j]);
         if (source == kEncJobs) continue;
         if (plans[j].two_pass) {
             m.g[chosen++] = plans[j].a.g;
@@ -1283,7 +1275,8 @@ static int run_plans(const EncodePlan* plans, uint32_t jobs, int dt, uint32_t bu
             b.job[b.jobs++] = plans[k].a;
             done[k] = true;
         }
-        b.common.through = codes_through(b.common, b.jobs);
+        // (where narrow codes go straight through the L2: see store_through)
+        b.common.through = b.common.tl.n * b.jobs * b.common.qp.bits >= 120000000u ? 1u : 0u;
         const int rc = dt == NDQ_F32 ? run_encode_mode<0>(b, plans[j], bucket, s)
                                      : run_encode_mode<1>(b, plans[j], bucket, s);
         if (rc != NDQ_OK) return rc;

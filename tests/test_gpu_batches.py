@@ -268,7 +268,7 @@ def test_steps_of_a_batch_in_every_form_of_the_max_norm_pass(dtype, W, n, bucket
 
 @pytest.mark.parametrize("kind,arg,bucket", [("dq", 3, 2048), ("nested", 4, 512), ("dq", 2, 8192), ("dq", 3, 0), ("nested", 2, 0)])
 def test_codes_stored_through_the_cache_or_not_are_the_same(kind, arg, bucket):
-    # narrow codes of binary32 vectors: stored through the L2 when a launch has 120 M bits of them, else plainly; sixteen
+    # narrow codes of binary32 vectors in buckets: stored through the L2 when a launch has 120 M bits of them, else plainly; sixteen
     # vectors in one call against one call each, and the last one against the oracle
     bits = ndq.ndq_code_bits(arg)
     n, W = (1 << 23) // bits + 77, 16
