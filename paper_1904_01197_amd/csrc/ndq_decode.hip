@@ -947,7 +947,8 @@ __device__ __forceinline__ void store_row_lines(float* row, int lane, const floa
 #ifndef NDQ_CHAIN_PIPED_WAVES
 #define NDQ_CHAIN_PIPED_WAVES NDQ_CHAIN_STREAM_WAVES
 #endif
-template <int RMODE, int W0, int WR, bool RAGGED, int FORM>
+// LINES: one tile per wave, its results stored with store_row_lines.
+template <int RMODE, int W0, int WR, bool RAGGED, bool LINES, int FORM>
 __global__ __launch_bounds__(kBlock)
 __attribute__((amdgpu_waves_per_eu(FORM == kPiped ? NDQ_CHAIN_PIPED_WAVES : kChainStreamWaves, FORM == kPiped ? NDQ_CHAIN_PIPED_WAVES : kChainStreamWaves)))
 void chain_stream_kernel(ChainArgs a_by_value)
@@ -1058,25 +1059,19 @@ void chain_stream_kernel(ChainArgs a_by_value)
         float* out = out_base + start;
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) {
+            const uint32_t o = (uint32_t)(r * kWave + lane) * kLaneElems;
             if (apply_scale) {       // wave-uniform
 #pragma unroll
                 for (int k = 0; k < 8; ++k) S[r][k] = scale * S[r][k];
             }
             if (PIPED) {
-                const uint32_t o = (uint32_t)(r * kWave + lane) * kLaneElems;
                 *(float4*)(out_stage + o) = make_float4(S[r][0], S[r][1], S[r][2], S[r][3]);
                 *(float4*)(out_stage + o + 4) = make_float4(S[r][4], S[r][5], S[r][6], S[r][7]);
-            }
-        }
-        if (!PIPED && W < (RMODE == kDq ? 4u : 3u)) {
-#pragma unroll
-            for (int r = 0; r < ROWS; ++r) store_row_lines(out + r * kWave * kLaneElems, lane, S[r]);
-        } else if (!PIPED) {
-#pragma unroll
-            for (int r = 0; r < ROWS; ++r) {
-                float* p = out + (r * kWave + lane) * kLaneElems;
-                store_streaming(p, S[r][0], S[r][1], S[r][2], S[r][3]);
-                store_streaming(p + 4, S[r][4], S[r][5], S[r][6], S[r][7]);
+            } else if (LINES) {
+                store_row_lines(out + r * kWave * kLaneElems, lane, S[r]);
+            } else {
+                store_streaming(out + o, S[r][0], S[r][1], S[r][2], S[r][3]);
+                store_streaming(out + o + 4, S[r][4], S[r][5], S[r][6], S[r][7]);
             }
         }
         if (PIPED) {
@@ -1422,14 +1417,21 @@ static int launch_chain_stream(ChainArgs& a, uint64_t bucket_len, hipStream_t s)
     const bool ragged = (uint64_t)tiles * tile < a.n;     // one more wave takes the ragged last tile
     const uint32_t all = tiles + (ragged ? 1u : 0u);
     const dim3 grid(persistent ? persistent_blocks(all, 1024u * NDQ_CHAIN_PIPED_WAVES) : blocks_for(all)), block(kBlock);
-    if (persistent)
-        return ragged ? launch((chain_stream_kernel<RMODE, W0, WR, true, kPiped>), grid, block, s, a)
-                      : launch((chain_stream_kernel<RMODE, W0, WR, false, kPiped>), grid, block, s, a);
-    if (short_vector)
-        return ragged ? launch((chain_stream_kernel<RMODE, W0, WR, true, kOneRow>), grid, block, s, a)
-                      : launch((chain_stream_kernel<RMODE, W0, WR, false, kOneRow>), grid, block, s, a);
-    return ragged ? launch((chain_stream_kernel<RMODE, W0, WR, true, kOneTile>), grid, block, s, a)
-                  : launch((chain_stream_kernel<RMODE, W0, WR, false, kOneTile>), grid, block, s, a);
+    auto run = [&](auto lines, auto form) {
+        constexpr bool LINES = decltype(lines)::value;
+        constexpr int FORM = decltype(form)::value;
+        return ragged ? launch((chain_stream_kernel<RMODE, W0, WR, true, LINES, FORM>), grid, block, s, a)
+                      : launch((chain_stream_kernel<RMODE, W0, WR, false, LINES, FORM>), grid, block, s, a);
+    };
+    if (persistent) return run(std::false_type{}, std::integral_constant<int, kPiped>{});
+    if (short_vector) {
+        // (a launch of rows is bound by its stores only with one worker: 2 M elements 4.4 -> 4.0 us; 2 of 1.6 M 4.1 -> 4.2)
+        if constexpr (RMODE == kDq && W0 == WR)
+            if (a.W == 1u) return run(std::true_type{}, std::integral_constant<int, kOneRow>{});
+        return run(std::false_type{}, std::integral_constant<int, kOneRow>{});
+    }
+    return a.W < (RMODE == kDq ? 4u : 3u) ? run(std::true_type{}, std::integral_constant<int, kOneTile>{})
+                                          : run(std::false_type{}, std::integral_constant<int, kOneTile>{});
 }
 
 template <int RMODE, int W0>
