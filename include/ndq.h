@@ -249,9 +249,10 @@ int ndq_sqdiff(const float* a, const float* b, size_t n, double* workspace, doub
  * (the fixed grid and the array are sized for vectors below that).  The first
  * call on a device looks up the array's address on that device (no allocation;
  * make that call outside a graph capture); NDQ_ELAUNCH if the runtime refuses.
- * All calls on one GPU share the array -- every call overwrites all of it before
- * reading it, so nothing needs clearing, but two calls that overlap in time on
- * one GPU (different streams) race; calls on one stream are safe. */
+ * All calls on one GPU share the array.  Nothing needs clearing, but two calls that
+ * overlap in time on one GPU (different streams) disturb each other: their workgroups
+ * may wait for sums that the other call has overwritten and work them out again, so
+ * keep such calls on one stream. */
 int ndq_sqdiff_static(const float* a, const float* b, size_t n, double* out, void* stream);
 
 /* Server side of Algorithm 1, last step: out_i = scale * sum_w gs[w][i], summed

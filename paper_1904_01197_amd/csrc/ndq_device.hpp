@@ -525,6 +525,11 @@ __device__ __forceinline__ void store_through(uint64_t* p, uint64_t x)
     __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+__device__ __forceinline__ uint64_t load_through(const uint64_t* p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 __device__ __forceinline__ float4 load_streaming_f4(const float* p)
 {
 #if defined(NDQ_NO_STREAMING) || defined(NDQ_NO_STREAMING_RMW_LOADS)

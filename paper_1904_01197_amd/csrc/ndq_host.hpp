@@ -6,6 +6,8 @@
 #include <stdint.h>
 #include <stdlib.h>
 
+#include <atomic>
+#include <chrono>
 #include <tuple>
 #include <utility>
 
@@ -75,6 +77,18 @@ inline DitherStream make_stream(const ndq_dither* d)
     s.step = d->step;
     s.worker = d->worker;
     return s;
+}
+
+// 64 bits that no other call of the process has, and nothing else is likely to hold: a call's workgroups mark with them
+// what they leave in memory that nobody has cleared (the multiplications and shifts are invertible, so distinct
+// counts give distinct tags).  A call recorded in a graph keeps its tag: its marks are gone when it ends.
+inline uint64_t call_tag()
+{
+    static std::atomic<uint64_t> calls{(uint64_t)std::chrono::steady_clock::now().time_since_epoch().count() << 20};
+    uint64_t x = calls.fetch_add(1u, std::memory_order_relaxed) * 0x9E3779B97F4A7C15u;
+    x = (x ^ (x >> 30)) * 0xBF58476D1CE4E5B9u;
+    x = (x ^ (x >> 27)) * 0x94D049BB133111EBu;
+    return x ^ (x >> 31);
 }
 
 // Launches `kernel` on `stream` and reports the launch call's OWN status.  (The

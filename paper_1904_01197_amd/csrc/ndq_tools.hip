@@ -587,66 +587,107 @@ static int run_dense(DenseArgs& a, uint32_t k, uint32_t bits, bool pack, hipStre
 
 // ---------------------------------------------------------------------------
 // sum_i (a_i - b_i)^2 in binary64 (the sigma_z^2 estimate behind Thm 4's parameter
-// choice).  Two passes over a fixed grid so that the reduction order, and hence
-// the result, does not depend on scheduling.
+// choice).  A fixed grid and fixed orders of adding, so that the result does not depend on scheduling.
+//
+// One launch: every workgroup leaves its sum in a slot of the workspace and the last one of the grid collects
+// them (with a launch of its own for that 11 M elements take 17.1 us, so 16.7; 0.1 M 5.0 and 4.4).
+// Nobody has cleared the workspace, so a slot says by itself whether it is filled: two words, each half of the
+// sum beside half of the call's tag.  The other workgroups wait for nothing, so the collector's wait ends; a slot that
+// has not come after kSqPolls looks (two calls that wrongly share a workspace) it works out by itself.  It
+// empties the slots, so that a call replayed from a graph, with the same tag, finds none of them filled.
 // ---------------------------------------------------------------------------
-constexpr uint32_t kSqBlocks = 1024;
+constexpr uint32_t kSqBlocks = 512;
+constexpr uint32_t kSqThreads = 512;
+constexpr uint32_t kSqPolls = 1u << 18;          // of about a microsecond each
+static_assert(kSqBlocks == kSqThreads, "a thread of the collector per slot");
 
-__device__ __forceinline__ double block_sum_256(double x, double* sh)
+struct SqSlot { uint64_t word[2]; };
+
+// the workgroup's sum, in its first thread
+__device__ __forceinline__ double block_sum(double x, double* sh)
 {
     const uint32_t tid = threadIdx.x;
+    __syncthreads();                             // (sh may still be read from the time before)
     sh[tid] = x;
     __syncthreads();
-    for (uint32_t s = 128; s >= 1; s >>= 1) {
+    for (uint32_t s = kSqThreads / 2u; s >= 1; s >>= 1) {
         if (tid < s) sh[tid] += sh[tid + s];
         __syncthreads();
     }
     return sh[0];
 }
 
-__global__ __launch_bounds__(256) void sqdiff_partial_kernel(const float* __restrict__ a,
-                                                             const float* __restrict__ b, uint64_t n,
-                                                             double* partial)
+// the sum of workgroup `block` of the grid, called by all threads of a workgroup
+__device__ __forceinline__ double sqdiff_share(const float* __restrict__ a, const float* __restrict__ b, uint64_t n,
+                                               uint32_t block, double* sh)
 {
-    __shared__ double sh[256];
     const uint64_t n4 = n >> 2;
     double acc = 0.0;
-    for (uint64_t i = (uint64_t)blockIdx.x * 256u + threadIdx.x; i < n4; i += (uint64_t)kSqBlocks * 256u) {
+    for (uint64_t i = (uint64_t)block * kSqThreads + threadIdx.x; i < n4; i += (uint64_t)kSqBlocks * kSqThreads) {
         const float4 x = ((const float4*)a)[i], y = ((const float4*)b)[i];
         const double d0 = (double)x.x - (double)y.x, d1 = (double)x.y - (double)y.y;
         const double d2 = (double)x.z - (double)y.z, d3 = (double)x.w - (double)y.w;
         acc += d0 * d0; acc += d1 * d1; acc += d2 * d2; acc += d3 * d3;
     }
-    if (blockIdx.x == 0 && threadIdx.x < (n & 3u)) {       // the last n mod 4 elements
+    if (block == 0u && threadIdx.x < (n & 3u)) {       // the last n mod 4 elements
         const uint64_t i = (n4 << 2) + threadIdx.x;
         const double d = (double)a[i] - (double)b[i];
         acc += d * d;
     }
-    const double total = block_sum_256(acc, sh);
-    if (threadIdx.x == 0) partial[blockIdx.x] = total;
+    return block_sum(acc, sh);
 }
 
-__global__ __launch_bounds__(256) void sqdiff_final_kernel(const double* partial, double* out)
+__global__ __launch_bounds__(kSqThreads) void sqdiff_kernel(const float* __restrict__ a, const float* __restrict__ b,
+                                                            uint64_t n, SqSlot* slots, uint64_t tag, uint32_t polls,
+                                                            double* out)
 {
-    __shared__ double sh[256];
-    double acc = 0.0;
-    for (uint32_t j = 0; j < kSqBlocks / 256u; ++j) acc += partial[j * 256u + threadIdx.x];
-    const double total = block_sum_256(acc, sh);
-    if (threadIdx.x == 0) out[0] = total;
+    __shared__ double sh[kSqThreads];
+    __shared__ uint32_t missing[kSqBlocks];
+    const uint32_t tid = threadIdx.x;
+    const uint32_t low = (uint32_t)tag, high = (uint32_t)(tag >> 32);
+    const double total = sqdiff_share(a, b, n, blockIdx.x, sh);
+    if (blockIdx.x != kSqBlocks - 1u) {
+        if (tid == 0u) {
+            const uint64_t bits = (uint64_t)__double_as_longlong(total);
+            store_through(&slots[blockIdx.x].word[0], bits >> 32 << 32 | low);
+            store_through(&slots[blockIdx.x].word[1], bits << 32 | high);
+        }
+        return;
+    }
+    double mine = total;                         // (its own sum has no slot to go through)
+    bool have = tid == kSqBlocks - 1u;
+    for (uint32_t poll = 0; !have && poll < polls; ++poll) {
+        const uint64_t w0 = load_through(&slots[tid].word[0]), w1 = load_through(&slots[tid].word[1]);
+        have = (uint32_t)w0 == low && (uint32_t)w1 == high;
+        if (have) mine = __longlong_as_double((long long)(w0 >> 32 << 32 | w1 >> 32));
+        else __builtin_amdgcn_s_sleep(1);
+    }
+    missing[tid] = have ? 0u : 1u;
+#pragma unroll
+    for (int w = 0; w < 2; ++w)                  // (a result that lies inside the workspace is written below)
+        if (&slots[tid].word[w] != (uint64_t*)out) store_through(&slots[tid].word[w], 0u);
+    if (__syncthreads_count(have ? 0 : 1) != 0)
+        for (uint32_t block = 0; block < kSqBlocks; ++block) {
+            if (missing[block] == 0u) continue;
+            const double share = sqdiff_share(a, b, n, block, sh);
+            if (tid == block) mine = share;
+        }
+    const double sum = block_sum(mine, sh);
+    if (tid == 0u) out[0] = sum;
 }
 
-// Partial sums of ndq_sqdiff_static: one per workgroup of the first pass, in
+// Slots of ndq_sqdiff_static: one per workgroup, in
 // memory the library owns (8 KB on every GPU it runs on, until the process ends).
 // In host code this name is only a handle for hipGetSymbolAddress; the kernels get
 // the per-device address kept in g_scratch_ptr.
-static __device__ __align__(256) double scratch[kSqBlocks];
+static __device__ __align__(256) SqSlot scratch[kSqBlocks];
 
 constexpr int kMaxDevices = 64;
 static std::mutex g_scratch_mutex;
-static double* g_scratch_ptr[kMaxDevices];   // address of `scratch` on each device, looked up once
+static SqSlot* g_scratch_ptr[kMaxDevices];   // address of `scratch` on each device, looked up once
 
 // Address of `scratch` on the current device (null: the runtime refused).
-static double* scratch_on_current_device()
+static SqSlot* scratch_on_current_device()
 {
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return nullptr;
@@ -654,24 +695,33 @@ static double* scratch_on_current_device()
     if (!g_scratch_ptr[dev]) {
         void* p = nullptr;
         if (hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)) != hipSuccess) return nullptr;
-        g_scratch_ptr[dev] = (double*)p;
+        g_scratch_ptr[dev] = (SqSlot*)p;
     }
     return g_scratch_ptr[dev];
 }
 
-// Argument checks and the two launches shared by ndq_sqdiff and ndq_sqdiff_static.
-static int sqdiff_common(const float* a, const float* b, size_t n, double* partial, double* out,
-                         void* stream)
+// Looks at a slot before the collector works it out.  NDQ_COLLECT_POLLS, read once per process, sets it, so that
+// tests can make the collector do all of them (0).
+static uint32_t collector_polls()
+{
+    static const uint32_t polls = [] {
+        const char* e = getenv("NDQ_COLLECT_POLLS");
+        return e ? (uint32_t)strtoul(e, nullptr, 10) : kSqPolls;
+    }();
+    return polls;
+}
+
+// Argument checks and the launch shared by ndq_sqdiff and ndq_sqdiff_static.
+static int sqdiff_common(const float* a, const float* b, size_t n, SqSlot* slots, double* out, void* stream)
 {
     if (!out) return NDQ_EINVAL;
     if (n != 0 && (!a || !b)) return NDQ_EINVAL;
     if (n >= kMaxN) return NDQ_EUNSUPPORTED;
-    if (((uintptr_t)partial & 7u) || ((uintptr_t)out & 7u)) return NDQ_EALIGN;
+    if (((uintptr_t)slots & 7u) || ((uintptr_t)out & 7u)) return NDQ_EALIGN;
     if (n != 0 && (!aligned16(a) || !aligned16(b))) return NDQ_EALIGN;
-    hipStream_t s = (hipStream_t)stream;
-    if (launch(sqdiff_partial_kernel, dim3(kSqBlocks), dim3(256), s, a, b, (uint64_t)n, partial) != NDQ_OK)
-        return NDQ_ELAUNCH;
-    return launch(sqdiff_final_kernel, dim3(1), dim3(256), s, (const double*)partial, out);
+    // (an emptied slot holds no tag: neither half is 0)
+    return launch(sqdiff_kernel, dim3(kSqBlocks), dim3(kSqThreads), (hipStream_t)stream, a, b, (uint64_t)n, slots,
+                  call_tag() | 0x100000001u, collector_polls(), out);
 }
 
 }  // namespace ndq
@@ -812,21 +862,21 @@ uint32_t ndq_nesting_ratio_for_error(double delta1, double alpha, double sigma_z
     return M <= 256 ? M : 0;
 }
 
-size_t ndq_sqdiff_workspace(void) { return ndq::kSqBlocks * sizeof(double); }
+size_t ndq_sqdiff_workspace(void) { return ndq::kSqBlocks * sizeof(ndq::SqSlot); }
 
 int ndq_sqdiff(const float* a, const float* b, size_t n, double* workspace, double* out,
                void* stream)
 {
     if (!workspace) return NDQ_EINVAL;
-    return ndq::sqdiff_common(a, b, n, workspace, out, stream);
+    return ndq::sqdiff_common(a, b, n, (ndq::SqSlot*)workspace, out, stream);
 }
 
 int ndq_sqdiff_static(const float* a, const float* b, size_t n, double* out, void* stream)
 {
     if (n >= ndq::kMaxN) return NDQ_EUNSUPPORTED;   // beyond what the fixed grid is sized for
-    double* partial = ndq::scratch_on_current_device();
-    if (!partial) return NDQ_ELAUNCH;
-    return ndq::sqdiff_common(a, b, n, partial, out, stream);
+    ndq::SqSlot* slots = ndq::scratch_on_current_device();
+    if (!slots) return NDQ_ELAUNCH;
+    return ndq::sqdiff_common(a, b, n, slots, out, stream);
 }
 
 const char* ndq_strerror(int rc)
