@@ -31,23 +31,79 @@ constexpr uint32_t kHistThreads = 1024;
 constexpr uint32_t kHistBlocks = 256;
 constexpr uint32_t kHistCopies = 32;
 
-// The workgroup that finishes last closes the histogram inside the counting kernel
-// (no launch of its own): it fills in a bin that was left to be derived and computes
-// the entropy.  `ticket` is a 64-bit word that is zero when the kernel starts.
-// A workgroup's atomics on the histogram all come from its FIRST WAVE: that wave's fence waits for
+// The call is one launch when a word holds its ticket: the entropy's eight bytes, or those of the bin that is derived.
+// Nobody has cleared the bins (a launch of its own for that costs the call 1.5 to 2.5 us: 25.6 M codes of 4 bits
+// 12.8 -> 11.0, 1 M 7.6 -> 6.1, 0.2 M of 5 bits 7.4 -> 5.8), so whoever finds the ticket without the call's tag puts it
+// there, clears the bins and says so.  That is the first workgroup, which counts nothing, while the others count; a
+// workgroup that wants to add and finds nothing done yet does it itself.  So one waits only for a workgroup that runs
+// and waits for nobody (after kOpenPolls looks, which takes two calls that wrongly share their results, it goes on).
+// Every workgroup draws a ticket, so none comes after the last one, when the tag is gone.  A workgroup that is alone
+// stores its counts (0.2 M codes of 2 bits 6.8 -> 4.2 us).
+//
+// The workgroup that finishes last closes the histogram: it fills in a bin that was left to be derived and computes
+// the entropy.  A workgroup's atomics on the histogram all come from its FIRST WAVE: that wave's fence waits for
 // them before the workgroup's ticket, and no barrier would (it does not wait for
 // atomics that return nothing, so another wave's could still be in flight when the ticket is
 // drawn; letting every wave wait for its own takes 10.8 -> 12.0 us at 4 M 7-bit codes, this nothing).
 // (A fence per thread would write
 // back and invalidate the L2 sixteen times per workgroup while the others still stream through it.)
-// Every thread calls this.  The workgroup that draws the last ticket therefore finds all counts in
+// Every thread calls last_workgroup.  The one that draws the last ticket therefore finds all counts in
 // memory; it reads them with atomics of device scope, like the additions that made them.
-__device__ __forceinline__ bool last_workgroup(unsigned long long* ticket, uint32_t* flag)
+constexpr unsigned long long kTicketBits = 0xFFFFull;       // the low bits of the word: tickets drawn (at most 256)
+constexpr unsigned long long kOpening = 0x8000ull;          // ... or this, while the bins are being cleared
+constexpr uint32_t kOpenPolls = 1u << 18;                   // of about a microsecond each
+
+// What the first wave of a workgroup knows of the opening.  All functions are called by that whole wave.
+struct HistogramOpening {
+    unsigned long long* hist;
+    unsigned long long* ticket;
+    unsigned long long tag, look;
+    uint32_t first_bin, nbins;
+    bool open;
+    __device__ __forceinline__ HistogramOpening(unsigned long long* hist_, uint32_t first_bin_, uint32_t nbins_,
+                                                unsigned long long* ticket_, unsigned long long tag_)
+        : hist(hist_), ticket(ticket_), tag(tag_), look(0ull), first_bin(first_bin_), nbins(nbins_), open(false) {}
+    // A look between two rounds of counting: by the end it has been seen that the bins are clear.  (Looks at the end, when
+    // everyone else draws tickets, queue up with those: 25.6 M codes of 4 bits 13.0 us with them alone, 11.3 so.  Codes of
+    // 1 and 2 bits have few workgroups and rounds, and a look among those rounds costs more than it spares: 8.6 / 9.1.)
+    __device__ __forceinline__ void glance()
+    {
+        if (open) return;
+        look = __hip_atomic_load(ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        open = (look & ~kTicketBits) == tag && (look & kOpening) == 0ull;
+    }
+    // Returns when the bins are clear.
+    __device__ __forceinline__ void await()
+    {
+#pragma unroll 1
+        for (uint32_t poll = 0; !open && poll < kOpenPolls; ++poll) {
+            glance();
+            if ((look & ~kTicketBits) != tag) clear();
+            else if (!open) __builtin_amdgcn_s_sleep(1);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");       // (the additions that follow are atomics of device scope)
+    }
+    __device__ __forceinline__ void clear()
+    {
+        const uint32_t lane = threadIdx.x & (kWave - 1u);
+        int first = 0;
+        if (lane == 0u)
+            first = __hip_atomic_compare_exchange_strong(ticket, &look, tag | kOpening, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                         __HIP_MEMORY_SCOPE_AGENT);
+        if (__builtin_amdgcn_readfirstlane(first) == 0) return;
+        for (uint32_t b = first_bin + lane; b < nbins; b += kWave)
+            __hip_atomic_store(hist + b, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __threadfence();             // the wave's stores, before the word says that they are done
+        if (lane == 0u) __hip_atomic_store(ticket, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+};
+
+__device__ __forceinline__ bool last_workgroup(unsigned long long* ticket, unsigned long long tag, uint32_t* flag)
 {
     __syncthreads();
     if (threadIdx.x == 0u) {
         __threadfence();
-        *flag = atomicAdd(ticket, 1ull) == (unsigned long long)gridDim.x - 1ull ? 1u : 0u;
+        *flag = atomicAdd(ticket, 1ull) == tag + (unsigned long long)gridDim.x - 1ull ? 1u : 0u;
         __threadfence();
     }
     __syncthreads();
@@ -56,7 +112,8 @@ __device__ __forceinline__ bool last_workgroup(unsigned long long* ticket, uint3
 
 // -sum p log2 p over at most 256 bins, binary64, fixed reduction order; called by all
 // threads of one workgroup of at least 256 threads.  derive_bin0 (at most 4 bins):
-// bin 0 was not counted and is what the other bins leave of n.
+// bin 0 was not counted and is what the other bins leave of n.  (In a workgroup that is alone every thread reads the bin
+// that it has stored.)
 __device__ __forceinline__ void close_histogram(unsigned long long* hist, uint32_t nbins, uint64_t n,
                                                 double* entropy_out, bool derive_bin0, double* term,
                                                 unsigned long long* few)
@@ -81,13 +138,17 @@ __device__ __forceinline__ void close_histogram(unsigned long long* hist, uint32
         const double p = (double)h / (double)n;
         t = -p * log2(p);
     }
-    if (tid < 256u) term[tid] = t;
-    __syncthreads();
-    for (uint32_t s = 128; s >= 1; s >>= 1) {
-        if (tid < s) term[tid] += term[tid + s];
+    // pairs that are 128, 64, ... 1 apart: across waves through LDS, then within the first
+    t += 0.0;                     // (what absent bins add: -0 becomes 0)
+    if (nbins > (uint32_t)kWave) {
+        if (tid < 256u) term[tid] = t;
         __syncthreads();
+        if (tid < 128u) term[tid] += term[tid + 128u];
+        __syncthreads();
+        if (tid < 64u) t = term[tid] + term[tid + 64u];
     }
-    if (tid == 0u) entropy_out[0] = term[0];
+    for (int s = 32; s >= 1; s >>= 1) t += __shfl_down(t, s, kWave);
+    if (tid == 0u) entropy_out[0] = t;
 }
 
 template <int BITS>
@@ -112,7 +173,8 @@ __device__ __forceinline__ void load_unit(const uint32_t* __restrict__ words, ui
 // LDS or more.
 template <int BITS>
 __global__ __launch_bounds__(kHistThreads) void histogram_kernel(const uint32_t* __restrict__ words, uint64_t n,
-                                                                 unsigned long long* hist, double* entropy_out)
+                                                                 unsigned long long* hist, double* entropy_out,
+                                                                 unsigned long long tag)
 {
     constexpr uint32_t NB = 1u << BITS;
     constexpr uint32_t MASK = NB - 1u;
@@ -125,14 +187,21 @@ __global__ __launch_bounds__(kHistThreads) void histogram_kernel(const uint32_t*
     __shared__ double term[256];
     __shared__ uint32_t flag;
     const uint32_t tid = threadIdx.x;
+    // the entropy's eight bytes hold the ticket until the last workgroup writes the entropy there
+    unsigned long long* ticket = reinterpret_cast<unsigned long long*>(entropy_out);
+    const bool alone = ticket && gridDim.x == 1u, opens = ticket && gridDim.x != 1u && blockIdx.x == 0u;
+    HistogramOpening opening(hist, 0u, NB, ticket, tag);
+    if (opens && tid < kWave) opening.await();
+    const bool watches = ticket && !alone && !opens && __builtin_amdgcn_readfirstlane(tid / kWave) == 0u;
     for (uint32_t i = tid; i < SLOTS * kHistCopies; i += kHistThreads) cnt[i] = 0u;
     if (tid < NB) single[tid] = 0u;
     __syncthreads();
 
     const uint32_t copy = tid & (kHistCopies - 1u);
     const uint64_t units = n >> 5;                  // whole units; the last n mod 32 codes below
-    const uint64_t stride = (uint64_t)gridDim.x * kHistThreads;
-    uint64_t u = (uint64_t)blockIdx.x * kHistThreads + tid;
+    const uint32_t first_counter = ticket && !alone ? 1u : 0u;
+    const uint64_t stride = (uint64_t)(gridDim.x - first_counter) * kHistThreads;
+    uint64_t u = opens ? units : (uint64_t)(blockIdx.x - first_counter) * kHistThreads + tid;
     uint32_t w[BITS], ahead[BITS];
     if (u < units) load_unit<BITS>(words, u, w);
     while (u < units) {
@@ -147,10 +216,11 @@ __global__ __launch_bounds__(kHistThreads) void histogram_kernel(const uint32_t*
         }
 #pragma unroll
         for (int k = 0; k < BITS; ++k) w[k] = ahead[k];
+        if (watches) opening.glance();
         u = un;
     }
     const uint32_t rest = (uint32_t)(n & 31u);
-    if (blockIdx.x == 0 && tid < rest) {
+    if (blockIdx.x == first_counter && tid < rest) {
         // one code per thread; a code that crosses into the next word is a valid code,
         // so that word lies inside the stream
         const uint64_t bit = ((units << 5) + tid) * BITS;
@@ -178,14 +248,21 @@ __global__ __launch_bounds__(kHistThreads) void histogram_kernel(const uint32_t*
             if (lane == 0u) total[code] = sum;
         }
         __syncthreads();
-        if (tid < NB && total[tid]) atomicAdd(hist + tid, total[tid]);
+        if (alone) {
+            if (tid < NB) hist[tid] = total[tid];
+        } else if (tid < kWave) {
+            if (watches) opening.await();
+            if (tid < NB && total[tid]) atomicAdd(hist + tid, total[tid]);
+        }
     } else {
+        if (watches) opening.await();
         // (64 bins or fewer: the first wave's own; more: it takes them over through LDS)
         if (tid < NB) {
             unsigned long long sum = single[tid];
             for (uint32_t c = 0; c < kHistCopies; ++c)
                 sum += cnt[tid * kHistCopies + ((c + tid) & (kHistCopies - 1u))];
             if constexpr (NB > kWave) total[tid] = sum;
+            else if (alone) hist[tid] = sum;
             else if (sum) atomicAdd(hist + tid, sum);
         }
         if constexpr (NB > kWave) {
@@ -193,12 +270,12 @@ __global__ __launch_bounds__(kHistThreads) void histogram_kernel(const uint32_t*
             if (tid < kWave) {
 #pragma unroll
                 for (uint32_t b = tid; b < NB; b += kWave)
-                    if (total[b]) atomicAdd(hist + b, total[b]);
+                    if (total[b] && !alone) atomicAdd(hist + b, total[b]);
             }
+            if (alone && tid < NB) hist[tid] = total[tid];
         }
     }
-    // the entropy's eight bytes hold the ticket until the last workgroup writes the entropy there
-    if (entropy_out && last_workgroup(reinterpret_cast<unsigned long long*>(entropy_out), &flag))
+    if (ticket && (alone || last_workgroup(ticket, tag, &flag)))
         close_histogram(hist, NB, n, entropy_out, false, term, nullptr);
 }
 
@@ -237,7 +314,7 @@ __device__ __forceinline__ void count_small(const uint4& x, uint32_t& c1, uint32
 template <int BITS>
 __global__ __launch_bounds__(kSmallThreads) void histogram_small_kernel(const uint4* __restrict__ vec, uint64_t n,
                                                                         unsigned long long* hist,
-                                                                        double* entropy_out)
+                                                                        double* entropy_out, unsigned long long tag)
 {
     constexpr uint32_t bits = BITS;
     __shared__ uint32_t part[3][kSmallThreads / 64];
@@ -245,13 +322,21 @@ __global__ __launch_bounds__(kSmallThreads) void histogram_small_kernel(const ui
     __shared__ unsigned long long few[4];
     __shared__ uint32_t flag;
     const uint32_t tid = threadIdx.x;
+    // bins 1..3 (or bin 1) are counted; bin 0 is not: its eight bytes hold the
+    // ticket, and the last workgroup writes there what the other bins leave of n
+    constexpr uint32_t nbins = 1u << BITS;
+    const bool alone = gridDim.x == 1u, opens = !alone && blockIdx.x == 0u;
+    HistogramOpening opening(hist, 1u, nbins, hist, tag);
+    if (opens && tid < kWave) opening.await();
+    const bool watches = !alone && !opens && __builtin_amdgcn_readfirstlane(tid / kWave) == 0u;
     // whole 16-byte vectors here; the last, partial one (the stream is allocated in
     // multiples of 16 bytes) is masked to its valid bits below.  Bits masked away
     // read as code 0, and bin 0 is n minus the other bins anyway.
     const uint64_t vectors = (n * bits) >> 7;
-    const uint64_t stride = (uint64_t)gridDim.x * kSmallThreads;
+    const uint32_t first_counter = alone ? 0u : 1u;
+    const uint64_t stride = (uint64_t)(gridDim.x - first_counter) * kSmallThreads;
     uint32_t c[3] = {0u, 0u, 0u};
-    uint64_t u = (uint64_t)blockIdx.x * kSmallThreads + tid;
+    uint64_t u = opens ? vectors : (uint64_t)(blockIdx.x - first_counter) * kSmallThreads + tid;
     for (; u + (kSmallInFlight - 1) * stride < vectors; u += kSmallInFlight * stride) {
         uint4 x[kSmallInFlight];
 #pragma unroll
@@ -261,7 +346,7 @@ __global__ __launch_bounds__(kSmallThreads) void histogram_small_kernel(const ui
     }
     for (; u < vectors; u += stride) count_small<BITS>(vec[u], c[0], c[1], c[2]);
     const uint32_t tail_bits = (uint32_t)((n * bits) & 127u);
-    if (blockIdx.x == 0 && tid == 0 && tail_bits != 0u) {
+    if (blockIdx.x == first_counter && tid == 0 && tail_bits != 0u) {
         const uint4 x = vec[vectors];
         const uint32_t w[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
@@ -277,19 +362,18 @@ __global__ __launch_bounds__(kSmallThreads) void histogram_small_kernel(const ui
         if ((tid & 63u) == 0u) part[b][tid >> 6] = c[b];
     }
     __syncthreads();
-    // bins 1..3 (or bin 1) by atomics; bin 0 is not counted: its eight bytes hold the
-    // ticket, and the last workgroup writes there what the other bins leave of n
-    const uint32_t nbins = 1u << bits;
+    if (watches) opening.await();
     if (tid >= 1u && tid < nbins) {
         unsigned long long sum = 0u;
         for (uint32_t w = 0; w < kSmallThreads / 64u; ++w) sum += part[tid - 1u][w];
-        if (sum) atomicAdd(hist + tid, sum);
+        if (alone) hist[tid] = sum;
+        else if (sum) atomicAdd(hist + tid, sum);
     }
-    if (last_workgroup(hist, &flag)) close_histogram(hist, nbins, n, entropy_out, true, term, few);
+    if (alone || last_workgroup(hist, tag, &flag)) close_histogram(hist, nbins, n, entropy_out, true, term, few);
 }
 
-// clears the bins and, when an entropy is wanted, its eight bytes (+0.0: the entropy of
-// an empty stream, and the zero the ticket starts from)
+// For what nobody holds a ticket of: clears the bins and, when an entropy is wanted, its eight bytes (+0.0: the
+// entropy of an empty stream).
 __global__ void clear_histogram_kernel(unsigned long long* hist, uint32_t nbins, unsigned long long* entropy_bits)
 {
     if (threadIdx.x < nbins) hist[threadIdx.x] = 0ull;
@@ -748,8 +832,12 @@ int ndq_code_entropy(const void* codes, size_t n, uint32_t bits, uint64_t* hist_
     if (n != 0 && !aligned16(codes)) return NDQ_EALIGN;
     hipStream_t s = (hipStream_t)stream;
     const uint32_t nbins = 1u << bits;
-    if (launch(clear_histogram_kernel, dim3(1), dim3(256), s, (unsigned long long*)hist_out, nbins,
-               (unsigned long long*)entropy_out) != NDQ_OK)
+    // a ticket's word: bin 0 of a narrow stream, else the entropy's; a count is below 2^40 and an entropy not negative, so
+    // neither is taken for a tag
+    const bool ticket = n != 0u && (bits <= 2u || entropy_out);
+    const unsigned long long tag = (call_tag() | (uint64_t)1 << 63) & ~kTicketBits;
+    if (!ticket && launch(clear_histogram_kernel, dim3(1), dim3(256), s, (unsigned long long*)hist_out, nbins,
+                          (unsigned long long*)entropy_out) != NDQ_OK)
         return NDQ_ELAUNCH;
     if (n == 0) return NDQ_OK;
     if (bits <= 2u) {
@@ -757,33 +845,36 @@ int ndq_code_entropy(const void* codes, size_t n, uint32_t bits, uint64_t* hist_
         uint64_t blocks = (vectors + kSmallInFlight * kSmallThreads - 1) / (kSmallInFlight * kSmallThreads);
         if (blocks > kSmallBlocks) blocks = kSmallBlocks;
         if (blocks == 0u) blocks = 1u;
+        if (blocks > 1u) ++blocks;           // and the one that opens the histogram
         if (bits == 1u)
             return launch(histogram_small_kernel<1>, dim3((uint32_t)blocks), dim3(kSmallThreads), s,
-                          (const uint4*)codes, (uint64_t)n, (unsigned long long*)hist_out, entropy_out);
+                          (const uint4*)codes, (uint64_t)n, (unsigned long long*)hist_out, entropy_out, tag);
         return launch(histogram_small_kernel<2>, dim3((uint32_t)blocks), dim3(kSmallThreads), s,
-                      (const uint4*)codes, (uint64_t)n, (unsigned long long*)hist_out, entropy_out);
+                      (const uint4*)codes, (uint64_t)n, (unsigned long long*)hist_out, entropy_out, tag);
     }
     const uint64_t units = (uint64_t)n >> 5;
     uint64_t blocks = (units + kHistThreads - 1) / kHistThreads;
-    if (bits <= 4u && blocks < (uint64_t)kHistBlocks * kHistBlocks) {
-        // Paired codes: a workgroup's closing atomics cost the call 25 ns, a round of units about
-        // 0.6 us, so 0.025 B + 0.6 blocks / B is smallest at B = sqrt(24 blocks).  4-bit calls
-        // against the full grid: 4 M codes 9.3 -> 8.2 us, 25.6 M 14.2 -> 12.1, 134 M 22.4 both.
+    if (blocks < (uint64_t)kHistBlocks * kHistBlocks) {
+        // A workgroup's closing atomics cost the call 25 ns, a round of units about
+        // 0.6 us, so 0.025 B + 0.6 blocks / B is smallest at B = sqrt(24 blocks).  Against the full grid:
+        // 4-bit calls of 4 M codes 9.3 -> 8.2 us, 25.6 M 14.2 -> 12.1, 134 M 22.4 both; 5-bit ones of 4 M 9.8 -> 8.0,
+        // 25.6 M 16.0 -> 14.1; 8-bit 10.4 -> 8.9, 17.0 -> 15.3, 100 M 28.1 both.
         uint64_t fewer = (uint64_t)sqrt(24.0 * (double)blocks);
         if (fewer < blocks) blocks = fewer;
     }
     if (blocks > kHistBlocks) blocks = kHistBlocks;
     if (blocks == 0u) blocks = 1u;
+    if (ticket && blocks > 1u) ++blocks;     // and the one that opens the histogram
     const dim3 grid((uint32_t)blocks), block(kHistThreads);
     const uint32_t* words = (const uint32_t*)codes;
     unsigned long long* h = (unsigned long long*)hist_out;
     switch (bits) {
-    case 3: return launch(histogram_kernel<3>, grid, block, s, words, (uint64_t)n, h, entropy_out);
-    case 4: return launch(histogram_kernel<4>, grid, block, s, words, (uint64_t)n, h, entropy_out);
-    case 5: return launch(histogram_kernel<5>, grid, block, s, words, (uint64_t)n, h, entropy_out);
-    case 6: return launch(histogram_kernel<6>, grid, block, s, words, (uint64_t)n, h, entropy_out);
-    case 7: return launch(histogram_kernel<7>, grid, block, s, words, (uint64_t)n, h, entropy_out);
-    default: return launch(histogram_kernel<8>, grid, block, s, words, (uint64_t)n, h, entropy_out);
+    case 3: return launch(histogram_kernel<3>, grid, block, s, words, (uint64_t)n, h, entropy_out, tag);
+    case 4: return launch(histogram_kernel<4>, grid, block, s, words, (uint64_t)n, h, entropy_out, tag);
+    case 5: return launch(histogram_kernel<5>, grid, block, s, words, (uint64_t)n, h, entropy_out, tag);
+    case 6: return launch(histogram_kernel<6>, grid, block, s, words, (uint64_t)n, h, entropy_out, tag);
+    case 7: return launch(histogram_kernel<7>, grid, block, s, words, (uint64_t)n, h, entropy_out, tag);
+    default: return launch(histogram_kernel<8>, grid, block, s, words, (uint64_t)n, h, entropy_out, tag);
     }
 }
 

@@ -1,15 +1,105 @@
-"""Calls whose workgroups meet in memory that nobody has cleared: the sum of squared differences, whatever lies in
-the result and the workspace; and the collector that gives up waiting."""
+"""Calls whose workgroups meet in memory that nobody has cleared: the histogram with its entropy and the sum
+of squared differences.  Whatever lies in the results and the workspace, in eager calls and in replays of a
+graph, on one stream and on several; and the collector that gives up waiting."""
 import os
 import subprocess
 import sys
 
+import numpy as np
 import pytest
 import torch
 
+import oracle
 from paper_1904_01197_amd import ndq
 
 pytestmark = pytest.mark.gpu
+# codes: one workgroup, two, an uneven share, a full grid
+SIZES = [1, 31, 60001, 32 * 1024, 32 * 1024 + 32, (1 << 20) + 64, 3000001, 32 * 1024 * 256 + 63]
+
+
+def _stream(bits, n, seed=0):
+    rng = np.random.default_rng(seed + n + bits)
+    codes = np.minimum(rng.geometric(0.4, size=n) - 1, (1 << bits) - 1).astype(np.uint32)
+    return torch.from_numpy(oracle.pack(codes, bits)).cuda(), np.bincount(codes, minlength=1 << bits)
+
+
+def _entropy(counts):
+    p = counts[counts > 0] / counts.sum()
+    return float(-(p * np.log2(p)).sum())
+
+
+@pytest.mark.parametrize("bits", range(1, 9))
+def test_histogram_into_memory_that_holds_anything(bits):
+    rng = np.random.default_rng(bits)
+    for n in SIZES:
+        packed, ref = _stream(bits, n)
+        hist = torch.empty(1 << bits, dtype=torch.int64, device="cuda")
+        ent = torch.empty(1, dtype=torch.float64, device="cuda")
+        # zeros, ones, any bits, then twice over the call's own results
+        for fill in (np.int64(0), np.int64(-1), None, "own", "own"):
+            if fill is None:
+                hist.copy_(torch.from_numpy(rng.integers(-2**63, 2**63 - 1, hist.numel())))
+                ent.view(torch.int64).copy_(torch.from_numpy(rng.integers(-2**63, 2**63 - 1, 1)))
+            elif not isinstance(fill, str):
+                hist.fill_(int(fill))
+                ent.view(torch.int64).fill_(int(fill))
+            ndq.ndq_code_entropy(packed, n, bits, hist, ent)
+            assert np.array_equal(hist.cpu().numpy(), ref), (n, fill)
+            # (at most 256 terms, each to a few units in the last place)
+            assert abs(float(ent.item()) - _entropy(ref)) <= 1e-12, (n, fill)
+
+
+def test_histograms_of_several_streams_at_once():
+    streams = [torch.cuda.Stream() for _ in range(4)]
+    calls = [(bits, n) + _stream(bits, n, seed=s) for s, (bits, n) in
+             enumerate([(4, 3000001), (2, 30000001), (7, 4000000), (3, 70001), (1, 60000001), (8, 2000000), (5, 33000), (4, 9000000)])]
+    out = [(torch.full((1 << bits,), -5, device="cuda", dtype=torch.int64), torch.full((1,), 3.0, device="cuda", dtype=torch.float64))
+           for bits, *_ in calls]
+    torch.cuda.synchronize()
+    for _ in range(20):
+        for i, (bits, n, packed, _) in enumerate(calls):
+            with torch.cuda.stream(streams[i % 4]):
+                ndq.ndq_code_entropy(packed, n, bits, *out[i])
+    torch.cuda.synchronize()
+    for (bits, n, _, ref), (hist, ent) in zip(calls, out):
+        assert np.array_equal(hist.cpu().numpy(), ref) and abs(float(ent.item()) - _entropy(ref)) <= 1e-12
+
+
+def test_replays_of_a_graph_follow_their_inputs():
+    n = 1000003
+    streams = {bits: _stream(bits, n) for bits in (1, 4, 7)}
+    packed = {bits: s[0] for bits, s in streams.items()}
+    hist = {bits: torch.empty(1 << bits, dtype=torch.int64, device="cuda") for bits in packed}
+    ent = {bits: torch.empty(1, dtype=torch.float64, device="cuda") for bits in packed}
+    a, b = torch.randn(n, device="cuda"), torch.randn(n, device="cuda")
+    work = torch.empty(ndq.ndq_sqdiff_workspace() // 8, dtype=torch.float64, device="cuda")
+    sq = torch.empty(1, dtype=torch.float64, device="cuda")
+
+    def run():
+        for bits in packed:
+            ndq.ndq_code_entropy(packed[bits], n, bits, hist[bits], ent[bits])
+        ndq.ndq_sqdiff(a, b, work, sq)
+
+    run()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        run()
+    for rep in range(4):
+        refs = {}
+        for bits in packed:                         # (nothing is overwritten: each replay finds the last one's results)
+            new, refs[bits] = _stream(bits, n, seed=10 * (rep + 1))
+            packed[bits].copy_(new)
+        a.copy_(torch.randn(n, device="cuda") * (rep + 1))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for bits in packed:
+            assert np.array_equal(hist[bits].cpu().numpy(), refs[bits]), (rep, bits)
+            assert abs(float(ent[bits].item()) - _entropy(refs[bits])) <= 1e-12, (rep, bits)
+        replayed = sq.clone()
+        ndq.ndq_sqdiff(a, b, work, sq)
+        assert torch.equal(replayed, sq), rep
 
 
 def _sqdiff_cases():
