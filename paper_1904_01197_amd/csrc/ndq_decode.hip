@@ -587,6 +587,7 @@ struct ChainArgs {
     uint32_t bucket_shift;
     uint32_t tiles;           // whole tiles
     uint32_t W;
+    uint32_t dq;              // MIXED: how many of the workers, the first ones, are DQSG
     int apply_scale;
     float scale;
 };
@@ -618,6 +619,18 @@ template <int FORM> struct ChainStreamTile {
 
 template <int ROWS> struct ChainCodes { uint32_t w[ROWS]; float step; };
 
+// a lane's eight codes of a row: WIDTH bytes
+template <int WIDTH>
+__device__ __forceinline__ uint32_t lane_codes(const unsigned char* p)
+{
+    if constexpr (WIDTH == 1) return *p;
+    if constexpr (WIDTH == 2) return *(const uint16_t*)p;
+    if constexpr (WIDTH == 4) return *(const uint32_t*)p;
+    uint16_t low;                     // three bytes at any address, and none behind them
+    __builtin_memcpy(&low, p, 2);
+    return (uint32_t)low | (uint32_t)p[2] << 16;
+}
+
 // a lane's eight codes of a row: `WIDTH` bytes at a multiple of WIDTH (full tiles).
 // `limit`: the largest byte offset inside the tile's codes that may be read (a multiple of
 // WIDTH); lanes past it read there instead.  Whole tiles pass 0xFFFFFFFF; for the vector's
@@ -632,8 +645,7 @@ __device__ __forceinline__ void stream_fetch(const unsigned char* codes, uint64_
     for (int r = 0; r < ROWS; ++r) {
         uint32_t off = (uint32_t)(r * kWave + lane) * WIDTH;
         off = off < limit ? off : limit;
-        const unsigned char* p = tile + off;
-        f.w[r] = WIDTH == 1 ? (uint32_t)*p : WIDTH == 2 ? (uint32_t)*(const uint16_t*)p : *(const uint32_t*)p;
+        f.w[r] = lane_codes<WIDTH>(tile + off);
     }
     f.step = 0.0f;     // whole tiles take their steps from the step lanes of the kernel
 }
@@ -650,8 +662,7 @@ __device__ __forceinline__ void stream_fetch_ragged(const unsigned char* codes, 
     for (int r = 0; r < ROWS; ++r) {
         const unsigned char* p = mine + (uint32_t)(r * kWave) * WIDTH;
         f.w[r] = 0u;
-        if ((uint32_t)(r * kWave + lane) * kLaneElems < len)
-            f.w[r] = WIDTH == 1 ? (uint32_t)*p : WIDTH == 2 ? (uint32_t)*(const uint16_t*)p : *(const uint32_t*)p;
+        if ((uint32_t)(r * kWave + lane) * kLaneElems < len) f.w[r] = lane_codes<WIDTH>(p);
     }
     f.step = steps[bucket];
 }
@@ -662,7 +673,7 @@ template <int MODE, int WIDTH, bool FIRST, int ROWS>
 __device__ __forceinline__ void stream_fold(const PhiloxUniform& keys, uint32_t block, uint32_t extra,
                                             const ChainCodes<ROWS>& f, float step, float inv, float (&S)[ROWS][8])
 {
-    constexpr int NF = WIDTH == 4 ? 4 : 8;
+    constexpr int NF = WIDTH > 2 ? 4 : 8;       // fields of a group that stay inside 23 bits
     // a power-of-two nesting ratio is 2^(code width): M and 1/M are compile-time constants
     constexpr float M_f = (float)(1u << WIDTH), inv_M_f = 1.0f / M_f;
     // DQSG: the code c itself, the index offset q_min going into the dither instead:
@@ -679,7 +690,7 @@ __device__ __forceinline__ void stream_fold(const PhiloxUniform& keys, uint32_t 
         fl.run();
         uint32_t words[4];
         fl.words(words);
-        const uint32_t lo = f.w[r], hi = WIDTH == 4 ? f.w[r] >> 16 : f.w[r];
+        const uint32_t lo = f.w[r], hi = f.w[r] >> (NF == 4 ? 4 * WIDTH : 0);
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
             const float x = (k & 1) ? dither_raised<true>(words[k >> 1], dither_bits)
@@ -777,7 +788,7 @@ template <int MODE, int WIDTH, bool FIRST> struct RowOrder {
 template <int MODE, int WIDTH, bool FIRST>
 struct RowFold {
     static constexpr bool BIT = RowOrder<MODE, WIDTH, FIRST>::BIT;
-    static constexpr int NF = WIDTH == 4 ? 4 : 8;
+    static constexpr int NF = WIDTH > 2 ? 4 : 8;
     static constexpr float M_f = (float)(1u << WIDTH), inv_M_f = 1.0f / M_f;
     const uint32_t (&words)[4];
     uint32_t code, code_hi, dither_bits;
@@ -824,7 +835,7 @@ __device__ __forceinline__ void fold_row_piped(const uint32_t (&words)[4], uint3
     // raised dither: v + 64 (DQSG: v - q_min + 64, so that c minus it is (c + q_min) - v; nested: divided by M)
     const uint32_t dither_bits = MODE == kDq ? kDitherBits - (extra << 17)
                                              : Fold::BIT ? kDitherBits - ((uint32_t)WIDTH << 23) : kDitherBits;
-    Fold f = {words, Fold::BIT ? code << 23 : code, code >> 16, dither_bits, step, inv, __uint_as_float(extra), S, fl,
+    Fold f = {words, Fold::BIT ? code << 23 : code, code >> (4 * WIDTH), dither_bits, step, inv, __uint_as_float(extra), S, fl,
               {}, {}, {}, {}};
     f.run_all(std::make_integer_sequence<int, RowOrder<MODE, WIDTH, FIRST>::program.n>());
 }
@@ -848,7 +859,7 @@ __device__ __forceinline__ void stream_fold_piped(const PhiloxUniform& keys, uin
 }
 
 // The ragged last tile with the same folds: lanes past the end decode zeros and store nothing.
-template <int RMODE, int W0, int WR, int ROWS>
+template <int RMODE, int W0, int WR, bool MIXED, int ROWS>
 __device__ __forceinline__ void stream_ragged_tile(ChainArgsPtr a, uint64_t start, uint32_t len, uint32_t bucket,
                                                    int lane)
 {
@@ -856,15 +867,23 @@ __device__ __forceinline__ void stream_ragged_tile(ChainArgsPtr a, uint64_t star
     const uint32_t block = (uint32_t)(start >> 3) + (uint32_t)lane;
     float S[ROWS][8];
     ChainCodes<ROWS> cur, nxt;
+    const uint32_t dq = MIXED ? a->dq : 1u;
+    auto fetch = [&](uint32_t w) __attribute__((always_inline)) {
+        if (MIXED && w < dq) stream_fetch_ragged<W0, ROWS>(a->w[w].codes, a->steps[w], start, len, bucket, lane, nxt);
+        else stream_fetch_ragged<WR, ROWS>(a->w[w].codes, a->steps[w], start, len, bucket, lane, nxt);
+    };
     stream_fetch_ragged<W0, ROWS>(a->w[0].codes, a->steps[0], start, len, bucket, lane, cur);
     nxt = cur;
-    if (W > 1u) stream_fetch_ragged<WR, ROWS>(a->w[1].codes, a->steps[1], start, len, bucket, lane, nxt);
+    if (W > 1u) fetch(1u);
     stream_fold<kDq, W0, true, ROWS>(uniform_keys(&a->w[0]), a->w[0].block + block, a->w[0].extra, cur, cur.step, 0.0f, S);
     cur = nxt;
     for (uint32_t w = 1; w < W; ++w) {
-        if (w + 1u < W) stream_fetch_ragged<WR, ROWS>(a->w[w + 1u].codes, a->steps[w + 1u], start, len, bucket, lane, nxt);
-        stream_fold<RMODE, WR, false, ROWS>(uniform_keys(&a->w[w]), a->w[w].block + block, a->w[w].extra, cur, cur.step,
-                                            inv_step(cur.step), S);
+        if (w + 1u < W) fetch(w + 1u);
+        if (MIXED && w < dq)
+            stream_fold<kDq, W0, false, ROWS>(uniform_keys(&a->w[w]), a->w[w].block + block, a->w[w].extra, cur, cur.step, 0.0f, S);
+        else
+            stream_fold<RMODE, WR, false, ROWS>(uniform_keys(&a->w[w]), a->w[w].block + block, a->w[w].extra, cur, cur.step,
+                                                inv_step(cur.step), S);
         cur = nxt;
     }
     float* out = a->out + start;
@@ -881,7 +900,7 @@ __device__ __forceinline__ void stream_ragged_tile(ChainArgsPtr a, uint64_t star
 
 // The wave's tiles that have a step outside the range fold_row_piped is exact in, decoded
 // again in the plain form.
-template <int RMODE, int W0, int WR>
+template <int RMODE, int W0, int WR, bool MIXED>
 __device__ __forceinline__ void redo_out_of_range(ChainArgsPtr a, uint32_t first, uint32_t stride,
                                                            uint32_t tiles_all, int lane)
 {
@@ -892,7 +911,7 @@ __device__ __forceinline__ void redo_out_of_range(ChainArgsPtr a, uint32_t first
         if (__builtin_amdgcn_ballot_w64(step_out_of_range(my_steps[bucket])) == 0) continue;
         const uint64_t start = (uint64_t)tile * kChainTile;
         const uint64_t left = a->n - start;
-        stream_ragged_tile<RMODE, W0, WR, kChainRows>(a, start, left < kChainTile ? (uint32_t)left : kChainTile, bucket,
+        stream_ragged_tile<RMODE, W0, WR, MIXED, kChainRows>(a, start, left < kChainTile ? (uint32_t)left : kChainTile, bucket,
                                                       lane);
     }
 }
@@ -948,7 +967,8 @@ __device__ __forceinline__ void store_row_lines(float* row, int lane, const floa
 #define NDQ_CHAIN_PIPED_WAVES NDQ_CHAIN_STREAM_WAVES
 #endif
 // LINES: one tile per wave, its results stored with store_row_lines.
-template <int RMODE, int W0, int WR, bool RAGGED, bool LINES, int FORM>
+// MIXED: the first `dq` workers are DQSG, the rest nested; a loop for each kind.
+template <int RMODE, int W0, int WR, bool MIXED, bool RAGGED, bool LINES, int FORM>
 __global__ __launch_bounds__(kBlock)
 __attribute__((amdgpu_waves_per_eu(FORM == kPiped ? NDQ_CHAIN_PIPED_WAVES : kChainStreamWaves, FORM == kPiped ? NDQ_CHAIN_PIPED_WAVES : kChainStreamWaves)))
 void chain_stream_kernel(ChainArgs a_by_value)
@@ -968,7 +988,7 @@ void chain_stream_kernel(ChainArgs a_by_value)
     float* out_stage = out_stage_all[PIPED ? wave_in_block : 0u];
     const uint32_t tiles = a->tiles;                       // whole tiles: ids 0 .. tiles-1
     const uint32_t tiles_all = TAIL ? tiles + 1u : tiles;  // TAIL: and the ragged one, id `tiles`
-    const uint32_t W = a->W;
+    const uint32_t W = a->W, dq = MIXED ? a->dq : 1u;
     float* out_base = a->out;
     const float scale = a->scale;
     const bool apply_scale = __builtin_amdgcn_readfirstlane(a->apply_scale) != 0;
@@ -977,7 +997,7 @@ void chain_stream_kernel(ChainArgs a_by_value)
     // latencies; as a kernel of its own, or at the end, it would run alone at a fifth of the rate.
     const uint64_t whole = (uint64_t)tiles * TILE;
     if (RAGGED && !PIPED && whole < a->n && first == (stride > tiles ? tiles : 0u))
-        stream_ragged_tile<RMODE, W0, WR, ROWS>(a, whole, (uint32_t)(a->n - whole), bucket_of(a, tiles), lane);
+        stream_ragged_tile<RMODE, W0, WR, MIXED, ROWS>(a, whole, (uint32_t)(a->n - whole), bucket_of(a, tiles), lane);
     if (first >= tiles_all) return;
     const uint32_t my_tiles = (tiles_all - first + stride - 1u) / stride;
     // TAIL: elements of the ragged tile, and per code width the last byte offset inside its
@@ -1034,7 +1054,8 @@ void chain_stream_kernel(ChainArgs a_by_value)
         };
         // Folds worker `w`, whose codes are in `cur`, and fetches the next worker's, or the first
         // worker's of the next tile.
-        auto fold = [&](auto mode, auto width, auto is_first, StreamWorkerPtr w, uint32_t index)
+        // `dq_follows`: MIXED, the next worker is DQSG too.
+        auto fold = [&](auto mode, auto width, auto is_first, StreamWorkerPtr w, uint32_t index, bool dq_follows)
             __attribute__((always_inline)) {
             constexpr int MODE = decltype(mode)::value, WIDTH = decltype(width)::value;
             constexpr bool FIRST = decltype(is_first)::value;
@@ -1045,17 +1066,23 @@ void chain_stream_kernel(ChainArgs a_by_value)
             const unsigned char* codes_next = wn->codes;
             ChainCodes<ROWS> nxt;
             if (last) stream_fetch<W0, ROWS>(codes_next, (uint64_t)next * TILE, lane, nxt, limit_for(next, limit0));
+            else if (MIXED && MODE == kDq && dq_follows) stream_fetch<W0, ROWS>(codes_next, start, lane, nxt, limit_for(tile, limit0));
             else stream_fetch<WR, ROWS>(codes_next, start, lane, nxt, limit_for(tile, limitr));
-            const float step = from_lane(FIRST ? steps_here : scaled_here, index), inv = FIRST ? 0.0f : from_lane(invs_here, index);
+            const float step = from_lane(MODE == kDq ? steps_here : scaled_here, index);
+            const float inv = MODE == kDq ? 0.0f : from_lane(invs_here, index);
             if constexpr (PIPED) stream_fold_piped<MODE, WIDTH, FIRST>(keys, here, keys_next, ahead, extra, cur, step, inv, S, fl);
             else stream_fold<MODE, WIDTH, FIRST, ROWS>(keys, here, extra, cur, step, inv, S);
             keys = keys_next;
             cur = nxt;
         };
-        fold(std::integral_constant<int, kDq>{}, std::integral_constant<int, W0>{}, std::true_type{}, first_worker, 0u);
+        fold(std::integral_constant<int, kDq>{}, std::integral_constant<int, W0>{}, std::true_type{}, first_worker, 0u, MIXED && dq > 1u);
         uint32_t index = 1u;
-        for (StreamWorkerPtr w = first_worker + 1; w != end_worker; ++w, ++index)
-            fold(std::integral_constant<int, RMODE>{}, std::integral_constant<int, WR>{}, std::false_type{}, w, index);
+        StreamWorkerPtr w = first_worker + 1;
+        if constexpr (MIXED)
+            for (; index < dq; ++w, ++index)
+                fold(std::integral_constant<int, kDq>{}, std::integral_constant<int, W0>{}, std::false_type{}, w, index, index + 1u < dq);
+        for (; w != end_worker; ++w, ++index)
+            fold(std::integral_constant<int, RMODE>{}, std::integral_constant<int, WR>{}, std::false_type{}, w, index, false);
         float* out = out_base + start;
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) {
@@ -1106,7 +1133,7 @@ void chain_stream_kernel(ChainArgs a_by_value)
         else if (done == lower2) __builtin_amdgcn_s_setprio(2);
     }
     if (SCALED && __builtin_amdgcn_ballot_w64(out_of_range) != 0)
-        redo_out_of_range<RMODE, W0, WR>(a, first, stride, tiles_all, lane);
+        redo_out_of_range<RMODE, W0, WR, MIXED>(a, first, stride, tiles_all, lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -1391,7 +1418,7 @@ static uint32_t persistent_from(uint32_t W, bool all_dq, uint32_t slots)
     return W <= 3u ? 2u * slots : W < 8u ? slots : kShortTiles;
 }
 
-template <int RMODE, int W0, int WR>
+template <int RMODE, int W0, int WR, bool MIXED>
 static int launch_chain_stream(ChainArgs& a, uint64_t bucket_len, hipStream_t s)
 {
     // Persistent waves, kChainStreamWaves on every SIMD, every wave with the same number of tiles (give or
@@ -1403,9 +1430,15 @@ static int launch_chain_stream(ChainArgs& a, uint64_t bucket_len, hipStream_t s)
         full != 0u && (tuning.threshold_from_env ? full >= tuning.chain_min_tiles_per_wave * slots
                                                  : full >= persistent_from(a.W, RMODE == kDq, slots) ||
                                                        (full >= slots && full < slots + slots / 16u));
-    const bool short_vector = !persistent && full < kShortTiles;
+    constexpr bool RARER = MIXED || W0 == 3;     // (see chain_streams)
+    // Few workers of the rarer plans store whole lines from fewer tiles on: rows / tiles at 1.0, 1.3, 1.6, 2.0 M elements
+    //   2 workers   4.63/4.67  5.32/5.05  5.79/5.13  6.12/5.40 (3-bit and a 2-bit nested)  4.35/4.39  4.70/4.69  5.06/4.73  5.42/4.94
+    //   3           5.13/5.88  5.91/6.00  6.32/6.19  6.68/6.72                             4.76/5.17  5.17/5.54  5.79/5.49  6.10/5.68
+    const uint32_t rows_below = RARER && a.W == 2u ? 1280u : RARER && a.W == 3u ? 1536u : kShortTiles;
+    const bool short_vector = !persistent && full < rows_below;
     const uint32_t tile = short_vector ? ChainStreamTile<kOneRow>::N : kChainTile;
-    const uint32_t tiles = (uint32_t)(a.n / tile);
+    // the rarer plans have the kernels with a ragged last tile only: a whole one takes its place
+    const uint32_t tiles = (uint32_t)((RARER ? a.n - 1u : a.n) / tile);
     if (tiles == 0u) return 1;
     a.tiles = tiles;
     // (see bucket_of; a bucket is a multiple of the tile.  A tile's number times the magic stays below 2^63)
@@ -1420,8 +1453,9 @@ static int launch_chain_stream(ChainArgs& a, uint64_t bucket_len, hipStream_t s)
     auto run = [&](auto lines, auto form) {
         constexpr bool LINES = decltype(lines)::value;
         constexpr int FORM = decltype(form)::value;
-        return ragged ? launch((chain_stream_kernel<RMODE, W0, WR, true, LINES, FORM>), grid, block, s, a)
-                      : launch((chain_stream_kernel<RMODE, W0, WR, false, LINES, FORM>), grid, block, s, a);
+        if constexpr (RARER) return launch((chain_stream_kernel<RMODE, W0, WR, MIXED, true, LINES, FORM>), grid, block, s, a);
+        else return ragged ? launch((chain_stream_kernel<RMODE, W0, WR, MIXED, true, LINES, FORM>), grid, block, s, a)
+                           : launch((chain_stream_kernel<RMODE, W0, WR, MIXED, false, LINES, FORM>), grid, block, s, a);
     };
     if (persistent) return run(std::false_type{}, std::integral_constant<int, kPiped>{});
     if (short_vector) {
@@ -1434,40 +1468,39 @@ static int launch_chain_stream(ChainArgs& a, uint64_t bucket_len, hipStream_t s)
                                           : run(std::false_type{}, std::integral_constant<int, kOneTile>{});
 }
 
-template <int RMODE, int W0>
-static int launch_chain_stream_w(ChainArgs& a, uint64_t bucket_len, uint32_t wr, hipStream_t s)
-{
-    if (wr == 1u) return launch_chain_stream<RMODE, W0, 1>(a, bucket_len, s);
-    if (wr == 2u) return launch_chain_stream<RMODE, W0, 2>(a, bucket_len, s);
-    return launch_chain_stream<RMODE, W0, 4>(a, bucket_len, s);
-}
+// The plans the streaming kernel has.
+enum ChainPlan { kNoStream = 0,
+                 kPurePlan = 1,     // all DQSG, or one DQSG worker and nested ones; codes of 1, 2 and 4 bits
+                 // The rarer plans: several DQSG workers and then nested ones, or 3-bit codes; codes of 2 to 4 bits and of
+                 // 1 to 3.  In kernels of their own, so that the others' stay as they are.  chain_kernel / this, us, at 1.05, 4 and
+                 // 16.8 M elements: 1 x 8 levels 4.1/3.4 6.8/5.6 21.2/13.3, 8 x 8 levels 10.0/7.5 17.5/14.4 50.7/38.2, 8 levels and M = 4
+                 // 4.9/4.5 7.5/6.8 19.5/16.9, 2 x 16 levels and 2 x M = 8 6.7/5.7 11.4/10.1 31.8/27.3, 8 x 16 levels and 8 x M = 4
+                 // 17.5/12.9 34.4/26.6 113.9/84.2, 16 levels and 15 x M = 8 17.8/15.1 37.2/33.9 130/103.
+                 kMixedPlan = 2 };
 
-// Whether the streaming kernel has the plan and the tiling; *rmode and *wr are the mode and the code width of
-// the workers after the first.
-static bool chain_streams(const GeneralChainArgs& a, uint32_t bucket, uint32_t* rmode, uint32_t* wr)
+// Whether it has the plan and the tiling; *dq are the DQSG workers and *wr the code width of the workers after them.
+static ChainPlan chain_streams(const GeneralChainArgs& a, uint32_t bucket, uint32_t* dq, uint32_t* wr)
 {
-    if (a.row_buckets || a.continue_sum) return false;
-    if (!(bucket == 0u || bucket % kChainTile == 0u)) return false;
+    if (a.row_buckets || a.continue_sum) return kNoStream;
+    if (!(bucket == 0u || bucket % kChainTile == 0u)) return kNoStream;
     const uint32_t w0 = a.w[0].bits;
-    if (a.w[0].mode != kDq || !(w0 == 1u || w0 == 2u || w0 == 4u)) return false;
-    *rmode = kDq;
-    *wr = w0;
-    if (a.W > 1u) {
-        *rmode = a.w[1].mode;
-        *wr = a.w[1].bits;
-        if (*rmode != kDq && *rmode != kNestedPow2) return false;
-        if (!(*wr == 1u || *wr == 2u || *wr == 4u)) return false;
-        for (uint32_t j = 2; j < a.W; ++j)
-            if (a.w[j].mode != *rmode || a.w[j].bits != *wr) return false;
-    }
+    uint32_t first = 0u;
+    while (first < a.W && a.w[first].mode == kDq && a.w[first].bits == w0) ++first;
+    if (first == 0u || w0 > 4u) return kNoStream;
+    *dq = first;
+    *wr = first < a.W ? a.w[first].bits : w0;
+    for (uint32_t j = first; j < a.W; ++j)
+        if (a.w[j].mode != kNestedPow2 || a.w[j].bits != *wr) return kNoStream;
     // the high word of the dither's block number is the same for the whole call (it changes every 2^35 elements)
     for (uint32_t j = 0; j < a.W; ++j)
-        if ((a.w[j].index0 >> 35) != ((a.w[j].index0 + a.tl.n - 1u) >> 35)) return false;
-    return true;
+        if ((a.w[j].index0 >> 35) != ((a.w[j].index0 + a.tl.n - 1u) >> 35)) return kNoStream;
+    if (first == a.W) return w0 == 3u ? kMixedPlan : kPurePlan;
+    if (first == 1u && w0 != 3u && (*wr == 1u || *wr == 2u || *wr == 4u)) return kPurePlan;
+    return w0 >= 2u && *wr <= 3u ? kMixedPlan : kNoStream;
 }
 
 // Runs the streaming kernel for a plan that chain_streams accepts; returns 1 when the vector holds no whole tile.
-static int run_chain_stream(const GeneralChainArgs& a, uint32_t bucket, uint32_t rmode, uint32_t wr, hipStream_t s)
+static int run_chain_stream(const GeneralChainArgs& a, uint32_t bucket, ChainPlan plan, uint32_t dq, uint32_t wr, hipStream_t s)
 {
     const uint32_t w0 = a.w[0].bits;
     ChainArgs b;
@@ -1484,17 +1517,36 @@ static int run_chain_stream(const GeneralChainArgs& a, uint32_t bucket, uint32_t
     b.out = a.out;
     b.n = a.tl.n;
     b.W = a.W;
+    b.dq = dq;
     b.apply_scale = a.apply_scale;
     b.scale = a.scale;
     // (a bucket that holds the whole vector is no different from none)
     const uint64_t bucket_len = bucket != 0u && bucket < b.n ? bucket : b.n;
-    if (rmode == kDq)
-        return w0 == 1u ? launch_chain_stream_w<kDq, 1>(b, bucket_len, wr, s)
-                        : w0 == 2u ? launch_chain_stream_w<kDq, 2>(b, bucket_len, wr, s)
-                                   : launch_chain_stream_w<kDq, 4>(b, bucket_len, wr, s);
-    return w0 == 1u ? launch_chain_stream_w<kNestedPow2, 1>(b, bucket_len, wr, s)
-                    : w0 == 2u ? launch_chain_stream_w<kNestedPow2, 2>(b, bucket_len, wr, s)
-                               : launch_chain_stream_w<kNestedPow2, 4>(b, bucket_len, wr, s);
+    auto run = [&](auto rmode, auto first, auto rest, auto mixed) {
+        return launch_chain_stream<decltype(rmode)::value, decltype(first)::value, decltype(rest)::value, decltype(mixed)::value>(
+            b, bucket_len, s);
+    };
+    constexpr std::integral_constant<int, kDq> all_dq{};
+    constexpr std::integral_constant<int, kNestedPow2> nested{};
+    constexpr std::integral_constant<int, 1> b1{};
+    constexpr std::integral_constant<int, 2> b2{};
+    constexpr std::integral_constant<int, 3> b3{};
+    constexpr std::integral_constant<int, 4> b4{};
+    constexpr std::true_type yes{};
+    constexpr std::false_type no{};
+    if (dq == a.W)
+        return w0 == 1u ? run(all_dq, b1, b1, no) : w0 == 2u ? run(all_dq, b2, b2, no) : w0 == 3u ? run(all_dq, b3, b3, no)
+                                                                                                : run(all_dq, b4, b4, no);
+    if (plan == kPurePlan) {
+        auto rest = [&](auto first) {
+            return wr == 1u ? run(nested, first, b1, no) : wr == 2u ? run(nested, first, b2, no) : run(nested, first, b4, no);
+        };
+        return w0 == 1u ? rest(b1) : w0 == 2u ? rest(b2) : rest(b4);
+    }
+    auto rest = [&](auto first) {
+        return wr == 1u ? run(nested, first, b1, yes) : wr == 2u ? run(nested, first, b2, yes) : run(nested, first, b3, yes);
+    };
+    return w0 == 2u ? rest(b2) : w0 == 3u ? rest(b3) : rest(b4);
 }
 
 // Longest vector chain_short_kernel takes.  A workgroup keeps all workers of a row in LDS, so a compute unit holds six of
@@ -1702,9 +1754,9 @@ int ndq_decode_chain(const ndq_worker* workers, uint32_t W, size_t n, uint32_t b
         bool any_m = false;
         for (uint32_t j = 0; j < a.W; ++j) any_m = any_m || a.w[j].mode == kNestedAnyM;
         hipStream_t hs = (hipStream_t)stream;
-        uint32_t rmode, wr;
-        const bool streams = W <= kChainMax && chain_streams(a, bucket, &rmode, &wr);
-        if (W <= kChainMax && n <= short_chain_most(W, streams)) {
+        uint32_t dq, wr;
+        const ChainPlan plan = W <= kChainMax ? chain_streams(a, bucket, &dq, &wr) : kNoStream;
+        if (W <= kChainMax && n <= short_chain_most(W, plan == kPurePlan)) {
             a.tl.bucket_len = bucket != 0u ? bucket : n;
             const dim3 grid((uint32_t)((n + kShortTile - 1u) / kShortTile)), block(kBlock);
             return W <= 8u ? launch(chain_short_kernel<8>, grid, block, hs, a)
@@ -1712,8 +1764,8 @@ int ndq_decode_chain(const ndq_worker* workers, uint32_t W, size_t n, uint32_t b
                                       : launch(chain_short_kernel<32>, grid, block, hs, a);
         }
 #ifndef NDQ_NO_STREAM_CHAIN
-        if (streams) {
-            const int rc_stream = run_chain_stream(a, bucket, rmode, wr, hs);
+        if (plan != kNoStream) {
+            const int rc_stream = run_chain_stream(a, bucket, plan, dq, wr, hs);
             if (rc_stream != 1) return rc_stream;
         }
 #endif

@@ -1,0 +1,98 @@
+"""Chain decoder, plans with several DQSG workers before the nested ones and with 3-bit codes, in the streaming
+kernel's forms (one row or one tile per wave, persistent), against the oracle bit for bit: whole and ragged last
+tiles, codes up to the last byte of a stream, buckets of whole tiles, steps that are 0 or far from 1."""
+import os
+import subprocess
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+import launch_recording as lr
+import oracle
+from oracle import pipeline as opipe
+from paper_1904_01197_amd import ndq
+
+F = np.float32
+DQ, NESTED = "dq", "nested"
+PLANS = {
+    "1 of 8": [(DQ, 8)], "2 of 5": [(DQ, 5)] * 2, "8 and 5 of 3 bits": [(DQ, 8), (DQ, 5)] * 4, "8, M 4": [(DQ, 8), (NESTED, 4)],
+    "5, M 2": [(DQ, 5), (NESTED, 2)], "16, M 8": [(DQ, 16)] + [(NESTED, 8)] * 2, "3 and 4, M 2": [(DQ, 3), (DQ, 4), (NESTED, 2), (NESTED, 2)],
+    "4, M 4": [(DQ, 4)] * 2 + [(NESTED, 4)], "4, M 8": [(DQ, 4)] * 3 + [(NESTED, 8)], "8, M 2": [(DQ, 8)] * 2 + [(NESTED, 2)] * 3,
+    "8, M 8": [(DQ, 8)] * 2 + [(NESTED, 8)], "16, M 2": [(DQ, 16)] * 2 + [(NESTED, 2)] * 2, "16, M 4": [(DQ, 16)] * 8 + [(NESTED, 4)] * 8,
+}
+ROWS = [513, 512 * 2, 512 * 9 + 1, 512 * 40 - 1, 1024 * 15 + 8, 1024 * 33 + 512]
+TILES = [1024 * 12, 1024 * 40, 1024 * 37 + 100, 1024 * 3 + 8, 1024 * 13 + 1, 1024 * 24 + 1023, 1025]
+
+
+def _check(plan, n, bucket, offset, scale):
+    """Any codes and steps are a message."""
+    rng = np.random.default_rng(n + bucket + len(plan))
+    ds_o = opipe.dithers(len(plan), [7 + w for w in range(len(plan))], step=3, offset=offset)
+    codes, steps, workers = [], [], []
+    for w, (kind, arg) in enumerate(plan):
+        codes.append(oracle.pack(rng.integers(0, arg, n).astype(np.uint32), oracle.code_bits(arg)))
+        s = (F(0.01) * (F(1) + rng.random(oracle.num_buckets(n, bucket), dtype=F))).astype(F)
+        if s.size > 3:
+            s[rng.integers(0, s.size, 3)] = [F(0), F(2.0 ** 52), F(2.0 ** -62)]      # outside the range of the fold divided by M
+        steps.append(s)
+        workers.append((torch.from_numpy(codes[w]).cuda(), torch.from_numpy(s).cuda(),
+                        ndq.NDQ_WORKER_DQ if kind == DQ else ndq.NDQ_WORKER_NESTED, arg, ndq.ndq_dither(7 + w, 3, w, offset)))
+    ref = opipe.decode_chain(plan, bucket, n, codes, steps, ds_o, scale)
+    out = torch.full((n + 16,), -3.0, device="cuda")
+    ndq.ndq_decode_chain(workers, n, bucket, scale, out[:n])
+    got = out[:n].cpu().numpy()
+    assert np.array_equal(got, ref), (plan, n, bucket, np.nonzero(got != ref)[0][:5])
+    assert bool((out[n:] == -3.0).all())
+
+
+def _sweep(sizes):
+    for name, plan in PLANS.items():
+        for i, n in enumerate(sizes):
+            bucket = (0, 1024, 2048, 8192)[(i + len(plan)) % 4]
+            print(name, n, bucket, flush=True)
+            _check(plan, n, bucket, 8 * (n % 4099), 1.0 if i % 2 else 0.25)
+            if bucket:
+                _check(plan, n, 0, 0, 1.0)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", list(PLANS))
+def test_rows_and_tiles_match_oracle(name):
+    plan = PLANS[name]
+    long = 1024 * (1280 if len(plan) == 2 else 1536 if len(plan) == 3 else 2048)
+    for n, bucket in [(n, b) for n in ROWS for b in (0, 1024)] + [(long - 1, 0), (long, 0), (long + 1, 2048), (long + 4 * 1024 + 700, 0)]:
+        _check(plan, n, bucket, 8 * (n % 129), 1.0 / len(plan))
+
+
+@pytest.mark.gpu
+def test_persistent_form_matches_oracle_on_short_vectors():
+    # (the library reads the thresholds once per process)
+    env = dict(os.environ, NDQ_STREAM_MIN_TILES_PER_WAVE="0", NDQ_STREAM_MAX_BLOCKS="3", PYTHONPATH=os.pathsep.join(sys.path))
+    code = "import sys; sys.path.insert(0, %r); import test_gpu_chain_plans as t; t._sweep(t.TILES); print('PLANS_OK')" % os.path.dirname(
+        os.path.abspath(__file__))
+    res = subprocess.run([sys.executable, "-u", "-c", code], env=env, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True,
+                         timeout=300)
+    assert res.returncode == 0 and "PLANS_OK" in res.stdout, "\n".join(res.stdout.splitlines()[-15:])
+
+
+@pytest.fixture(scope="module")
+def recorder(tmp_path_factory):
+    return lr.build(tmp_path_factory.mktemp("recorder"))
+
+
+@pytest.mark.parametrize("name", list(PLANS))
+def test_plans_reach_the_streaming_kernel(recorder, name):
+    plan = PLANS[name]
+    workers = [{"codes": 0x20000000, "steps": 0x30000000, "kind": 0 if kind == DQ else 1, "levels_or_M": arg, "alpha": 1.0,
+                "dither": [1, 2, 3, 0]} for kind, arg in plan]
+    sizes = [1024 * 1024, 1024 * 2048, 1024 * 12288]
+    calls = [["ndq_decode_chain", workers, len(plan), n, 0, 1.0, 0x40000000, None] for n in sizes]
+    calls.append(["ndq_decode_chain", [dict(w, alpha=0.9) for w in workers], len(plan), sizes[1], 0, 1.0, 0x40000000, None])
+    got = lr.record(recorder, calls)
+    for (rc, launches), form in zip(got, (2, 0 if len(plan) in (1, 16) else 1, 0)):
+        assert rc == 0 and len(launches) == 1 and "chain_stream_kernel" in launches[0][0], launches
+        assert launches[0][0].endswith("ELi%dEEEvNS_9ChainArgsE" % form), launches
+    # a worker that shrinks: the general kernel
+    assert ("chain_stream_kernel" in got[3][1][0][0]) == all(kind == DQ for kind, _ in plan)
