@@ -35,13 +35,11 @@ template <int MODE, int ACC> struct DecRows {
 enum Acc { kStore = 0, kAccumulate = 1, kAccumulateInPlace = 2 };  // in place: out == side
 
 // Four elements of a row: res = decoded value (stored, or added to ps / ys).
-// Returns whether a fast quotient was too close to a rounding tie (see Div).
-template <int MODE, int ACC, int DIV>
-__device__ __forceinline__ bool decode_row(const DecodeArgs& a, uint32_t packed, uint32_t bits,
+template <int MODE, int ACC>
+__device__ __forceinline__ void decode_row(const DecodeArgs& a, uint32_t packed, uint32_t bits,
                                            const float (&ys)[4], const float (&ps)[4], const float (&v)[4],
                                            float step, float inv, float (&res)[4])
 {
-    bool near_tie = false;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const uint32_t c = __builtin_amdgcn_ubfe(packed, k * bits, bits);   // bit-field extract
@@ -50,7 +48,7 @@ __device__ __forceinline__ bool decode_row(const DecodeArgs& a, uint32_t packed,
             q = (float)((int32_t)c + a.qp.q_min);
         } else {
             yk = ys[k] * a.side_scale;
-            q = coset_index_f<MODE, DIV>((float)c, yk, inv, v[k], a.qp, near_tie);
+            q = coset_index_f<MODE>((float)c, yk, inv, v[k], a.qp);
         }
         const float val = (MODE == kDqHalf) ? step * q
                                             : shrink<MODE>(index_value(q, step, v[k]), yk, a.qp);
@@ -58,7 +56,6 @@ __device__ __forceinline__ bool decode_row(const DecodeArgs& a, uint32_t packed,
         else if (ACC == kAccumulate) res[k] = ps[k] + val;
         else res[k] = ys[k] + val;
     }
-    return near_tie;
 }
 
 // One wave decodes one tile.  FULL: every element valid, no guards.  STRADDLE:
@@ -123,10 +120,7 @@ __device__ __forceinline__ void decode_tile(const DecodeArgs& a, const TileRef& 
         const float ys[4] = {y[r].x, y[r].y, y[r].z, y[r].w};
         const float ps[4] = {prev[r].x, prev[r].y, prev[r].z, prev[r].w};
         float res[4];
-        const bool near_tie = decode_row<MODE, ACC, kDivFast>(a, packed[r], bits, ys, ps, v, step, inv, res);
-        // wave-uniform and rare (M not a power of two only): redo the row with the division
-        if (MODE == kNestedAnyM && __builtin_amdgcn_ballot_w64(near_tie) != 0)
-            decode_row<MODE, ACC, kDivExact>(a, packed[r], bits, ys, ps, v, step, inv, res);
+        decode_row<MODE, ACC>(a, packed[r], bits, ys, ps, v, step, inv, res);
         if (FULL || o + 4 <= t.len) {
             store_streaming(out + o, res[0], res[1], res[2], res[3]);
         } else {
@@ -239,28 +233,18 @@ __device__ __forceinline__ void chain_fetch(const GeneralChainArgs& a, const Cha
     }
 }
 
-// N elements of one worker: next = S + (this worker's decoded
-// values), the side information being S scaled.  Returns whether any element's
-// fast quotient was too close to a rounding tie to be trusted (see Div).
-template <int MODE, bool FIRST, int DIV, int N>
-__device__ __forceinline__ bool chain_row(float side_scale, const Quant& qp, const float (&c_f)[N],
-                                          const float (&v)[N], float step, float inv,
-                                          const float (&S)[N], float (&next)[N])
+// One element of one worker: S + (the worker's decoded value), or that value (FIRST), the side information being S scaled.
+// c_f: the code as a float, plus q_min for DQSG.
+template <int MODE, bool FIRST>
+__device__ __forceinline__ float chain_element(float side_scale, const Quant& qp, float c_f, float v, float step, float inv, float S)
 {
-    bool near_tie = false;
-#pragma unroll
-    for (int k = 0; k < N; ++k) {
-        float q, yk = 0.0f;
-        if (MODE == kDq) {
-            q = c_f[k];
-        } else {
-            yk = S[k] * side_scale;
-            q = coset_index_f<MODE, DIV>(c_f[k], yk, inv, v[k], qp, near_tie);
-        }
-        const float val = shrink<MODE>(index_value(q, step, v[k]), yk, qp);
-        next[k] = FIRST ? val : S[k] + val;
+    float q = c_f, y = 0.0f;
+    if (MODE != kDq) {
+        y = S * side_scale;
+        q = coset_index_f<MODE>(c_f, y, inv, v, qp);
     }
-    return near_tie;
+    const float val = shrink<MODE>(index_value(q, step, v), y, qp);
+    return FIRST ? val : S + val;
 }
 
 // Folds one worker into the running sum S of a tile.  NARROW: codes of at most
@@ -286,43 +270,16 @@ __device__ __forceinline__ void chain_fold(const ChainWorker& cw, const ChainFet
         const uint32_t half[2] = {(uint32_t)f.codes[r], (uint32_t)(f.codes[r] >> (4u * bits))};
         float v[8];
         dither8(cw.ds, block0 + (o >> 3), v);
-        if (MODE == kNestedAnyM) {
-            // the eight residues as floats, a fast pass, and -- wave-uniform and rare -- the
-            // row again with the true division where a quotient sat too close to a tie
-            float c_f[8];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                if (NARROW) c_f[k] = field.get(half[k >> 2], k & 3);
-                else c_f[k] = (float)__builtin_amdgcn_ubfe(half[k >> 2], (k & 3) * bits, bits);
+        for (int k = 0; k < 8; ++k) {
+            float c_f;
+            if (NARROW) {
+                c_f = field.get(half[k >> 2], k & 3);
+            } else {
+                const uint32_t c = __builtin_amdgcn_ubfe(half[k >> 2], (k & 3) * bits, bits);
+                c_f = MODE == kDq ? (float)((int32_t)c + qp.q_min) : (float)c;
             }
-            float next[8];
-            const bool near_tie = chain_row<MODE, FIRST, kDivFast>(cw.side_scale, qp, c_f, v, step, inv, S[r], next);
-            if (__builtin_amdgcn_ballot_w64(near_tie) != 0)
-                chain_row<MODE, FIRST, kDivExact>(cw.side_scale, qp, c_f, v, step, inv, S[r], next);
-#pragma unroll
-            for (int k = 0; k < 8; ++k) S[r][k] = next[k];
-        } else {
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                // the code as a float: plus q_min for DQSG, as it is for a nested worker
-                float c_f;
-                if (NARROW) {
-                    c_f = field.get(half[k >> 2], k & 3);
-                } else {
-                    const uint32_t c = __builtin_amdgcn_ubfe(half[k >> 2], (k & 3) * bits, bits);
-                    c_f = MODE == kDq ? (float)((int32_t)c + qp.q_min) : (float)c;
-                }
-                float q, yk = 0.0f;
-                bool unused = false;
-                if (MODE == kDq) {
-                    q = c_f;
-                } else {
-                    yk = S[r][k] * cw.side_scale;
-                    q = coset_index_f<MODE, kDivExact>(c_f, yk, inv, v[k], qp, unused);
-                }
-                const float val = shrink<MODE>(index_value(q, step, v[k]), yk, qp);
-                S[r][k] = FIRST ? val : S[r][k] + val;
-            }
+            S[r][k] = chain_element<MODE, FIRST>(cw.side_scale, qp, c_f, v[k], step, inv, S[r][k]);
         }
     }
 }
@@ -335,7 +292,7 @@ __device__ __forceinline__ void chain_fold_width(const ChainWorker& cw, const Ch
     else chain_fold<MODE, false, FIRST, ROWB, ROWS>(cw, f, block0, lane, S);
 }
 
-template <bool FULL, bool ROWB, bool ANYM, int ROWS>
+template <bool FULL, bool ROWB, int ROWS>
 __device__ __forceinline__ void chain_tile(const GeneralChainArgs& a, const TileRef& t, int lane)
 {
     float S[ROWS][8];
@@ -363,7 +320,7 @@ __device__ __forceinline__ void chain_tile(const GeneralChainArgs& a, const Tile
             chain_fold_width<kNestedPow2, false, ROWB, ROWS>(cw, cur, block0, lane, S);
         } else if (cw.mode == kNestedPow2Shrink) {
             chain_fold_width<kNestedPow2Shrink, false, ROWB, ROWS>(cw, cur, block0, lane, S);
-        } else if (ANYM) {
+        } else {
             chain_fold_width<kNestedAnyM, false, ROWB, ROWS>(cw, cur, block0, lane, S);
         }
         cur = nxt;
@@ -390,12 +347,9 @@ __device__ __forceinline__ void chain_tile(const GeneralChainArgs& a, const Tile
 #ifndef NDQ_CHAIN_WAVES_PER_EU
 #define NDQ_CHAIN_WAVES_PER_EU 6
 #endif
-// ANYM: some worker's nesting ratio is not a power of two.  Those workers take
-// the two-pass rows of chain_fold, which need more registers: that instantiation
-// runs four waves per SIMD, and the common one does not carry their code at all.
-template <bool ROWB, bool ANYM, int ROWS>
+template <bool ROWB, int ROWS>
 __global__ __launch_bounds__(kBlock)
-__attribute__((amdgpu_waves_per_eu(ANYM ? 4 : NDQ_CHAIN_WAVES_PER_EU)))
+__attribute__((amdgpu_waves_per_eu(NDQ_CHAIN_WAVES_PER_EU)))
 void chain_kernel(GeneralChainArgs a)
 {
     constexpr uint32_t TILE = kWave * kLaneElems * ROWS;
@@ -403,8 +357,8 @@ void chain_kernel(GeneralChainArgs a)
     const uint32_t tile_id =
         blockIdx.x * kWavesPerBlock + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const TileRef t = locate_tile(a.tl, tile_id, TILE);
-    if (t.len == TILE && t.start + TILE + 64u <= a.tl.n) chain_tile<true, ROWB, ANYM, ROWS>(a, t, lane);
-    else if (t.len != 0) chain_tile<false, ROWB, ANYM, ROWS>(a, t, lane);
+    if (t.len == TILE && t.start + TILE + 64u <= a.tl.n) chain_tile<true, ROWB, ROWS>(a, t, lane);
+    else if (t.len != 0) chain_tile<false, ROWB, ROWS>(a, t, lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -426,12 +380,8 @@ template <int MODE, bool FIRST>
 __device__ __forceinline__ void short_fold(float side_scale, const Quant& qp, const float (&c_f)[2], const float (&v)[2],
                                            float step, float inv, float (&S)[2])
 {
-    float next[2];
-    const bool near_tie = chain_row<MODE, FIRST, kDivFast>(side_scale, qp, c_f, v, step, inv, S, next);
-    if (MODE == kNestedAnyM && __builtin_amdgcn_ballot_w64(near_tie) != 0)
-        chain_row<MODE, FIRST, kDivExact>(side_scale, qp, c_f, v, step, inv, S, next);
-    S[0] = next[0];
-    S[1] = next[1];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) S[k] = chain_element<MODE, FIRST>(side_scale, qp, c_f[k], v[k], step, inv, S[k]);
 }
 
 template <uint32_t WMAX>
@@ -554,7 +504,7 @@ __global__ __launch_bounds__(kBlock) void chain_short_kernel(GeneralChainArgs by
 // worker's, and at the end the next tile's, code words while it folds the
 // current worker in.
 //
-// Arithmetic per element of a nested worker, bit for bit that of chain_row with
+// Arithmetic per element of a nested worker, bit for bit that of chain_element with
 // kNestedPow2 (every scaling below is by a power of two, which commutes with
 // rounding; k and m/M + k are exact or rounded exactly like m + M k):
 //   m' = m / M (from the packed field, exact)      y = S * side_scale
@@ -1751,8 +1701,6 @@ int ndq_decode_chain(const ndq_worker* workers, uint32_t W, size_t n, uint32_t b
                                  : (wk.alpha == 1.0f ? kNestedPow2 : kNestedPow2Shrink));
             cw.first = (p0 + j) == 0u;
         }
-        bool any_m = false;
-        for (uint32_t j = 0; j < a.W; ++j) any_m = any_m || a.w[j].mode == kNestedAnyM;
         hipStream_t hs = (hipStream_t)stream;
         uint32_t dq, wr;
         const ChainPlan plan = W <= kChainMax ? chain_streams(a, bucket, &dq, &wr) : kNoStream;
@@ -1774,13 +1722,9 @@ int ndq_decode_chain(const ndq_worker* workers, uint32_t W, size_t n, uint32_t b
             a.row_buckets = 0u;
         }
         const dim3 grid(blocks_for(a.tl.total_tiles)), block(kBlock);
-        int rc_launch;
-        if (short_vector && any_m) rc_launch = launch((chain_kernel<false, true, 1>), grid, block, hs, a);
-        else if (short_vector) rc_launch = launch((chain_kernel<false, false, 1>), grid, block, hs, a);
-        else if (a.row_buckets && any_m) rc_launch = launch((chain_kernel<true, true, kChainRows>), grid, block, hs, a);
-        else if (a.row_buckets) rc_launch = launch((chain_kernel<true, false, kChainRows>), grid, block, hs, a);
-        else if (any_m) rc_launch = launch((chain_kernel<false, true, kChainRows>), grid, block, hs, a);
-        else rc_launch = launch((chain_kernel<false, false, kChainRows>), grid, block, hs, a);
+        const int rc_launch = short_vector ? launch((chain_kernel<false, 1>), grid, block, hs, a)
+                              : a.row_buckets ? launch((chain_kernel<true, kChainRows>), grid, block, hs, a)
+                                              : launch((chain_kernel<false, kChainRows>), grid, block, hs, a);
         if (rc_launch != NDQ_OK) return NDQ_ELAUNCH;
     }
     return NDQ_OK;

@@ -381,32 +381,26 @@ struct FieldScaled {
 // below 2^24 and otherwise rounded once, exactly like converting the exact
 // integer; eq. (8) puts no bound on k and neither does this.
 //
-// How coset_index_f divides by M.  kDivExact: the correctly rounded quotient, as
-// the decoder is defined.  kDivFast: the product with the rounded reciprocal,
-// which differs from that quotient by less than 2^-22 |quotient| and therefore
-// rounds to the same integer unless it lies that close to a half-integer; the
-// caller is told (`near_tie`) and repeats the few affected rows with kDivExact.
-// For a power of two M the two coincide and near_tie is never set.
-enum Div { kDivExact = 0, kDivFast = 1 };
+// The quotient by M is the correctly rounded one.  M a power of two: the product with 1/M.  Otherwise from the product
+// q with the rounded reciprocal y = 1/M by one correction, q + y (x - M q) (Markstein 1990: exact where q is a faithful
+// rounding; every mantissa with every M from 3 to 255 is checked by tests/test_kernel_identities.py).  x - M q is exact; where
+// x is so small that it is not, the quotient rounds to 0 either way.  An infinite x makes it NaN: the fix-up of the
+// division gives the infinity back.  (Four instructions; a product whose doubtful roundings are found and then done
+// again by the division takes eight and a branch: chains of 4 workers of
+// 5 levels and 4 with M = 3, 0.27 and 4 M elements, 6.56 -> 6.47 and 22.75 -> 21.7 us, 1 + 1 worker 8.7 -> 8.1.)
+__device__ __forceinline__ float divide_by_ratio(float x, const Quant& qp)
+{
+    const float q = x * qp.inv_M_f;
+    const float rest = __builtin_fmaf(-qp.M_f, q, x);
+    return __builtin_amdgcn_div_fixupf(__builtin_fmaf(rest, qp.inv_M_f, q), qp.M_f, x);
+}
 
-template <int MODE, int DIV>
-__device__ __forceinline__ float coset_index_f(float m_f, float y, float inv, float v,
-                                               const Quant& qp, bool& near_tie)
+template <int MODE>
+__device__ __forceinline__ float coset_index_f(float m_f, float y, float inv, float v, const Quant& qp)
 {
     const float c = __builtin_fmaf(y, inv, v);
     const float diff = c - m_f;
-    float k;
-    if (MODE == kNestedPow2 || MODE == kNestedPow2Shrink) {
-        k = __builtin_rintf(diff * qp.inv_M_f);        // exact scaling
-    } else if (DIV == kDivFast) {
-        const float approx = diff * qp.inv_M_f;
-        k = __builtin_rintf(approx);
-        const float off = approx - k;                                  // exact, in [-1/2, 1/2]
-        const float tol = __builtin_fmaf(__builtin_fabsf(approx), 0x1p-21f, 0x1p-21f);
-        near_tie = near_tie || (__builtin_fabsf(off) + tol >= 0.5f);
-    } else {
-        k = __builtin_rintf(diff / qp.M_f);
-    }
+    const float k = __builtin_rintf(MODE == kNestedAnyM ? divide_by_ratio(diff, qp) : diff * qp.inv_M_f);
     return __builtin_fmaf(k, qp.M_f, m_f);
 }
 
