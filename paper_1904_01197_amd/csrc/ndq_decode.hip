@@ -538,6 +538,7 @@ struct ChainArgs {
     uint32_t tiles;           // whole tiles
     uint32_t W;
     uint32_t dq;              // MIXED: how many of the workers, the first ones, are DQSG
+    float ratio, inv_ratio;   // kNestedAnyM: the nested workers' M, and 1/M rounded
     int apply_scale;
     float scale;
 };
@@ -620,7 +621,7 @@ __device__ __forceinline__ void stream_fetch_ragged(const unsigned char* codes, 
 // `block`: low word of the number of the lane's first block (the high word is the same for the whole
 // call and part of the keys).
 template <int MODE, int WIDTH, bool FIRST, int ROWS>
-__device__ __forceinline__ void stream_fold(const PhiloxUniform& keys, uint32_t block, uint32_t extra,
+__device__ __forceinline__ void stream_fold(const PhiloxUniform& keys, uint32_t block, uint32_t extra, float ratio, float inv_ratio,
                                             const ChainCodes<ROWS>& f, float step, float inv, float (&S)[ROWS][8])
 {
     constexpr int NF = WIDTH > 2 ? 4 : 8;       // fields of a group that stay inside 23 bits
@@ -629,8 +630,11 @@ __device__ __forceinline__ void stream_fold(const PhiloxUniform& keys, uint32_t 
     // DQSG: the code c itself, the index offset q_min going into the dither instead:
     // (c + q_min) - v and c - (v - q_min) are the same exact value rounded once, and
     // v - q_min is exact for |q_min| <= 8 (code widths up to 4 bits); raised by 64.5, the dither
-    // leaves c + 64.5 to subtract it from.  Nested: m' = c / M.
-    const FieldScaled<NF> field((uint32_t)WIDTH, MODE == kDq ? 0u : (uint32_t)WIDTH, MODE == kDq ? 64.5f : 0.0f);
+    // leaves c + 64.5 to subtract it from.  Nested: m' = c / M (a ratio that is no power of two: c).
+    const FieldScaled<NF> field((uint32_t)WIDTH, MODE == kNestedPow2 ? (uint32_t)WIDTH : 0u, MODE == kDq ? 64.5f : 0.0f);
+    Quant qp;                       // (what the coset decoder reads of it)
+    qp.M_f = ratio;
+    qp.inv_M_f = inv_ratio;
     const uint32_t dither_bits = MODE == kDq ? kDitherBits - (extra << 17) : kDitherBits;
     const float side_scale = __uint_as_float(extra);
 #pragma unroll
@@ -649,6 +653,9 @@ __device__ __forceinline__ void stream_fold(const PhiloxUniform& keys, uint32_t 
             float val;
             if (MODE == kDq) {
                 val = step * (c_f - x);
+            } else if (MODE == kNestedAnyM) {
+                const float v = x - 64.5f;
+                val = index_value(coset_index_f<kNestedAnyM>(c_f, S[r][k] * side_scale, inv, v, qp), step, v);
             } else {
                 const float v = x - 64.5f;
                 const float y = S[r][k] * side_scale;
@@ -697,11 +704,13 @@ __device__ __forceinline__ bool step_out_of_range(float step)
 // block's multiplies and xors are spread evenly among them.
 //   nested  x raised dither  v dither/M  a masked code [b m']  y S/count  c c'  t c' - m'  r rint
 //           q + m'  d - v/M  p times M Delta  s added to S
+//           a ratio that is no power of two: undivided, and between t and r the quotient of divide_by_ratio in its three
+//           pieces Q R N (S and c are finite where the steps are in range, so it needs no fix-up)
 //   DQSG    x raised dither  a masked code  b c + 64.5  d minus x  p times Delta  [s added to S]
 //   m, X    the next multiply, the next xor of the Philox block
 struct RowProgram {
-    char op[160];
-    uint8_t element[160];
+    char op[176];
+    uint8_t element[176];
     int n;
 };
 constexpr RowProgram row_program(const char* stages, int lag)
@@ -728,11 +737,14 @@ constexpr RowProgram row_program(const char* stages, int lag)
 constexpr int kRowLag = 2;
 
 // nested workers with 1-bit codes take the fold divided by M
-template <int MODE, int WIDTH> struct RowScaled { static constexpr bool value = MODE != kDq && WIDTH == 1; };
+template <int MODE, int WIDTH> struct RowScaled { static constexpr bool value = MODE == kNestedPow2 && WIDTH == 1; };
+// folds that are only right while the steps are in range
+template <int MODE, int WIDTH> struct RowRanged { static constexpr bool value = RowScaled<MODE, WIDTH>::value || MODE == kNestedAnyM; };
 template <int MODE, int WIDTH, bool FIRST> struct RowOrder {
     static constexpr bool BIT = RowScaled<MODE, WIDTH>::value;
     static constexpr RowProgram program =
-        row_program(MODE == kDq ? (FIRST ? "xabdp" : "xabdps") : BIT ? "xvayctrqdps" : "xvabyctrqdps", kRowLag);
+        row_program(MODE == kDq ? (FIRST ? "xabdp" : "xabdps") : MODE == kNestedAnyM ? "xvabyctQRNrqdps"
+                                : BIT ? "xvayctrqdps" : "xvabyctrqdps", kRowLag);
 };
 
 template <int MODE, int WIDTH, bool FIRST>
@@ -742,10 +754,10 @@ struct RowFold {
     static constexpr float M_f = (float)(1u << WIDTH), inv_M_f = 1.0f / M_f;
     const uint32_t (&words)[4];
     uint32_t code, code_hi, dither_bits;
-    float step, inv, side_scale;
+    float step, inv, side_scale, ratio, inv_ratio;
     float (&S)[8];
     PhiloxFlight& fl;
-    float x[8], v[8], m[8], w[8];
+    float x[8], v[8], m[8], w[8], z[8];
 
     template <int I> __device__ __forceinline__ void run()
     {
@@ -754,7 +766,8 @@ struct RowFold {
         constexpr int j = NF == 8 ? k : (k & 3);
         constexpr float bit_scale = __builtin_bit_cast(float, (uint32_t)(253u - (1u << (k & 7))) << 23);   // 2^(126 - 2^k)
         constexpr uint32_t mask = ((1u << WIDTH) - 1u) << (j * WIDTH);
-        constexpr uint32_t base = (150u - j * WIDTH - (MODE == kDq ? 0u : WIDTH)) << 23;
+        constexpr uint32_t base = (150u - j * WIDTH - (MODE == kNestedPow2 ? WIDTH : 0u)) << 23;
+        constexpr bool ANY = MODE == kNestedAnyM;
         if constexpr (op == 'm') fl.next_multiply();
         if constexpr (op == 'X') fl.next_xor();
         if constexpr (op == 'x') x[k] = dither_raised<(k & 1) != 0>(words[k >> 1], dither_bits);
@@ -765,10 +778,13 @@ struct RowFold {
         if constexpr (op == 'b') m[k] = m[k] - (__builtin_bit_cast(float, base) - (MODE == kDq ? 64.5f : 0.0f));
         if constexpr (op == 'y') w[k] = S[k] * side_scale;
         if constexpr (op == 'c') w[k] = __builtin_fmaf(w[k], inv, v[k]);
-        if constexpr (op == 't') w[k] = BIT ? __builtin_fmaf(m[k], -bit_scale, w[k]) : __builtin_fmaf(w[k], inv_M_f, -m[k]);
+        if constexpr (op == 't') w[k] = ANY ? w[k] - m[k] : BIT ? __builtin_fmaf(m[k], -bit_scale, w[k]) : __builtin_fmaf(w[k], inv_M_f, -m[k]);
+        if constexpr (op == 'Q') z[k] = w[k] * inv_ratio;
+        if constexpr (op == 'R') w[k] = __builtin_fmaf(-ratio, z[k], w[k]);
+        if constexpr (op == 'N') w[k] = __builtin_fmaf(w[k], inv_ratio, z[k]);
         if constexpr (op == 'r') w[k] = __builtin_rintf(w[k]);
-        if constexpr (op == 'q') w[k] = BIT ? __builtin_fmaf(m[k], bit_scale, w[k]) : w[k] + m[k];
-        if constexpr (op == 'd') w[k] = MODE == kDq ? m[k] - x[k] : BIT ? w[k] - v[k] : __builtin_fmaf(w[k], M_f, -v[k]);
+        if constexpr (op == 'q') w[k] = ANY ? __builtin_fmaf(w[k], ratio, m[k]) : BIT ? __builtin_fmaf(m[k], bit_scale, w[k]) : w[k] + m[k];
+        if constexpr (op == 'd') w[k] = MODE == kDq ? m[k] - x[k] : BIT || ANY ? w[k] - v[k] : __builtin_fmaf(w[k], M_f, -v[k]);
         if constexpr (op == 'p' && FIRST) S[k] = step * w[k];
         if constexpr (op == 'p' && !FIRST) w[k] = step * w[k];
         if constexpr (op == 's') S[k] = S[k] + w[k];
@@ -779,14 +795,14 @@ struct RowFold {
 
 template <int MODE, int WIDTH, bool FIRST>
 __device__ __forceinline__ void fold_row_piped(const uint32_t (&words)[4], uint32_t code, float step, float inv,
-                                               uint32_t extra, float (&S)[8], PhiloxFlight& fl)
+                                               uint32_t extra, float ratio, float inv_ratio, float (&S)[8], PhiloxFlight& fl)
 {
     using Fold = RowFold<MODE, WIDTH, FIRST>;
     // raised dither: v + 64 (DQSG: v - q_min + 64, so that c minus it is (c + q_min) - v; nested: divided by M)
     const uint32_t dither_bits = MODE == kDq ? kDitherBits - (extra << 17)
                                              : Fold::BIT ? kDitherBits - ((uint32_t)WIDTH << 23) : kDitherBits;
-    Fold f = {words, Fold::BIT ? code << 23 : code, code >> (4 * WIDTH), dither_bits, step, inv, __uint_as_float(extra), S, fl,
-              {}, {}, {}, {}};
+    Fold f = {words, Fold::BIT ? code << 23 : code, code >> (4 * WIDTH), dither_bits, step, inv, __uint_as_float(extra),
+              ratio, inv_ratio, S, fl, {}, {}, {}, {}, {}};
     f.run_all(std::make_integer_sequence<int, RowOrder<MODE, WIDTH, FIRST>::program.n>());
 }
 
@@ -794,9 +810,9 @@ __device__ __forceinline__ void fold_row_piped(const uint32_t (&words)[4], uint3
 // way: the second row's with this worker's keys, then the next worker's first with its keys.
 template <int MODE, int WIDTH, bool FIRST>
 __device__ __forceinline__ void stream_fold_piped(const PhiloxUniform& keys, uint32_t block, const PhiloxUniform& keys_next,
-                                                  uint32_t block_next, uint32_t extra,
-                                                  const ChainCodes<kChainRows>& f, float step, float inv,
-                                                  float (&S)[kChainRows][8], PhiloxFlight& fl)
+                                                  uint32_t block_next, uint32_t extra, float ratio, float inv_ratio,
+                                                  const ChainCodes<kChainRows>& f, const float (&step)[kChainRows],
+                                                  const float (&inv)[kChainRows], float (&S)[kChainRows][8], PhiloxFlight& fl)
 {
 #pragma unroll
     for (int r = 0; r < kChainRows; ++r) {
@@ -804,7 +820,7 @@ __device__ __forceinline__ void stream_fold_piped(const PhiloxUniform& keys, uin
         fl.words(words);
         if (r + 1 < kChainRows) fl.start(keys, block + (uint32_t)((r + 1) * kWave));
         else fl.start(keys_next, block_next);
-        fold_row_piped<MODE, WIDTH, FIRST>(words, f.w[r], step, inv, extra, S[r], fl);
+        fold_row_piped<MODE, WIDTH, FIRST>(words, f.w[r], step[r], inv[r], extra, ratio, inv_ratio, S[r], fl);
     }
 }
 
@@ -825,15 +841,17 @@ __device__ __forceinline__ void stream_ragged_tile(ChainArgsPtr a, uint64_t star
     stream_fetch_ragged<W0, ROWS>(a->w[0].codes, a->steps[0], start, len, bucket, lane, cur);
     nxt = cur;
     if (W > 1u) fetch(1u);
-    stream_fold<kDq, W0, true, ROWS>(uniform_keys(&a->w[0]), a->w[0].block + block, a->w[0].extra, cur, cur.step, 0.0f, S);
+    stream_fold<kDq, W0, true, ROWS>(uniform_keys(&a->w[0]), a->w[0].block + block, a->w[0].extra, 0.0f, 0.0f, cur, cur.step,
+                                     0.0f, S);
     cur = nxt;
     for (uint32_t w = 1; w < W; ++w) {
         if (w + 1u < W) fetch(w + 1u);
         if (MIXED && w < dq)
-            stream_fold<kDq, W0, false, ROWS>(uniform_keys(&a->w[w]), a->w[w].block + block, a->w[w].extra, cur, cur.step, 0.0f, S);
+            stream_fold<kDq, W0, false, ROWS>(uniform_keys(&a->w[w]), a->w[w].block + block, a->w[w].extra, 0.0f, 0.0f, cur,
+                                              cur.step, 0.0f, S);
         else
-            stream_fold<RMODE, WR, false, ROWS>(uniform_keys(&a->w[w]), a->w[w].block + block, a->w[w].extra, cur, cur.step,
-                                                inv_step(cur.step), S);
+            stream_fold<RMODE, WR, false, ROWS>(uniform_keys(&a->w[w]), a->w[w].block + block, a->w[w].extra, a->ratio, a->inv_ratio,
+                                                cur, cur.step, inv_step(cur.step), S);
         cur = nxt;
     }
     float* out = a->out + start;
@@ -850,20 +868,23 @@ __device__ __forceinline__ void stream_ragged_tile(ChainArgsPtr a, uint64_t star
 
 // The wave's tiles that have a step outside the range fold_row_piped is exact in, decoded
 // again in the plain form.
-template <int RMODE, int W0, int WR, bool MIXED>
+template <int RMODE, int W0, int WR, bool MIXED, bool ROWB>
 __device__ __forceinline__ void redo_out_of_range(ChainArgsPtr a, uint32_t first, uint32_t stride,
                                                            uint32_t tiles_all, int lane)
 {
     const uint32_t W = a->W;
     const float* my_steps = a->steps[(uint32_t)lane < W ? (uint32_t)lane : W - 1u];
-    for (uint32_t tile = first; tile < tiles_all; tile += stride) {
-        const uint32_t bucket = bucket_of(a, tile);
-        if (__builtin_amdgcn_ballot_w64(step_out_of_range(my_steps[bucket])) == 0) continue;
-        const uint64_t start = (uint64_t)tile * kChainTile;
-        const uint64_t left = a->n - start;
-        stream_ragged_tile<RMODE, W0, WR, MIXED, kChainRows>(a, start, left < kChainTile ? (uint32_t)left : kChainTile, bucket,
-                                                      lane);
-    }
+    constexpr int ROWS = ROWB ? 1 : kChainRows;          // rows that share a step
+    constexpr uint32_t PART = kWave * kLaneElems * ROWS;
+    for (uint32_t tile = first; tile < tiles_all; tile += stride)
+        for (uint32_t r = 0; r < kChainTile / PART; ++r) {
+            const uint64_t start = (uint64_t)tile * kChainTile + r * PART;
+            if (start >= a->n) break;
+            const uint32_t bucket = ROWB ? tile * kChainRows + r : bucket_of(a, tile);
+            if (__builtin_amdgcn_ballot_w64(step_out_of_range(my_steps[bucket])) == 0) continue;
+            const uint64_t left = a->n - start;
+            stream_ragged_tile<RMODE, W0, WR, MIXED, ROWS>(a, start, left < PART ? (uint32_t)left : PART, bucket, lane);
+        }
 }
 
 // The one-tile forms of few workers are bound by their stores: a lane's eight results are 32 bytes, so a store of 16 bytes a
@@ -918,7 +939,8 @@ __device__ __forceinline__ void store_row_lines(float* row, int lane, const floa
 #endif
 // LINES: one tile per wave, its results stored with store_row_lines.
 // MIXED: the first `dq` workers are DQSG, the rest nested; a loop for each kind.
-template <int RMODE, int W0, int WR, bool MIXED, bool RAGGED, bool LINES, int FORM>
+// ROWB (persistent): a bucket is one row, so a tile has a step for each of its rows.
+template <int RMODE, int W0, int WR, bool MIXED, bool ROWB, bool RAGGED, bool LINES, int FORM>
 __global__ __launch_bounds__(kBlock)
 __attribute__((amdgpu_waves_per_eu(FORM == kPiped ? NDQ_CHAIN_PIPED_WAVES : kChainStreamWaves, FORM == kPiped ? NDQ_CHAIN_PIPED_WAVES : kChainStreamWaves)))
 void chain_stream_kernel(ChainArgs a_by_value)
@@ -927,8 +949,8 @@ void chain_stream_kernel(ChainArgs a_by_value)
     constexpr bool TAIL = RAGGED && PIPED;     // the ragged tile runs through the main loop
     constexpr int ROWS = ChainStreamTile<FORM>::ROWS;
     constexpr uint32_t TILE = ChainStreamTile<FORM>::N;
-    constexpr bool SCALED = PIPED && RowScaled<RMODE, WR>::value;
-    constexpr float kM = RMODE == kDq ? 1.0f : (float)(1u << WR), kInvM = 1.0f / kM;
+    constexpr bool SCALED = PIPED && RowScaled<RMODE, WR>::value, RANGED = PIPED && RowRanged<RMODE, WR>::value;
+    constexpr float kM = SCALED ? (float)(1u << WR) : 1.0f, kInvM = 1.0f / kM;
     const ChainArgsPtr a = (ChainArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
     const int lane = threadIdx.x & (kWave - 1);
     const uint32_t stride = gridDim.x * kWavesPerBlock;
@@ -942,6 +964,7 @@ void chain_stream_kernel(ChainArgs a_by_value)
     float* out_base = a->out;
     const float scale = a->scale;
     const bool apply_scale = __builtin_amdgcn_readfirstlane(a->apply_scale) != 0;
+    const float ratio = RMODE == kNestedAnyM ? a->ratio : 0.0f, inv_ratio = RMODE == kNestedAnyM ? a->inv_ratio : 0.0f;
     // The ragged last tile goes first, to a wave that has no whole tile if the grid has one
     // (one tile per wave), else to wave 0: at the start every SIMD is full and hides its
     // latencies; as a kernel of its own, or at the end, it would run alone at a fifth of the rate.
@@ -982,7 +1005,21 @@ void chain_stream_kernel(ChainArgs a_by_value)
     // for all workers (at most 32, one per lane), instead of one per worker in every lane; a
     // worker's step and reciprocal are then read from its lane into scalar registers.
     const float* my_steps = a->steps[(uint32_t)lane < W ? (uint32_t)lane : W - 1u];
-    float steps_ahead = my_steps[bucket_of(a, first)];
+    constexpr int STEPS = ROWB ? ROWS : 1;
+    auto load_steps = [&](uint32_t tile, float (&to)[STEPS]) __attribute__((always_inline)) {
+        if constexpr (ROWB) {
+            const uint32_t last = (uint32_t)((a->n - 1u) / (kWave * kLaneElems));
+#pragma unroll
+            for (int r = 0; r < STEPS; ++r) {
+                const uint32_t b = tile * ROWS + (uint32_t)r;
+                to[r] = my_steps[b < last ? b : last];       // (a row behind the end is not stored: any step will do)
+            }
+        } else {
+            to[0] = my_steps[bucket_of(a, tile)];
+        }
+    };
+    float steps_ahead[STEPS];
+    load_steps(first, steps_ahead);
     bool out_of_range = false;
     for (uint32_t tile = first; tile < tiles_all; tile += stride) {
         const uint64_t start = (uint64_t)tile * TILE;
@@ -991,13 +1028,19 @@ void chain_stream_kernel(ChainArgs a_by_value)
         const uint32_t block_here = tile * (TILE / kLaneElems) + (uint32_t)lane;
         const uint32_t block_ahead = next * (TILE / kLaneElems) + (uint32_t)lane;
         float S[ROWS][8];
-        const float steps_here = steps_ahead;
-        steps_ahead = my_steps[bucket_of(a, next)];
-        float invs_here = inv_step(steps_here), scaled_here = steps_here;
-        if (SCALED) {
-            invs_here = invs_here * kInvM;
-            scaled_here = steps_here * kM;
-            out_of_range = out_of_range || step_out_of_range(steps_here);
+        float steps_here[STEPS], invs_here[STEPS], scaled_here[STEPS];
+#pragma unroll
+        for (int r = 0; r < STEPS; ++r) steps_here[r] = steps_ahead[r];
+        load_steps(next, steps_ahead);
+#pragma unroll
+        for (int r = 0; r < STEPS; ++r) {
+            invs_here[r] = inv_step(steps_here[r]);
+            scaled_here[r] = steps_here[r];
+            if (SCALED) {
+                invs_here[r] = invs_here[r] * kInvM;
+                scaled_here[r] = steps_here[r] * kM;
+            }
+            if (RANGED) out_of_range = out_of_range || step_out_of_range(steps_here[r]);
         }
         auto from_lane = [](float x, uint32_t w) __attribute__((always_inline)) {
             return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(x), (int)w));
@@ -1018,10 +1061,14 @@ void chain_stream_kernel(ChainArgs a_by_value)
             if (last) stream_fetch<W0, ROWS>(codes_next, (uint64_t)next * TILE, lane, nxt, limit_for(next, limit0));
             else if (MIXED && MODE == kDq && dq_follows) stream_fetch<W0, ROWS>(codes_next, start, lane, nxt, limit_for(tile, limit0));
             else stream_fetch<WR, ROWS>(codes_next, start, lane, nxt, limit_for(tile, limitr));
-            const float step = from_lane(MODE == kDq ? steps_here : scaled_here, index);
-            const float inv = MODE == kDq ? 0.0f : from_lane(invs_here, index);
-            if constexpr (PIPED) stream_fold_piped<MODE, WIDTH, FIRST>(keys, here, keys_next, ahead, extra, cur, step, inv, S, fl);
-            else stream_fold<MODE, WIDTH, FIRST, ROWS>(keys, here, extra, cur, step, inv, S);
+            float step[ROWS], inv[ROWS];
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) {
+                step[r] = r < STEPS ? from_lane(MODE == kDq ? steps_here[r % STEPS] : scaled_here[r % STEPS], index) : step[0];
+                inv[r] = MODE == kDq ? 0.0f : r < STEPS ? from_lane(invs_here[r % STEPS], index) : inv[0];
+            }
+            if constexpr (PIPED) stream_fold_piped<MODE, WIDTH, FIRST>(keys, here, keys_next, ahead, extra, ratio, inv_ratio, cur, step, inv, S, fl);
+            else stream_fold<MODE, WIDTH, FIRST, ROWS>(keys, here, extra, ratio, inv_ratio, cur, step[0], inv[0], S);
             keys = keys_next;
             cur = nxt;
         };
@@ -1082,8 +1129,8 @@ void chain_stream_kernel(ChainArgs a_by_value)
         else if (done == lower1) __builtin_amdgcn_s_setprio(1);
         else if (done == lower2) __builtin_amdgcn_s_setprio(2);
     }
-    if (SCALED && __builtin_amdgcn_ballot_w64(out_of_range) != 0)
-        redo_out_of_range<RMODE, W0, WR, MIXED>(a, first, stride, tiles_all, lane);
+    if (RANGED && __builtin_amdgcn_ballot_w64(out_of_range) != 0)
+        redo_out_of_range<RMODE, W0, WR, MIXED, ROWB>(a, first, stride, tiles_all, lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -1368,7 +1415,29 @@ static uint32_t persistent_from(uint32_t W, bool all_dq, uint32_t slots)
     return W <= 3u ? 2u * slots : W < 8u ? slots : kShortTiles;
 }
 
-template <int RMODE, int W0, int WR, bool MIXED>
+// The same for the rarer plans (see chain_streams), at 2.2 / 3.1 / 4.3 / 5.3 / 6.5 / 7.7 / 8.6 / 10.8 / 12.9 M elements:
+//   3 bits, 1 DQSG   1.08 1.07 1.01 0.94 0.91 0.92 0.91 0.84 0.81
+//           2 DQSG   1.05 1.04 1.05 1.07 1.00 0.99 0.97 0.98 0.94
+//           4 DQSG   1.02 0.95 0.97 1.02 0.97 0.97 0.97 0.91 0.92
+//           8 DQSG   0.97 0.88 0.93 0.96 0.91 0.95 0.94 0.87 0.90
+//   1 + 1 nested     1.19 1.18 1.14 1.13 1.03 1.02 1.02 1.00 0.97
+//   2 + 2            1.11 1.07 1.09 1.07 1.07 1.06 1.05 1.02 1.00
+//   4 + 4            1.07 1.05 1.06 1.04 1.04 1.03 1.03 1.01 1.02
+//   8 + 8            1.02 1.02 0.99 1.03 1.02 1.03 1.02 0.99 1.02
+//   M = 3, 4 + 4     1.09 1.07 1.04 1.04 1.01 1.02 1.00 1.00 1.00
+//          1 + 7     1.00 1.00 1.00 0.98 0.97 0.96 0.96 0.96 0.95
+//          1 + 15    0.96 0.95 0.95 0.95 0.94 0.95 0.95 0.94 0.94
+// (a second round that is nearly empty costs them no more than the persistent form does).  Buckets of a row, over one row per
+// wave:  4 DQSG 1.15 1.08 1.04 0.99 1.00 0.99 0.99 0.95 0.93    1 + 1 1.19 1.09 1.04 0.99 0.97 0.94 0.93 0.89 0.86
+//        M = 3, 1 + 1 1.42 1.33 1.25 1.16 1.09 1.04 1.01 0.96 0.96    8 + 8 1.16 1.03 1.08 0.96 1.04 1.00 1.01 0.98 0.98
+static uint32_t rarer_persistent_from(uint32_t W, uint32_t dq, bool any_ratio, bool row_buckets, uint32_t slots)
+{
+    if (row_buckets) return slots / 3u * 4u;
+    if (dq == W) return W == 1u ? slots / 4u * 3u : W < 8u ? slots : kShortTiles;
+    return any_ratio && W - dq >= 7u ? kShortTiles : slots / 3u * 5u;
+}
+
+template <int RMODE, int W0, int WR, bool MIXED, bool ROWB = false>
 static int launch_chain_stream(ChainArgs& a, uint64_t bucket_len, hipStream_t s)
 {
     // Persistent waves, kChainStreamWaves on every SIMD, every wave with the same number of tiles (give or
@@ -1376,75 +1445,91 @@ static int launch_chain_stream(ChainArgs& a, uint64_t bucket_len, hipStream_t s)
     const uint32_t slots = 1024u * kChainStreamWaves;
     const uint32_t full = (uint32_t)(a.n / kChainTile);
     const StreamTuning& tuning = stream_tuning();
+    constexpr bool RARER = MIXED || W0 == 3 || ROWB;     // (see chain_streams)
+    // buckets of one row: ROWB has the persistent form only
+    const bool rows_only = bucket_len < kChainTile && !ROWB;
+    const uint32_t from = RARER ? rarer_persistent_from(a.W, RMODE == kDq ? a.W : a.dq, RMODE == kNestedAnyM, ROWB, slots)
+                                : persistent_from(a.W, RMODE == kDq, slots);
     const bool persistent =
-        full != 0u && (tuning.threshold_from_env ? full >= tuning.chain_min_tiles_per_wave * slots
-                                                 : full >= persistent_from(a.W, RMODE == kDq, slots) ||
-                                                       (full >= slots && full < slots + slots / 16u));
-    constexpr bool RARER = MIXED || W0 == 3;     // (see chain_streams)
+        full != 0u && !rows_only && (tuning.threshold_from_env ? full >= tuning.chain_min_tiles_per_wave * slots
+                                                               : full >= from || (!RARER && full >= slots && full < slots + slots / 16u));
     // Few workers of the rarer plans store whole lines from fewer tiles on: rows / tiles at 1.0, 1.3, 1.6, 2.0 M elements
     //   2 workers   4.63/4.67  5.32/5.05  5.79/5.13  6.12/5.40 (3-bit and a 2-bit nested)  4.35/4.39  4.70/4.69  5.06/4.73  5.42/4.94
     //   3           5.13/5.88  5.91/6.00  6.32/6.19  6.68/6.72                             4.76/5.17  5.17/5.54  5.79/5.49  6.10/5.68
     const uint32_t rows_below = RARER && a.W == 2u ? 1280u : RARER && a.W == 3u ? 1536u : kShortTiles;
-    const bool short_vector = !persistent && full < rows_below;
+    const bool short_vector = !persistent && (full < rows_below || rows_only);
     const uint32_t tile = short_vector ? ChainStreamTile<kOneRow>::N : kChainTile;
     // the rarer plans have the kernels with a ragged last tile only: a whole one takes its place
     const uint32_t tiles = (uint32_t)((RARER ? a.n - 1u : a.n) / tile);
-    if (tiles == 0u) return 1;
+    if (tiles == 0u || (ROWB && !persistent)) return 1;
     a.tiles = tiles;
     // (see bucket_of; a bucket is a multiple of the tile.  A tile's number times the magic stays below 2^63)
     const uint64_t per_bucket = bucket_len / tile;
     uint32_t log2 = 0u;
     while (((uint64_t)1 << log2) < per_bucket) ++log2;
     a.bucket_shift = 31u + log2;
-    a.bucket_magic = bucket_len == a.n ? 0u : (((uint64_t)1 << a.bucket_shift) + per_bucket - 1u) / per_bucket;
+    a.bucket_magic = ROWB || bucket_len == a.n ? 0u : (((uint64_t)1 << a.bucket_shift) + per_bucket - 1u) / per_bucket;
     const bool ragged = (uint64_t)tiles * tile < a.n;     // one more wave takes the ragged last tile
     const uint32_t all = tiles + (ragged ? 1u : 0u);
     const dim3 grid(persistent ? persistent_blocks(all, 1024u * NDQ_CHAIN_PIPED_WAVES) : blocks_for(all)), block(kBlock);
     auto run = [&](auto lines, auto form) {
         constexpr bool LINES = decltype(lines)::value;
         constexpr int FORM = decltype(form)::value;
-        if constexpr (RARER) return launch((chain_stream_kernel<RMODE, W0, WR, MIXED, true, LINES, FORM>), grid, block, s, a);
-        else return ragged ? launch((chain_stream_kernel<RMODE, W0, WR, MIXED, true, LINES, FORM>), grid, block, s, a)
-                           : launch((chain_stream_kernel<RMODE, W0, WR, MIXED, false, LINES, FORM>), grid, block, s, a);
+        if constexpr (RARER) return launch((chain_stream_kernel<RMODE, W0, WR, MIXED, ROWB, true, LINES, FORM>), grid, block, s, a);
+        else return ragged ? launch((chain_stream_kernel<RMODE, W0, WR, MIXED, ROWB, true, LINES, FORM>), grid, block, s, a)
+                           : launch((chain_stream_kernel<RMODE, W0, WR, MIXED, ROWB, false, LINES, FORM>), grid, block, s, a);
     };
     if (persistent) return run(std::false_type{}, std::integral_constant<int, kPiped>{});
-    if (short_vector) {
-        // (a launch of rows is bound by its stores only with one worker: 2 M elements 4.4 -> 4.0 us; 2 of 1.6 M 4.1 -> 4.2)
-        if constexpr (RMODE == kDq && W0 == WR)
-            if (a.W == 1u) return run(std::true_type{}, std::integral_constant<int, kOneRow>{});
-        return run(std::false_type{}, std::integral_constant<int, kOneRow>{});
+    if constexpr (!ROWB) {
+        // Rows of long vectors store whole lines, whatever they fold: halves / lines at 2.2, 4 and 16.8 M elements, 2 x 16 levels
+        // 5.7/5.0 8.2/6.7 19.1/16.6, 8 x 16 levels 10.3/9.9 14.4/13.8 43.6/42.5, 4 levels and 3 x M = 2 7.9/7.4 11.5/10.5 31.4/30.5.
+        if (rows_only && full >= rows_below) return run(std::true_type{}, std::integral_constant<int, kOneRow>{});
+        if (short_vector) {
+            // (a launch of rows is bound by its stores only with one worker: 2 M elements 4.4 -> 4.0 us; 2 of 1.6 M 4.1 -> 4.2)
+            if constexpr (RMODE == kDq && W0 == WR)
+                if (a.W == 1u) return run(std::true_type{}, std::integral_constant<int, kOneRow>{});
+            return run(std::false_type{}, std::integral_constant<int, kOneRow>{});
+        }
+        return a.W < (RMODE == kDq ? 4u : 3u) ? run(std::true_type{}, std::integral_constant<int, kOneTile>{})
+                                              : run(std::false_type{}, std::integral_constant<int, kOneTile>{});
     }
-    return a.W < (RMODE == kDq ? 4u : 3u) ? run(std::true_type{}, std::integral_constant<int, kOneTile>{})
-                                          : run(std::false_type{}, std::integral_constant<int, kOneTile>{});
+    return 1;
 }
 
 // The plans the streaming kernel has.
 enum ChainPlan { kNoStream = 0,
                  kPurePlan = 1,     // all DQSG, or one DQSG worker and nested ones; codes of 1, 2 and 4 bits
-                 // The rarer plans: several DQSG workers and then nested ones, or 3-bit codes; codes of 2 to 4 bits and of
-                 // 1 to 3.  In kernels of their own, so that the others' stay as they are.  chain_kernel / this, us, at 1.05, 4 and
+                 // The rarer plans: several DQSG workers and then nested ones, 3-bit codes, or a ratio that is no power of two;
+                 // codes of 2 to 4 bits and of 1 to 3.  In kernels of their own, so that the others' stay as they are.  chain_kernel / this, us, at 1.05, 4 and
                  // 16.8 M elements: 1 x 8 levels 4.1/3.4 6.8/5.6 21.2/13.3, 8 x 8 levels 10.0/7.5 17.5/14.4 50.7/38.2, 8 levels and M = 4
                  // 4.9/4.5 7.5/6.8 19.5/16.9, 2 x 16 levels and 2 x M = 8 6.7/5.7 11.4/10.1 31.8/27.3, 8 x 16 levels and 8 x M = 4
-                 // 17.5/12.9 34.4/26.6 113.9/84.2, 16 levels and 15 x M = 8 17.8/15.1 37.2/33.9 130/103.
+                 // 17.5/12.9 34.4/26.6 113.9/84.2, 16 levels and 15 x M = 8 17.8/15.1 37.2/33.9 130/103, 4 x 5 levels and 4 x M = 3
+                 // 11.5/9.1 22.2/18.6 65.9/52.3, 16 levels and 3 x M = 3 7.4/5.8 14.4/11.6 39.0/31.9.
+                 // Buckets of one row, any of these plans, at 2.2, 4 and 16.8 M: 4 x 16 levels 8.4/6.6 10.6/9.0 29.7/22.9, 16 levels and
+                 // 15 x M = 4 26.1/21.7 37.1/30.7 131/99.7, 16 levels and M = 4 6.0/5.4 7.4/7.1 21.1/17.5.
                  kMixedPlan = 2 };
 
 // Whether it has the plan and the tiling; *dq are the DQSG workers and *wr the code width of the workers after them.
 static ChainPlan chain_streams(const GeneralChainArgs& a, uint32_t bucket, uint32_t* dq, uint32_t* wr)
 {
-    if (a.row_buckets || a.continue_sum) return kNoStream;
-    if (!(bucket == 0u || bucket % kChainTile == 0u)) return kNoStream;
+    if (a.continue_sum) return kNoStream;
+    if (!(bucket == 0u || bucket % kChainTile == 0u || bucket == kWave * kLaneElems)) return kNoStream;
     const uint32_t w0 = a.w[0].bits;
     uint32_t first = 0u;
     while (first < a.W && a.w[first].mode == kDq && a.w[first].bits == w0) ++first;
     if (first == 0u || w0 > 4u) return kNoStream;
     *dq = first;
     *wr = first < a.W ? a.w[first].bits : w0;
+    const bool any_ratio = first < a.W && a.w[first].mode == kNestedAnyM;
     for (uint32_t j = first; j < a.W; ++j)
-        if (a.w[j].mode != kNestedPow2 || a.w[j].bits != *wr) return kNoStream;
+        if (a.w[j].mode != (any_ratio ? kNestedAnyM : kNestedPow2) || a.w[j].bits != *wr || a.w[j].alpha != 1.0f ||
+            a.w[j].M != a.w[first].M)
+            return kNoStream;
     // the high word of the dither's block number is the same for the whole call (it changes every 2^35 elements)
     for (uint32_t j = 0; j < a.W; ++j)
         if ((a.w[j].index0 >> 35) != ((a.w[j].index0 + a.tl.n - 1u) >> 35)) return kNoStream;
     if (first == a.W) return w0 == 3u ? kMixedPlan : kPurePlan;
+    if (any_ratio) return w0 >= 2u && *wr <= 3u ? kMixedPlan : kNoStream;
     if (first == 1u && w0 != 3u && (*wr == 1u || *wr == 2u || *wr == 4u)) return kPurePlan;
     return w0 >= 2u && *wr <= 3u ? kMixedPlan : kNoStream;
 }
@@ -1468,16 +1553,26 @@ static int run_chain_stream(const GeneralChainArgs& a, uint32_t bucket, ChainPla
     b.n = a.tl.n;
     b.W = a.W;
     b.dq = dq;
+    b.ratio = a.w[a.W - 1u].M_f;
+    b.inv_ratio = a.w[a.W - 1u].inv_M_f;
     b.apply_scale = a.apply_scale;
     b.scale = a.scale;
     // (a bucket that holds the whole vector is no different from none)
     const uint64_t bucket_len = bucket != 0u && bucket < b.n ? bucket : b.n;
     auto run = [&](auto rmode, auto first, auto rest, auto mixed) {
-        return launch_chain_stream<decltype(rmode)::value, decltype(first)::value, decltype(rest)::value, decltype(mixed)::value>(
-            b, bucket_len, s);
+        constexpr int RMODE = decltype(rmode)::value, W0 = decltype(first)::value, WR = decltype(rest)::value;
+        constexpr bool MIXED = decltype(mixed)::value;
+        // buckets of one row, persistent: one DQSG worker is the mixed plan that has one
+        if constexpr (W0 >= 2 && (RMODE == kDq || WR <= 3))
+            if (bucket_len < kChainTile) {
+                const int rc = launch_chain_stream<RMODE, W0, WR, RMODE != kDq, true>(b, bucket_len, s);
+                if (rc != 1) return rc;
+            }
+        return launch_chain_stream<RMODE, W0, WR, MIXED>(b, bucket_len, s);
     };
     constexpr std::integral_constant<int, kDq> all_dq{};
     constexpr std::integral_constant<int, kNestedPow2> nested{};
+    constexpr std::integral_constant<int, kNestedAnyM> any_ratio{};
     constexpr std::integral_constant<int, 1> b1{};
     constexpr std::integral_constant<int, 2> b2{};
     constexpr std::integral_constant<int, 3> b3{};
@@ -1492,6 +1587,10 @@ static int run_chain_stream(const GeneralChainArgs& a, uint32_t bucket, ChainPla
             return wr == 1u ? run(nested, first, b1, no) : wr == 2u ? run(nested, first, b2, no) : run(nested, first, b4, no);
         };
         return w0 == 1u ? rest(b1) : w0 == 2u ? rest(b2) : rest(b4);
+    }
+    if (a.w[a.W - 1u].mode == kNestedAnyM) {
+        auto rest = [&](auto first) { return wr == 2u ? run(any_ratio, first, b2, yes) : run(any_ratio, first, b3, yes); };
+        return w0 == 2u ? rest(b2) : w0 == 3u ? rest(b3) : rest(b4);
     }
     auto rest = [&](auto first) {
         return wr == 1u ? run(nested, first, b1, yes) : wr == 2u ? run(nested, first, b2, yes) : run(nested, first, b3, yes);

@@ -1,6 +1,7 @@
-"""Chain decoder, plans with several DQSG workers before the nested ones and with 3-bit codes, in the streaming
-kernel's forms (one row or one tile per wave, persistent), against the oracle bit for bit: whole and ragged last
-tiles, codes up to the last byte of a stream, buckets of whole tiles, steps that are 0 or far from 1."""
+"""Chain decoder, plans with several DQSG workers before the nested ones, with 3-bit codes, with ratios that are no
+powers of two and with buckets of one row, in the streaming kernel's forms (one row or one tile per wave, persistent),
+against the oracle bit for bit: whole and ragged last tiles, codes up to the last byte of a stream, buckets of whole
+tiles, steps that are 0 or far from 1."""
 import os
 import subprocess
 import sys
@@ -21,7 +22,12 @@ PLANS = {
     "5, M 2": [(DQ, 5), (NESTED, 2)], "16, M 8": [(DQ, 16)] + [(NESTED, 8)] * 2, "3 and 4, M 2": [(DQ, 3), (DQ, 4), (NESTED, 2), (NESTED, 2)],
     "4, M 4": [(DQ, 4)] * 2 + [(NESTED, 4)], "4, M 8": [(DQ, 4)] * 3 + [(NESTED, 8)], "8, M 2": [(DQ, 8)] * 2 + [(NESTED, 2)] * 3,
     "8, M 8": [(DQ, 8)] * 2 + [(NESTED, 8)], "16, M 2": [(DQ, 16)] * 2 + [(NESTED, 2)] * 2, "16, M 4": [(DQ, 16)] * 8 + [(NESTED, 4)] * 8,
+    "5, M 3": [(DQ, 5)] * 4 + [(NESTED, 3)] * 4, "16, M 7": [(DQ, 16), (NESTED, 7)], "4, M 5": [(DQ, 4)] * 2 + [(NESTED, 5)],
+    "3, M 3": [(DQ, 3)] + [(NESTED, 3)] * 7, "8, M 6": [(DQ, 8)] * 2 + [(NESTED, 6)],
 }
+# with buckets of one row (also plans whose other kernels are not the rarer plans')
+ROW_PLANS = dict(PLANS, **{"2": [(DQ, 2)] * 2, "2, M 2": [(DQ, 2), (NESTED, 2)], "4, M 2": [(DQ, 4)] + [(NESTED, 2)] * 3, "16": [(DQ, 16)] * 3,
+                           "16, M 16": [(DQ, 16), (NESTED, 16)], "16 and M 4": [(DQ, 16)] + [(NESTED, 4)] * 2})
 ROWS = [513, 512 * 2, 512 * 9 + 1, 512 * 40 - 1, 1024 * 15 + 8, 1024 * 33 + 512]
 TILES = [1024 * 12, 1024 * 40, 1024 * 37 + 100, 1024 * 3 + 8, 1024 * 13 + 1, 1024 * 24 + 1023, 1025]
 
@@ -48,11 +54,12 @@ def _check(plan, n, bucket, offset, scale):
 
 
 def _sweep(sizes):
-    for name, plan in PLANS.items():
+    for name, plan in ROW_PLANS.items():
         for i, n in enumerate(sizes):
             bucket = (0, 1024, 2048, 8192)[(i + len(plan)) % 4]
             print(name, n, bucket, flush=True)
             _check(plan, n, bucket, 8 * (n % 4099), 1.0 if i % 2 else 0.25)
+            _check(plan, n, 512, 0, 1.0)
             if bucket:
                 _check(plan, n, 0, 0, 1.0)
 
@@ -64,6 +71,14 @@ def test_rows_and_tiles_match_oracle(name):
     long = 1024 * (1280 if len(plan) == 2 else 1536 if len(plan) == 3 else 2048)
     for n, bucket in [(n, b) for n in ROWS for b in (0, 1024)] + [(long - 1, 0), (long, 0), (long + 1, 2048), (long + 4 * 1024 + 700, 0)]:
         _check(plan, n, bucket, 8 * (n % 129), 1.0 / len(plan))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", list(ROW_PLANS))
+def test_buckets_of_a_row_match_oracle(name):
+    plan = ROW_PLANS[name]
+    for n in ROWS + [1024 * 2048 - 1, 1024 * 2048 + 513, 1024 * 2100]:
+        _check(plan, n, 512, 8 * (n % 129), 1.0 / len(plan))
 
 
 @pytest.mark.gpu
@@ -91,8 +106,18 @@ def test_plans_reach_the_streaming_kernel(recorder, name):
     calls = [["ndq_decode_chain", workers, len(plan), n, 0, 1.0, 0x40000000, None] for n in sizes]
     calls.append(["ndq_decode_chain", [dict(w, alpha=0.9) for w in workers], len(plan), sizes[1], 0, 1.0, 0x40000000, None])
     got = lr.record(recorder, calls)
-    for (rc, launches), form in zip(got, (2, 0 if len(plan) in (1, 16) else 1, 0)):
+    # (eight DQSG workers of 3 bits and seven nested ones with such a ratio: persistent from 2,048 tiles on)
+    for (rc, launches), form in zip(got, (2, 0 if name in ("8 and 5 of 3 bits", "3, M 3") else 1, 0)):
         assert rc == 0 and len(launches) == 1 and "chain_stream_kernel" in launches[0][0], launches
         assert launches[0][0].endswith("ELi%dEEEvNS_9ChainArgsE" % form), launches
     # a worker that shrinks: the general kernel
     assert ("chain_stream_kernel" in got[3][1][0][0]) == all(kind == DQ for kind, _ in plan)
+
+
+@pytest.mark.parametrize("name,tiles,form", [("16", 8191, 2), ("16", 8192, 0), ("4, M 2", 8192, 0), ("2", 8192, 2), ("16, M 16", 20000, 2),
+                                             ("5, M 3", 8191, 2), ("5, M 3", 8192, 0), ("1 of 8", 8192, 0)])
+def test_form_for_buckets_of_a_row(recorder, name, tiles, form):
+    workers = [{"codes": 0x20000000, "steps": 0x30000000, "kind": 0 if kind == DQ else 1, "levels_or_M": arg, "alpha": 1.0,
+                "dither": [1, 2, 3, 0]} for kind, arg in ROW_PLANS[name]]
+    (rc, launches), = lr.record(recorder, [["ndq_decode_chain", workers, len(workers), 1024 * tiles + 1, 512, 1.0, 0x40000000, None]])
+    assert rc == 0 and len(launches) == 1 and launches[0][0].endswith("ELi%dEEEvNS_9ChainArgsE" % form), launches
