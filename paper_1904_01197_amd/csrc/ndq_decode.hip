@@ -582,6 +582,18 @@ __device__ __forceinline__ uint32_t lane_codes(const unsigned char* p)
     return (uint32_t)low | (uint32_t)p[2] << 16;
 }
 
+// The size of a stream of n codes, and what is left of it for the vector's last lane, whose eight codes need not all exist.
+// Only for 3-bit codes (16 is no multiple of three) can that be less than the eight codes' bytes.
+__device__ __forceinline__ uint64_t stream_bytes(uint64_t n, uint32_t width)
+{
+    return (((n * width + 7u) >> 3) + 15u) & ~(uint64_t)15u;
+}
+template <int WIDTH>
+__device__ __forceinline__ bool last_lane_is_short(uint64_t n)
+{
+    return WIDTH == 3 && stream_bytes(n, 3u) - (n - 1u) / 8u * 3u < 3u;
+}
+
 // a lane's eight codes of a row: `WIDTH` bytes at a multiple of WIDTH (full tiles).
 // `limit`: the largest byte offset inside the tile's codes that may be read (a multiple of
 // WIDTH); lanes past it read there instead.  Whole tiles pass 0xFFFFFFFF; for the vector's
@@ -603,9 +615,10 @@ __device__ __forceinline__ void stream_fetch(const unsigned char* codes, uint64_
 
 // The same for the vector's ragged last tile of `len` elements: a lane fetches its bytes
 // only if its first code exists (they then lie inside the stream, whose size is padded to
-// a multiple of 16 bytes: (o/8 + 1) * WIDTH <= the padded size of the tile's codes).
+// a multiple of 16 bytes: (o/8 + 1) * WIDTH <= the padded size of the tile's codes; three bytes each by itself,
+// see last_lane_is_short).
 template <int WIDTH, int ROWS>
-__device__ __forceinline__ void stream_fetch_ragged(const unsigned char* codes, const float* steps, uint64_t start,
+__device__ __forceinline__ void stream_fetch_ragged(const unsigned char* codes, const float* steps, uint64_t n, uint64_t start,
                                                     uint32_t len, uint32_t bucket, int lane, ChainCodes<ROWS>& f)
 {
     const unsigned char* mine = codes + (start >> 3) * WIDTH + (uint32_t)lane * WIDTH;
@@ -613,7 +626,16 @@ __device__ __forceinline__ void stream_fetch_ragged(const unsigned char* codes, 
     for (int r = 0; r < ROWS; ++r) {
         const unsigned char* p = mine + (uint32_t)(r * kWave) * WIDTH;
         f.w[r] = 0u;
-        if ((uint32_t)(r * kWave + lane) * kLaneElems < len) f.w[r] = lane_codes<WIDTH>(p);
+        if ((uint32_t)(r * kWave + lane) * kLaneElems < len) {
+            if constexpr (WIDTH == 3) {
+                const uint64_t left = stream_bytes(n, 3u) - (uint64_t)(p - codes);
+                f.w[r] = p[0];
+                if (left > 1u) f.w[r] |= (uint32_t)p[1] << 8;
+                if (left > 2u) f.w[r] |= (uint32_t)p[2] << 16;
+            } else {
+                f.w[r] = lane_codes<WIDTH>(p);
+            }
+        }
     }
     f.step = steps[bucket];
 }
@@ -835,10 +857,10 @@ __device__ __forceinline__ void stream_ragged_tile(ChainArgsPtr a, uint64_t star
     ChainCodes<ROWS> cur, nxt;
     const uint32_t dq = MIXED ? a->dq : 1u;
     auto fetch = [&](uint32_t w) __attribute__((always_inline)) {
-        if (MIXED && w < dq) stream_fetch_ragged<W0, ROWS>(a->w[w].codes, a->steps[w], start, len, bucket, lane, nxt);
-        else stream_fetch_ragged<WR, ROWS>(a->w[w].codes, a->steps[w], start, len, bucket, lane, nxt);
+        if (MIXED && w < dq) stream_fetch_ragged<W0, ROWS>(a->w[w].codes, a->steps[w], a->n, start, len, bucket, lane, nxt);
+        else stream_fetch_ragged<WR, ROWS>(a->w[w].codes, a->steps[w], a->n, start, len, bucket, lane, nxt);
     };
-    stream_fetch_ragged<W0, ROWS>(a->w[0].codes, a->steps[0], start, len, bucket, lane, cur);
+    stream_fetch_ragged<W0, ROWS>(a->w[0].codes, a->steps[0], a->n, start, len, bucket, lane, cur);
     nxt = cur;
     if (W > 1u) fetch(1u);
     stream_fold<kDq, W0, true, ROWS>(uniform_keys(&a->w[0]), a->w[0].block + block, a->w[0].extra, 0.0f, 0.0f, cur, cur.step,
@@ -867,11 +889,12 @@ __device__ __forceinline__ void stream_ragged_tile(ChainArgsPtr a, uint64_t star
 }
 
 // The wave's tiles that have a step outside the range fold_row_piped is exact in, decoded
-// again in the plain form.
+// again in the plain form; `last_too`: and the last tile.
 template <int RMODE, int W0, int WR, bool MIXED, bool ROWB>
 __device__ __forceinline__ void redo_out_of_range(ChainArgsPtr a, uint32_t first, uint32_t stride,
-                                                           uint32_t tiles_all, int lane)
+                                                           uint32_t tiles_all, bool last_too, int lane)
 {
+    constexpr bool RANGED = RowRanged<RMODE, WR>::value;
     const uint32_t W = a->W;
     const float* my_steps = a->steps[(uint32_t)lane < W ? (uint32_t)lane : W - 1u];
     constexpr int ROWS = ROWB ? 1 : kChainRows;          // rows that share a step
@@ -881,7 +904,8 @@ __device__ __forceinline__ void redo_out_of_range(ChainArgsPtr a, uint32_t first
             const uint64_t start = (uint64_t)tile * kChainTile + r * PART;
             if (start >= a->n) break;
             const uint32_t bucket = ROWB ? tile * kChainRows + r : bucket_of(a, tile);
-            if (__builtin_amdgcn_ballot_w64(step_out_of_range(my_steps[bucket])) == 0) continue;
+            const bool last = last_too && tile + 1u == tiles_all;
+            if (!last && (!RANGED || __builtin_amdgcn_ballot_w64(step_out_of_range(my_steps[bucket])) == 0)) continue;
             const uint64_t left = a->n - start;
             stream_ragged_tile<RMODE, W0, WR, MIXED, ROWS>(a, start, left < PART ? (uint32_t)left : PART, bucket, lane);
         }
@@ -1129,8 +1153,11 @@ void chain_stream_kernel(ChainArgs a_by_value)
         else if (done == lower1) __builtin_amdgcn_s_setprio(1);
         else if (done == lower2) __builtin_amdgcn_s_setprio(2);
     }
-    if (RANGED && __builtin_amdgcn_ballot_w64(out_of_range) != 0)
-        redo_out_of_range<RMODE, W0, WR, MIXED, ROWB>(a, first, stride, tiles_all, lane);
+    // (the main loop has read the bytes before the end in place of the last lane's if that has less than its three)
+    constexpr bool THREE = TAIL && (W0 == 3 || WR == 3);
+    const bool last_too = THREE && (last_lane_is_short<W0>(a->n) || last_lane_is_short<WR>(a->n));
+    if ((RANGED && __builtin_amdgcn_ballot_w64(out_of_range) != 0) || (THREE && last_too))
+        redo_out_of_range<RMODE, W0, WR, MIXED, ROWB>(a, first, stride, tiles_all, last_too, lane);
 }
 
 // ---------------------------------------------------------------------------

@@ -28,8 +28,21 @@ PLANS = {
 # with buckets of one row (also plans whose other kernels are not the rarer plans')
 ROW_PLANS = dict(PLANS, **{"2": [(DQ, 2)] * 2, "2, M 2": [(DQ, 2), (NESTED, 2)], "4, M 2": [(DQ, 4)] + [(NESTED, 2)] * 3, "16": [(DQ, 16)] * 3,
                            "16, M 16": [(DQ, 16), (NESTED, 16)], "16 and M 4": [(DQ, 16)] + [(NESTED, 4)] * 2})
-ROWS = [513, 512 * 2, 512 * 9 + 1, 512 * 40 - 1, 1024 * 15 + 8, 1024 * 33 + 512]
-TILES = [1024 * 12, 1024 * 40, 1024 * 37 + 100, 1024 * 3 + 8, 1024 * 13 + 1, 1024 * 24 + 1023, 1025]
+
+
+def _tight(n):
+    """The next length whose 3-bit stream ends with one byte, and with two, of the last lane's three."""
+    out = []
+    for left in (1, 2):
+        m = n
+        while oracle.packed_bytes(m, 3) - m // 8 * 3 != left or m % 8 == 0:
+            m += 1
+        out.append(m)
+    return out
+
+
+ROWS = [513, 512 * 2, 512 * 9 + 1, 512 * 40 - 1, 1024 * 15 + 8, 1024 * 33 + 512] + _tight(530) + _tight(1024 * 8)
+TILES = [1024 * 12, 1024 * 40, 1024 * 37 + 100, 1024 * 3 + 8, 1024 * 13 + 1, 1024 * 24 + 1023, 1025] + _tight(1024 * 14) + _tight(1024 * 25 + 640)
 
 
 def _check(plan, n, bucket, offset, scale):
@@ -69,7 +82,8 @@ def _sweep(sizes):
 def test_rows_and_tiles_match_oracle(name):
     plan = PLANS[name]
     long = 1024 * (1280 if len(plan) == 2 else 1536 if len(plan) == 3 else 2048)
-    for n, bucket in [(n, b) for n in ROWS for b in (0, 1024)] + [(long - 1, 0), (long, 0), (long + 1, 2048), (long + 4 * 1024 + 700, 0)]:
+    for n, bucket in [(n, b) for n in ROWS for b in (0, 1024)] + [(long - 1, 0), (long, 0), (long + 1, 2048), (long + 4 * 1024 + 700, 0)] + [
+            (n, 0) for n in _tight(long + 300)]:
         _check(plan, n, bucket, 8 * (n % 129), 1.0 / len(plan))
 
 
