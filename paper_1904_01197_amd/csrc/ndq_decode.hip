@@ -1478,7 +1478,7 @@ static int launch_chain_stream(ChainArgs& a, uint64_t bucket_len, hipStream_t s)
     const uint32_t from = RARER ? rarer_persistent_from(a.W, RMODE == kDq ? a.W : a.dq, RMODE == kNestedAnyM, ROWB, slots)
                                 : persistent_from(a.W, RMODE == kDq, slots);
     const bool persistent =
-        full != 0u && !rows_only && (tuning.threshold_from_env ? full >= tuning.chain_min_tiles_per_wave * slots
+        full != 0u && !rows_only && (tuning.threshold_from_env ? full >= tuning.min_tiles_per_wave * slots
                                                                : full >= from || (!RARER && full >= slots && full < slots + slots / 16u));
     // Few workers of the rarer plans store whole lines from fewer tiles on: rows / tiles at 1.0, 1.3, 1.6, 2.0 M elements
     //   2 workers   4.63/4.67  5.32/5.05  5.79/5.13  6.12/5.40 (3-bit and a 2-bit nested)  4.35/4.39  4.70/4.69  5.06/4.73  5.42/4.94

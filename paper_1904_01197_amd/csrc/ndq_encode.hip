@@ -913,6 +913,27 @@ static int launch_stream(const EncodeBatch& b, uint32_t full_tiles, hipStream_t 
     return launch((encode_stream_kernel<DT, MODE, FUSED, BITSW>), dim3(blocks), dim3(kBlock), s, b, full_tiles);
 }
 
+// Tiles of a launch from which the streaming kernel is the faster one (bfloat16; the time of one tile per wave is what
+// has come down since it was made, by code widths known at compile time).  Encoder calls, us, one tile per wave / this, at
+// 4 x 8.4 M, 50 M, 2 x 50 M, 8 x 16 M, 134 M, 4 x 60 M, 3 x 134 M elements (8 k to 98 k tiles):
+//   4 levels, buckets of a tile   17.4/17.7 23.5/24.1 42.7/41.2 53.4/51.2 55.1/54.0 99.0/95.9 167/156
+//   M = 2                         16.1/16.4 22.0/23.1 39.9/39.2 49.0/47.0 51.3/48.4 92.5/89.9 155/149
+//   16 levels                     17.9/18.2 23.9/25.5 44.8/46.3 55.5/56.5 57.9/58.6 103/103 173/167
+//   M = 4                         16.0/17.3 21.7/23.7 39.2/40.6 49.2/52.5 51.7/53.9 93.4/96.0 153/158
+//   4 levels, one step            31.3/31.4 41.1/43.9 71.6/74.6 90.8/93.0 93.0/97.6 163/169 267/280
+//   M = 2                         28.4/28.7 37.3/40.1 68.6/71.9 86.3/89.3 88.2/93.4 158/165 258/272
+//   16 levels                     30.6/31.2 38.6/41.3 76.5/80.0 94.7/96.7 97.1/99.6 170/175 279/285
+// Buckets smaller than a tile and codes of 3 bits gain 3 to 5 % at 8 x 16 M and lose as much below 2 x 50 M: they are left
+// to the other kernel.
+static uint64_t stream_from_tiles(bool fused, bool nested, uint32_t bits)
+{
+    const StreamTuning& tuning = stream_tuning();
+    if (tuning.threshold_from_env) return (uint64_t)tuning.min_tiles_per_wave * kStreamSlots;
+    if (!fused) return ~(uint64_t)0;
+    if (bits == 1u || (bits == 2u && !nested)) return 5u * kStreamSlots;
+    return nested ? ~(uint64_t)0 : 16u * kStreamSlots;
+}
+
 // The streaming kernel serves vectors cut into whole tiles (a ragged last one aside):
 // bucket == tile (fused max-norm) or one step for the whole vector (preset, or found by
 // the max-norm pass), in the quantizer modes and code widths of the common
@@ -924,8 +945,7 @@ static int try_stream(const EncodeBatch& b, bool fused, bool multi, uint32_t buc
     constexpr uint32_t TILE = EncTile<DT>::N;
     // binary32 input: one tile per wave is faster at every length (2^27 elements: 112 against 120 us,
     // 25.6 M: 22.8 against 23.2; its tile carries half the arithmetic of a bfloat16 tile per byte, so
-    // the kernel is nearer to a plain copy, which gains nothing from persistence); bfloat16: the
-    // persistent kernel wins from two tiles per wave slot on (3-9 %)
+    // the kernel is nearer to a plain copy, which gains nothing from persistence)
     if constexpr (DT == 0 || (MODE != kDqNarrow && MODE != kNestedPow2Bounded && MODE != kNestedPow2)) {
         return 1;
     } else {
@@ -933,12 +953,10 @@ static int try_stream(const EncodeBatch& b, bool fused, bool multi, uint32_t buc
     if (!(bucket == TILE || bucket == 0u)) return 1;
     if (fused != (bucket == TILE)) return 1;
     const uint32_t full_tiles = (uint32_t)(a.tl.n / TILE);
-    // shorter vectors: with only a few tiles per wave a fixed share leaves SIMDs idle at the end
-    const uint64_t all_tiles = (uint64_t)full_tiles * b.jobs;
-    if (full_tiles == 0u || all_tiles < stream_tuning().enc_min_tiles_per_wave * kStreamSlots ||
-        all_tiles >= ((uint64_t)1 << 31))
-        return 1;
     const uint32_t bits = a.qp.bits;
+    const uint64_t all_tiles = (uint64_t)full_tiles * b.jobs;
+    if (full_tiles == 0u || all_tiles < stream_from_tiles(fused, MODE != kDqNarrow, bits) || all_tiles >= ((uint64_t)1 << 31))
+        return 1;
     if (bits != 1u && bits != 2u && bits != 4u) return 1;
     if (fused) {
         if constexpr (MODE == kNestedPow2) {

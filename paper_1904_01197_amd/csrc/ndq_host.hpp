@@ -115,28 +115,23 @@ inline int launch(void (*kernel)(Params...), dim3 grid, dim3 block, hipStream_t 
 
 inline uint32_t blocks_for(uint32_t tiles) { return (tiles + kWavesPerBlock - 1) / kWavesPerBlock; }
 
-// When the persistent ("streaming") kernels take over from the one-tile-per-wave
-// ones: a vector needs at least `min_tiles_per_wave` tiles for every wave the
-// persistent grid would hold, or its fixed shares leave SIMDs idle at the end.
-// Two environment variables, read once per process, override the defaults; they
+// When the persistent ("streaming") kernels take over from the one-tile-per-wave ones is a rule of each
+// (stream_from_tiles, persistent_from).  Two environment variables, read once per process, override them; they
 // exist for tuning and so that tests can drive the persistent kernels with short
 // vectors:
-//   NDQ_STREAM_MIN_TILES_PER_WAVE   threshold for both kernels (0: always persistent)
+//   NDQ_STREAM_MIN_TILES_PER_WAVE   for both kernels, tiles for every wave the persistent grid holds (0: always persistent)
 //   NDQ_STREAM_MAX_BLOCKS           cap on the persistent grid, in workgroups (0: none)
 struct StreamTuning {
-    uint32_t enc_min_tiles_per_wave, chain_min_tiles_per_wave, max_blocks;
+    uint32_t min_tiles_per_wave, max_blocks;
     bool threshold_from_env;
 };
 
 inline const StreamTuning& stream_tuning()
 {
     static const StreamTuning t = [] {
-        // measured over vector lengths, each kernel in both forms in one run: the persistent bfloat16
-        // encoders win by 3-9 % from two tiles per wave slot on (the chain decoder's own rule, used unless the
-        // threshold comes from the environment, is persistent_from)
-        StreamTuning v = {2u, 0u, 0u, false};
+        StreamTuning v = {0u, 0u, false};
         if (const char* e = getenv("NDQ_STREAM_MIN_TILES_PER_WAVE")) {
-            v.enc_min_tiles_per_wave = v.chain_min_tiles_per_wave = (uint32_t)strtoul(e, nullptr, 10);
+            v.min_tiles_per_wave = (uint32_t)strtoul(e, nullptr, 10);
             v.threshold_from_env = true;
         }
         if (const char* e = getenv("NDQ_STREAM_MAX_BLOCKS")) v.max_blocks = (uint32_t)strtoul(e, nullptr, 10);
