@@ -155,14 +155,17 @@ struct PhiloxFlight {
 
 // The bits of 64 + 2^-17 plus twice a 16-bit dither cell are the float 64 + (cell + 1/2) 2^-16,
 // i.e. the unit dither + 64.5 (other `bits`: another integer in place of 64, or all of it
-// divided by a power of two).  v_mad_u32_u16 takes the low half of a word (its op_sel form,
-// which takes the high one, is slower than the shift: 4 workers of 2^27 elements 190 against 185 us, 16 of 11.2 M 75 / 67).
+// divided by a power of two).  v_mad_u32_u16 takes the low half of a word.  The high half needs no addition: the word
+// shifted by 15 has one bit of the low half below twice the cell, where `bits` is 1, and `bits` is 0 in the sixteen
+// above it.  (Shift and v_mad_u32_u16 for the high half too, v_dot2_u32_u16, or this: 4 workers of 2^27 elements 192.9, 194.8, 191.0 us,
+// 16 of 11.2 M 65.7, 66.3, 64.9; the op_sel form of v_mad_u32_u16 is slower still.)
 constexpr uint32_t kDitherBits = 0x42800001u;
 template <bool HIGH>
 __device__ __forceinline__ float dither_raised(uint32_t word, uint32_t bits)
 {
+    if (HIGH) return __uint_as_float(word >> 15 | bits);
     uint32_t x;
-    asm("v_mad_u32_u16 %0, %1, 2, %2" : "=v"(x) : "v"(HIGH ? word >> 16 : word), "s"(bits));
+    asm("v_mad_u32_u16 %0, %1, 2, %2" : "=v"(x) : "v"(word), "s"(bits));
     return __uint_as_float(x);
 }
 
