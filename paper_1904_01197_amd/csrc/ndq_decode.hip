@@ -143,6 +143,20 @@ __global__ __launch_bounds__(kBlock) void decode_kernel(DecodeArgs a)
     else if (t.len != 0) decode_tile<MODE, ACC, false, STRADDLE>(a, t, lane);
 }
 
+// A worker after the other, a short launch waits for each cache line of its arguments: all its waves read a line for the
+// first time at the same moment, and the L2 has none of them yet.  So every lane first reads a word of a line of its own,
+// which brings the first `bytes` (at most 4,096) into the L2 side by side; nobody waits for it until arguments_read(),
+// after the first worker.  us without / with it at 0.3, 0.5 and 1.05 M elements: chain_stream_kernel, one row per wave, 2 x 16 levels
+// 3.50/3.30 3.70/3.52 4.21/4.01, 8 x 16 levels 6.42/5.62 6.65/5.87 7.20/6.72, 16 levels and 15 x M = 4 at 0.5 M 12.5/10.5; chain_kernel,
+// 8 x 100 levels, at 1.05 and 2 M 10.1/8.9 11.7/11.0; decode_mean_kernel, 4 workers, at 0.06, 0.27 and 1.66 M 5.9/5.3 6.3/5.7 10.7/10.5,
+// 16 workers 17.7/15.3 18.5/16.9 29.8/29.7.
+__device__ __forceinline__ uint32_t read_arguments_ahead(const __attribute__((address_space(4))) void* arguments, uint32_t bytes, int lane)
+{
+    const uint32_t at = (uint32_t)lane * 64u;
+    return ((const __attribute__((address_space(4))) uint32_t*)arguments)[(at < bytes ? at : 0u) / 4u];
+}
+__device__ __forceinline__ void arguments_read(uint32_t word) { asm volatile("" ::"v"(word)); }
+
 // ---------------------------------------------------------------------------
 // Chain decoder: the whole server loop of Algorithm 2 in one pass.  The running
 // sum of a lane's elements lives in registers while the workers are folded in
@@ -293,7 +307,7 @@ __device__ __forceinline__ void chain_fold_width(const ChainWorker& cw, const Ch
 }
 
 template <bool FULL, bool ROWB, int ROWS>
-__device__ __forceinline__ void chain_tile(const GeneralChainArgs& a, const TileRef& t, int lane)
+__device__ __forceinline__ void chain_tile(const GeneralChainArgs& a, const TileRef& t, int lane, uint32_t warm)
 {
     float S[ROWS][8];
     float* out = a.out + t.start;
@@ -323,6 +337,7 @@ __device__ __forceinline__ void chain_tile(const GeneralChainArgs& a, const Tile
         } else {
             chain_fold_width<kNestedAnyM, false, ROWB, ROWS>(cw, cur, block0, lane, S);
         }
+        if (w == 0u) arguments_read(warm);
         cur = nxt;
     }
 #pragma unroll
@@ -357,8 +372,12 @@ void chain_kernel(GeneralChainArgs a)
     const uint32_t tile_id =
         blockIdx.x * kWavesPerBlock + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const TileRef t = locate_tile(a.tl, tile_id, TILE);
-    if (t.len == TILE && t.start + TILE + 64u <= a.tl.n) chain_tile<true, ROWB, ROWS>(a, t, lane);
-    else if (t.len != 0) chain_tile<false, ROWB, ROWS>(a, t, lane);
+    uint32_t warm = 0u;
+    if (a.W > 1u)
+        warm = read_arguments_ahead((const __attribute__((address_space(4))) void*)__builtin_amdgcn_kernarg_segment_ptr(),
+                                    a.W * (uint32_t)sizeof(ChainWorker), lane);
+    if (t.len == TILE && t.start + TILE + 64u <= a.tl.n) chain_tile<true, ROWB, ROWS>(a, t, lane, warm);
+    else if (t.len != 0) chain_tile<false, ROWB, ROWS>(a, t, lane, warm);
 }
 
 // ---------------------------------------------------------------------------
@@ -1016,6 +1035,9 @@ void chain_stream_kernel(ChainArgs a_by_value)
     if (my_tiles > 1u) __builtin_amdgcn_s_setprio(3);
 
     const StreamWorkerPtr first_worker = &a->w[0], end_worker = &a->w[W];
+    constexpr bool WARM = FORM == kOneRow;      // (longer launches: nothing gained)
+    uint32_t warm = 0u;
+    if (WARM && W > 1u) warm = read_arguments_ahead(a, W * (uint32_t)sizeof(StreamWorker), lane);
     ChainCodes<ROWS> cur;
     stream_fetch<W0, ROWS>(first_worker->codes, (uint64_t)first * TILE, lane, cur, limit_for(first, limit0));
     // PIPED: the dither of the row after the current one is always in flight; here the first row's
@@ -1097,6 +1119,7 @@ void chain_stream_kernel(ChainArgs a_by_value)
             cur = nxt;
         };
         fold(std::integral_constant<int, kDq>{}, std::integral_constant<int, W0>{}, std::true_type{}, first_worker, 0u, MIXED && dq > 1u);
+        if (WARM) arguments_read(warm);
         uint32_t index = 1u;
         StreamWorkerPtr w = first_worker + 1;
         if constexpr (MIXED)
@@ -1286,6 +1309,8 @@ __device__ __forceinline__ void mean_tile(MeanArgsPtr a, const TileRef& t, uint3
             const uint32_t e = (uint32_t)(r * kWave + lane) * 4u + k;
             acc[r][k] = (a->continue_sum && (FULL || e < t.len)) ? a->out[t.start + e] : 0.0f;
         }
+    uint32_t warm = 0u;
+    if (W > 1u && a->tl.total_tiles < 4096u) warm = read_arguments_ahead(a, W * (uint32_t)sizeof(MeanWorker), lane);
     uint64_t window[kMeanRows], ahead[kMeanRows];
     float step[STEPS], step_ahead[STEPS] = {};
     mean_fetch<FULL, SMALL>(a, 0u, t, lane, bucket, window, step);
@@ -1316,6 +1341,7 @@ __device__ __forceinline__ void mean_tile(MeanArgsPtr a, const TileRef& t, uint3
                     if (o + k < t.len) decoded[o + k] = res[k];
             }
         }
+        if (w == 0u) arguments_read(warm);
 #pragma unroll
         for (int r = 0; r < kMeanRows; ++r) window[r] = ahead[r];
 #pragma unroll
