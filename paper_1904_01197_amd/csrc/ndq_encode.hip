@@ -914,24 +914,20 @@ static int launch_stream(const EncodeBatch& b, uint32_t full_tiles, hipStream_t 
 }
 
 // Tiles of a launch from which the streaming kernel is the faster one (bfloat16; the time of one tile per wave is what
-// has come down since it was made, by code widths known at compile time).  Encoder calls, us, one tile per wave / this, at
-// 4 x 8.4 M, 50 M, 2 x 50 M, 8 x 16 M, 134 M, 4 x 60 M, 3 x 134 M elements (8 k to 98 k tiles):
-//   4 levels, buckets of a tile   17.4/17.7 23.5/24.1 42.7/41.2 53.4/51.2 55.1/54.0 99.0/95.9 167/156
-//   M = 2                         16.1/16.4 22.0/23.1 39.9/39.2 49.0/47.0 51.3/48.4 92.5/89.9 155/149
-//   16 levels                     17.9/18.2 23.9/25.5 44.8/46.3 55.5/56.5 57.9/58.6 103/103 173/167
-//   M = 4                         16.0/17.3 21.7/23.7 39.2/40.6 49.2/52.5 51.7/53.9 93.4/96.0 153/158
-//   4 levels, one step            31.3/31.4 41.1/43.9 71.6/74.6 90.8/93.0 93.0/97.6 163/169 267/280
-//   M = 2                         28.4/28.7 37.3/40.1 68.6/71.9 86.3/89.3 88.2/93.4 158/165 258/272
-//   16 levels                     30.6/31.2 38.6/41.3 76.5/80.0 94.7/96.7 97.1/99.6 170/175 279/285
-// Buckets smaller than a tile and codes of 3 bits gain 3 to 5 % at 8 x 16 M and lose as much below 2 x 50 M: they are left
-// to the other kernel.
+// has come down since it was made, by code widths known at compile time).  One tile per wave over this, encoder calls on
+// vectors that are in no cache, at 4 x 8.4 M, 4 x 11.2 M, 67 M, 2 x 50 M, 8 x 16 M, 3 x 134 M elements (2 to 24 tiles per wave slot):
+//   buckets of a tile   4 levels 1.02 0.98 1.07 1.00 0.99         2 levels 0.98 0.97 1.02 1.00 1.01
+//                       16 levels 1.00 0.99 1.02 1.06 1.07        M = 2 0.97 0.95 1.05 1.00 1.00     M = 4 0.95 0.91 1.00 0.99 0.99 1.05
+//   one step            4 levels 0.94 0.95 1.02 0.97 0.97 0.95    2 levels 0.96 0.95 0.98 0.98 0.98 0.94
+//                       16 levels 0.99 0.95 0.98 0.97 0.98 0.97   M = 2 0.94 0.97 1.00 0.98 0.99 0.95   M = 4 0.93 0.95 1.03 1.00 0.98 0.97
+// (us persistent, buckets of a tile, 4 levels 17.4 23.4 30.0 44.3 54.7.)  Buckets smaller than a tile and codes of 3 bits gain 3
+// to 5 % by it at 8 x 16 M and lose as much below 2 x 50 M: they are left to the other kernel.
 static uint64_t stream_from_tiles(bool fused, bool nested, uint32_t bits)
 {
     const StreamTuning& tuning = stream_tuning();
     if (tuning.threshold_from_env) return (uint64_t)tuning.min_tiles_per_wave * kStreamSlots;
     if (!fused) return ~(uint64_t)0;
-    if (bits == 1u || (bits == 2u && !nested)) return 5u * kStreamSlots;
-    return nested ? ~(uint64_t)0 : 16u * kStreamSlots;
+    return (nested && bits == 2u ? 16u : 3u) * kStreamSlots;
 }
 
 // The streaming kernel serves vectors cut into whole tiles (a ragged last one aside):
