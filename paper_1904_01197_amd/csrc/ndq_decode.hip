@@ -512,11 +512,11 @@ __global__ __launch_bounds__(kBlock) void chain_short_kernel(GeneralChainArgs by
 }
 
 // ---------------------------------------------------------------------------
-// Streaming chain decoder for the common plans: a first DQSG worker, then
-// workers that are all alike -- all DQSG, or all nested with a power-of-two
-// nesting ratio and no shrinkage -- with code widths of 1, 2 or 4 bits, and a
-// vector cut into whole tiles.  One instantiation of the fold serves every
-// worker after the first, so the sixteen running sums of a lane stay in the same
+// Streaming chain decoder for the plans of chain_streams: DQSG workers of one code
+// width, then workers that are all alike -- more of them, or nested ones of one ratio
+// without shrinkage -- with codes of up to 4 bits, and a
+// vector cut into whole tiles or rows.  One instantiation of the fold serves every
+// worker of a kind, so the sixteen running sums of a lane stay in the same
 // registers from the first worker to the store (the general kernel dispatches on
 // mode and width after every worker and moves them around each time).  Waves are
 // persistent: a wave walks over tiles wave, wave + W, ... and fetches the next
