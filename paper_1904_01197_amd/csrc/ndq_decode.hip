@@ -673,9 +673,11 @@ __device__ __forceinline__ void stream_fold(const PhiloxUniform& keys, uint32_t 
     // v - q_min is exact for |q_min| <= 8 (code widths up to 4 bits); raised by 64.5, the dither
     // leaves c + 64.5 to subtract it from.  Nested: m' = c / M (a ratio that is no power of two: c).
     const FieldScaled<NF> field((uint32_t)WIDTH, MODE == kNestedPow2 ? (uint32_t)WIDTH : 0u, MODE == kDq ? 64.5f : 0.0f);
-    Quant qp;                       // (what the coset decoder reads of it)
+    Quant qp;                       // (what the coset decoder and `shrink` read of it)
     qp.M_f = ratio;
     qp.inv_M_f = inv_ratio;
+    qp.alpha = 1.0f;                // (an infinite running mean becomes NaN, as in chain_kernel: 0 times it is added, which costs 0 to 2 %)
+    qp.beta = 0.0f;
     const uint32_t dither_bits = MODE == kDq ? kDitherBits - (extra << 17) : kDitherBits;
     const float side_scale = __uint_as_float(extra);
 #pragma unroll
@@ -696,7 +698,8 @@ __device__ __forceinline__ void stream_fold(const PhiloxUniform& keys, uint32_t 
                 val = step * (c_f - x);
             } else if (MODE == kNestedAnyM) {
                 const float v = x - 64.5f;
-                val = index_value(coset_index_f<kNestedAnyM>(c_f, S[r][k] * side_scale, inv, v, qp), step, v);
+                const float y = S[r][k] * side_scale;
+                val = shrink<kNestedAnyM>(index_value(coset_index_f<kNestedAnyM>(c_f, y, inv, v, qp), step, v), y, qp);
             } else {
                 const float v = x - 64.5f;
                 const float y = S[r][k] * side_scale;
@@ -746,7 +749,7 @@ __device__ __forceinline__ bool step_out_of_range(float step)
 //   nested  x raised dither  v dither/M  a masked code [b m']  y S/count  c c'  t c' - m'  r rint
 //           q + m'  d - v/M  p times M Delta  s added to S
 //           a ratio that is no power of two: undivided, and between t and r the quotient of divide_by_ratio in its three
-//           pieces Q R N (S and c are finite where the steps are in range, so it needs no fix-up)
+//           pieces Q R N (S and c are finite where the steps are in range, so it needs no fix-up, nor 0 times y added)
 //   DQSG    x raised dither  a masked code  b c + 64.5  d minus x  p times Delta  [s added to S]
 //   m, X    the next multiply, the next xor of the Philox block
 struct RowProgram {

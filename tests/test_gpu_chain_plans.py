@@ -106,6 +106,30 @@ def test_persistent_form_matches_oracle_on_short_vectors():
     assert res.returncode == 0 and "PLANS_OK" in res.stdout, "\n".join(res.stdout.splitlines()[-15:])
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("plan", [[(DQ, 5)] * 4 + [(NESTED, 3)] * 4, [(DQ, 3)] + [(NESTED, 3)] * 7, [(DQ, 16), (NESTED, 7)]])
+def test_sums_beyond_binary32_do_not_depend_on_the_kernel(plan):
+    # an infinite running mean: a nested worker whose ratio is no power of two makes it NaN.  Short chains, the general kernel
+    # (buckets of 64), one row and one tile per wave, persistent tiles, buckets of a row in both forms
+    for n, bucket in ((5000, 0), (5000, 512), (5000, 64), (1024 * 1100 + 5, 1024), (1024 * 2200 + 5, 2048), (1024 * 2200 + 5, 512),
+                      (1024 * 10300 + 5, 4096), (1024 * 8300 + 5, 512)):
+        print(plan, n, bucket, flush=True)
+        rng = np.random.default_rng(n + bucket)
+        ds = opipe.dithers(len(plan), [7 + w for w in range(len(plan))], step=3, offset=0)
+        codes, steps, workers = [], [], []
+        for w, (kind, arg) in enumerate(plan):
+            codes.append(oracle.pack(rng.integers(0, arg, n).astype(np.uint32), oracle.code_bits(arg)))
+            s = np.full(oracle.num_buckets(n, bucket), 0.01, dtype=F)
+            s[::3] = F(1.5 * 2.0 ** 126)
+            steps.append(s)
+            workers.append((torch.from_numpy(codes[w]).cuda(), torch.from_numpy(s).cuda(),
+                            ndq.NDQ_WORKER_DQ if kind == DQ else ndq.NDQ_WORKER_NESTED, arg, ndq.ndq_dither(7 + w, 3, w, 0)))
+        ref = opipe.decode_chain(plan, bucket, n, codes, steps, ds, 1.0)
+        assert np.isnan(ref).sum() > n // 100
+        got = ndq.ndq_decode_chain(workers, n, bucket, 1.0).cpu().numpy()
+        assert np.array_equal(got, ref, equal_nan=True), (plan, n, bucket, np.nonzero(~((got == ref) | (np.isnan(got) & np.isnan(ref))))[0][:5])
+
+
 @pytest.fixture(scope="module")
 def recorder(tmp_path_factory):
     return lr.build(tmp_path_factory.mktemp("recorder"))
