@@ -1527,6 +1527,8 @@ static int launch_chain_stream(ChainArgs& a, uint64_t bucket_len, hipStream_t s)
     a.bucket_magic = ROWB || bucket_len == a.n ? 0u : (((uint64_t)1 << a.bucket_shift) + per_bucket - 1u) / per_bucket;
     const bool ragged = (uint64_t)tiles * tile < a.n;     // one more wave takes the ragged last tile
     const uint32_t all = tiles + (ragged ? 1u : 0u);
+    // (a grid has fewer than 2^32 threads: close to 2^35 elements a wave takes two rows, in chain_kernel)
+    if (rows_only && blocks_for(all) > 0xFFFFFFFFu / (uint32_t)kBlock) return 1;
     const dim3 grid(persistent ? persistent_blocks(all, 1024u * NDQ_CHAIN_PIPED_WAVES) : blocks_for(all)), block(kBlock);
     auto run = [&](auto lines, auto form) {
         constexpr bool LINES = decltype(lines)::value;

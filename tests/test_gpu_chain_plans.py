@@ -159,3 +159,14 @@ def test_form_for_buckets_of_a_row(recorder, name, tiles, form):
                 "dither": [1, 2, 3, 0]} for kind, arg in ROW_PLANS[name]]
     (rc, launches), = lr.record(recorder, [["ndq_decode_chain", workers, len(workers), 1024 * tiles + 1, 512, 1.0, 0x40000000, None]])
     assert rc == 0 and len(launches) == 1 and launches[0][0].endswith("ELi%dEEEvNS_9ChainArgsE" % form), launches
+
+
+# (the stream's block numbers go no further than 2^35 elements)
+@pytest.mark.parametrize("n", [(1 << 35) - 2048, (1 << 35) - 2047, 1 << 35])
+@pytest.mark.parametrize("name", ["2", "16, M 16", "16"])
+def test_longest_vectors_with_buckets_of_a_row_fit_a_grid(recorder, name, n):
+    workers = [{"codes": 0x20000000, "steps": 0x30000000, "kind": 0 if kind == DQ else 1, "levels_or_M": arg, "alpha": 1.0,
+                "dither": [1, 2, 3, 0]} for kind, arg in ROW_PLANS[name]]
+    (rc, launches), = lr.record(recorder, [["ndq_decode_chain", workers, len(workers), n, 512, 1.0, 0x40000000, None]])
+    # (workgroups of 256 threads, fewer than 2^32 threads)
+    assert rc == 0 and len(launches) == 1 and launches[0][1] * 256 < 1 << 32, launches
