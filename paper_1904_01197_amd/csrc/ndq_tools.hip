@@ -674,11 +674,12 @@ static int run_dense(DenseArgs& a, uint32_t k, uint32_t bits, bool pack, hipStre
 // choice).  A fixed grid and fixed orders of adding, so that the result does not depend on scheduling.
 //
 // One launch: every workgroup leaves its sum in a slot of the workspace and the last one of the grid collects
-// them (with a launch of its own for that 11 M elements take 17.1 us, so 16.7; 0.1 M 5.0 and 4.4).
+// them (with a launch of its own for that, replayed from a graph, 11 M elements take 17.5 us, so 16.7; 0.1 M 4.4 and 4.2).
 // Nobody has cleared the workspace, so a slot says by itself whether it is filled: two words, each half of the
 // sum beside half of the call's tag.  The other workgroups wait for nothing, so the collector's wait ends; a slot that
-// has not come after kSqPolls looks (two calls that wrongly share a workspace) it works out by itself.  It
-// empties the slots, so that a call replayed from a graph, with the same tag, finds none of them filled.
+// has not come after kSqPolls looks (two calls that wrongly share a workspace, a workgroup that is kept from running) it works
+// out by itself.  A call replayed from a graph has the same tag, so no slot is left filled: the collector empties what it has seen and
+// marks the words it gave up on as closed, and whoever comes to a word second, the collector or its workgroup, empties it.
 // ---------------------------------------------------------------------------
 constexpr uint32_t kSqBlocks = 512;
 constexpr uint32_t kSqThreads = 512;
@@ -686,6 +687,12 @@ constexpr uint32_t kSqPolls = 1u << 18;          // of about a microsecond each
 static_assert(kSqBlocks == kSqThreads, "a thread of the collector per slot");
 
 struct SqSlot { uint64_t word[2]; };
+
+// Workgroup `block`'s slot.  `skip`, one more than are needed, is left out: the one a result inside the workspace lies in.
+__device__ __forceinline__ SqSlot* slot_of(SqSlot* slots, uint32_t block, uint32_t skip) { return slots + block + (block >= skip ? 1u : 0u); }
+
+// what a word with this half of the tag holds once the collector has given it up
+__device__ __forceinline__ uint64_t closed_word(uint32_t half) { return (uint64_t)~half << 32 | (uint32_t)~half; }
 
 // the workgroup's sum, in its first thread
 __device__ __forceinline__ double block_sum(double x, double* sh)
@@ -722,34 +729,42 @@ __device__ __forceinline__ double sqdiff_share(const float* __restrict__ a, cons
 }
 
 __global__ __launch_bounds__(kSqThreads) void sqdiff_kernel(const float* __restrict__ a, const float* __restrict__ b,
-                                                            uint64_t n, SqSlot* slots, uint64_t tag, uint32_t polls,
-                                                            double* out)
+                                                            uint64_t n, SqSlot* slots, uint32_t skip, uint64_t tag,
+                                                            uint32_t polls, double* out)
 {
     __shared__ double sh[kSqThreads];
     __shared__ uint32_t missing[kSqBlocks];
     const uint32_t tid = threadIdx.x;
-    const uint32_t low = (uint32_t)tag, high = (uint32_t)(tag >> 32);
+    const uint32_t half[2] = {(uint32_t)tag, (uint32_t)(tag >> 32)};
     const double total = sqdiff_share(a, b, n, blockIdx.x, sh);
     if (blockIdx.x != kSqBlocks - 1u) {
         if (tid == 0u) {
             const uint64_t bits = (uint64_t)__double_as_longlong(total);
-            store_through(&slots[blockIdx.x].word[0], bits >> 32 << 32 | low);
-            store_through(&slots[blockIdx.x].word[1], bits << 32 | high);
+            const uint64_t filled[2] = {bits >> 32 << 32 | half[0], bits << 32 | half[1]};
+            uint64_t* word = slot_of(slots, blockIdx.x, skip)->word;
+            const uint64_t before[2] = {exchange_through(&word[0], filled[0]), exchange_through(&word[1], filled[1])};
+#pragma unroll
+            for (int w = 0; w < 2; ++w)
+                if (before[w] == closed_word(half[w])) store_through(&word[w], 0u);
         }
         return;
     }
     double mine = total;                         // (its own sum has no slot to go through)
-    bool have = tid == kSqBlocks - 1u;
+    const bool own = tid == kSqBlocks - 1u;
+    bool have = own;
+    uint64_t* word = slot_of(slots, own ? 0u : tid, skip)->word;
     for (uint32_t poll = 0; !have && poll < polls; ++poll) {
-        const uint64_t w0 = load_through(&slots[tid].word[0]), w1 = load_through(&slots[tid].word[1]);
-        have = (uint32_t)w0 == low && (uint32_t)w1 == high;
+        const uint64_t w0 = load_through(&word[0]), w1 = load_through(&word[1]);
+        have = (uint32_t)w0 == half[0] && (uint32_t)w1 == half[1];
         if (have) mine = __longlong_as_double((long long)(w0 >> 32 << 32 | w1 >> 32));
         else __builtin_amdgcn_s_sleep(1);
     }
     missing[tid] = have ? 0u : 1u;
+    if (!own) {
 #pragma unroll
-    for (int w = 0; w < 2; ++w)                  // (a result that lies inside the workspace is written below)
-        if (&slots[tid].word[w] != (uint64_t*)out) store_through(&slots[tid].word[w], 0u);
+        for (int w = 0; w < 2; ++w)
+            if (have || (uint32_t)exchange_through(&word[w], closed_word(half[w])) == half[w]) store_through(&word[w], 0u);
+    }
     if (__syncthreads_count(have ? 0 : 1) != 0)
         for (uint32_t block = 0; block < kSqBlocks; ++block) {
             if (missing[block] == 0u) continue;
@@ -803,8 +818,11 @@ static int sqdiff_common(const float* a, const float* b, size_t n, SqSlot* slots
     if (n >= kMaxN) return NDQ_EUNSUPPORTED;
     if (((uintptr_t)slots & 7u) || ((uintptr_t)out & 7u)) return NDQ_EALIGN;
     if (n != 0 && (!aligned16(a) || !aligned16(b))) return NDQ_EALIGN;
+    // a result may lie inside the workspace
+    const uintptr_t inside = (uintptr_t)out - (uintptr_t)slots;
+    const uint32_t skip = inside < kSqBlocks * sizeof(SqSlot) ? (uint32_t)(inside / sizeof(SqSlot)) : kSqBlocks - 1u;
     // (an emptied slot holds no tag: neither half is 0)
-    return launch(sqdiff_kernel, dim3(kSqBlocks), dim3(kSqThreads), (hipStream_t)stream, a, b, (uint64_t)n, slots,
+    return launch(sqdiff_kernel, dim3(kSqBlocks), dim3(kSqThreads), (hipStream_t)stream, a, b, (uint64_t)n, slots, skip,
                   call_tag() | 0x100000001u, collector_polls(), out);
 }
 

@@ -133,3 +133,38 @@ def test_squared_differences_with_and_without_a_patient_collector():
                          stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
     assert res.returncode == 0, res.stdout[-2000:]
     assert res.stdout.split("SUMS")[1].split() == here
+
+
+def _impatient_replays():
+    """A collector that looks once or never: replays of a call with other inputs, and what the call leaves in the workspace."""
+    for n in (5, 3000, 4 * 512 * 512, 1000003, 11173962):
+        a, b = torch.zeros(n, device="cuda"), torch.randn(n, device="cuda")
+        slots = torch.empty(ndq.ndq_sqdiff_workspace() // 8, dtype=torch.int64, device="cuda").random_(-2**62, 2**62)
+        work = slots.view(torch.float64)
+        for inside in (None, 78, 79):                # (a result in the workspace; else its last slot is not used)
+            out = torch.empty(1, dtype=torch.float64, device="cuda") if inside is None else work[inside:inside + 1]
+            ndq.ndq_sqdiff(a, b, work, out)
+            torch.cuda.synchronize()
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph):
+                ndq.ndq_sqdiff(a, b, work, out)
+            unused = slice(1022, 1024) if inside is None else slice(78, 80)
+            for rep in range(8):
+                print("replay", n, inside, rep, flush=True)
+                a.copy_(torch.randn(n, device="cuda") * (rep + 1))
+                torch.cuda.synchronize()
+                graph.replay()
+                torch.cuda.synchronize()
+                got, left = float(out.item()), slots.clone()
+                ref = float((a.double() - b.double()).square().sum().item())
+                assert abs(got - ref) <= n * 2.0 ** -52 * ref, (n, inside, rep, got, ref)
+                left[unused] = 0
+                assert not bool(left.any()), (n, inside, rep, int((left != 0).sum()))
+
+
+@pytest.mark.parametrize("polls", ["0", "1", "3"])
+def test_replays_after_a_collector_that_gave_up(polls):
+    code = "import sys; sys.path.insert(0, %r); import test_gpu_one_launch as t; t._impatient_replays(); print('REPLAYS_OK')" % os.path.dirname(__file__)
+    res = subprocess.run([sys.executable, "-u", "-c", code], env=dict(os.environ, NDQ_COLLECT_POLLS=polls, PYTHONPATH=os.pathsep.join(sys.path)),
+                         stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=100)
+    assert res.returncode == 0 and "REPLAYS_OK" in res.stdout, res.stdout[-1500:]
