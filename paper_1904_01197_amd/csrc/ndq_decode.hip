@@ -513,7 +513,7 @@ __global__ __launch_bounds__(kBlock) void chain_short_kernel(GeneralChainArgs by
 
 // ---------------------------------------------------------------------------
 // Streaming chain decoder for the plans of chain_streams: DQSG workers of one code
-// width, then workers that are all alike -- more of them, or nested ones of one ratio
+// width, then workers that are all alike -- more of them, also of another width after the first, or nested ones of one ratio
 // without shrinkage -- with codes of up to 4 bits, and a
 // vector cut into whole tiles or rows.  One instantiation of the fold serves every
 // worker of a kind, so the sixteen running sums of a lane stay in the same
@@ -1502,6 +1502,7 @@ static int launch_chain_stream(ChainArgs& a, uint64_t bucket_len, hipStream_t s)
     const uint32_t full = (uint32_t)(a.n / kChainTile);
     const StreamTuning& tuning = stream_tuning();
     constexpr bool RARER = MIXED || W0 == 3 || ROWB;     // (see chain_streams)
+    constexpr bool TWO_WIDTHS = RMODE == kDq && W0 != WR;
     // buckets of one row: ROWB has the persistent form only
     const bool rows_only = bucket_len < kChainTile && !ROWB;
     const uint32_t from = RARER ? rarer_persistent_from(a.W, RMODE == kDq ? a.W : a.dq, RMODE == kNestedAnyM, ROWB, slots)
@@ -1541,7 +1542,8 @@ static int launch_chain_stream(ChainArgs& a, uint64_t bucket_len, hipStream_t s)
     if constexpr (!ROWB) {
         // Rows of long vectors store whole lines, whatever they fold: halves / lines at 2.2, 4 and 16.8 M elements, 2 x 16 levels
         // 5.7/5.0 8.2/6.7 19.1/16.6, 8 x 16 levels 10.3/9.9 14.4/13.8 43.6/42.5, 4 levels and 3 x M = 2 7.9/7.4 11.5/10.5 31.4/30.5.
-        if (rows_only && full >= rows_below) return run(std::true_type{}, std::integral_constant<int, kOneRow>{});
+        if constexpr (!TWO_WIDTHS)
+            if (rows_only && full >= rows_below) return run(std::true_type{}, std::integral_constant<int, kOneRow>{});
         if (short_vector) {
             // (a launch of rows is bound by its stores only with one worker: 2 M elements 4.4 -> 4.0 us; 2 of 1.6 M 4.1 -> 4.2)
             if constexpr (RMODE == kDq && W0 == WR)
@@ -1556,7 +1558,7 @@ static int launch_chain_stream(ChainArgs& a, uint64_t bucket_len, hipStream_t s)
 
 // The plans the streaming kernel has.
 enum ChainPlan { kNoStream = 0,
-                 kPurePlan = 1,     // all DQSG, or one DQSG worker and nested ones; codes of 1, 2 and 4 bits
+                 kPurePlan = 1,     // all DQSG (the first may have another width), or one DQSG worker and nested ones; codes of 1, 2 and 4 bits
                  // The rarer plans: several DQSG workers and then nested ones, 3-bit codes, or a ratio that is no power of two;
                  // codes of 2 to 4 bits and of 1 to 3.  In kernels of their own, so that the others' stay as they are.  chain_kernel / this, us, at 1.05, 4 and
                  // 16.8 M elements: 1 x 8 levels 4.1/3.4 6.8/5.6 21.2/13.3, 8 x 8 levels 10.0/7.5 17.5/14.4 50.7/38.2, 8 levels and M = 4
@@ -1578,17 +1580,27 @@ static ChainPlan chain_streams(const GeneralChainArgs& a, uint32_t bucket, uint3
     if (first == 0u || w0 > 4u) return kNoStream;
     *dq = first;
     *wr = first < a.W ? a.w[first].bits : w0;
+    auto pure_width = [](uint32_t bits) { return bits == 1u || bits == 2u || bits == 4u; };
+    // DQSG workers of two widths, the first one's and the others' (buckets of one row: chain_kernel).  chain_kernel / this, us, at
+    // 1.05, 4.2 and 25.6 M elements: 4 and 16 levels 4.2/3.5 6.9/5.6 29.0/20.9, 4 and 3 x 16 levels 5.5/4.3 10.1/8.3 41.4/32.4,
+    // 2 and 7 x 4 levels 8.0/6.0 17.9/13.9 68.8/54.8
+    const bool two_widths = first == 1u && a.W > 1u && a.w[1].mode == kDq;
     const bool any_ratio = first < a.W && a.w[first].mode == kNestedAnyM;
-    for (uint32_t j = first; j < a.W; ++j)
-        if (a.w[j].mode != (any_ratio ? kNestedAnyM : kNestedPow2) || a.w[j].bits != *wr || a.w[j].alpha != 1.0f ||
-            a.w[j].M != a.w[first].M)
-            return kNoStream;
+    for (uint32_t j = first; j < a.W; ++j) {
+        if (a.w[j].mode != (two_widths ? kDq : any_ratio ? kNestedAnyM : kNestedPow2) || a.w[j].bits != *wr) return kNoStream;
+        if (!two_widths && (a.w[j].alpha != 1.0f || a.w[j].M != a.w[first].M)) return kNoStream;
+    }
+    if (two_widths && (a.row_buckets || !pure_width(w0) || !pure_width(*wr))) return kNoStream;
     // the high word of the dither's block number is the same for the whole call (it changes every 2^35 elements)
     for (uint32_t j = 0; j < a.W; ++j)
         if ((a.w[j].index0 >> 35) != ((a.w[j].index0 + a.tl.n - 1u) >> 35)) return kNoStream;
+    if (two_widths) {
+        *dq = a.W;
+        return kPurePlan;
+    }
     if (first == a.W) return w0 == 3u ? kMixedPlan : kPurePlan;
     if (any_ratio) return w0 >= 2u && *wr <= 3u ? kMixedPlan : kNoStream;
-    if (first == 1u && w0 != 3u && (*wr == 1u || *wr == 2u || *wr == 4u)) return kPurePlan;
+    if (first == 1u && pure_width(w0) && pure_width(*wr)) return kPurePlan;
     return w0 >= 2u && *wr <= 3u ? kMixedPlan : kNoStream;
 }
 
@@ -1621,7 +1633,7 @@ static int run_chain_stream(const GeneralChainArgs& a, uint32_t bucket, ChainPla
         constexpr int RMODE = decltype(rmode)::value, W0 = decltype(first)::value, WR = decltype(rest)::value;
         constexpr bool MIXED = decltype(mixed)::value;
         // buckets of one row, persistent: one DQSG worker is the mixed plan that has one
-        if constexpr (W0 >= 2 && (RMODE == kDq || WR <= 3))
+        if constexpr (W0 >= 2 && (RMODE == kDq ? W0 == WR : WR <= 3))
             if (bucket_len < kChainTile) {
                 const int rc = launch_chain_stream<RMODE, W0, WR, RMODE != kDq, true>(b, bucket_len, s);
                 if (rc != 1) return rc;
@@ -1637,6 +1649,11 @@ static int run_chain_stream(const GeneralChainArgs& a, uint32_t bucket, ChainPla
     constexpr std::integral_constant<int, 4> b4{};
     constexpr std::true_type yes{};
     constexpr std::false_type no{};
+    if (dq == a.W && w0 != wr) {
+        if (w0 == 1u) return wr == 2u ? run(all_dq, b1, b2, no) : run(all_dq, b1, b4, no);
+        if (w0 == 2u) return wr == 1u ? run(all_dq, b2, b1, no) : run(all_dq, b2, b4, no);
+        return wr == 1u ? run(all_dq, b4, b1, no) : run(all_dq, b4, b2, no);
+    }
     if (dq == a.W)
         return w0 == 1u ? run(all_dq, b1, b1, no) : w0 == 2u ? run(all_dq, b2, b2, no) : w0 == 3u ? run(all_dq, b3, b3, no)
                                                                                                 : run(all_dq, b4, b4, no);

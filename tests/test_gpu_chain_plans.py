@@ -170,3 +170,23 @@ def test_longest_vectors_with_buckets_of_a_row_fit_a_grid(recorder, name, n):
     (rc, launches), = lr.record(recorder, [["ndq_decode_chain", workers, len(workers), n, 512, 1.0, 0x40000000, None]])
     # (workgroups of 256 threads, fewer than 2^32 threads)
     assert rc == 0 and len(launches) == 1 and launches[0][1] * 256 < 1 << 32, launches
+
+
+# (that their values match the oracle: test_gpu_chain_streaming.py and streaming_cases.py, every pair of widths)
+@pytest.mark.parametrize("first,other", [(a, b) for a in (2, 4, 16) for b in (2, 4, 16) if a != b])
+@pytest.mark.parametrize("others", [1, 2, 4])
+def test_quantizers_of_two_widths_reach_the_streaming_kernel(recorder, first, other, others):
+    workers = [{"codes": 0x20000000, "steps": 0x30000000, "kind": 0, "levels_or_M": arg, "alpha": 1.0, "dither": [1, 2, 3, 0]}
+               for arg in [first] + [other] * others]
+    sizes = [(512, 0), (1024 * 1024, 0), (1024 * 2048, 2048), (1024 * 12288, 0), (1024 * 12288 + 1, 1024), (1024 * 2048, 512)]
+    calls = [["ndq_decode_chain", workers, len(workers), n, bucket, 1.0, 0x40000000, None] for n, bucket in sizes]
+    calls.append(["ndq_decode_chain", workers + [dict(workers[0])], len(workers) + 1, 1024 * 2048, 0, 1.0, 0x40000000, None])   # the first width again
+    got = lr.record(recorder, calls)
+    short = others >= 3                               # (the kernel for short chains: four workers and more)
+    for (n, bucket), (rc, launches), form in zip(sizes, got, (2, 2, 1, 0, 0)):
+        assert rc == 0 and len(launches) == 1, launches
+        if short and n == 512:
+            assert "chain_short_kernel" in launches[0][0]
+            continue
+        assert "chain_stream_kernel" in launches[0][0] and launches[0][0].endswith("ELi%dEEEvNS_9ChainArgsE" % form), (n, launches)
+    assert all(rc == 0 and len(launches) == 1 and "12chain_kernel" in launches[0][0] for rc, launches in got[5:]), got[5:]
