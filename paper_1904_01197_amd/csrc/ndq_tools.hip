@@ -31,7 +31,8 @@ constexpr uint32_t kHistThreads = 1024;
 constexpr uint32_t kHistBlocks = 256;
 constexpr uint32_t kHistCopies = 32;
 
-// The call is one launch when a word holds its ticket: the entropy's eight bytes, or those of the bin that is derived.
+// The call is one launch when a word holds its ticket (the entropy's eight bytes, or those of the bin that is derived) and the
+// stream is not a long one of 1 or 2 bits (kSmallCleared).
 // Nobody has cleared the bins (a launch of its own for that costs the call 1.5 to 2.5 us: 25.6 M codes of 4 bits
 // 12.8 -> 11.0, 1 M 7.6 -> 6.1, 0.2 M of 5 bits 7.4 -> 5.8), so whoever finds the ticket without the call's tag puts it
 // there, clears the bins and says so.  That is the first workgroup, which counts nothing, while the others count; a
@@ -49,8 +50,9 @@ constexpr uint32_t kHistCopies = 32;
 // back and invalidate the L2 sixteen times per workgroup while the others still stream through it.)
 // Every thread calls last_workgroup.  The one that draws the last ticket therefore finds all counts in
 // memory; it reads them with atomics of device scope, like the additions that made them.
-constexpr unsigned long long kTicketBits = 0xFFFFull;       // the low bits of the word: tickets drawn (at most 256)
+constexpr unsigned long long kTicketBits = 0xFFFFull;       // the low bits of the word: tickets drawn (a workgroup each, and the opening one)
 constexpr unsigned long long kOpening = 0x8000ull;          // ... or this, while the bins are being cleared
+static_assert(kHistBlocks + 1u < kOpening, "tickets");
 constexpr uint32_t kOpenPolls = 1u << 18;                   // of about a microsecond each
 
 // What the first wave of a workgroup knows of the opening.  All functions are called by that whole wave.
@@ -286,6 +288,13 @@ __global__ __launch_bounds__(kHistThreads) void histogram_kernel(const uint32_t*
 // most n / 2^18 + 1024 codes (n < 2^40), a wave 64 times that: 32-bit counts up to
 // the wave's sum, 64-bit ones across waves.
 constexpr uint32_t kSmallBlocks = 256;
+static_assert(kSmallBlocks < kOpening, "tickets");
+// Counting workgroups from which a launch of its own clears the bins: the workgroups of a stream this long all end at once, and
+// their looks at the ticket's word then queue up with the additions and tickets on the same line (and have no rounds to go
+// between).  us cleared by a launch / by the first workgroup, 2-bit codes, 60, 80, 100, 130, 160, 300 and 1500 M (115, 153, 191, 248,
+// 256 workgroups): 11.1/10.8 12.8/12.6 14.1/14.5 17.4/20.1 18.0/24.1 22.7/28.1 76.4/78.5; 1-bit codes, 130, 160, 200 and 300 M (124,
+// 153, 191, 256): 10.9/10.4 12.4/12.4 13.8/14.6 17.8/21.4.
+constexpr uint32_t kSmallCleared = 160;
 constexpr uint32_t kSmallThreads = 1024;
 constexpr int kSmallInFlight = 8;
 
@@ -324,16 +333,17 @@ __global__ __launch_bounds__(kSmallThreads) void histogram_small_kernel(const ui
     const uint32_t tid = threadIdx.x;
     // bins 1..3 (or bin 1) are counted; bin 0 is not: its eight bytes hold the
     // ticket, and the last workgroup writes there what the other bins leave of n
+    // (no tag: the bins have been cleared by a launch of its own, and tickets count from 0)
     constexpr uint32_t nbins = 1u << BITS;
-    const bool alone = gridDim.x == 1u, opens = !alone && blockIdx.x == 0u;
+    const bool alone = gridDim.x == 1u, cleared = tag == 0ull, opens = !alone && !cleared && blockIdx.x == 0u;
     HistogramOpening opening(hist, 1u, nbins, hist, tag);
     if (opens && tid < kWave) opening.await();
-    const bool watches = !alone && !opens && __builtin_amdgcn_readfirstlane(tid / kWave) == 0u;
+    const bool watches = !alone && !cleared && !opens && __builtin_amdgcn_readfirstlane(tid / kWave) == 0u;
     // whole 16-byte vectors here; the last, partial one (the stream is allocated in
     // multiples of 16 bytes) is masked to its valid bits below.  Bits masked away
     // read as code 0, and bin 0 is n minus the other bins anyway.
     const uint64_t vectors = (n * bits) >> 7;
-    const uint32_t first_counter = alone ? 0u : 1u;
+    const uint32_t first_counter = alone || cleared ? 0u : 1u;
     const uint64_t stride = (uint64_t)(gridDim.x - first_counter) * kSmallThreads;
     uint32_t c[3] = {0u, 0u, 0u};
     uint64_t u = opens ? vectors : (uint64_t)(blockIdx.x - first_counter) * kSmallThreads + tid;
@@ -372,7 +382,7 @@ __global__ __launch_bounds__(kSmallThreads) void histogram_small_kernel(const ui
     if (alone || last_workgroup(hist, tag, &flag)) close_histogram(hist, nbins, n, entropy_out, true, term, few);
 }
 
-// For what nobody holds a ticket of: clears the bins and, when an entropy is wanted, its eight bytes (+0.0: the
+// For what nobody holds a ticket of, and long streams: clears the bins and, when an entropy is wanted, its eight bytes (+0.0: the
 // entropy of an empty stream).
 __global__ void clear_histogram_kernel(unsigned long long* hist, uint32_t nbins, unsigned long long* entropy_bits)
 {
@@ -863,12 +873,13 @@ int ndq_code_entropy(const void* codes, size_t n, uint32_t bits, uint64_t* hist_
         uint64_t blocks = (vectors + kSmallInFlight * kSmallThreads - 1) / (kSmallInFlight * kSmallThreads);
         if (blocks > kSmallBlocks) blocks = kSmallBlocks;
         if (blocks == 0u) blocks = 1u;
-        if (blocks > 1u) ++blocks;           // and the one that opens the histogram
-        if (bits == 1u)
-            return launch(histogram_small_kernel<1>, dim3((uint32_t)blocks), dim3(kSmallThreads), s,
-                          (const uint4*)codes, (uint64_t)n, (unsigned long long*)hist_out, entropy_out, tag);
-        return launch(histogram_small_kernel<2>, dim3((uint32_t)blocks), dim3(kSmallThreads), s,
-                      (const uint4*)codes, (uint64_t)n, (unsigned long long*)hist_out, entropy_out, tag);
+        const bool cleared = blocks >= kSmallCleared;
+        if (cleared && launch(clear_histogram_kernel, dim3(1), dim3(256), s, (unsigned long long*)hist_out, nbins,
+                              (unsigned long long*)nullptr) != NDQ_OK)
+            return NDQ_ELAUNCH;
+        if (blocks > 1u && !cleared) ++blocks;           // and the one that opens the histogram
+        return launch(bits == 1u ? histogram_small_kernel<1> : histogram_small_kernel<2>, dim3((uint32_t)blocks), dim3(kSmallThreads),
+                      s, (const uint4*)codes, (uint64_t)n, (unsigned long long*)hist_out, entropy_out, cleared ? 0ull : tag);
     }
     const uint64_t units = (uint64_t)n >> 5;
     uint64_t blocks = (units + kHistThreads - 1) / kHistThreads;

@@ -49,6 +49,36 @@ def test_histogram_into_memory_that_holds_anything(bits):
             assert abs(float(ent.item()) - _entropy(ref)) <= 1e-12, (n, fill)
 
 
+@pytest.mark.parametrize("bits,n", [(1, 160 * 8192 * 128 + 77), (1, 400000007), (2, 159 * 8192 * 64 - 5), (2, 160 * 8192 * 64 + 31), (2, 200000003)])
+def test_histogram_of_long_streams(bits, n):
+    # (both ways of clearing the bins; eager, then replays that find their own results)
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    packed = torch.randint(0, 256, (ndq.ndq_packed_bytes(n, bits),), dtype=torch.uint8, device="cuda", generator=gen)
+    hist = torch.full((1 << bits,), -7, dtype=torch.int64, device="cuda")
+    ent = torch.full((1,), -7.0, dtype=torch.float64, device="cuda")
+    per, whole = 8 // bits, n * bits // 8
+    ndq.ndq_code_entropy(packed, n, bits, hist, ent)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ndq.ndq_code_entropy(packed, n, bits, hist, ent)
+    for rep in range(4):
+        if rep:
+            packed.bitwise_and_(torch.randint(0, 256, packed.shape, dtype=torch.uint8, device="cuda", generator=gen))
+            torch.cuda.synchronize()
+            graph.replay()
+        torch.cuda.synchronize()
+        bytes_ = torch.bincount(packed[:whole], minlength=256).cpu().numpy()
+        ref = np.zeros(1 << bits, dtype=np.int64)
+        for byte, count in enumerate(bytes_):
+            for k in range(per):
+                ref[byte >> k * bits & (1 << bits) - 1] += count
+        for k in range(n - whole * per):
+            ref[int(packed[whole]) >> k * bits & (1 << bits) - 1] += 1
+        assert np.array_equal(hist.cpu().numpy(), ref), (n, rep)
+        assert abs(float(ent.item()) - _entropy(ref)) <= 1e-12, (n, rep)
+
+
 def test_histograms_of_several_streams_at_once():
     streams = [torch.cuda.Stream() for _ in range(4)]
     calls = [(bits, n) + _stream(bits, n, seed=s) for s, (bits, n) in

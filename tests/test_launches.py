@@ -167,3 +167,13 @@ def test_encoders_that_know_their_code_width(recorder, dt, M, bucket, width):
     (rc, launches), = lr.record(recorder, [call])
     assert rc == 0 and len(launches) == 1
     assert ("ELi%dEEEvNS_11EncodeBatch" % width) in launches[0][0], launches
+
+
+# (counting workgroups of 1- and 2-bit codes take 8,192 vectors of 16 bytes at a time; from 160 of them on a launch of its own clears the bins)
+@pytest.mark.parametrize("bits,n,kernels,grid", [
+    (1, 159 * 8192 * 128, 1, 160), (1, 159 * 8192 * 128 + 128, 2, 160), (2, 159 * 8192 * 64, 1, 160), (2, 159 * 8192 * 64 + 64, 2, 160),
+    (2, 1500000000, 2, 256), (4, 1500000000, 1, 257), (2, 8192 * 64, 1, 1), (2, 8192 * 64 + 64, 1, 3)])
+def test_launches_of_the_entropy(recorder, bits, n, kernels, grid):
+    (rc, launches), = lr.record(recorder, [["ndq_code_entropy", 0x10000000, n, bits, 0x20000000, 0x30000000, None]])
+    assert rc == 0 and len(launches) == kernels and launches[-1][1] == grid, launches
+    assert kernels == 1 or "clear_histogram" in launches[0][0]
