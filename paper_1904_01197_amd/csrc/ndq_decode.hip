@@ -1513,7 +1513,16 @@ static int launch_chain_stream(ChainArgs& a, uint64_t bucket_len, hipStream_t s)
     // Few workers of the rarer plans store whole lines from fewer tiles on: rows / tiles at 1.0, 1.3, 1.6, 2.0 M elements
     //   2 workers   4.63/4.67  5.32/5.05  5.79/5.13  6.12/5.40 (3-bit and a 2-bit nested)  4.35/4.39  4.70/4.69  5.06/4.73  5.42/4.94
     //   3           5.13/5.88  5.91/6.00  6.32/6.19  6.68/6.72                             4.76/5.17  5.17/5.54  5.79/5.49  6.10/5.68
-    const uint32_t rows_below = RARER && a.W == 2u ? 1280u : RARER && a.W == 3u ? 1536u : kShortTiles;
+    // Four and more workers of them take rows for longer, 3-bit DQSG ones almost until the chip holds a tile per wave slot: a second
+    // round of rows is as full as the tiles' first.  chain_kernel / rows / tiles at 2.1, 2.4, 2.7, 3.6, 4.7 and 5.4 M elements
+    //   4 x 8 levels                  7.0/6.2/7.4  7.8/6.9/8.7  8.3/7.6/8.5  9.2/9.1/9.4  11.2/10.4/11.1  12.4/11.8/10.4
+    //   7 x 8 levels                  10.2/9.0/10.6  11.4/10.0/12.3  12.6/11.0/12.3  13.8/12.6/14.4  17.4/14.8/16.7  19.5/16.8/16.2
+    //   4 x 16 levels, 4 x M = 4      13.3/10.9/11.4  13.6/11.4/11.7  15.2/12.8/11.7  17.0/14.6/14.1
+    //   4 x 5 levels, 4 x M = 3       14.6/12.3/13.7  14.9/13.0/13.9  16.6/14.6/13.8  18.6/17.5/16.6
+    //   16 levels, 7 x M = 8          14.2/13.1/14.8  14.5/13.6/15.2  16.2/15.2/15.1  17.9/18.1/18.1
+    //   16 levels, 15 x M = 8         27.3/24.8/30.6  27.2/25.3/31.0  30.6/27.8/30.3  33.0/32.0/34.3  (tiles vary by a seventh with the length)
+    const uint32_t rows_below = !RARER || a.W == 1u ? kShortTiles : a.W == 2u ? 1280u : a.W == 3u ? 1536u : RMODE == kDq ? 4864u
+                                : RMODE == kNestedPow2 && WR == 3 && a.W >= 12u ? 4096u : 2600u;
     const bool short_vector = !persistent && (full < rows_below || rows_only);
     const uint32_t tile = short_vector ? ChainStreamTile<kOneRow>::N : kChainTile;
     // the rarer plans have the kernels with a ragged last tile only: a whole one takes its place
@@ -1543,7 +1552,7 @@ static int launch_chain_stream(ChainArgs& a, uint64_t bucket_len, hipStream_t s)
         // Rows of long vectors store whole lines, whatever they fold: halves / lines at 2.2, 4 and 16.8 M elements, 2 x 16 levels
         // 5.7/5.0 8.2/6.7 19.1/16.6, 8 x 16 levels 10.3/9.9 14.4/13.8 43.6/42.5, 4 levels and 3 x M = 2 7.9/7.4 11.5/10.5 31.4/30.5.
         if constexpr (!TWO_WIDTHS)
-            if (rows_only && full >= rows_below) return run(std::true_type{}, std::integral_constant<int, kOneRow>{});
+            if (rows_only && full >= (rows_below < kShortTiles ? rows_below : kShortTiles)) return run(std::true_type{}, std::integral_constant<int, kOneRow>{});
         if (short_vector) {
             // (a launch of rows is bound by its stores only with one worker: 2 M elements 4.4 -> 4.0 us; 2 of 1.6 M 4.1 -> 4.2)
             if constexpr (RMODE == kDq && W0 == WR)

@@ -23,7 +23,8 @@ PLANS = {
     "4, M 4": [(DQ, 4)] * 2 + [(NESTED, 4)], "4, M 8": [(DQ, 4)] * 3 + [(NESTED, 8)], "8, M 2": [(DQ, 8)] * 2 + [(NESTED, 2)] * 3,
     "8, M 8": [(DQ, 8)] * 2 + [(NESTED, 8)], "16, M 2": [(DQ, 16)] * 2 + [(NESTED, 2)] * 2, "16, M 4": [(DQ, 16)] * 8 + [(NESTED, 4)] * 8,
     "5, M 3": [(DQ, 5)] * 4 + [(NESTED, 3)] * 4, "16, M 7": [(DQ, 16), (NESTED, 7)], "4, M 5": [(DQ, 4)] * 2 + [(NESTED, 5)],
-    "3, M 3": [(DQ, 3)] + [(NESTED, 3)] * 7, "8, M 6": [(DQ, 8)] * 2 + [(NESTED, 6)],
+    "3, M 3": [(DQ, 3)] + [(NESTED, 3)] * 7, "8, M 6": [(DQ, 8)] * 2 + [(NESTED, 6)], "4 of 8": [(DQ, 8)] * 4,
+    "16, 15 of M 8": [(DQ, 16)] + [(NESTED, 8)] * 15,
 }
 # with buckets of one row (also plans whose other kernels are not the rarer plans')
 ROW_PLANS = dict(PLANS, **{"2": [(DQ, 2)] * 2, "2, M 2": [(DQ, 2), (NESTED, 2)], "4, M 2": [(DQ, 4)] + [(NESTED, 2)] * 3, "16": [(DQ, 16)] * 3,
@@ -39,6 +40,19 @@ def _tight(n):
             m += 1
         out.append(m)
     return out
+
+
+def _tiles_from(plan):
+    """Tiles of 1,024 elements from which a wave takes two rows (fewer where the persistent form comes first)."""
+    W, dq = len(plan), sum(kind == DQ for kind, _ in plan)
+    if W < 4:
+        return {1: 2048, 2: 1280, 3: 1536}[W]
+    if dq == W:
+        return 4864 if W < 8 else 2048
+    any_ratio = plan[-1][1] in (3, 5, 6, 7)
+    if any_ratio and W - dq >= 7:
+        return 2048
+    return 4096 if plan[-1][1] == 8 and W >= 12 else 2600
 
 
 ROWS = [513, 512 * 2, 512 * 9 + 1, 512 * 40 - 1, 1024 * 15 + 8, 1024 * 33 + 512] + _tight(530) + _tight(1024 * 8)
@@ -81,7 +95,7 @@ def _sweep(sizes):
 @pytest.mark.parametrize("name", list(PLANS))
 def test_rows_and_tiles_match_oracle(name):
     plan = PLANS[name]
-    long = 1024 * (1280 if len(plan) == 2 else 1536 if len(plan) == 3 else 2048)
+    long = 1024 * _tiles_from(plan)
     for n, bucket in [(n, b) for n in ROWS for b in (0, 1024)] + [(long - 1, 0), (long, 0), (long + 1, 2048), (long + 4 * 1024 + 700, 0)] + [
             (n, 0) for n in _tight(long + 300)]:
         _check(plan, n, bucket, 8 * (n % 129), 1.0 / len(plan))
@@ -140,7 +154,8 @@ def test_plans_reach_the_streaming_kernel(recorder, name):
     plan = PLANS[name]
     workers = [{"codes": 0x20000000, "steps": 0x30000000, "kind": 0 if kind == DQ else 1, "levels_or_M": arg, "alpha": 1.0,
                 "dither": [1, 2, 3, 0]} for kind, arg in plan]
-    sizes = [1024 * 1024, 1024 * 2048, 1024 * 12288]
+    line = _tiles_from(plan)
+    sizes = [1024 * (line - 1) + 1023, 1024 * line, 1024 * 12288]
     calls = [["ndq_decode_chain", workers, len(plan), n, 0, 1.0, 0x40000000, None] for n in sizes]
     calls.append(["ndq_decode_chain", [dict(w, alpha=0.9) for w in workers], len(plan), sizes[1], 0, 1.0, 0x40000000, None])
     got = lr.record(recorder, calls)
