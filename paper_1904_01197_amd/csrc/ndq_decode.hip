@@ -1698,13 +1698,40 @@ static int run_chain_stream(const GeneralChainArgs& a, uint32_t bucket, ChainPla
 //                                 6, 8          0.64/0.66  0.72/0.71  0.81/0.77  0.86/0.84  0.94/0.89  1.02/0.96  1.09/1.03
 //                                 12, 16        0.56/0.51  0.66/0.57  0.76/0.67  0.80/0.76  0.89/0.86  0.98/0.95  1.06/1.03
 //                                 20 to 32      0.53/0.46  0.60/0.54  0.81/0.77  0.86/0.85  0.96/0.95  1.12/1.12  1.19/1.19
+// at 131 k, 262 k, 393 k, 458 k, 524 k, 655 k, 786 k (as far as the lines are near)
+//   against chain_stream_kernel, the rarer plans
+//     3-bit DQSG      2   0.98/1.02 1.08/1.05 1.16/1.09
+//                     3   0.87/0.94 0.96/0.98 1.06/1.06
+//                     4   0.78/0.94 0.86/0.96 0.95/0.99 1.05/1.05
+//                     6   0.76/0.86 0.83/0.93 0.90/0.96 0.99/1.03
+//                     8   0.66/0.76 0.72/0.80 0.82/0.88 0.92/0.96 0.95/0.98 1.00/0.99 1.10/1.09
+//                     16  0.57/0.64 0.63/0.68 0.75/0.78 0.87/0.88 0.87/0.88 0.95/0.96 1.07/1.08
+//                     20  0.56/0.59 0.61/0.63 0.74/0.75 1.04/1.04
+//     half nested,    2   0.96/1.01 1.06/1.00 1.12/1.09
+//     1 or 2 bits     3   0.94/1.02 1.00/1.00 1.08/1.06
+//                     4   0.87/0.98 0.93/0.98 1.03/1.02 1.12/1.06
+//                     8   0.77/0.84 0.85/0.90 0.96/0.97 1.08/1.07
+//                     16  0.68/0.74 0.74/0.79 0.88/0.89 1.01/1.02
+//                     20  0.67/0.70 0.73/0.76 0.87/0.88 1.25/1.25
+//     half M = 3      2   0.95/1.01 1.04/1.03 1.11/1.10
+//                     4   0.81/0.92 0.87/0.95 0.96/0.97 1.06/1.08
+//                     8   0.69/0.78 0.77/0.84 0.87/0.92 1.00/1.00 1.00/1.04
+//                     16  0.61/0.67 0.68/0.71 0.80/0.82 0.93/0.95 0.94/0.95 0.97/0.97 1.11/1.10
+//                     20  0.60/0.63 0.66/0.67 0.79/0.80 1.13/1.13
+//     15 of M = 8     16  0.56/0.59 0.61/0.63 0.71/0.72 0.82/0.83 0.83/0.83 0.86/0.85 0.97/0.97
 // One worker alone has nothing to wait for twice.  (A streaming threshold from the environment means that
 // kernel, whatever the length.)
-static uint32_t short_chain_most(uint32_t W, bool streams)
+// `dq` DQSG workers, then nested ones with codes of `wr` bits.
+static uint32_t short_chain_most(uint32_t W, ChainPlan plan, uint32_t dq, uint32_t wr, bool any_ratio)
 {
-    if (!streams) return W < 2u ? 0u : 131072u * (W > 16u ? 6u : W < 6u ? W + 1u : 7u);
-    if (W < 4u || stream_tuning().threshold_from_env) return 0u;
-    return 196608u + 12288u * (W < 16u ? W : 16u);
+    if (plan == kNoStream) return W < 2u ? 0u : 131072u * (W > 16u ? 6u : W < 6u ? W + 1u : 7u);
+    if (stream_tuning().threshold_from_env) return 0u;
+    if (plan == kPurePlan) return W < 4u ? 0u : 196608u + 12288u * (W < 16u ? W : 16u);
+    if (W < 4u) return 131072u * (W - 1u);
+    // (longer folds gain the more by being prepared side by side)
+    if (W > 16u) return 3u * 131072u;
+    if (dq == W) return 131072u * (W >= 8u ? 5u : 3u);
+    return 131072u * (W < 12u ? 3u : any_ratio ? 5u : wr == 3u ? 6u : 3u);
 }
 
 }  // namespace ndq
@@ -1885,9 +1912,9 @@ int ndq_decode_chain(const ndq_worker* workers, uint32_t W, size_t n, uint32_t b
             cw.first = (p0 + j) == 0u;
         }
         hipStream_t hs = (hipStream_t)stream;
-        uint32_t dq, wr;
+        uint32_t dq = 0u, wr = 0u;
         const ChainPlan plan = W <= kChainMax ? chain_streams(a, bucket, &dq, &wr) : kNoStream;
-        if (W <= kChainMax && n <= short_chain_most(W, plan == kPurePlan)) {
+        if (W <= kChainMax && n <= short_chain_most(W, plan, dq, wr, plan != kNoStream && a.w[W - 1u].mode == kNestedAnyM)) {
             a.tl.bucket_len = bucket != 0u ? bucket : n;
             const dim3 grid((uint32_t)((n + kShortTile - 1u) / kShortTile)), block(kBlock);
             return W <= 8u ? launch(chain_short_kernel<8>, grid, block, hs, a)

@@ -147,9 +147,14 @@ def test_a_streaming_threshold_from_the_environment_reaches_the_persistent_encod
 # longest vector that the kernel for short chains takes, by its plan: (kind, levels or M) of every worker
 @pytest.mark.parametrize("plan,most", [
     ([(0, 16)] * 3, 0), ([(0, 16), (1, 4)], 0), ([(0, 16)] * 4, 245760), ([(0, 4)] + [(1, 2)] * 7, 294912),
-    ([(0, 16)] + [(1, 4)] * 15, 393216), ([(0, 16)] * 32, 393216), ([(0, 5)], 0), ([(0, 8), (1, 4)], 393216),
-    ([(0, 5)] * 2 + [(1, 3)] * 2, 655360), ([(0, 5)] * 5, 786432), ([(0, 16)] * 8 + [(1, 4)] * 8, 917504),
-    ([(0, 8)] + [(1, 8)] * 31, 786432)])
+    ([(0, 16)] + [(1, 4)] * 15, 393216), ([(0, 16)] * 32, 393216), ([(0, 5)], 0),
+    # the rarer plans of the streaming kernel
+    ([(0, 8), (1, 4)], 131072), ([(0, 5)] * 2, 131072), ([(0, 16)] * 2 + [(1, 4)], 262144), ([(0, 5)] * 2 + [(1, 3)] * 2, 393216),
+    ([(0, 5)] * 7, 393216), ([(0, 5)] * 8, 655360), ([(0, 16)] * 8 + [(1, 4)] * 8, 393216), ([(0, 16)] * 8 + [(1, 8)] * 3, 393216),
+    ([(0, 16)] * 8 + [(1, 8)] * 4, 786432), ([(0, 5)] + [(1, 3)] * 15, 655360), ([(0, 5)] * 17, 393216), ([(0, 8)] + [(1, 8)] * 31, 393216),
+    # and those of the general kernel
+    ([(0, 100), (1, 4)], 393216), ([(0, 32)] * 2 + [(1, 3)] * 2, 655360), ([(0, 32)] * 5, 786432), ([(0, 16)] * 8 + [(1, 4)] * 7 + [(1, 2)], 917504),
+    ([(0, 8)] + [(1, 8)] * 30 + [(1, 2)], 786432)])
 def test_longest_vector_of_the_short_chain_kernel(recorder, plan, most):
     workers = [{"codes": 0x20000000, "steps": 0x30000000, "kind": kind, "levels_or_M": arg, "alpha": 1.0,
                 "dither": [1, 2, 3, 0]} for kind, arg in plan]
@@ -177,3 +182,14 @@ def test_launches_of_the_entropy(recorder, bits, n, kernels, grid):
     (rc, launches), = lr.record(recorder, [["ndq_code_entropy", 0x10000000, n, bits, 0x20000000, 0x30000000, None]])
     assert rc == 0 and len(launches) == kernels and launches[-1][1] == grid, launches
     assert kernels == 1 or "clear_histogram" in launches[0][0]
+
+
+@pytest.mark.parametrize("plan,bucket", [([(0, 8), (1, 4)], 0), ([(0, 5)] * 4 + [(1, 3)] * 4, 0), ([(0, 16)] * 8 + [(1, 8)] * 8, 1024),
+                                         ([(0, 16)] * 2 + [(1, 4)] * 2, 512), ([(0, 8)] * 5, 512), ([(0, 16)] + [(1, 7)], 512)])
+def test_a_streaming_threshold_from_the_environment_reaches_the_persistent_chain_decoder(recorder, plan, bucket):
+    workers = [{"codes": 0x20000000, "steps": 0x30000000, "kind": kind, "levels_or_M": arg, "alpha": 1.0, "dither": [1, 2, 3, 0]}
+               for kind, arg in plan]
+    calls = [["ndq_decode_chain", workers, len(workers), n, bucket, 1.0, 0x40000000, None] for n in (1025, 12 * 1024, 40 * 1024 + 7)]
+    for rc, launches in lr.record(recorder, calls, {"NDQ_STREAM_MIN_TILES_PER_WAVE": "0", "NDQ_STREAM_MAX_BLOCKS": "3"}):
+        assert rc == 0 and len(launches) == 1 and launches[0][1] <= 3, launches
+        assert "chain_stream_kernel" in launches[0][0] and launches[0][0].endswith("ELi0EEEvNS_9ChainArgsE"), launches
