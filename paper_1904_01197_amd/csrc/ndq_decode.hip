@@ -497,9 +497,10 @@ __global__ __launch_bounds__(kBlock) void chain_short_kernel(GeneralChainArgs by
             if (w == 0u) short_fold<kDq, true>(side, qp, c_f, v, step, inv, S);
             else short_fold<kDq, false>(side, qp, c_f, v, step, inv, S);
         } else {
+            // (shrinking workers of any ratio together, the corrected quotient of a power of two being the product itself: with a
+            // branch more the compiler sends the common case through two further jumps per worker)
             const float c_f[2] = {(float)c0, (float)c1};
             if (mode == kNestedPow2) short_fold<kNestedPow2, false>(side, qp, c_f, v, step, inv, S);
-            else if (mode == kNestedPow2Shrink) short_fold<kNestedPow2Shrink, false>(side, qp, c_f, v, step, inv, S);
             else short_fold<kNestedAnyM, false>(side, qp, c_f, v, step, inv, S);
         }
     }
