@@ -56,6 +56,8 @@ def _tiles_from(plan):
 
 
 ROWS = [513, 512 * 2, 512 * 9 + 1, 512 * 40 - 1, 1024 * 15 + 8, 1024 * 33 + 512] + _tight(530) + _tight(1024 * 8)
+# (up to 786,432 elements several workers are the kernel for short chains': rows of them from there on)
+LONG_ROWS = [1024 * 772 + 513, 1024 * 772 + 512 * 9 + 8] + _tight(1024 * 773 + 530)
 TILES = [1024 * 12, 1024 * 40, 1024 * 37 + 100, 1024 * 3 + 8, 1024 * 13 + 1, 1024 * 24 + 1023, 1025] + _tight(1024 * 14) + _tight(1024 * 25 + 640)
 
 
@@ -96,8 +98,9 @@ def _sweep(sizes):
 def test_rows_and_tiles_match_oracle(name):
     plan = PLANS[name]
     long = 1024 * _tiles_from(plan)
-    for n, bucket in [(n, b) for n in ROWS for b in (0, 1024)] + [(long - 1, 0), (long, 0), (long + 1, 2048), (long + 4 * 1024 + 700, 0)] + [
-            (n, 0) for n in _tight(long + 300)]:
+    rows = ROWS + (LONG_ROWS if len(plan) > 1 else [])
+    for n, bucket in [(n, b) for n in rows for b in (0, 1024)] + [(long - 1, 0), (long, 0), (long + 1, 2048), (long + 4 * 1024 + 700, 0)] + [
+            (n, 0) for n in _tight(long + 300)[:1 if len(plan) > 8 else 2]]:
         _check(plan, n, bucket, 8 * (n % 129), 1.0 / len(plan))
 
 
@@ -105,8 +108,21 @@ def test_rows_and_tiles_match_oracle(name):
 @pytest.mark.parametrize("name", list(ROW_PLANS))
 def test_buckets_of_a_row_match_oracle(name):
     plan = ROW_PLANS[name]
-    for n in ROWS + [1024 * 2048 - 1, 1024 * 2048 + 513, 1024 * 2100]:
+    rows = ROWS + (LONG_ROWS if len(plan) > 1 else [])
+    for n in rows + [1024 * 2048 - 1, 1024 * 2048 + 513, 1024 * 2100]:
         _check(plan, n, 512, 8 * (n % 129), 1.0 / len(plan))
+
+
+# DQSG and nested workers, 3-bit codes up to the stream's last byte, a ratio that is no power of two, a step per row
+@pytest.mark.gpu
+@pytest.mark.parametrize("plan,tiles,bucket", [
+    ([(DQ, 16)] * 2 + [(NESTED, 4)], 10240, 4096), ([(DQ, 8), (NESTED, 2)], 10240, 0), ([(DQ, 8), (DQ, 5)] * 4, 2048, 2048),
+    ([(DQ, 3)] + [(NESTED, 3)] * 7, 2048, 1024), ([(DQ, 5)] * 2 + [(NESTED, 3)], 10240, 0),
+    ([(DQ, 4), (NESTED, 2)], 8192, 512), ([(DQ, 16)] * 2, 8192, 512), ([(DQ, 5), (NESTED, 3)], 8192, 512), ([(DQ, 8)] * 2 + [(NESTED, 8)], 8192, 512)])
+def test_persistent_form_matches_oracle_on_its_own_grid(plan, tiles, bucket):
+    for n in (1024 * tiles, _tight(1024 * tiles + 530)[0]):
+        print(plan, n, bucket, flush=True)
+        _check(plan, n, bucket, 8 * (n % 129), 1.0 / len(plan))
 
 
 @pytest.mark.gpu
