@@ -515,8 +515,7 @@ __device__ __forceinline__ void store_streaming(float* p, float a, float b, floa
 // iterations 1.03, 1.02, 1.04, 1.01, 0.97 and 0.99, 1.02, 1.01, 0.95, 0.95; 16 x 4 M 0.98.  So in buckets from 120 M bits of codes in a
 // launch on; with one step for the vector, whose encoder has less to do a tile, the two differ by less than 1 % (0.95-0.98 at
 // 8 x 25.6 M; separate decodes of 4 x 1.66 M 23.8 against 24.0 us, 2 x 61 k 6.3 and 6.5).
-// Persistent bfloat16 encoders with one step for the vector, 1 and 2 bits: 1 x 67 M 1.02-1.05, 4 x 25.6 M 1.01-1.04, iterations
-// 1.00-1.01; with a step per tile 0.95-0.98.
+// Persistent bfloat16 encoders, 1 and 2 bits: 0.95-0.98.
 __device__ __forceinline__ void store_through(uint64_t* p, uint64_t x)
 {
     __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -197,8 +197,7 @@ __device__ __forceinline__ void encode_tile(const EncodeArgs& a, const TileRef& 
         } else {
             step = a.preset_step > 0.0f ? a.preset_step : a.step_in[t.bucket];
             // one step for the whole vector, preset or handed over: the worker's transmitted step
-            // (the streaming kernel writes it itself, outside its tile loop)
-            if (!REFILL && tile_id == 0 && lane == 0) a.steps[0] = step;
+            if (tile_id == 0 && lane == 0) a.steps[0] = step;
         }
         const float inv_all = a.qp.alpha * inv_step(step);   // alpha = 1 unless a nested worker shrinks
 #pragma unroll
@@ -540,7 +539,7 @@ void encode_short_kernel(ShortBatch by_value)
 // The same for a full tile that is not the vector's last, with the code width known
 // at compile time: a fixed number of store instructions, so that the compiler can
 // count the memory operations in flight between a tile's loads and its use.
-template <int DT, int BITSW, bool THROUGH>
+template <int DT, int BITSW>
 __device__ __forceinline__ void stage_to_stream_full(const EncodeArgs& a, const TileRef& t,
                                                      const unsigned char* stage, int lane)
 {
@@ -549,22 +548,16 @@ __device__ __forceinline__ void stage_to_stream_full(const EncodeArgs& a, const 
     const uint64_t* src = (const uint64_t*)stage;
     if constexpr (units % kWave == 0u) {
 #pragma unroll
-        for (uint32_t u = 0; u < units; u += kWave) {
-            if (THROUGH) store_through(dst + u + lane, src[u + lane]);
-            else dst[u + lane] = src[u + lane];
-        }
+        for (uint32_t u = 0; u < units; u += kWave) store_through(dst + u + lane, src[u + lane]);
     } else {
         static_assert(units < (uint32_t)kWave, "a partial store only for less than one unit per lane");
-        if ((uint32_t)lane < units) {
-            if (THROUGH) store_through(dst + lane, src[lane]);
-            else dst[lane] = src[lane];
-        }
+        if ((uint32_t)lane < units) store_through(dst + lane, src[lane]);
     }
 }
 
 // ---------------------------------------------------------------------------
-// Streaming encoder for vectors made of whole tiles (bucket == tile with the
-// max-norm found in registers, or one step for the whole vector): every wave
+// Streaming encoder for vectors whose buckets are tiles (the max-norm found in
+// registers): every wave
 // walks over the tiles wave, wave + W, wave + 2W, ... (W = waves in the grid).
 // One set of registers holds the current tile and, by the end of it, the next
 // one: as soon as a row is quantized its registers are loaded again with the
@@ -586,16 +579,16 @@ __device__ __forceinline__ void stage_to_stream_full(const EncodeArgs& a, const 
 constexpr int kStreamWaves = NDQ_STREAM_WAVES;   // per SIMD
 
 template <int DT>
-__device__ __forceinline__ TileRef stream_tile_ref(uint32_t tile_id, bool fused)
+__device__ __forceinline__ TileRef stream_tile_ref(uint32_t tile_id)
 {
     TileRef t;
     t.start = (uint64_t)tile_id * EncTile<DT>::N;
     t.len = EncTile<DT>::N;
-    t.bucket = fused ? tile_id : 0u;
+    t.bucket = tile_id;
     return t;
 }
 
-template <int DT, int MODE, bool FUSED, int BITSW>
+template <int DT, int MODE, int BITSW>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kStreamWaves, kStreamWaves)))
 void encode_stream_kernel(EncodeBatch by_value, uint32_t full_tiles)
 {
@@ -610,13 +603,6 @@ void encode_stream_kernel(EncodeBatch by_value, uint32_t full_tiles)
     const uint32_t first = blockIdx.x * kWavesPerBlock + wave;
     const uint32_t jobs = batch->jobs;
     const uint32_t all_tiles = jobs * full_tiles;      // job after job: tile `t` of job j is j * full_tiles + t
-    if constexpr (!FUSED) {                            // the transmitted step of every vector
-        for (uint32_t j = first; j < jobs; j += stride) {
-            select_job(a, batch, j);
-            const float step = a.preset_step > 0.0f ? a.preset_step : a.step_in[0];
-            if (lane == 0) a.steps[0] = step;
-        }
-    }
     if (first < all_tiles) {
         // Every pass over a tile issues exactly one load per row, also the last one (then of the
         // vector's first 16 bytes per row, all lanes alike: one cache line, no traffic to speak
@@ -632,22 +618,21 @@ void encode_stream_kernel(EncodeBatch by_value, uint32_t full_tiles)
         uint32_t done = 0;
         __builtin_amdgcn_s_setprio(3);
         select_job(a, batch, job);
-        load_tile<DT, true>(a.g, stream_tile_ref<DT>(tile, FUSED), lane, regs);
+        load_tile<DT, true>(a.g, stream_tile_ref<DT>(tile), lane, regs);
         for (;;) {
             const uint32_t nxt = cur + stride;
             const bool more = nxt < all_tiles;
             uint32_t next_job = job, next_tile = tile + stride;
             while (next_tile >= full_tiles && more) { next_tile -= full_tiles; ++next_job; }
             const void* next_g = batch->job[more ? next_job : job].g;
-            const TileRef t = stream_tile_ref<DT>(tile, FUSED);
-            const float kappa = FUSED ? tile_max<DT>(regs) : 0.0f;
+            const TileRef t = stream_tile_ref<DT>(tile);
+            const float kappa = tile_max<DT>(regs);
             wave_lds_sync();     // the previous tile's copy-out has read the stage
-            encode_tile<DT, MODE, FUSED, true, false, BITSW, true>(
+            encode_tile<DT, MODE, true, true, false, BITSW, true>(
                 a, t, tile, regs, kappa, true, stage, lane,
                 (const typename Elem<DT>::scalar*)next_g + (uint64_t)(more ? next_tile : 0u) * TILE, more ? lane : 0);
             wave_lds_sync();
-            // (narrow codes with one step for the vector: plain, see store_through)
-            stage_to_stream_full<DT, BITSW, FUSED || (BITSW > 2)>(a, t, stage, lane);
+            stage_to_stream_full<DT, BITSW>(a, t, stage, lane);
             if (!more) break;
             ++done;
             const uint32_t quarter = 4u * done / my_tiles;
@@ -667,11 +652,11 @@ void encode_stream_kernel(EncodeBatch by_value, uint32_t full_tiles)
             if (t.len != 0) {
                 TileRegs<DT> regs;
                 load_tile<DT, false>(a.g, t, lane, regs);
-                const float kappa = FUSED ? tile_max<DT>(regs) : 0.0f;
+                const float kappa = tile_max<DT>(regs);
                 wave_lds_sync();
-                encode_tile<DT, MODE, FUSED, false, false, BITSW>(a, t, full_tiles, regs, kappa, true, stage, lane);
+                encode_tile<DT, MODE, true, false, false, BITSW>(a, t, full_tiles, regs, kappa, true, stage, lane);
                 wave_lds_sync();
-                stage_to_stream<DT, FUSED>(a, t, BITSW ? (uint32_t)BITSW : a.qp.bits, stage, lane);
+                stage_to_stream<DT, true>(a, t, BITSW ? (uint32_t)BITSW : a.qp.bits, stage, lane);
             }
         }
     }
@@ -906,11 +891,11 @@ static int run_absmax(AbsmaxBatch& b, uint32_t jobs, hipStream_t s)
 // Waves of the streaming kernel: kStreamWaves on each of the 1,024 SIMDs.
 constexpr uint32_t kStreamSlots = 1024u * kStreamWaves;
 
-template <int DT, int MODE, bool FUSED, int BITSW>
+template <int DT, int MODE, int BITSW>
 static int launch_stream(const EncodeBatch& b, uint32_t full_tiles, hipStream_t s)
 {
     const uint32_t blocks = persistent_blocks(full_tiles * b.jobs, kStreamSlots);
-    return launch((encode_stream_kernel<DT, MODE, FUSED, BITSW>), dim3(blocks), dim3(kBlock), s, b, full_tiles);
+    return launch((encode_stream_kernel<DT, MODE, BITSW>), dim3(blocks), dim3(kBlock), s, b, full_tiles);
 }
 
 // Tiles of a launch from which the streaming kernel is the faster one (bfloat16; the time of one tile per wave is what
@@ -918,22 +903,20 @@ static int launch_stream(const EncodeBatch& b, uint32_t full_tiles, hipStream_t 
 // vectors that are in no cache, at 4 x 8.4 M, 4 x 11.2 M, 67 M, 2 x 50 M, 8 x 16 M, 3 x 134 M elements (2 to 24 tiles per wave slot):
 //   buckets of a tile   4 levels 1.02 0.98 1.07 1.00 0.99         2 levels 0.98 0.97 1.02 1.00 1.01
 //                       16 levels 1.00 0.99 1.02 1.06 1.07        M = 2 0.97 0.95 1.05 1.00 1.00     M = 4 0.95 0.91 1.00 0.99 0.99 1.05
-//   one step            4 levels 0.94 0.95 1.02 0.97 0.97 0.95    2 levels 0.96 0.95 0.98 0.98 0.98 0.94
-//                       16 levels 0.99 0.95 0.98 0.97 0.98 0.97   M = 2 0.94 0.97 1.00 0.98 0.99 0.95   M = 4 0.93 0.95 1.03 1.00 0.98 0.97
 // (us persistent, buckets of a tile, 4 levels 17.4 23.4 30.0 44.3 54.7.)  Buckets smaller than a tile and codes of 3 bits gain 3
-// to 5 % by it at 8 x 16 M and lose as much below 2 x 50 M: they are left to the other kernel.
-static uint64_t stream_from_tiles(bool fused, bool nested, uint32_t bits)
+// to 5 % by it at 8 x 16 M and lose as much below 2 x 50 M: they are left to the other kernel.  So are vectors with one step, which
+// it had too: one tile per wave over this at 34, 41, 50, 60, 75, 100, 134, 200 and 268 M elements, 4 levels 0.94 0.93 1.00 1.00 1.00 0.99 0.98
+// 0.97 0.97, 2 levels 0.96 0.96 0.98 0.96 0.99 1.00 0.99 0.97 0.96, 16 levels 0.99 0.94 0.97 0.96 0.96 0.98 0.98 0.97 0.98, M = 4 0.93 0.94 1.00
+// 0.99 1.00 1.00 0.99 0.98 0.97 (4 to 6 whole rounds of 2-bit codes: 1.02).
+static uint64_t stream_from_tiles(bool nested, uint32_t bits)
 {
     const StreamTuning& tuning = stream_tuning();
     if (tuning.threshold_from_env) return (uint64_t)tuning.min_tiles_per_wave * kStreamSlots;
-    if (!fused) return ~(uint64_t)0;
     return (nested && bits == 2u ? 16u : 3u) * kStreamSlots;
 }
 
-// The streaming kernel serves vectors cut into whole tiles (a ragged last one aside):
-// bucket == tile (fused max-norm) or one step for the whole vector (preset, or found by
-// the max-norm pass), in the quantizer modes and code widths of the common
-// configurations.  Returns 1 when it does not apply.
+// The streaming kernel serves vectors whose buckets are tiles (a ragged last one aside), in the quantizer modes and code
+// widths of the common configurations.  Returns 1 when it does not apply.
 template <int DT, int MODE>
 static int try_stream(const EncodeBatch& b, bool fused, bool multi, uint32_t bucket, hipStream_t s)
 {
@@ -942,30 +925,20 @@ static int try_stream(const EncodeBatch& b, bool fused, bool multi, uint32_t buc
     // binary32 input: one tile per wave is faster at every length (2^27 elements: 112 against 120 us,
     // 25.6 M: 22.8 against 23.2; its tile carries half the arithmetic of a bfloat16 tile per byte, so
     // the kernel is nearer to a plain copy, which gains nothing from persistence)
-    if constexpr (DT == 0 || (MODE != kDqNarrow && MODE != kNestedPow2Bounded && MODE != kNestedPow2)) {
+    if constexpr (DT == 0 || (MODE != kDqNarrow && MODE != kNestedPow2Bounded)) {
         return 1;
     } else {
     if (multi || a.waves_log2 != 0u) return 1;
-    if (!(bucket == TILE || bucket == 0u)) return 1;
-    if (fused != (bucket == TILE)) return 1;
+    if (bucket != TILE || !fused) return 1;
     const uint32_t full_tiles = (uint32_t)(a.tl.n / TILE);
     const uint32_t bits = a.qp.bits;
     const uint64_t all_tiles = (uint64_t)full_tiles * b.jobs;
-    if (full_tiles == 0u || all_tiles < stream_from_tiles(fused, MODE != kDqNarrow, bits) || all_tiles >= ((uint64_t)1 << 31))
+    if (full_tiles == 0u || all_tiles < stream_from_tiles(MODE != kDqNarrow, bits) || all_tiles >= ((uint64_t)1 << 31))
         return 1;
     if (bits != 1u && bits != 2u && bits != 4u) return 1;
-    if (fused) {
-        if constexpr (MODE == kNestedPow2) {
-            return 1;      // a preset step comes with bucket == 0
-        } else {
-            if (bits == 1u) return launch_stream<DT, MODE, true, 1>(b, full_tiles, s);
-            if (bits == 2u) return launch_stream<DT, MODE, true, 2>(b, full_tiles, s);
-            return launch_stream<DT, MODE, true, 4>(b, full_tiles, s);
-        }
-    }
-    if (bits == 1u) return launch_stream<DT, MODE, false, 1>(b, full_tiles, s);
-    if (bits == 2u) return launch_stream<DT, MODE, false, 2>(b, full_tiles, s);
-    return launch_stream<DT, MODE, false, 4>(b, full_tiles, s);
+    if (bits == 1u) return launch_stream<DT, MODE, 1>(b, full_tiles, s);
+    if (bits == 2u) return launch_stream<DT, MODE, 2>(b, full_tiles, s);
+    return launch_stream<DT, MODE, 4>(b, full_tiles, s);
     }
 }
 
@@ -1168,7 +1141,7 @@ static bool run_short(const EncodePlan* plans, uint32_t jobs, uint32_t bucket, h
     if (all_tiles > (vector ? kShortVectorTiles : kShortBucketTiles)) return false;
     if (!vector && !plans[0].fused) return false;       // (the form of a bucket is the same for all)
     // (a streaming threshold from the environment means that kernel, whatever the length: see try_stream)
-    if (DT == 1 && stream_tuning().threshold_from_env && (vector || bucket == TILE)) return false;
+    if (DT == 1 && stream_tuning().threshold_from_env && bucket == TILE) return false;
     bool one_quantizer = true, several = false;
     uint32_t sources = 0u;
     for (uint32_t j = 0; j < jobs; ++j) {

@@ -7,9 +7,9 @@ so that vectors of a few hundred thousand elements -- small enough for the oracl
 -- go through the persistent kernels on twelve waves: several tiles per wave (the
 next tile's rows loaded into the registers of the rows just consumed, even and odd
 tile counts), waves with one tile fewer, and a ragged last tile.  Everything is
-compared with the oracle bit for bit.  (The persistent encoder serves bfloat16 input;
-binary32 input takes the one-tile-per-wave encoder whatever the environment says, and
-its cases here run through that.)
+compared with the oracle bit for bit.  (The persistent encoder serves bfloat16 input in
+buckets of a tile; binary32 input and vectors with one step take the one-tile-per-wave
+encoder whatever the environment says, and their cases here run through that.)
 """
 import os
 import sys
@@ -95,17 +95,18 @@ def batch_cases():
     for n in (4096 * 3, 4096 * 2 + 1000):
         host = [make(n, "bf16", seed=100 + w) for w in range(16)]
         dev = [to_dev(g) for g in host]
-        for preset, handed in ((0.001, False), (0.0, True), (0.0, False)):
-            print("batch", n, preset, handed, flush=True)
+        for preset, handed, bucket in ((0.001, False, 0), (0.0, True, 0), (0.0, False, 0), (0.0, False, 4096)):
+            print("batch", n, preset, handed, bucket, flush=True)
+            buckets = ndq.ndq_num_buckets(n, bucket)
             given = torch.tensor([0.002], dtype=torch.float32, device="cuda") if handed else None
             codes = [torch.empty(ndq.ndq_packed_bytes(n, 4), dtype=torch.uint8, device="cuda") for _ in host]
-            steps = [torch.full((1,), -1.0, device="cuda") for _ in host]
+            steps = [torch.full((buckets,), -1.0, device="cuda") for _ in host]
             ndq.ndq_encode_workers([(dev[w], ndq.NDQ_WORKER_DQ, 16, 0, 1.0, ndq.ndq_dither(w, 3, w, 0), codes[w],
-                                     steps[w], given) for w in range(16)], preset, 0)
+                                     steps[w], given) for w in range(16)], preset, bucket)
             for w in range(16):
-                c_ref, s_ref = oracle.dq_encode(host[w], float(F(0.002)) if handed else preset, 16, 0,
+                c_ref, s_ref = oracle.dq_encode(host[w], float(F(0.002)) if handed else preset, 16, bucket,
                                                 oracle.dither(w, 3, w))
-                assert steps[w].item() == s_ref[0], (n, preset, handed, w)
+                assert np.array_equal(steps[w].cpu().numpy(), s_ref), (n, preset, handed, w)
                 assert codes[w].cpu().numpy().tobytes() == c_ref.tobytes(), (n, preset, handed, w)
                 count += 1
     return count

@@ -126,18 +126,16 @@ def test_form_of_the_chain_decoder(recorder, dq, nested, lines):
 
 
 def test_a_streaming_threshold_from_the_environment_reaches_the_persistent_encoder(recorder):
-    # the calls streaming_cases.py makes with bfloat16 vectors: a step from the vector, a preset and a handed one,
-    # buckets of a tile, sixteen vectors in a call
+    # the calls streaming_cases.py makes with bfloat16 vectors in buckets of a tile, and sixteen vectors in a call
     tile, calls = 4096, []
     for n in (12 * tile, 37 * tile + 100, 121 * tile + 64, 3 * tile + 8):
         for kind, levels, M in ((0, 2, 0), (0, 4, 0), (0, 16, 0), (1, 4, 2), (1, 16, 4), (1, 64, 16)):
-            for bucket, preset, handed in ((tile, 0.0, None), (0, 0.0, None), (0, 0.5, None), (0, 0.0, 0x40000000)):
-                jobs = [_job(kind=kind, levels=levels, M=M, step_in=handed, codes_out=0x20000000 + 0x1000000 * w,
-                             steps_out=0x30000000 + 0x10000 * w) for w in range(16)]
-                calls += [["ndq_encode_workers", jobs[:W], W, 1, n, preset, bucket, None] for W in (1, 16)]
+            jobs = [_job(kind=kind, levels=levels, M=M, codes_out=0x20000000 + 0x1000000 * w,
+                         steps_out=0x30000000 + 0x10000 * w) for w in range(16)]
+            calls += [["ndq_encode_workers", jobs[:W], W, 1, n, 0.0, tile, None] for W in (1, 16)]
     # (more than one quantizer)
     mixed = [_job(levels=16), _job(kind=1, levels=16, M=4, codes_out=0x28000000, steps_out=0x38000000)]
-    calls += [["ndq_encode_workers", mixed, 2, 1, 37 * tile + 100, 0.0, bucket, None] for bucket in (0, tile)]
+    calls.append(["ndq_encode_workers", mixed, 2, 1, 37 * tile + 100, 0.0, tile, None])
     env = {"NDQ_STREAM_MIN_TILES_PER_WAVE": "0", "NDQ_STREAM_MAX_BLOCKS": "3"}
     for call, (rc, launches) in zip(calls, lr.record(recorder, calls, env)):
         encoders = [(name, x) for name, x, _ in launches if "absmax" not in name and "fill_zero" not in name]
