@@ -22,13 +22,14 @@
  *     checked before anything is launched: with NDQ_EINVAL, NDQ_EALIGN or
  *     NDQ_EUNSUPPORTED nothing has been enqueued.  NDQ_ELAUNCH comes from the
  *     runtime's launch call itself; calls made of several kernels (a max-norm
- *     pass before the encoder, ndq_absmax, ndq_encode_workers, ndq_code_entropy, ndq_sqdiff, more than
- *     32 workers in ndq_decode_chain / ndq_decode_mean / ndq_aggregate) may then already have enqueued
+ *     pass before the encoder, ndq_absmax, ndq_encode_workers, ndq_code_entropy of a long stream or without an
+ *     entropy, more than 32 workers in ndq_decode_chain / ndq_decode_mean / ndq_aggregate) may then already have enqueued
  *     their first kernels, and the outputs are unspecified.  n == 0 is a successful no-op.
  *   - g, codes, out and side must be 16-byte aligned; steps 4-byte aligned.
  *     bucket must be 0 or a multiple of 64; d->offset a multiple of 8 (and of
  *     bucket when a slice of a bucketed vector is processed).
- *   - Inputs must be finite; this is not checked.
+ *   - Inputs must be finite; this is not checked.  A running sum beyond binary32 becomes
+ *     an infinity or NaN, the same one whichever kernels a call is made of.
  *   - No global state: calls are thread-safe.  Calls that write the same buffers
  *     on different streams race.
  *

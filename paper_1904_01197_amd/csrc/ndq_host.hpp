@@ -80,8 +80,9 @@ inline DitherStream make_stream(const ndq_dither* d)
 }
 
 // 64 bits that no other call of the process has, and nothing else is likely to hold: a call's workgroups mark with them
-// what they leave in memory that nobody has cleared (the multiplications and shifts are invertible, so distinct
-// counts give distinct tags).  A call recorded in a graph keeps its tag: its marks are gone when it ends.
+// what they leave in memory that nobody has cleared (a count of the calls through the mixing function of splitmix64, Steele,
+// Lea and Flood 2014, which is invertible, so distinct counts give distinct tags; the calls that take one fix 2 or 17 of its
+// bits).  A call recorded in a graph keeps its tag: its marks are gone when it ends.
 inline uint64_t call_tag()
 {
     static std::atomic<uint64_t> calls{(uint64_t)std::chrono::steady_clock::now().time_since_epoch().count() << 20};
