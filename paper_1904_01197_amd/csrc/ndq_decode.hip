@@ -146,8 +146,8 @@ __global__ __launch_bounds__(kBlock) void decode_kernel(DecodeArgs a)
 // A worker after the other, a short launch waits for each cache line of its arguments: all its waves read a line for the
 // first time at the same moment, and the L2 has none of them yet.  So every lane first reads a word of a line of its own,
 // which brings the first `bytes` (at most 4,096) into the L2 side by side; nobody waits for it until arguments_read(),
-// after the first worker or the last (a test for the first one inside the loop makes the compiler take the loop apart: decode_mean_kernel,
-// 12 to 32 workers, 2 to 5 % slower at 0.6, 1.7 and 2.5 M elements).  us without / with it at 0.3, 0.5 and 1.05 M elements: chain_stream_kernel, one row per wave, 2 x 16 levels
+// after the first worker, or the last: a test for the first one inside the loop makes the compiler take the loop apart, which
+// chain_kernel gains from (4 x 32 levels 4 to 14 M elements 1 to 4 %) and decode_mean_kernel loses by (12 to 32 workers, 0.6, 1.7 and 2.5 M, 2 to 5 %).  us without / with it at 0.3, 0.5 and 1.05 M elements: chain_stream_kernel, one row per wave, 2 x 16 levels
 // 3.50/3.30 3.70/3.52 4.21/4.01, 8 x 16 levels 6.42/5.62 6.65/5.87 7.20/6.72, 16 levels and 15 x M = 4 at 0.5 M 12.5/10.5; chain_kernel,
 // 8 x 100 levels, at 1.05 and 2 M 10.1/8.9 11.7/11.0; decode_mean_kernel, 4 workers, at 0.06, 0.27 and 1.66 M 5.9/5.3 6.3/5.7 10.7/10.5,
 // 16 workers 17.7/15.3 18.5/16.9 29.8/29.7.
@@ -338,9 +338,9 @@ __device__ __forceinline__ void chain_tile(const GeneralChainArgs& a, const Tile
         } else {
             chain_fold_width<kNestedAnyM, false, ROWB, ROWS>(cw, cur, block0, lane, S);
         }
+        if (w == 0u) arguments_read(warm);
         cur = nxt;
     }
-    arguments_read(warm);
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) {
         const uint32_t o = (uint32_t)(r * kWave + lane) * kLaneElems;
