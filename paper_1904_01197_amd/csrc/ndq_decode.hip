@@ -307,7 +307,7 @@ __device__ __forceinline__ void chain_fold_width(const ChainWorker& cw, const Ch
     else chain_fold<MODE, false, FIRST, ROWB, ROWS>(cw, f, block0, lane, S);
 }
 
-template <bool FULL, bool ROWB, int ROWS>
+template <bool FULL, bool ROWB, bool ANYM, int ROWS>
 __device__ __forceinline__ void chain_tile(const GeneralChainArgs& a, const TileRef& t, int lane, uint32_t warm)
 {
     float S[ROWS][8];
@@ -335,7 +335,7 @@ __device__ __forceinline__ void chain_tile(const GeneralChainArgs& a, const Tile
             chain_fold_width<kNestedPow2, false, ROWB, ROWS>(cw, cur, block0, lane, S);
         } else if (cw.mode == kNestedPow2Shrink) {
             chain_fold_width<kNestedPow2Shrink, false, ROWB, ROWS>(cw, cur, block0, lane, S);
-        } else {
+        } else if (ANYM) {
             chain_fold_width<kNestedAnyM, false, ROWB, ROWS>(cw, cur, block0, lane, S);
         }
         if (w == 0u) arguments_read(warm);
@@ -363,7 +363,11 @@ __device__ __forceinline__ void chain_tile(const GeneralChainArgs& a, const Tile
 #ifndef NDQ_CHAIN_WAVES_PER_EU
 #define NDQ_CHAIN_WAVES_PER_EU 6
 #endif
-template <bool ROWB, int ROWS>
+// ANYM: has the code for ratios that are no powers of two.  Plans without such a ratio take the kernel with it too, but for two
+// workers that do not shrink, in tiles of two rows: 2 x 32 and 2 x 100 levels at 5.3, 6.6, 8.4 and 14 M elements 8.2/7.8 10.5/9.3 12.9/12.2
+// 19.2/17.9 and 8.0/7.8 9.5/9.0 12.8/11.8 18.2/16.9 with / without, but 4 x 32 levels 11.4/12.3 12.6/13.7 15.6/16.9 22.8/25.1, 16 levels and a
+// shrinking M = 4 7.9/8.0 9.2/9.4 11.5/11.7 17.0/17.2.
+template <bool ROWB, bool ANYM, int ROWS>
 __global__ __launch_bounds__(kBlock)
 __attribute__((amdgpu_waves_per_eu(NDQ_CHAIN_WAVES_PER_EU)))
 void chain_kernel(GeneralChainArgs a)
@@ -377,8 +381,8 @@ void chain_kernel(GeneralChainArgs a)
     if (a.W > 1u)
         warm = read_arguments_ahead((const __attribute__((address_space(4))) void*)__builtin_amdgcn_kernarg_segment_ptr(),
                                     a.W * (uint32_t)sizeof(ChainWorker), lane);
-    if (t.len == TILE && t.start + TILE + 64u <= a.tl.n) chain_tile<true, ROWB, ROWS>(a, t, lane, warm);
-    else if (t.len != 0) chain_tile<false, ROWB, ROWS>(a, t, lane, warm);
+    if (t.len == TILE && t.start + TILE + 64u <= a.tl.n) chain_tile<true, ROWB, ANYM, ROWS>(a, t, lane, warm);
+    else if (t.len != 0) chain_tile<false, ROWB, ANYM, ROWS>(a, t, lane, warm);
 }
 
 // ---------------------------------------------------------------------------
@@ -1934,9 +1938,12 @@ int ndq_decode_chain(const ndq_worker* workers, uint32_t W, size_t n, uint32_t b
             a.row_buckets = 0u;
         }
         const dim3 grid(blocks_for(a.tl.total_tiles)), block(kBlock);
-        const int rc_launch = short_vector ? launch((chain_kernel<false, 1>), grid, block, hs, a)
-                              : a.row_buckets ? launch((chain_kernel<true, kChainRows>), grid, block, hs, a)
-                                              : launch((chain_kernel<false, kChainRows>), grid, block, hs, a);
+        const bool two_workers = a.W == 2u && (a.w[1].mode == kDq || a.w[1].mode == kNestedPow2);      // (see chain_kernel)
+        const int rc_launch = short_vector ? launch((chain_kernel<false, true, 1>), grid, block, hs, a)
+                              : a.row_buckets && two_workers ? launch((chain_kernel<true, false, kChainRows>), grid, block, hs, a)
+                              : a.row_buckets ? launch((chain_kernel<true, true, kChainRows>), grid, block, hs, a)
+                              : two_workers ? launch((chain_kernel<false, false, kChainRows>), grid, block, hs, a)
+                                            : launch((chain_kernel<false, true, kChainRows>), grid, block, hs, a);
         if (rc_launch != NDQ_OK) return NDQ_ELAUNCH;
     }
     return NDQ_OK;

@@ -85,6 +85,9 @@ def test_short_vectors_take_one_row_per_wave(plan, fine, bucket):
     ((("dq", 8),), 8, 0, (1, 7, 8, 63, 511, 513, 520, 575, 1089)), ((("dq", 32),), 32, 0, (1, 7, 8, 63, 511, 513, 520, 575, 1089)),
     ((("dq", 64),), 64, 0, (1, 7, 8, 63, 511, 513, 520, 575, 1089)), ((("dq", 128),), 128, 0, (1, 7, 8, 63, 511, 513, 520, 575, 1089)),
     ((("dq", 256),), 256, 0, (1, 7, 8, 63, 511, 513, 520, 575, 1089)),
+    # the general kernel's form for two workers in tiles of two rows, whole and ragged
+    ((("dq", 32),) * 2, 32, 0, (1024 * 4200, 1024 * 4200 + 517)), ((("dq", 32),) * 2, 32, 512, (1024 * 4200, 1024 * 4200 + 517)),
+    ((("dq", 100), ("nested", 64)), 100, 3072, (1024 * 4203, 1024 * 4200 + 8)),
     # (3-bit codes are the general kernel's where buckets are neither rows nor tiles; with one row per wave and with two)
     ((("dq", 8),), 8, 192, (1, 7, 8, 63, 511, 513, 520, 575, 1089, 1024 * 4200 + 3, 1024 * 4200 + 513))])
 def test_few_workers_match_oracle(plan, fine, bucket, sizes):

@@ -191,3 +191,14 @@ def test_a_streaming_threshold_from_the_environment_reaches_the_persistent_chain
     for rc, launches in lr.record(recorder, calls, {"NDQ_STREAM_MIN_TILES_PER_WAVE": "0", "NDQ_STREAM_MAX_BLOCKS": "3"}):
         assert rc == 0 and len(launches) == 1 and launches[0][1] <= 3, launches
         assert "chain_stream_kernel" in launches[0][0] and launches[0][0].endswith("ELi0EEEvNS_9ChainArgsE"), launches
+
+
+@pytest.mark.parametrize("plan,bucket,name", [
+    ([(0, 32)] * 2, 0, "ILb0ELb0ELi2E"), ([(0, 100), (1, 64)], 2048, "ILb0ELb0ELi2E"), ([(0, 32), (1, 32)], 512, "ILb1ELb0ELi2E"),
+    ([(0, 32)] * 3, 512, "ILb1ELb1ELi2E"),
+    ([(0, 32), (1, 3)], 0, "ILb0ELb1ELi2E"), ([(0, 32)] * 3, 0, "ILb0ELb1ELi2E"), ([(0, 32)] * 34, 0, "ILb0ELb1ELi2E")])
+def test_forms_of_the_general_chain_kernel(recorder, plan, bucket, name):
+    workers = [{"codes": 0x20000000, "steps": 0x30000000, "kind": kind, "levels_or_M": arg, "alpha": 1.0, "dither": [1, 2, 3, 0]}
+               for kind, arg in plan]
+    (rc, launches), = lr.record(recorder, [["ndq_decode_chain", workers, len(workers), 6600000, bucket, 1.0, 0x40000000, None]])
+    assert rc == 0 and ("chain_kernel" + name) in launches[0][0], launches
