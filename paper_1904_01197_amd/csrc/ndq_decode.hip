@@ -147,7 +147,7 @@ __global__ __launch_bounds__(kBlock) void decode_kernel(DecodeArgs a)
 // first time at the same moment, and the L2 has none of them yet.  So every lane first reads a word of a line of its own,
 // which brings the first `bytes` (at most 4,096) into the L2 side by side; nobody waits for it until arguments_read(),
 // after the first worker, or the last: a test for the first one inside the loop makes the compiler take the loop apart, which
-// chain_kernel gains from (4 x 32 levels 4 to 14 M elements 1 to 4 %) and decode_mean_kernel loses by (12 to 32 workers, 0.6, 1.7 and 2.5 M, 2 to 5 %).  us without / with it at 0.3, 0.5 and 1.05 M elements: chain_stream_kernel, one row per wave, 2 x 16 levels
+// chain_kernel gains from (4 x 32 levels 4 to 14 M elements 1 to 4 %), and decode_mean_kernel with few workers, but not with many (kMeanFew).  us without / with it at 0.3, 0.5 and 1.05 M elements: chain_stream_kernel, one row per wave, 2 x 16 levels
 // 3.50/3.30 3.70/3.52 4.21/4.01, 8 x 16 levels 6.42/5.62 6.65/5.87 7.20/6.72, 16 levels and 15 x M = 4 at 0.5 M 12.5/10.5; chain_kernel,
 // 8 x 100 levels, at 1.05 and 2 M 10.1/8.9 11.7/11.0; decode_mean_kernel, 4 workers, at 0.06, 0.27 and 1.66 M 5.9/5.3 6.3/5.7 10.7/10.5,
 // 16 workers 17.7/15.3 18.5/16.9 29.8/29.7.
@@ -1295,7 +1295,8 @@ __device__ __forceinline__ void mean_fetch(MeanArgsPtr a, uint32_t w, const Tile
     for (int r = 0; r < MeanSteps<SMALL>::N; ++r) step[r] = a->w[w].steps[bucket[r]];
 }
 
-template <bool FULL, bool SMALL>
+// FEW: see kMeanFew.
+template <bool FULL, bool SMALL, bool FEW>
 __device__ __forceinline__ void mean_tile(MeanArgsPtr a, const TileRef& t, uint32_t tile_id, int lane)
 {
     const uint32_t W = a->W;
@@ -1350,12 +1351,13 @@ __device__ __forceinline__ void mean_tile(MeanArgsPtr a, const TileRef& t, uint3
                     if (o + k < t.len) decoded[o + k] = res[k];
             }
         }
+        if (FEW && w == 0u) arguments_read(warm);
 #pragma unroll
         for (int r = 0; r < kMeanRows; ++r) window[r] = ahead[r];
 #pragma unroll
         for (int r = 0; r < STEPS; ++r) step[r] = step_ahead[r];
     }
-    arguments_read(warm);
+    if (!FEW) arguments_read(warm);
     float* out = a->out + t.start;
     const float scale = a->scale;
     const bool finish = a->finish != 0;
@@ -1375,7 +1377,11 @@ __device__ __forceinline__ void mean_tile(MeanArgsPtr a, const TileRef& t, uint3
     }
 }
 
-template <bool SMALL>
+// Workers up to which the read of the arguments is waited for after the first of them (see read_arguments_ahead).  After the last over this:
+// 2 workers 1.00 to 1.03, 4 0.99 to 1.02 (4 of 3 levels, 1.66 M elements, whole call 22.95 -> 23.10 us), 8 0.98 to 1.05, 12 to 32 0.95 to 1.00.
+constexpr uint32_t kMeanFew = 8;
+
+template <bool SMALL, bool FEW>
 __global__ __launch_bounds__(kBlock) void decode_mean_kernel(MeanArgs by_value)
 {
     const MeanArgsPtr a = (MeanArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
@@ -1384,8 +1390,8 @@ __global__ __launch_bounds__(kBlock) void decode_mean_kernel(MeanArgs by_value)
     const uint32_t tile_id =
         blockIdx.x * kWavesPerBlock + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const TileRef t = locate_tile(tl, tile_id, kMeanTile);
-    if (t.len == kMeanTile) mean_tile<true, SMALL>(a, t, tile_id, lane);
-    else if (t.len != 0) mean_tile<false, SMALL>(a, t, tile_id, lane);
+    if (t.len == kMeanTile) mean_tile<true, SMALL, FEW>(a, t, tile_id, lane);
+    else if (t.len != 0) mean_tile<false, SMALL, FEW>(a, t, tile_id, lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -1850,9 +1856,9 @@ int ndq_decode_mean(const ndq_worker* workers, float* const* decoded, uint32_t W
                       make_stream(&wk.dither), -(int32_t)(wk.levels_or_M / 2u), code_bits(wk.levels_or_M)};
         }
         const dim3 grid(blocks_for(a.tl.total_tiles)), block(kBlock);
-        if ((small ? launch(decode_mean_kernel<true>, grid, block, (hipStream_t)stream, a)
-                   : launch(decode_mean_kernel<false>, grid, block, (hipStream_t)stream, a)) != NDQ_OK)
-            return NDQ_ELAUNCH;
+        auto* kernel = a.W <= kMeanFew ? (small ? decode_mean_kernel<true, true> : decode_mean_kernel<false, true>)
+                                       : (small ? decode_mean_kernel<true, false> : decode_mean_kernel<false, false>);
+        if (launch(kernel, grid, block, (hipStream_t)stream, a) != NDQ_OK) return NDQ_ELAUNCH;
     }
     return NDQ_OK;
 }
