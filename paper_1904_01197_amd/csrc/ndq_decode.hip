@@ -1944,7 +1944,9 @@ int ndq_decode_chain(const ndq_worker* workers, uint32_t W, size_t n, uint32_t b
             a.row_buckets = 0u;
         }
         const dim3 grid(blocks_for(a.tl.total_tiles)), block(kBlock);
-        const bool two_workers = a.W == 2u && (a.w[1].mode == kDq || a.w[1].mode == kNestedPow2);      // (see chain_kernel)
+        // (see chain_kernel; the first worker of a later launch can be any)
+        auto plain = [&](uint32_t j) { return a.w[j].mode == kDq || a.w[j].mode == kNestedPow2; };
+        const bool two_workers = a.W == 2u && plain(0u) && plain(1u);
         const int rc_launch = short_vector ? launch((chain_kernel<false, true, 1>), grid, block, hs, a)
                               : a.row_buckets && two_workers ? launch((chain_kernel<true, false, kChainRows>), grid, block, hs, a)
                               : a.row_buckets ? launch((chain_kernel<true, true, kChainRows>), grid, block, hs, a)

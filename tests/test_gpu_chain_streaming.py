@@ -109,3 +109,26 @@ def test_one_tile_forms_of_every_pair_of_widths_match_oracle(kind, first, other)
 def test_buckets_of_a_row_with_a_ratio_that_is_no_power_of_two():
     n = 2050 * 1024 + 77
     _check((("dq", 4), ("nested", 3)), 4, 512, _gradients(2, n, 5), 8, 0.5)
+
+
+@pytest.mark.parametrize("last", [[(ndq.NDQ_WORKER_NESTED, 3, 1.0), (ndq.NDQ_WORKER_DQ, 32, 1.0)], [(ndq.NDQ_WORKER_NESTED, 4, 0.9), (ndq.NDQ_WORKER_NESTED, 4, 1.0)],
+                                  [(ndq.NDQ_WORKER_NESTED, 4, 1.0), (ndq.NDQ_WORKER_DQ, 32, 1.0)]])
+def test_the_last_two_of_34_workers_in_a_launch_of_their_own(last):
+    # long enough for tiles of two rows; against the single calls, which other tests compare with the oracle
+    n = 1024 * 4200 + 517
+    gen = torch.Generator(device="cuda").manual_seed(len(last))
+    workers, out = [], torch.empty(n, device="cuda")
+    for w, (kind, arg, alpha) in enumerate([(ndq.NDQ_WORKER_DQ, 32, 1.0)] * 32 + last):
+        # (codes below M: 3 of 4 two-bit values, by clearing the high bit of the fourth)
+        codes = torch.randint(0, 256, (ndq.ndq_packed_bytes(n, oracle.code_bits(arg)),), dtype=torch.uint8, device="cuda", generator=gen)
+        if arg == 3:
+            codes = codes & ~((codes << 1) & 0xAA)
+        d = ndq.ndq_dither(7 + w, 3, w, 64)
+        step = torch.full((1,), 0.01 * (w + 1), device="cuda")
+        workers.append((codes, step, kind, arg, d, alpha))
+        if kind == ndq.NDQ_WORKER_DQ:
+            ndq.ndq_dq_decode(codes, n, arg, 0, step, d, out, accumulate=w > 0)
+        else:
+            ndq.ndq_nested_decode(codes, n, arg, alpha, 0, step, d, out, float(F(1) / F(w)), out, accumulate=True)
+    got = ndq.ndq_decode_chain(workers, n, 0, 1.0)
+    assert torch.equal(got, out)

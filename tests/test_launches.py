@@ -202,3 +202,13 @@ def test_forms_of_the_general_chain_kernel(recorder, plan, bucket, name):
                for kind, arg in plan]
     (rc, launches), = lr.record(recorder, [["ndq_decode_chain", workers, len(workers), 6600000, bucket, 1.0, 0x40000000, None]])
     assert rc == 0 and ("chain_kernel" + name) in launches[0][0], launches
+
+
+@pytest.mark.parametrize("last,name", [([(0, 32), (1, 4)], "ILb0ELb0ELi2E"), ([(1, 4), (0, 32)], "ILb0ELb0ELi2E"), ([(1, 3), (0, 32)], "ILb0ELb1ELi2E"),
+                                       ([(0, 32), (1, 3)], "ILb0ELb1ELi2E"), ([(1, 4, 0.9), (1, 4)], "ILb0ELb1ELi2E"), ([(1, 4), (1, 4, 0.9)], "ILb0ELb1ELi2E")])
+def test_the_last_two_of_34_workers(recorder, last, name):
+    # the second launch of a call begins with any worker
+    workers = [{"codes": 0x20000000, "steps": 0x30000000, "kind": w[0], "levels_or_M": w[1], "alpha": w[2] if len(w) > 2 else 1.0,
+                "dither": [1, 2, 3, 0]} for w in [(0, 32)] * 32 + last]
+    (rc, launches), = lr.record(recorder, [["ndq_decode_chain", workers, 34, 6600000, 0, 1.0, 0x40000000, None]])
+    assert rc == 0 and len(launches) == 2 and ("chain_kernel" + name) in launches[1][0], launches
